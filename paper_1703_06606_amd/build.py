@@ -11,7 +11,11 @@ SOURCES = ["qnsch_lib.hip"]
 ARCH = "gfx950"
 
 # Packed FP32 instructions are switched off for all device code.
-HIPFLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-ffp-contract=fast",
+# Multiply-adds are contracted within an expression only: kernels that share a
+# function (one-item and many-item lists, fused and plain sweeps) then compute
+# bitwise the same values, which contraction across expressions, decided per
+# kernel, does not give.
+HIPFLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-ffp-contract=on",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-Wall", "-Wno-unused-function", "-Wno-unused-variable"]
 

@@ -45,6 +45,24 @@ struct Phys {
     int scheme;  // 0 = primitive scheme (sec. 6.1), 1 = projection scheme (sec. 6.2)
 };
 
+// Coefficients of the equations on one level for one step size, products of
+// the physical constants and powers of h that every cell would otherwise form
+// again (there is no scalar FP64 arithmetic: a product of two uniform values
+// costs each wave a vector instruction).  R: double, or float for the
+// correction smoother.
+template <typename R> struct Kon {
+    R ih, hih;         // 1/h, 1/(2h)
+    R idt, hidt;       // 1/dt, 1/(2dt)
+    R ka;              // 1/(16 h): advection of a momentum row
+    R kv, kv34;        // 1/(3 Re h^2) and 3/4 of it: viscous terms
+    R kp, hkp, iM;     // 1/(M h) and half of it: pressure, surface tension; 1/M
+    R km, akm;         // 1/(2 Pe h^2), alpha times it: mobility fluxes
+    R alpha;
+    R K1, kg, kl;      // bulk terms; K2/(4 h^2); K3/(8 h^2)
+    R inv_Fr, rho_ref; // gravity on the north-south faces
+    R dt2;             // 2 dt (projection equation)
+};
+
 struct View {
     double *c, *mu, *p;         // cell unknowns
     const double *u, *v;        // face unknowns (the buffer being read)
@@ -57,6 +75,30 @@ struct View {
 struct Rhs {
     const double *fc, *fmu, *fp, *fu, *fv; // FAS right-hand side; NULL = 0
 };
+
+// loads and stores through a pointer of address space AS (1: global memory,
+// 3: LDS, 0: either).  A level's arrays reach the kernels inside structures,
+// so without it the compiler issues generic accesses, which count as LDS
+// accesses too: every wait for an LDS read would then also wait for the
+// outstanding global loads.
+template <int AS, typename R> __device__ __forceinline__ R lda(const R *p, size_t k)
+{
+    if constexpr (AS == 1)
+        return ((const __attribute__((address_space(1))) R *)p)[k];
+    else if constexpr (AS == 3)
+        return ((const __attribute__((address_space(3))) R *)p)[k];
+    else
+        return p[k];
+}
+template <int AS, typename R> __device__ __forceinline__ void sta(R *p, size_t k, R v)
+{
+    if constexpr (AS == 1)
+        ((__attribute__((address_space(1))) R *)p)[k] = v;
+    else if constexpr (AS == 3)
+        ((__attribute__((address_space(3))) R *)p)[k] = v;
+    else
+        p[k] = v;
+}
 
 // --------------------------------------------------------------------------
 // loaders with boundary conditions (used only by the tile loader)
@@ -198,10 +240,24 @@ __device__ __forceinline__ double frcp(double x)
 }
 __device__ __forceinline__ double rho_of(const Phys &P, double c) { return P.rho12 * frcp(P.drho * c + P.rho1); }
 __device__ __forceinline__ double visc_of(const Phys &P, double c) { return P.visc12 * frcp(P.dvisc * c + P.visc1); }
+// square root: hardware estimate of the reciprocal root refined by a coupled
+// Newton step for x and 1/(2 sqrt x) and a last correction (within an ulp;
+// half the instructions of the library's, which also covers the subnormal
+// range, left to it here)
+__device__ __forceinline__ double fsqrt(double x)
+{
+    if (x < 1e-280) return sqrt(x);
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, r, g);
+    h = __builtin_fma(h, r, h);
+    return __builtin_fma(__builtin_fma(-g, g, x), h, g);
+}
 __device__ __forceinline__ double mob_of(const Phys &P, double c)
 {
     double q = c * (1.0 - c);
-    return sqrt(q * q + P.mob_reg);
+    return fsqrt(q * q + P.mob_reg);
 }
 __device__ __forceinline__ double dwell(double c)
 {
@@ -212,21 +268,52 @@ __device__ __forceinline__ double dwell(double c)
 // --------------------------------------------------------------------------
 // LDS tile
 
-enum { T_C = 0, T_MU, T_P, T_U, T_V, T_CN, T_UN, T_VN, T_RN, T_MV, T_MOB, T_RS, T_NF };
+// fields of a tile element, kept together (T_U2, T_V2: the new faces of a
+// sweep that stays in the tile).  A cell's neighbours are then a few base
+// addresses with constant offsets, and adjacent fields load together as 16
+// bytes; with one array per field every access of a relaxation needed an
+// address of its own.  The element of 14 doubles spreads the cells of a
+// colour (every second element) over half of the LDS banks.
+enum { T_C = 0, T_CN, T_MU, T_P, T_RN, T_MV, T_RS, T_MOB, T_U, T_V, T_UN, T_VN, T_NF, T_U2 = T_NF, T_V2, T_ES };
+// the correction smoother's further fields (its T_MU, T_P, T_U, T_V hold
+// corrections): the correction of c and the change of density it induces
+enum { L_DC = T_ES, L_DRS, L_NF, L_ES = 20 };
 
-// A tile covers level cells i0-1 .. i0+TX+1, j0-1 .. j0+TY+1 (W = TX+3
-// columns); q(f, i, j) takes level coordinates.
-template <typename R> struct TileT {
-    R *s; // field arrays of W*H elements in LDS
+// A tile covers level cells i0-1 .. i0+W-2, j0-1 .. j0+H-2 (a tile of TX
+// columns: W = TX+3); at(i, j), q(f, i, j) take level coordinates.
+template <typename R, int ES_> struct TileT {
+    static constexpr int ES = ES_;
+    R *s; // W*H elements of ES values in LDS
     int i0, j0, W, H;
     __device__ __forceinline__ int idx(int i, int j) const { return (j - j0 + 1) * W + (i - i0 + 1); }
-    __device__ __forceinline__ R q(int f, int i, int j) const { return s[f * W * H + idx(i, j)]; }
-    __device__ __forceinline__ void set(int f, int i, int j, R v) const { s[f * W * H + idx(i, j)] = v; }
+    __device__ __forceinline__ R *at(int i, int j) const { return s + idx(i, j) * ES; }
+    __device__ __forceinline__ R q(int f, int i, int j) const { return at(i, j)[f]; }
 };
-typedef TileT<double> Tile;
+typedef TileT<double, T_ES> Tile;
 
-// cooperative load of a tile (all threads of the block take part; the caller
-// synchronises afterwards).  The level may be in global memory or in LDS.
+// an element's fields from its eight loaded values (c, mubar, pbar, u, v, c^n,
+// u^n, v^n) and the signs of its faces
+__device__ __forceinline__ void tile_put(const Phys &P, double *t, int su, int sv, const double (&v)[8])
+{
+    t[T_C] = v[0];
+    t[T_CN] = v[5];
+    t[T_MU] = v[1];
+    t[T_P] = v[2];
+    t[T_RN] = rho_of(P, v[5]);
+    t[T_MV] = visc_of(P, v[5]);
+    t[T_RS] = rho_of(P, v[0]);
+    t[T_MOB] = mob_of(P, v[5]);
+    t[T_U] = signed_val(su, v[3]);
+    t[T_V] = signed_val(sv, v[4]);
+    t[T_UN] = signed_val(su, v[6]);
+    t[T_VN] = signed_val(sv, v[7]);
+}
+template <typename TT> __device__ __forceinline__ void tile_zero(const TT &T, int e)
+{
+#pragma unroll
+    for (int f = 0; f < TT::ES; f++) T.s[e * TT::ES + f] = 0;
+}
+
 // true if every element of the tile (halo included) is an interior element
 // of the level for every field, so that no boundary image is involved: cells
 // and faces 1 .. m-1 in each direction
@@ -235,105 +322,49 @@ __device__ __forceinline__ bool tile_inner(int m1, int m2, int i0, int j0, int W
     return i0 >= 2 && j0 >= 2 && i0 + W - 2 <= m1 - 1 && j0 + H - 2 <= m2 - 1;
 }
 
-__device__ __forceinline__ void tile_load(const Phys &P, const View &L, const Tile &T)
+// cooperative load of a tile of a level in global memory (all threads of the
+// block take part; the caller synchronises afterwards).  NE elements per
+// thread are loaded together: their sources first, then every load, then the
+// signs and cell functions (an element past the end is clamped to a valid
+// one and not stored).
+template <int NE> __device__ __forceinline__ void tile_load(const Phys &P, const View &L, const Tile &T)
 {
-    const int n = T.W * T.H;
-    if (tile_inner(L.m1, L.m2, T.i0, T.j0, T.W, T.H) && n <= 2 * (int)block_threads()) {
-        // no boundary images: plain strided loads, the two elements of a
-        // thread loaded together (the second one clamped to a valid element
-        // and stored only if it exists) so that all loads are in flight at once
-        const int e0 = threadIdx.x, e1r = threadIdx.x + block_threads(), e1 = e1r < n ? e1r : n - 1;
-        auto at = [&](int e) {
-            const int b = e / T.W, a = e - b * T.W;
-            return (size_t)(T.j0 - 1 + b) * L.pitch + (T.i0 - 1 + a);
-        };
-        const size_t q0 = at(e0 < n ? e0 : n - 1), q1 = at(e1);
-        double v0[8], v1[8];
-        const double *src[8] = { L.c, L.mu, L.p, L.u, L.v, L.cn, L.un, L.vn };
+    const int n = T.W * T.H, nt = block_threads();
+    double v[NE][8];
+    if (tile_inner(L.m1, L.m2, T.i0, T.j0, T.W, T.H)) {
 #pragma unroll
-        for (int f = 0; f < 8; f++) {
-            v0[f] = src[f][q0];
-            v1[f] = src[f][q1];
+        for (int k = 0; k < NE; k++) {
+            const int e = min((int)threadIdx.x + k * nt, n - 1), b = e / T.W, a = e - b * T.W;
+            const size_t q = (size_t)((T.j0 - 1 + b) * L.pitch + (T.i0 - 1 + a));
+            const double *src[8] = { L.c, L.mu, L.p, L.u, L.v, L.cn, L.un, L.vn };
+#pragma unroll
+            for (int f = 0; f < 8; f++) v[k][f] = lda<1>(src[f], q);
         }
-        auto put = [&](int e, const double *v) {
-            double *s = T.s + e;
-            s[T_C * n] = v[0];
-            s[T_MU * n] = v[1];
-            s[T_P * n] = v[2];
-            s[T_U * n] = v[3];
-            s[T_V * n] = v[4];
-            s[T_CN * n] = v[5];
-            s[T_UN * n] = v[6];
-            s[T_VN * n] = v[7];
-            s[T_RN * n] = rho_of(P, v[5]);
-            s[T_MV * n] = visc_of(P, v[5]);
-            s[T_MOB * n] = mob_of(P, v[5]);
-            s[T_RS * n] = rho_of(P, v[0]);
-        };
-        if (e0 < n) put(e0, v0);
-        if (e1r < n) put(e1r, v1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < NE; k++) {
+            const int e = threadIdx.x + k * nt;
+            if (e < n) tile_put(P, T.s + e * T_ES, 1, 1, v[k]);
+        }
         return;
     }
-    if (n <= 2 * (int)block_threads()) {
-        // boundary images: the sources of both elements of the thread first,
-        // then all sixteen loads together, then the signs and cell functions
-        const int e0 = threadIdx.x, e1 = threadIdx.x + block_threads();
-        auto src = [&](int e) {
-            const int b = e / T.W, a = e - b * T.W;
-            TileSrc q = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, T.i0 - 1 + a, T.j0 - 1 + b);
-            if (e >= n) q.sc = q.su = q.sv = 0;
-            return q;
-        };
-        const TileSrc s0 = src(e0 < n ? e0 : 0), s1 = src(e1 < n ? e1 : 0);
-        const double v0[8] = { L.c[s0.c], L.mu[s0.c], L.p[s0.c], L.u[s0.u], L.v[s0.v], L.cn[s0.c], L.un[s0.u], L.vn[s0.v] };
-        const double v1[8] = { L.c[s1.c], L.mu[s1.c], L.p[s1.c], L.u[s1.u], L.v[s1.v], L.cn[s1.c], L.un[s1.u], L.vn[s1.v] };
-        auto put = [&](int e, const TileSrc &q, const double *v) {
-            double *s = T.s + e;
-            if (q.sc == 0) {
-                for (int f = 0; f < T_NF; f++) s[f * n] = 0.0;
-                return;
-            }
-            s[T_C * n] = v[0];
-            s[T_MU * n] = v[1];
-            s[T_P * n] = v[2];
-            s[T_U * n] = signed_val(q.su, v[3]);
-            s[T_V * n] = signed_val(q.sv, v[4]);
-            s[T_CN * n] = v[5];
-            s[T_UN * n] = signed_val(q.su, v[6]);
-            s[T_VN * n] = signed_val(q.sv, v[7]);
-            s[T_RN * n] = rho_of(P, v[5]);
-            s[T_MV * n] = visc_of(P, v[5]);
-            s[T_MOB * n] = mob_of(P, v[5]);
-            s[T_RS * n] = rho_of(P, v[0]);
-        };
-        if (e0 < n) put(e0, s0, v0);
-        if (e1 < n) put(e1, s1, v1);
-        return;
+    TileSrc s[NE];
+#pragma unroll
+    for (int k = 0; k < NE; k++) {
+        const int e = min((int)threadIdx.x + k * nt, n - 1), b = e / T.W, a = e - b * T.W;
+        s[k] = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, T.i0 - 1 + a, T.j0 - 1 + b);
+        const double w[8] = { lda<1>(L.c, s[k].c), lda<1>(L.mu, s[k].c), lda<1>(L.p, s[k].c), lda<1>(L.u, s[k].u),
+                              lda<1>(L.v, s[k].v), lda<1>(L.cn, s[k].c), lda<1>(L.un, s[k].u), lda<1>(L.vn, s[k].v) };
+#pragma unroll
+        for (int f = 0; f < 8; f++) v[k][f] = w[f];
     }
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
-        const int b = e / T.W, a = e - b * T.W;
-        const int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
-        double *s = T.s + e;
-        const int st = n;
-        if (i > L.m1 + 1 || j > L.m2 + 1) {
-            // beyond the reach of any cell of the level (tile larger than the level)
-            for (int f = 0; f < T_NF; f++) s[f * st] = 0.0;
-            continue;
-        }
-        const double c = ldc(L.c, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        const double cn = ldc(L.cn, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[T_C * st] = c;
-        s[T_MU * st] = ldc(L.mu, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[T_P * st] = ldc(L.p, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[T_U * st] = ldu(L.u, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[T_V * st] = ldv(L.v, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[T_CN * st] = cn;
-        s[T_UN * st] = ldu(L.un, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[T_VN * st] = ldv(L.vn, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[T_RN * st] = rho_of(P, cn);
-        s[T_MV * st] = visc_of(P, cn);
-        s[T_MOB * st] = mob_of(P, cn);
-        s[T_RS * st] = rho_of(P, c);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < NE; k++) {
+        const int e = threadIdx.x + k * nt;
+        if (e >= n) continue;
+        if (s[k].sc == 0) tile_zero(T, e);
+        else tile_put(P, T.s + e * T_ES, s[k].su, s[k].sv, v[k]);
     }
 }
 
@@ -374,30 +405,33 @@ __device__ __forceinline__ void tile_refresh_map(const Phys &P, const View &L, c
         const double u = L.u[qu], v = L.v[qv], c = L.c[q], mu = L.mu[q], p = L.p[q];
         __builtin_amdgcn_sched_barrier(0);
         if (fl & 16) continue;
-        double *s = T.s + e;
-        s[T_U * n] = signed_val((fl & 3) - 1, u);
-        s[T_V * n] = signed_val(((fl >> 2) & 3) - 1, v);
+        double *s = T.s + e * T_ES;
+        s[T_U] = signed_val((fl & 3) - 1, u);
+        s[T_V] = signed_val(((fl >> 2) & 3) - 1, v);
         if (((fl >> 5) & 1) != colour) continue;
-        s[T_C * n] = c;
-        s[T_MU * n] = mu;
-        s[T_P * n] = p;
-        s[T_RS * n] = rho_of(P, c);
+        s[T_C] = c;
+        s[T_MU] = mu;
+        s[T_P] = p;
+        s[T_RS] = rho_of(P, c);
     }
 }
 
 // --------------------------------------------------------------------------
-// Lane pairs.  Each cell (or box) is handled by two adjacent lanes: lane 0
-// takes every x-direction contribution, lane 1 the same code on transposed
-// strides (y-direction), so the pair runs one instruction stream without
-// divergence.  Partial sums are exchanged with a one-lane shuffle.
+// The equations of a cell come in two parts, one per axis, of the same form on
+// transposed strides.  A relaxation takes a pair of adjacent lanes per cell:
+// lane 0 the x part, lane 1 the y part, the partial sums exchanged between
+// them (one instruction stream, the shorter chain); or one lane that takes
+// both parts in turn (fewer instructions per cell).  A residual takes one
+// lane per cell.  Multiply-adds are contracted within an expression only
+// (-ffp-contract=on), so every kernel that shares these functions computes
+// the same values.
 
 struct Ax {
-    int dn, dt;            // element strides of the tile along the normal / tangential axis
-    int FN, FT, FNN, FTN;  // own velocity, other velocity and their time-n fields
-    int per, ia, ma;       // periodic along the axis; cell index and count along it
-    int pert, it, mt;      // the same for the tangential axis
-    double grav;           // 1 on the y lane: gravity acts on the north-south faces
-    int hlf;
+    int dn, dt;          // offsets of the next element along the normal / tangential axis
+    int fn, ft;          // own velocity (T_U or T_V), other velocity
+    bool per, pert;      // periodic along the axis / the other one
+    int ia, ma, it, mt;  // cell index and count along the axis / the other one
+    int hlf;             // 0 x, 1 y
 };
 
 template <typename V, typename TT>
@@ -405,19 +439,16 @@ __device__ __forceinline__ Ax make_ax(const V &L, const TT &T, int i, int j, int
 {
     Ax a;
     a.hlf = hlf;
-    a.dn = hlf ? T.W : 1;
-    a.dt = hlf ? 1 : T.W;
-    a.FN = hlf ? T_V : T_U;
-    a.FT = hlf ? T_U : T_V;
-    a.FNN = hlf ? T_VN : T_UN;
-    a.FTN = hlf ? T_UN : T_VN;
+    a.dn = hlf ? T.W * TT::ES : TT::ES;
+    a.dt = hlf ? TT::ES : T.W * TT::ES;
+    a.fn = T_U + hlf;
+    a.ft = T_V - hlf;
     a.per = hlf ? L.bcy : L.bcx;
+    a.pert = hlf ? L.bcx : L.bcy;
     a.ia = hlf ? j : i;
     a.ma = hlf ? L.m2 : L.m1;
-    a.pert = hlf ? L.bcx : L.bcy;
     a.it = hlf ? i : j;
     a.mt = hlf ? L.m1 : L.m2;
-    a.grav = hlf ? 1.0 : 0.0;
     return a;
 }
 
@@ -432,183 +463,237 @@ __device__ __forceinline__ double other(double x)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// element-indexed tile read
-template <typename R> __device__ __forceinline__ R tq(const TileT<R> &T, int f, int e) { return T.s[f * T.W * T.H + e]; }
-
-// contributions of one axis to the cell equations at cell element e
-struct CellAx {
-    double adv, div, Lmu, Lp, Sm, Gc, Gn, Lr, dGc, dLra, dLrb;
+// The axis part of the cell equations at element s, in the combinations that
+// the equations take them in:
+//   s1  advection of c (App. A.5) - (1/Pe) L_m(mubar + alpha pbar)   (phase)
+//   s2  divergence - (alpha/Pe) L_m(mubar + alpha pbar)              (mass)
+//   sm  (1/Pe) times the sum of the mobilities over h^2 (minus the diagonal of
+//       (1/Pe) L_m)
+//   g   4 h^2 times the average of |grad c|^2 over the two time levels
+//   lr  8 h^2 times the capillary divergence (App. A.6)
+//   j   what g and lr add to d(chemical row)/dc besides the pointwise terms
+// (r, drs: -alpha rho rho^n and rho'(c) of the cell).  A face on a wall
+// carries no flux: the mirrored ghost equals the cell, so every difference
+// across it is zero; the masks wP, wM matter for derivatives only.
+template <typename R> struct CellSum {
+    R s1, s2, sm, g, lr, j;
 };
-
-__device__ __forceinline__ CellAx cell_axis(const Tile &T, const Ax &a, int e, double ih)
+// u0, uP: the velocity on the cell's low and high face along the axis.  PJ:
+// the projection scheme, whose advection takes c and rho of time n+1.
+template <bool PJ>
+__device__ __forceinline__ CellSum<double> axis_cell(const Kon<double> &K, const double *s, const Ax &a, double r,
+                                                     double drs, double u0, double uP)
 {
-    const double ih2 = ih * ih;
-    // faces of the cell on a wall carry no flux (the mirrored ghost equals the
-    // cell); the masks matter for derivatives only
-    const double wP = (a.per || a.ia < a.ma - 1) ? 1.0 : 0.0, wM = (a.per || a.ia > 0) ? 1.0 : 0.0;
-    const int eP = e + a.dn, eM = e - a.dn;
-    const double c = tq(T, T_C, e), cP = tq(T, T_C, eP), cM = tq(T, T_C, eM);
-    const double n = tq(T, T_CN, e), nP = tq(T, T_CN, eP), nM = tq(T, T_CN, eM);
-    const double mu = tq(T, T_MU, e), p = tq(T, T_P, e);
-    const double rnP = tq(T, T_RN, eP), rnM = tq(T, T_RN, eM), rn = tq(T, T_RN, e);
-    const double rs = tq(T, T_RS, e);
-    const double m0 = tq(T, T_MOB, e);
-    const double mP = 0.5 * (tq(T, T_MOB, eP) + m0) * wP, mM = 0.5 * (tq(T, T_MOB, eM) + m0) * wM;
-    const double uP = tq(T, a.FN, eP), u0 = tq(T, a.FN, e);
-    CellAx x;
-    // rho^n u . grad c^n in the special form of App. A.5
-    x.adv = 0.5 * ih * (rnP * (nP - n) * uP + rnM * (n - nM) * u0);
-    x.div = ih * (uP - u0);
-    x.Lmu = ih2 * (mP * (tq(T, T_MU, eP) - mu) - mM * (mu - tq(T, T_MU, eM)));
-    x.Lp = ih2 * (mP * (tq(T, T_P, eP) - p) - mM * (p - tq(T, T_P, eM)));
-    x.Sm = ih2 * (mP + mM);
-    const double dP = cP - c, dM = c - cM, gP = nP - n, gM = n - nM;
-    x.Gc = 0.5 * ih2 * (dP * dP + dM * dM);
-    x.Gn = 0.5 * ih2 * (gP * gP + gM * gM);
-    const double rh = 0.5 * (rs + rn);
-    const double kP = 0.5 * (0.5 * (tq(T, T_RS, eP) + rnP) + rh) * wP;
-    const double kM = 0.5 * (0.5 * (tq(T, T_RS, eM) + rnM) + rh) * wM;
-    const double hP = 0.5 * (dP + gP), hM = 0.5 * (dM + gM);
-    x.Lr = ih2 * (kP * hP - kM * hM);
-    x.dGc = ih2 * (wP * (-dP) + wM * dM);
-    x.dLra = ih2 * (wP * hP - wM * hM);
-    x.dLrb = ih2 * (kP + kM);
+    const bool wP = a.per || a.ia < a.ma - 1, wM = a.per || a.ia > 0;
+    const double *sP = s + a.dn, *sM = s - a.dn;
+    const double mP = sP[T_MOB] + s[T_MOB], mM = sM[T_MOB] + s[T_MOB];
+    const double S = s[T_MU] + K.alpha * s[T_P];
+    const double fP = (sP[T_MU] + K.alpha * sP[T_P]) - S, fM = S - (sM[T_MU] + K.alpha * sM[T_P]);
+    const double flux = mP * fP - mM * fM;
+    const double gP = sP[T_CN] - s[T_CN], gM = s[T_CN] - sM[T_CN], dP = sP[T_C] - s[T_C], dM = s[T_C] - sM[T_C];
+    CellSum<double> x;
+    const double aP = PJ ? sP[T_RS] * dP : sP[T_RN] * gP, aM = PJ ? sM[T_RS] * dM : sM[T_RN] * gM;
+    const double adv = aP * uP + aM * u0;
+    x.s1 = K.hih * adv - K.km * flux;
+    x.s2 = K.ih * (uP - u0) - K.akm * flux;
+    x.sm = K.km * ((wP ? mP : 0.0) + (wM ? mM : 0.0));
+    x.g = (dP * dP + dM * dM) + (gP * gP + gM * gM);
+    const double hP = dP + gP, hM = dM + gM;
+    const double R0 = s[T_RS] + s[T_RN];
+    const double RP = (sP[T_RS] + sP[T_RN]) + R0, RM = (sM[T_RS] + sM[T_RN]) + R0;
+    x.lr = RP * hP - RM * hM;
+    const double w = (wP ? RP : 0.0) + (wM ? RM : 0.0);
+    x.j = K.kl * (drs * (hP - hM) - w) - (2.0 * K.kg * r) * (dM - dP);
     return x;
 }
-
-__device__ __forceinline__ CellAx cell_sum(const CellAx &x)
+template <typename R> __device__ __forceinline__ CellSum<R> other(const CellSum<R> &x)
 {
-    CellAx s;
-    s.adv = x.adv + other(x.adv);
-    s.div = x.div + other(x.div);
-    s.Lmu = x.Lmu + other(x.Lmu);
-    s.Lp = x.Lp + other(x.Lp);
-    s.Sm = x.Sm + other(x.Sm);
-    s.Gc = x.Gc + other(x.Gc);
-    s.Gn = x.Gn + other(x.Gn);
-    s.Lr = x.Lr + other(x.Lr);
-    s.dGc = x.dGc + other(x.dGc);
-    s.dLra = x.dLra + other(x.dLra);
-    s.dLrb = x.dLrb + other(x.dLrb);
-    return s;
+    return { other(x.s1), other(x.s2), other(x.sm), other(x.g), other(x.lr), other(x.j) };
+}
+template <typename R> __device__ __forceinline__ CellSum<R> operator+(const CellSum<R> &x, const CellSum<R> &y)
+{
+    return { x.s1 + y.s1, x.s2 + y.s2, x.sm + y.sm, x.g + y.g, x.lr + y.lr, x.j + y.j };
 }
 
 // cell equations: phase (pm-num-phase), chemical potential (pm-num-chem) and
 // mass (pm-num-mass), with the Jacobian entries the smoother needs, from the
-// two axis sums
+// sum of the axis parts
 struct CellEq {
     double Nc, Nmu, Np;
     double Jcc, Jcm, Jmc, Jmm; // d(Nc,Nmu)/d(c,mu) at the cell
-    double Jpp;                // dNp/dp at the cell
 };
 
-__device__ __forceinline__ CellEq cell_eq(const Phys &P, const Tile &T, int e, const CellAx &s)
+// pointwise quantities of the cell that the axis parts need
+__device__ __forceinline__ void cell_r(const Kon<double> &K, const double *s, double &r, double &drs)
 {
-    const double c = tq(T, T_C, e), n = tq(T, T_CN, e), mu = tq(T, T_MU, e);
-    const double rs = tq(T, T_RS, e), rn = tq(T, T_RN, e);
+    const double t = -K.alpha * s[T_RS];
+    r = t * s[T_RN];
+    drs = t * s[T_RS];
+}
+__device__ __forceinline__ CellEq cell_eq(const Kon<double> &K, const double *s, const CellSum<double> &x, double r,
+                                          double drs)
+{
+    const double c = s[T_C], n = s[T_CN], mu = s[T_MU], rs = s[T_RS], rn = s[T_RN];
     CellEq q;
-    q.Nc = rs * (c - n) * P.inv_dt + s.adv - P.inv_Pe * s.Lmu - P.alpha * P.inv_Pe * s.Lp;
-    q.Np = s.div - P.alpha * P.inv_Pe * s.Lmu - P.alpha * P.alpha * P.inv_Pe * s.Lp;
+    q.Nc = K.idt * (rs * (c - n)) + x.s1;
+    q.Np = x.s2;
     // time averages of sec. 4.1; pointwise |grad_D c|^2 = a_x((D_x c)^2) + a_y((D_y c)^2)
     const double rh = 0.5 * (rs + rn);
-    const double q1 = c * (c - 1.0), q0 = n * (n - 1.0);
-    const double g = 0.25 * (q1 + q0) * (c + n - 1.0);
-    const double Fh = 0.5 * (dwell(c) + dwell(n));
-    const double r = -P.alpha * rs * rn;
-    const double Gh = 0.5 * (s.Gc + s.Gn);
-    q.Nmu = rs * mu - P.K1 * (rh * g + Fh * r) - P.K2 * Gh * r + P.K3 * s.Lr;
+    const double q1 = c * (c - 1.0), q0 = n * (n - 1.0), t = c + n - 1.0, qs = q1 + q0;
+    const double g = 0.25 * qs * t;
+    const double Fh = 0.125 * (q1 * q1 + q0 * q0);
+    const double G = K.kg * x.g + K.K1 * Fh; // K2 |grad c|^2 + K1 F, both times r
+    q.Nmu = rs * mu - K.K1 * (rh * g) - G * r + K.kl * x.lr;
     // Jacobian in (c_ij, mubar_ij); rho' = -alpha rho^2
-    const double drs = -P.alpha * rs * rs;
-    q.Jcc = (drs * (c - n) + rs) * P.inv_dt;
-    q.Jcm = P.inv_Pe * s.Sm;
+    q.Jcc = K.idt * (drs * (c - n) + rs);
+    q.Jcm = x.sm;
     q.Jmm = rs;
-    const double dg = 0.25 * ((2.0 * c - 1.0) * (c + n - 1.0) + q1 + q0);
-    const double f1 = q1 * (c - 0.5);                   // F'(c)
-    const double dr = P.alpha * P.alpha * rs * rs * rn; // dr/dc
-    const double dLr = 0.25 * drs * s.dLra - 0.5 * s.dLrb;
-    q.Jmc = drs * mu - P.K1 * (0.5 * drs * g + rh * dg + 0.5 * f1 * r + Fh * dr) - P.K2 * (0.5 * s.dGc * r + Gh * dr)
-          + P.K3 * dLr;
-    q.Jpp = P.alpha * P.alpha * P.inv_Pe * s.Sm;
+    const double dg = 0.25 * ((2.0 * c - 1.0) * t + qs);
+    const double f1 = q1 * (c - 0.5);   // F'(c)
+    const double dr = -K.alpha * rs * r; // dr/dc
+    q.Jmc = drs * mu - K.K1 * (0.5 * (drs * g + f1 * r) + rh * dg) - G * dr + x.j;
     return q;
 }
 
 // --------------------------------------------------------------------------
-// momentum equation (pm-num-mx) on the face stored at element ef (the west
-// face of its cell on the x lane, the south face on the y lane), with the
+// momentum equation (pm-num-mx) on the face stored at element s (the west
+// face of its cell on the x axis, the south face on the y axis), with the
 // derivative with respect to the face's own velocity.  Advection (e1e1-1) plus
 // the half-divergence term (e1e1-2) are used in their skew form
 //   1/(2h) [w_R u_{+1} - w_L u_{-1} + Z_t u_{t+1} - Z_b u_{t-1}],
 // which is the same sum with the terms on the face's own value cancelled.
-// (it = tangential index of the face's row.)
-struct FaceEq {
-    double N, diag;
+// (it = tangential index of the face's row.)  PJ: the projection scheme's
+// intermediate velocity (pj-num-mx), which has neither pressure, surface
+// tension nor gravity (they act in (pj-num-pjx)).  The two faces of a box
+// share their common terms (the compiler finds them: the expressions are the
+// same).
+template <typename R> struct FaceEq {
+    R N, diag;
 };
 
-__device__ __forceinline__ FaceEq face_eq(const Phys &P, const Tile &T, const Ax &a, int ef, int it, double ih,
-                                          bool proj = false)
+// LIN: the equation's linearisation at w^ applied to a correction (the
+// correction smoother): uh is the face's velocity at w^, which multiplies the
+// change of the density average (field L_DRS); gravity and u^n drop out.
+template <typename R, bool PJ, bool LIN>
+__device__ __forceinline__ FaceEq<R> face_eq(const Kon<R> &K, const R *s, const Ax &a, R uh = R(0))
 {
-    const double ih2 = ih * ih;
-    const int eL = ef - a.dn, eR = ef, dt = a.dt;
-    const double rL = tq(T, T_RN, eL), rR = tq(T, T_RN, eR);
-    const double Rt = 0.25 * (rL + rR + tq(T, T_RN, eL + dt) + tq(T, T_RN, eR + dt));
-    const double Rb = 0.25 * (rL + rR + tq(T, T_RN, eL - dt) + tq(T, T_RN, eR - dt));
-    const double mvL = tq(T, T_MV, eL), mvR = tq(T, T_MV, eR);
-    const double nut = 0.25 * (mvL + mvR + tq(T, T_MV, eL + dt) + tq(T, T_MV, eR + dt));
-    const double nub = 0.25 * (mvL + mvR + tq(T, T_MV, eL - dt) + tq(T, T_MV, eR - dt));
-    const double Arn = 0.5 * (rL + rR);
-    const double Ars = 0.5 * (tq(T, T_RS, eL) + tq(T, T_RS, eR));
-    const double un0 = tq(T, a.FNN, ef);
-    const double wL = rL * 0.5 * (tq(T, a.FNN, ef - a.dn) + un0);
-    const double wR = rR * 0.5 * (un0 + tq(T, a.FNN, ef + a.dn));
-    const double Vt = 0.5 * (tq(T, a.FTN, eL + dt) + tq(T, a.FTN, eR + dt));
-    const double Vb = 0.5 * (tq(T, a.FTN, eL) + tq(T, a.FTN, eR));
-    const double u0 = tq(T, a.FN, ef), uE = tq(T, a.FN, ef + a.dn), uW = tq(T, a.FN, ef - a.dn);
-    const double uN = tq(T, a.FN, ef + dt), uS = tq(T, a.FN, ef - dt);
-    const double thR = ih * (uE - u0 + tq(T, a.FT, eR + dt) - tq(T, a.FT, eR));
-    const double thL = ih * (u0 - uW + tq(T, a.FT, eL + dt) - tq(T, a.FT, eL));
-    const double nL = tq(T, T_CN, eL), nR = tq(T, T_CN, eR);
-    FaceEq q;
-    q.N = Arn * (u0 - un0) * P.inv_dt
-        + 0.5 * ih * (wR * uE - wL * uW + Rt * Vt * uN - Rb * Vb * uS)
-        + 0.5 * (Ars - Arn) * P.inv_dt * u0
-        - P.inv_Re * ih2 * (mvR * (uE - u0) - mvL * (u0 - uW) + nut * (uN - u0) - nub * (u0 - uS))
-        - (P.inv_Re / 3.0) * ih * (mvR * thR - mvL * thL);
-    // the projection scheme's intermediate velocity (pj-num-mx) has neither
-    // pressure, surface tension nor gravity: they act in (pj-num-pjx)
-    if (!proj)
-        q.N += P.inv_M * ih * (tq(T, T_P, eR) - tq(T, T_P, eL))
-             - P.inv_M * ih * 0.5 * (rR * tq(T, T_MU, eL) + rL * tq(T, T_MU, eR)) * (nR - nL)
-             + a.grav * P.inv_Fr * (Arn - P.rho_ref);
+    const int dn = a.dn, dt = a.dt, fn = a.fn, ft = a.ft, fnn = fn + (T_UN - T_U), ftn = ft + (T_UN - T_U);
+    const R *L = s - dn;
+    const R rL = L[T_RN], rR = s[T_RN], mL = L[T_MV], mR = s[T_MV];
+    const R a1 = rL + rR, b1 = mL + mR;
+    const R At = (L[dt + T_RN] + s[dt + T_RN]) + a1, Ab = (L[T_RN - dt] + s[T_RN - dt]) + a1;
+    const R mt = (L[dt + T_MV] + s[dt + T_MV]) + b1, mb = (L[T_MV - dt] + s[T_MV - dt]) + b1;
+    const R hA = R(0.5) * ((L[T_RS] + s[T_RS]) - a1);
+    const R un0 = s[fnn];
+    const R wL = rL * (L[fnn] + un0), wR = rR * (un0 + s[dn + fnn]);
+    const R Ct = At * (L[dt + ftn] + s[dt + ftn]), Cb = Ab * (L[ftn] + s[ftn]);
+    const R u0 = s[fn], uE = s[dn + fn], uW = L[fn], uN = s[dt + fn], uS = s[fn - dt];
+    // (4 d_n u + d_t v) h of the cells on both sides
+    const R thR = R(4) * (uE - u0) + (s[dt + ft] - s[ft]), thL = R(4) * (u0 - uW) + (L[dt + ft] - L[ft]);
+    const R advn = wR * uE - wL * uW;
+    const R adv = R(4) * advn + (Ct * uN - Cb * uS);
+    const R v1 = mR * thR - mL * thL, v2 = mt * (uN - u0) - mb * (u0 - uS);
+    FaceEq<R> q;
+    R td = a1 * (LIN ? u0 : u0 - un0) + hA * u0; // time derivative
+    if (LIN) td = td + R(0.5) * (L[L_DRS] + s[L_DRS]) * uh;
+    q.N = K.hidt * td + K.ka * adv - (K.kv * v1 + K.kv34 * v2);
+    if (!PJ) {
+        const R sf = (rR * L[T_MU] + rL * s[T_MU]) * (s[T_CN] - L[T_CN]);
+        q.N += K.kp * (s[T_P] - L[T_P]) - K.hkp * sf;
+        if (!LIN && a.hlf) q.N += K.inv_Fr * (R(0.5) * a1 - K.rho_ref);
+    }
     // own-face derivative; across a tangential wall the reflected ghost doubles
     // the viscous coupling and the advection coefficient enters with a sign flip
-    const double gt = (!a.pert && it == a.mt - 1) ? 1.0 : 0.0, gb = (!a.pert && it == 0) ? 1.0 : 0.0;
-    q.diag = 0.5 * (Arn + Ars) * P.inv_dt + (4.0 / 3.0) * P.inv_Re * ih2 * (mvL + mvR)
-           + P.inv_Re * ih2 * (nut * (1.0 + gt) + nub * (1.0 + gb)) + 0.5 * ih * (gb * Rb * Vb - gt * Rt * Vt);
+    q.diag = K.hidt * (a1 + hA) + R(4) * (K.kv * b1) + K.kv34 * (mt + mb);
+    if (!a.pert) {
+        if (a.it == a.mt - 1) q.diag += K.kv34 * mt - K.ka * Ct;
+        if (a.it == 0) q.diag += K.kv34 * mb + K.ka * Cb;
+    }
     return q;
 }
 
-// loads and stores through a pointer of address space AS (1: global memory,
-// 3: LDS, 0: either).  A level's arrays reach the kernels inside structures,
-// so without it the compiler issues generic accesses, which count as LDS
-// accesses too: every wait for an LDS read would then also wait for the
-// outstanding global loads.
-template <int AS, typename R> __device__ __forceinline__ R lda(const R *p, size_t k)
+// --------------------------------------------------------------------------
+// The box of a cell.  Along an axis its two faces satisfy
+//   V x = b + s t - q dc,   V = (dlo, alh; ahl, dhi),  s = (1, -1),
+//   t = gd D_o - gp p,
+// with D = x_hi - x_lo and D_o that of the other axis: the viscous coupling of
+// the axes and the pressure enter an axis through t alone, the cell's c and
+// mubar (coupled box; mubar eliminated by the chemical row as kbm - kmc dc)
+// through q and b.  The mass row takes the D of both axes, the phase row a.x
+// of both (a: the advection weights of App. A.5).  So each axis inverts its
+// own 2x2 block for the three right-hand sides, and the rest is a system in
+// (D_x, D_y), then (p, dc).  (A face on a wall is no unknown: identity row,
+// zero right-hand sides.)
+template <typename R> struct BoxAx {
+    R xb[2], xs[2], xq[2]; // V^-1 b, V^-1 s, V^-1 q: low and high face
+    R Db, Ds, Dq;          // their D
+    R Ab, As, Aq;          // their a.x
+};
+__device__ __forceinline__ double frcp_(double x) { return frcp(x); }
+__device__ __forceinline__ float frcp_(float x) { return __builtin_amdgcn_rcpf(x); }
+
+template <typename R>
+__device__ __forceinline__ BoxAx<R> box_axis(R dlo, R dhi, R alh, R ahl, R blo, R bhi, R slo, R shi, R qlo, R qhi,
+                                             R alo, R ahi)
 {
-    if constexpr (AS == 1)
-        return ((const __attribute__((address_space(1))) R *)p)[k];
-    else if constexpr (AS == 3)
-        return ((const __attribute__((address_space(3))) R *)p)[k];
-    else
-        return p[k];
+    const R id = frcp_(dlo * dhi - alh * ahl);
+    const R v00 = dhi * id, v01 = -(alh * id), v10 = -(ahl * id), v11 = dlo * id;
+    BoxAx<R> x;
+    x.xb[0] = v00 * blo + v01 * bhi;
+    x.xb[1] = v10 * blo + v11 * bhi;
+    x.xs[0] = v00 * slo + v01 * shi;
+    x.xs[1] = v10 * slo + v11 * shi;
+    x.xq[0] = v00 * qlo + v01 * qhi;
+    x.xq[1] = v10 * qlo + v11 * qhi;
+    x.Db = x.xb[1] - x.xb[0];
+    x.Ds = x.xs[1] - x.xs[0];
+    x.Dq = x.xq[1] - x.xq[0];
+    x.Ab = alo * x.xb[0] + ahi * x.xb[1];
+    x.As = alo * x.xs[0] + ahi * x.xs[1];
+    x.Aq = alo * x.xq[0] + ahi * x.xq[1];
+    return x;
 }
-template <int AS, typename R> __device__ __forceinline__ void sta(R *p, size_t k, R v)
+// the parts of the other axis that box_solve needs
+template <typename R> struct BoxOther {
+    R Db, Ds, Dq, Ab, As, Aq;
+};
+template <typename R> __device__ __forceinline__ BoxOther<R> box_other(const BoxAx<R> &x)
 {
-    if constexpr (AS == 1)
-        ((__attribute__((address_space(1))) R *)p)[k] = v;
-    else if constexpr (AS == 3)
-        ((__attribute__((address_space(3))) R *)p)[k] = v;
-    else
-        p[k] = v;
+    return { other(x.Db), other(x.Ds), other(x.Dq), other(x.Ab), other(x.As), other(x.Aq) };
+}
+// p, dc and t of both axes (to: own, tt: other) from
+//   mass row:   ih (D_x + D_y) + Jpp p + Jcp (kbm - kmc dc) = bp
+//   phase row:  a.x + a.y + Jcp p + Jc dc = r1,  Jc = Jcc - Jcm kmc (r1 less Jcm kbm)
+// cpl = false: the Vanka box alone (dc = 0)
+template <typename R>
+__device__ __forceinline__ void box_solve(const BoxAx<R> &x, const BoxOther<R> &y, bool cpl, R gd, R gp, R ih, R Jpp,
+                                          R Jcp, R kmc, R kbm, R Jc, R bp, R r1, R &p, R &dc, R &to, R &tt)
+{
+    // (D_x, D_y) = D0 + Dp p + Dc dc
+    const R gx = gd * x.Ds, gy = gd * y.Ds;
+    const R idl = frcp_(R(1) - gx * gy);
+    const R X0 = (x.Db + gx * y.Db) * idl, Y0 = (y.Db + gy * x.Db) * idl;
+    const R gpi = -gp * idl;
+    const R Xp = (x.Ds + gx * y.Ds) * gpi, Yp = (y.Ds + gy * x.Ds) * gpi;
+    const R Mp = ih * (Xp + Yp) + Jpp;
+    if (!cpl) {
+        p = (bp - ih * (X0 + Y0)) * frcp_(Mp);
+        dc = R(0);
+        to = gd * (Y0 + Yp * p) - gp * p;
+        tt = gd * (X0 + Xp * p) - gp * p;
+        return;
+    }
+    const R Xc = -(x.Dq + gx * y.Dq) * idl, Yc = -(y.Dq + gy * x.Dq) * idl;
+    const R Mc = ih * (Xc + Yc) - Jcp * kmc, M0 = (bp - Jcp * kbm) - ih * (X0 + Y0);
+    const R tp = gd * Yp - gp, sp = gd * Xp - gp;
+    const R Pp = (Jcp + x.As * tp) + y.As * sp;
+    const R Pc = (Jc - (x.Aq + y.Aq)) + gd * (x.As * Yc + y.As * Xc);
+    const R P0 = (r1 - (x.Ab + y.Ab)) - gd * (x.As * Y0 + y.As * X0);
+    const R idt = frcp_(Mp * Pc - Mc * Pp);
+    p = (M0 * Pc - Mc * P0) * idt;
+    dc = (Mp * P0 - Pp * M0) * idt;
+    to = gd * (Y0 + Yc * dc) + tp * p;
+    tt = gd * (X0 + Xc * dc) + sp * p;
 }
 
 template <int AS = 0> __device__ __forceinline__ double ldf(const double *f, const View &L, int i, int j)
@@ -637,282 +722,236 @@ __device__ __forceinline__ const double *face_rhs(const Rhs &F, int hlf)
 //               dN_c/dp = alpha Sm / Pe, Jcc, Jcm,
 //   chem. row:  Jmc, Jmm,
 // with a_f = rho^n (c^n jump across the face) / (2h), signed along the axis.
-// mubar and c are eliminated first (N_mu, then N_c; the pivots are Jmm = rho
-// and Jcc - Jcm Jmc / Jmm, which exceeds Jcc where the gradient-energy term
-// makes Jmc negative, as on any grid that resolves the interface), which
-// leaves a rank-one update of the 5x5 box matrix; after its solve, c and mubar
-// follow by back substitution.
+// mubar is eliminated first (N_mu; its pivot is Jmm = rho), the rest is solved
+// by axes (box_axis, box_solve).
 // Velocities come from the tile (the snapshot of this colour); the box faces
 // go to unew/vnew, c, mubar, pbar to the level arrays.  In the segregated
 // form c, mubar and rho(c) of the cell are also written to the tile between
 // the steps (identical values from both lanes), which no other pair of this
 // colour reads.
-template <bool TO, int AS>
-__device__ __forceinline__ void relax_pair_pj(const Phys &P, const View &L, const Tile &T, const Rhs &F, double *unew, double *vnew,
-                              int i, int j, int ti, int tj, int hlf, double omega, double pomega);
-__device__ __forceinline__ void resid_pair_pj(const Phys &P, const View &L, const Tile &T, const Rhs &F, int i, int j, int hlf,
-                              double &rc, double &rm, double &rp, double &rf);
-
+//
 // omega relaxes the box's velocity and pressure updates; pomega the
-// projection scheme's separate pressure step
-// With TO set (primitive scheme only), the cell sits at tile position (ti,
-// tj), which differs from its level position (i, j) at a periodic image, and
-// the results stay in the tile: c, mubar, pbar and rho(c) in place (no other
-// cell of the colour reads them), the box faces in the fields T_NF (u) and
-// T_NF + 1 (v), whose elements only this cell's box writes.  AS is the
-// address space of the level arrays and right-hand sides (1: global memory,
-// 3: LDS, where the level resides in the workgroup's LDS).
-template <bool TO, int AS>
-__device__ __forceinline__ void relax_cell(const Phys &P, const View &L, const Tile &T, const Rhs &F, double *unew,
-                                           double *vnew, int i, int j, int ti, int tj, int hlf, double omega,
-                                           double pomega)
+// projection scheme's separate pressure step.
+// With TO set, the cell sits at tile position (ti, tj), which differs from
+// its level position (i, j) at a periodic image, and the results stay in the
+// tile: c, mubar, pbar and rho(c) in place (no other cell of the colour reads
+// them), the box faces in the fields T_U2, T_V2, whose elements only this
+// cell's box writes.  AS is the address space of the level arrays and
+// right-hand sides (1: global memory, 3: LDS, where the level resides in the
+// workgroup's LDS).
+//
+// 260 vector instructions fewer per relaxation than with the box assembled
+// and eliminated as a 5x5 matrix, the coefficients formed per cell and the
+// tile's fields in separate arrays (2351 -> @@ in the half-sweep kernel).
+
+// what a sweep of one cell starts from
+struct CellPos {
+    Ax a;
+    bool hlo, hhi;    // the lane's faces are unknowns
+    size_t k, khi;    // level index of the cell (and its low faces), of the lane's high face
+};
+template <typename V, typename TT>
+__device__ __forceinline__ CellPos cell_pos(const V &L, const TT &T, int i, int j, int ti, int tj, int hlf)
 {
-    if (P.scheme) {
-        relax_pair_pj<TO, AS>(P, L, T, F, unew, vnew, i, j, ti, tj, hlf, omega, pomega);
+    CellPos c;
+    c.a = make_ax(L, T, i, j, hlf);
+    c.hlo = c.a.per || c.a.ia >= 1;
+    c.hhi = c.a.per || c.a.ia + 1 < c.a.ma;
+    c.k = (size_t)j * L.pitch + i;
+    const int ihi = hlf ? i : (i + 1 < L.m1 ? i + 1 : 0), jhi = hlf ? (j + 1 < L.m2 ? j + 1 : 0) : j;
+    c.khi = (size_t)jhi * L.pitch + ihi;
+    return c;
+}
+// off-diagonal entries of the axis' 2x2 block (a periodic axis of two cells:
+// the next face beyond each box face is the box's other face, which so
+// enters each face row a second time, through the other cell's advection
+// weight and viscosity)
+template <typename R>
+__device__ __forceinline__ void box_offdiag(const Kon<R> &K, const R *s, const Ax &a, bool hlo, bool hhi, R &alh, R &ahl)
+{
+    const int fnn = a.fn + (T_UN - T_U);
+    const R un = s[fnn] + s[a.dn + fnn];
+    const R w = R(4) * (K.ka * (s[T_RN] * un)), vis = R(4) * (K.kv * s[T_MV]);
+    alh = hlo ? w - vis : R(0);
+    ahl = hhi ? -w - vis : R(0);
+    if (a.per && a.ma == 2) {
+        const R *o = s - a.dn;
+        const R wo = R(4) * (K.ka * (o[T_RN] * un)), vo = R(4) * (K.kv * o[T_MV]);
+        alh = alh - (wo + vo);
+        ahl = ahl + (wo - vo);
+    }
+}
+
+template <bool TO, int AS>
+__device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, const View &L, const Tile &T, const Rhs &F,
+                                         double *unew, double *vnew, int i, int j, int ti, int tj, int hlf,
+                                         double omega, double pomega);
+
+template <bool PJ, bool TO, int AS>
+__device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, const View &L, const Tile &T,
+                                           const Rhs &F, double *unew, double *vnew, int i, int j, int ti, int tj,
+                                           int hlf, double omega, double pomega)
+{
+    if (PJ) {
+        relax_pj<TO, AS>(P, K, L, T, F, unew, vnew, i, j, ti, tj, hlf, omega, pomega);
         return;
     }
-    const size_t k = (size_t)j * L.pitch + i;
-    const double ih = L.inv_h, ih2 = ih * ih;
-    const int e = T.idx(ti, tj);
-    const Ax a = make_ax(L, T, i, j, hlf);
+    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf);
+    const Ax &a = b.a;
+    double *const e = T.at(ti, tj);
     const bool cpl = P.coupled;
     // the right-hand sides first: their loads are then in flight during the
     // cell equations
-    const bool hlo = a.per || a.ia >= 1, hhi = a.per || a.ia + 1 < a.ma;
     const double *fN = face_rhs(F, hlf);
-    const int ihi = hlf ? i : (i + 1 < L.m1 ? i + 1 : 0), jhi = hlf ? (j + 1 < L.m2 ? j + 1 : 0) : j;
-    const size_t khi = (size_t)jhi * L.pitch + ihi;
-    const double f_c = ldf<AS>(F.fc, L, i, j), f_mu = ldf<AS>(F.fmu, L, i, j), f_p = ldf<AS>(F.fp, L, i, j);
-    const double f_lo = hlo ? ldf<AS>(fN, L, i, j) : 0.0, f_hi = hhi ? ldf<AS>(fN, L, ihi, jhi) : 0.0;
-    CellAx x = cell_axis(T, a, e, ih);
-    CellAx s = cell_sum(x);
-    CellEq q = cell_eq(P, T, e, s);
+    const double f_c = F.fc ? lda<AS>(F.fc, b.k) : 0.0, f_mu = F.fc ? lda<AS>(F.fmu, b.k) : 0.0,
+                 f_p = F.fc ? lda<AS>(F.fp, b.k) : 0.0;
+    const double f_lo = F.fc && b.hlo ? lda<AS>(fN, b.k) : 0.0, f_hi = F.fc && b.hhi ? lda<AS>(fN, b.khi) : 0.0;
+    double r, drs;
+    cell_r(K, e, r, drs);
+    const double ulo = e[a.fn], uhi = e[a.dn + a.fn];
+    const CellSum<double> xo = axis_cell<false>(K, e, a, r, drs, ulo, uhi), x = xo + other(xo);
+    const CellEq q = cell_eq(K, e, x, r, drs);
     const double r1 = f_c - q.Nc, r2 = f_mu - q.Nmu;
-    const double c0 = tq(T, T_C, e), m0 = tq(T, T_MU, e);
-    double cnew = c0, mnew = m0;
-    // coupled box: mubar eliminated by N_mu (pivot Jmm), then c by N_c (pivot
-    // 1/icc); what the box needs of the cell rows afterwards
-    double imm = 0.0, kmc = 0.0, kbm = 0.0, icc = 0.0, bc = 0.0, Jcp = 0.0, gc = 0.0;
+    const double c0 = e[T_C], m0 = e[T_MU], p0 = e[T_P];
+    const double Jcp = K.alpha * x.sm; // dN_c/dpbar = dN_p/dmubar
+    double bp = f_p - q.Np;
+    // coupled box: mubar eliminated by N_mu (pivot Jmm)
+    double kmc = 0.0, kbm = 0.0, Jc = 0.0, bc = 0.0, gc = 0.0;
     if (cpl) {
-        imm = frcp(q.Jmm);
+        const double imm = frcp(q.Jmm);
         kmc = q.Jmc * imm;
         kbm = r2 * imm;
-        icc = frcp(q.Jcc - q.Jcm * kmc);
+        Jc = q.Jcc - q.Jcm * kmc;
         bc = r1 - q.Jcm * kbm;
-        Jcp = P.alpha * P.inv_Pe * s.Sm; // dN_c/dpbar = dN_p/dmubar
-        const double rs = tq(T, T_RS, e);
-        gc = 0.25 * (-P.alpha * rs * rs) * P.inv_dt; // dN_f/dc per unit u_f
-    }
-    if (!cpl) {
+        gc = 0.5 * K.hidt * drs; // dN_f/dc per unit u_f
+    } else {
         // ---- step 1
         const double idet = frcp(q.Jcc * q.Jmm - q.Jcm * q.Jmc);
-        cnew = c0 + (q.Jmm * r1 - q.Jcm * r2) * idet;
-        mnew = m0 + (q.Jcc * r2 - q.Jmc * r1) * idet;
+        const double cnew = c0 + (q.Jmm * r1 - q.Jcm * r2) * idet;
+        const double dm = (q.Jcc * r2 - q.Jmc * r1) * idet, mnew = m0 + dm;
         if (!TO && hlf == 0) {
-            sta<AS>(L.c, k, cnew);
-            sta<AS>(L.mu, k, mnew);
+            sta<AS>(L.c, b.k, cnew);
+            sta<AS>(L.mu, b.k, mnew);
         }
-        T.s[T_C * T.W * T.H + e] = cnew;
-        T.s[T_MU * T.W * T.H + e] = mnew;
-        T.s[T_RS * T.W * T.H + e] = rho_of(P, cnew);
+        e[T_C] = cnew;
+        e[T_MU] = mnew;
+        e[T_RS] = rho_of(P, cnew);
+        // mass equation with the new mubar of the cell
+        bp -= Jcp * dm;
     }
     // ---- the box: this lane's two faces along its axis
-    const FaceEq flo = face_eq(P, T, a, e, a.it, ih);
-    const FaceEq fhi = face_eq(P, T, a, e + a.dn, a.it, ih);
-    const double blo = hlo ? f_lo - flo.N : 0.0, dlo = hlo ? flo.diag : 1.0;
-    const double bhi = hhi ? f_hi - fhi.N : 0.0, dhi = hhi ? fhi.diag : 1.0;
-    // mass equation with the new mubar of the cell (linear in it: -Sm per axis)
-    const double Lmu_new = s.Lmu - s.Sm * (mnew - m0);
-    const double bp = f_p - (s.div - P.alpha * P.inv_Pe * Lmu_new - P.alpha * P.alpha * P.inv_Pe * s.Lp);
-    // box-cell coefficients of the off-diagonal couplings
-    const double w_ax = tq(T, T_RN, e) * 0.5 * (tq(T, a.FNN, e) + tq(T, a.FNN, e + a.dn)); // rho^n a u^n
-    const double mv0 = tq(T, T_MV, e);
-    const double vis = (4.0 / 3.0) * P.inv_Re * ih2 * mv0, gd = P.inv_Re * ih2 * mv0 / 3.0;
-    const double gp = P.inv_M * ih;
-    // periodic axis of two cells: the next face beyond each box face is the
-    // box's other face, which so enters each face row a second time (through
-    // the other cell's advection weight and viscosity)
-    double xlo = 0.0, xhi = 0.0;
-    if (a.per && a.ma == 2) {
-        const double w_o = tq(T, T_RN, e - a.dn) * 0.5 * (tq(T, a.FNN, e) + tq(T, a.FNN, e + a.dn));
-        const double v_o = (4.0 / 3.0) * P.inv_Re * ih2 * tq(T, T_MV, e - a.dn);
-        xlo = -0.5 * ih * w_o - v_o;
-        xhi = 0.5 * ih * w_o - v_o;
-    }
-    // exchange: each lane of the pair now holds the rows of both axes.  A
-    // lane orders the box's unknowns with its own axis first: lane 0 as uW,
-    // uE, vS, vN, p, lane 1 as vS, vN, uW, uE, p; the rows of the two axes
-    // have the same form, so the matrix is assembled without selecting by
-    // lane, and each lane eliminates its own faces first (lane 0 in the
-    // order of the oracle, lane 1 with the axes swapped, a symmetric
-    // permutation that keeps the pivots positive)
-    const double o_blo = other(blo), o_dlo = other(dlo), o_bhi = other(bhi), o_dhi = other(dhi), o_w = other(w_ax);
-    const double o_xlo = other(xlo), o_xhi = other(xhi);
-    const int o_hlo = other((int)hlo), o_hhi = other((int)hhi);
-    double A[5][5], b[5];
-    b[0] = blo; b[1] = bhi; b[2] = o_blo; b[3] = o_bhi; b[4] = bp;
-    // rows: momentum at the own axis' low and high faces, the other axis' low
-    // and high faces, then mass; columns in the same order; a face on a wall
-    // is not an unknown (identity row, no coupling)
-    const double m0l = hlo ? 1.0 : 0.0, m0h = hhi ? 1.0 : 0.0, m1l = o_hlo ? 1.0 : 0.0, m1h = o_hhi ? 1.0 : 0.0;
-    A[0][0] = dlo; A[0][1] = m0l * (0.5 * ih * w_ax - vis) + xlo; A[0][2] = m0l * gd; A[0][3] = -m0l * gd; A[0][4] = m0l * gp;
-    A[1][1] = dhi; A[1][0] = m0h * (-0.5 * ih * w_ax - vis) + xhi; A[1][2] = -m0h * gd; A[1][3] = m0h * gd; A[1][4] = -m0h * gp;
-    A[2][2] = o_dlo; A[2][3] = m1l * (0.5 * ih * o_w - vis) + o_xlo; A[2][0] = m1l * gd; A[2][1] = -m1l * gd; A[2][4] = m1l * gp;
-    A[3][3] = o_dhi; A[3][2] = m1h * (-0.5 * ih * o_w - vis) + o_xhi; A[3][0] = -m1h * gd; A[3][1] = m1h * gd; A[3][4] = -m1h * gp;
-    A[4][0] = -m0l * ih; A[4][1] = m0h * ih; A[4][2] = -m1l * ih; A[4][3] = m1h * ih; A[4][4] = q.Jpp;
-    // coupled box: border of the c and mubar rows and columns, eliminated
-    // into the 5x5 system (see above)
-    double ac[5] = { 0.0, 0.0, 0.0, 0.0, 0.0 };
-    if (cpl) {
-        const int e1 = e + a.dn;
-        const double alo = hlo ? 0.5 * ih * tq(T, T_RN, e - a.dn) * (tq(T, T_CN, e) - tq(T, T_CN, e - a.dn)) : 0.0;
-        const double ahi = hhi ? 0.5 * ih * tq(T, T_RN, e1) * (tq(T, T_CN, e1) - tq(T, T_CN, e)) : 0.0;
-        const double ulo = hlo ? tq(T, a.FN, e) : 0.0, uhi = hhi ? tq(T, a.FN, e1) : 0.0;
-        ac[0] = alo; ac[1] = ahi; ac[2] = other(alo); ac[3] = other(ahi);
-        const double uf[4] = { ulo, uhi, other(ulo), other(uhi) };
-        ac[4] = Jcp;
-        double gam[5];
-#pragma unroll
-        for (int f = 0; f < 4; f++) {
-            const double lam = -P.inv_M * ac[f];
-            gam[f] = gc * uf[f] - lam * kmc;
-            b[f] -= lam * kbm;
-        }
-        gam[4] = -Jcp * kmc;
-        b[4] -= Jcp * kbm;
-#pragma unroll
-        for (int r = 0; r < 5; r++) {
-            const double t = gam[r] * icc;
-#pragma unroll
-            for (int cc = 0; cc < 5; cc++) A[r][cc] -= t * ac[cc];
-            b[r] -= t * bc;
-        }
-    }
-    // Gaussian elimination in the lane's order (own faces, other faces, p):
-    // the velocity block has a positive definite symmetric part (mass +
-    // viscous; advection is skew) and the last pivot is the positive pressure
-    // Schur complement
-    double inv[5];
-#pragma unroll
-    for (int c = 0; c < 4; c++) {
-        inv[c] = frcp(A[c][c]);
-#pragma unroll
-        for (int r = c + 1; r < 5; r++) {
-            const double l = A[r][c] * inv[c];
-#pragma unroll
-            for (int t = c + 1; t < 5; t++) A[r][t] -= l * A[c][t];
-            b[r] -= l * b[c];
-        }
-    }
-    inv[4] = frcp(A[4][4]);
-#pragma unroll
-    for (int c = 4; c >= 0; c--) {
-        double acc = b[c];
-#pragma unroll
-        for (int t = c + 1; t < 5; t++) acc -= A[c][t] * b[t];
-        b[c] = acc * inv[c];
-    }
-    if (cpl && hlf == 0) {
-        double acc = bc;
-#pragma unroll
-        for (int t = 0; t < 5; t++) acc -= ac[t] * b[t];
-        const double dc = acc * icc;
-        if (TO) {
-            const int n = T.W * T.H;
-            T.s[T_C * n + e] = c0 + dc;
-            T.s[T_MU * n + e] = m0 + kbm - kmc * dc;
-            T.s[T_RS * n + e] = rho_of(P, c0 + dc);
-        } else {
-            sta<AS>(L.c, k, c0 + dc);
-            sta<AS>(L.mu, k, m0 + kbm - kmc * dc);
-        }
-    }
-    const double nlo = tq(T, a.FN, e) + omega * b[0], nhi = tq(T, a.FN, e + a.dn) + omega * b[1];
+    const FaceEq<double> flo = face_eq<double, false, false>(K, e, a), fhi = face_eq<double, false, false>(K, e + a.dn, a);
+    const double *P1 = e + a.dn, *M1 = e - a.dn;
+    const double alo = b.hlo ? K.hih * (M1[T_RN] * (e[T_CN] - M1[T_CN])) : 0.0;
+    const double ahi = b.hhi ? K.hih * (P1[T_RN] * (P1[T_CN] - e[T_CN])) : 0.0;
+    double alh, ahl;
+    box_offdiag(K, e, a, b.hlo, b.hhi, alh, ahl);
+    const double sb = kbm * K.iM, sc = kmc * K.iM;
+    const double blo = b.hlo ? (f_lo - flo.N) + sb * alo : 0.0, bhi = b.hhi ? (f_hi - fhi.N) + sb * ahi : 0.0;
+    const double qlo = b.hlo ? gc * ulo + sc * alo : 0.0, qhi = b.hhi ? gc * uhi + sc * ahi : 0.0;
+    const BoxAx<double> X = box_axis(b.hlo ? flo.diag : 1.0, b.hhi ? fhi.diag : 1.0, alh, ahl, blo, bhi,
+                                     b.hlo ? 1.0 : 0.0, b.hhi ? -1.0 : 0.0, qlo, qhi, alo, ahi);
+    double dp, dc, t, tt;
+    box_solve(X, box_other(X), cpl, K.kv * e[T_MV], K.kp, K.ih, K.alpha * Jcp, Jcp, kmc, kbm, Jc, bp, bc, dp, dc, t, tt);
+    const double nlo = ulo + omega * ((X.xb[0] + t * X.xs[0]) - dc * X.xq[0]);
+    const double nhi = uhi + omega * ((X.xb[1] + t * X.xs[1]) - dc * X.xq[1]);
+    const double np = p0 + omega * dp;
     if (TO) {
-        const int n = T.W * T.H;
-        double *fo = T.s + (T_NF + hlf) * n;
-        if (hlo) fo[e] = nlo;
-        if (hhi) fo[e + a.dn] = nhi;
-        if (hlf == 0) T.s[T_P * n + e] = tq(T, T_P, e) + omega * b[4];
+        if (b.hlo) e[T_U2 + hlf] = nlo;
+        if (b.hhi) e[a.dn + T_U2 + hlf] = nhi;
+        if (hlf == 0) {
+            e[T_P] = np;
+            if (cpl) {
+                e[T_C] = c0 + dc;
+                e[T_MU] = m0 + (kbm - kmc * dc);
+                e[T_RS] = rho_of(P, c0 + dc);
+            }
+        }
         return;
     }
-    if (hlf) {
-        if (hlo) sta<AS>(vnew, k, nlo);
-        if (hhi) sta<AS>(vnew, khi, nhi);
-    } else {
-        if (hlo) sta<AS>(unew, k, nlo);
-        if (hhi) sta<AS>(unew, khi, nhi);
+    double *fo = hlf ? vnew : unew;
+    if (b.hlo) sta<AS>(fo, b.k, nlo);
+    if (b.hhi) sta<AS>(fo, b.khi, nhi);
+    if (hlf == 0) {
+        sta<AS>(L.p, b.k, np);
+        if (cpl) {
+            sta<AS>(L.c, b.k, c0 + dc);
+            sta<AS>(L.mu, b.k, m0 + (kbm - kmc * dc));
+        }
     }
-    if (hlf == 0) sta<AS>(L.p, k, tq(T, T_P, e) + omega * b[4]);
 }
-template <int AS>
-__device__ __forceinline__ void relax_pair(const Phys &P, const View &L, const Tile &T, const Rhs &F, double *unew,
-                                           double *vnew, int i, int j, int hlf, double omega, double pomega)
+
+// the projection scheme's phase and chemical rows, which differ from the
+// primitive ones in rho^n (c - c^n)/dt and rho^n mubar ((pj-num-phase),
+// (pj-num-chem); the advection at time n+1 is in x.s1)
+__device__ __forceinline__ void pj_cell(const Kon<double> &K, const double *s, const CellSum<double> &x, double drs, CellEq &q)
 {
-    relax_cell<false, AS>(P, L, T, F, unew, vnew, i, j, i, j, hlf, omega, pomega);
+    const double rs = s[T_RS], rn = s[T_RN], mu = s[T_MU];
+    q.Nc = K.idt * (rn * (s[T_C] - s[T_CN])) + x.s1;
+    q.Nmu -= (rs - rn) * mu;
+    q.Jcc = K.idt * rn; // and the advection's derivative
+    q.Jmm = rn;
+    q.Jmc -= drs * mu;
 }
 
 // residuals r = f - N(w) of the five equations attached to cell (i,j): the
-// cell equations and the momentum equation of its west face (lane 0) or south
-// face (lane 1); zero for a face on a wall.  Both lanes return rc, rm, rp;
-// rf is this lane's face residual.  The level and its right-hand sides are
-// in global memory.
-__device__ __forceinline__ void resid_pair(const Phys &P, const View &L, const Tile &T, const Rhs &F, int i, int j,
-                                           int hlf, double &rc, double &rm, double &rp, double &rf)
+// cell equations and the momentum equations of its west and south faces (zero
+// for a face on a wall), by one lane.  The level and its right-hand sides
+// (F.fc NULL: none) are in global memory.
+struct Resid {
+    double c, mu, p, u, v;
+};
+// the projection equation (pj-num-pjx) on the face at element s of an axis:
+//   u = u~ + dt / A rho (A(rho_ew mubar) D c / M - D pbar / M - grav),
+// rho = rho(c) and c, mubar of the iterate, grav = (1/Fr)(A_y rho - rho_ref)
+// on north-south faces (gravity acts in the projection equation, as in the
+// time-discrete scheme (pj-pj)); zero on a wall face.  ut is u~ on the face;
+// w receives 2 dt / (2 A rho).
+__device__ __forceinline__ double face_final(const Kon<double> &K, const double *s, const Ax &a, bool unk, double ut,
+                                             double &w)
 {
-    if (P.scheme) {
-        resid_pair_pj(P, L, T, F, i, j, hlf, rc, rm, rp, rf);
-        return;
+    const double *L = s - a.dn;
+    const double rL = L[T_RS], rR = s[T_RS], A2 = rL + rR;
+    const double st = 0.5 * (rR * L[T_MU] + rL * s[T_MU]) * (s[T_C] - L[T_C]);
+    double f = K.kp * (st - (s[T_P] - L[T_P]));
+    if (a.hlf) f -= K.inv_Fr * (0.5 * A2 - K.rho_ref);
+    w = K.dt2 * frcp(A2);
+    return unk ? ut + w * f : 0.0;
+}
+
+template <bool PJ>
+__device__ __forceinline__ Resid resid_cell(const Kon<double> &K, const View &L, const Tile &T, const Rhs &F, int i,
+                                            int j)
+{
+    const double *e = T.at(i, j);
+    const Ax ax = make_ax(L, T, i, j, 0), ay = make_ax(L, T, i, j, 1);
+    const size_t k = (size_t)j * L.pitch + i;
+    Resid f = {};
+    if (F.fc) f = { lda<1>(F.fc, k), lda<1>(F.fmu, k), lda<1>(F.fp, k), lda<1>(F.fu, k), lda<1>(F.fv, k) };
+    const bool hu = ax.per || i >= 1, hv = ay.per || j >= 1;
+    double ulo = e[T_U], uhi = e[ax.dn + T_U], vlo = e[T_V], vhi = e[ay.dn + T_V];
+    if (PJ) {
+        double w;
+        ulo = face_final(K, e, ax, hu, ulo, w);
+        uhi = face_final(K, e + ax.dn, ax, ax.per || i + 1 < L.m1, uhi, w);
+        vlo = face_final(K, e, ay, hv, vlo, w);
+        vhi = face_final(K, e + ay.dn, ay, ay.per || j + 1 < L.m2, vhi, w);
     }
-    const int e = T.idx(i, j);
-    const Ax a = make_ax(L, T, i, j, hlf);
-    const CellAx s = cell_sum(cell_axis(T, a, e, L.inv_h));
-    const CellEq q = cell_eq(P, T, e, s);
-    rc = ldf<1>(F.fc, L, i, j) - q.Nc;
-    rm = ldf<1>(F.fmu, L, i, j) - q.Nmu;
-    rp = ldf<1>(F.fp, L, i, j) - q.Np;
-    const bool hlo = a.per || a.ia >= 1;
-    const FaceEq f = face_eq(P, T, a, e, a.it, L.inv_h);
-    rf = hlo ? ldf<1>(face_rhs(F, hlf), L, i, j) - f.N : 0.0;
+    double r, drs;
+    cell_r(K, e, r, drs);
+    const CellSum<double> x = axis_cell<PJ>(K, e, ax, r, drs, ulo, uhi) + axis_cell<PJ>(K, e, ay, r, drs, vlo, vhi);
+    CellEq q = cell_eq(K, e, x, r, drs);
+    if (PJ) pj_cell(K, e, x, drs, q);
+    const FaceEq<double> fu = face_eq<double, PJ, false>(K, e, ax), fv = face_eq<double, PJ, false>(K, e, ay);
+    return { f.c - q.Nc, f.mu - q.Nmu, f.p - q.Np, hu ? f.u - fu.N : 0.0, hv ? f.v - fv.N : 0.0 };
 }
 
 // --------------------------------------------------------------------------
 // Projection scheme (sec. 6.2).  The unknowns are c, mubar, pbar and the
 // intermediate velocity u~, which the face fields (T_U, T_V) hold during a
 // step.  The velocity of time n+1 is eliminated through the projection
-// equation (pj-num-pjx): on the face at element ef of the lane's axis,
-//   u = u~ + dt / A rho (A(rho_ew mubar) D c / M - D pbar / M - grav),
-// rho = rho(c) and c, mubar of the iterate, grav = (1/Fr)(A_y rho - rho_ref)
-// on north-south faces (gravity acts in the projection equation, as in the
-// time-discrete scheme (pj-pj)); zero on a wall face.  ut is u~ on the face.
-__device__ __forceinline__ double face_final(const Phys &P, const Tile &T, const Ax &a, int ef, double ih, bool unk,
-                                             double ut)
-{
-    const int eL = ef - a.dn;
-    const double rL = tq(T, T_RS, eL), rR = tq(T, T_RS, ef), Ar = 0.5 * (rL + rR);
-    const double st = 0.5 * (rR * tq(T, T_MU, eL) + rL * tq(T, T_MU, ef)) * (tq(T, T_C, ef) - tq(T, T_C, eL)) * ih;
-    const double f = P.inv_M * (st - (tq(T, T_P, ef) - tq(T, T_P, eL)) * ih) - a.grav * P.inv_Fr * (Ar - P.rho_ref);
-    return unk ? ut + P.dt * frcp(Ar) * f : 0.0;
-}
-
-// axis parts of the projection cell equations from the velocity of time n+1
-// on the lane's two faces (ulo, uhi): the advection of (pj-num-phase) in the
-// form (e1e2) of App. A.5 at time n+1, its derivative in the cell's own c (the
-// velocities held fixed), and the divergence of (pj-num-mass)
-struct PjAx {
-    double adv, dadv, div;
-};
-__device__ __forceinline__ PjAx pj_axis(const Tile &T, const Ax &a, int e, double ih, double ulo, double uhi)
-{
-    const int eP = e + a.dn, eM = e - a.dn;
-    const double c = tq(T, T_C, e), rP = tq(T, T_RS, eP), rM = tq(T, T_RS, eM);
-    PjAx x;
-    x.adv = 0.5 * ih * (rP * (tq(T, T_C, eP) - c) * uhi + rM * (c - tq(T, T_C, eM)) * ulo);
-    x.dadv = 0.5 * ih * (rM * ulo - rP * uhi);
-    x.div = ih * (uhi - ulo);
-    return x;
-}
-
+// equation (face_final).
+//
 // Smoother of sec. 7.2 for one cell of the current colour, by a lane pair:
 //  1. one Newton step on (N_c, N_mu) in (c, mubar) of the cell, the velocity
 //     of time n+1 on its faces held at its value before the update; with the
@@ -924,175 +963,102 @@ __device__ __forceinline__ PjAx pj_axis(const Tile &T, const Ax &a, int e, doubl
 //  3. one Newton step in pbar on the mass equation (pj-num-mass) with the
 //     velocity of time n+1 from the new u~, c, mubar (exact: linear in pbar);
 //  4. the velocity of time n+1 is never stored, so nothing is left to update.
-// (pj-num-phase) and (pj-num-chem) differ from the primitive equations in
-// rho^n (c - c^n)/dt, the advection at time n+1 and rho^n mubar.  The tile
-// entries of the cell (c, mubar, rho(c)) are updated after step 1; no other
-// pair of this colour reads them.
+// The tile entries of the cell (c, mubar, rho(c)) are updated after step 1; no
+// other pair of this colour reads them.
 template <bool TO, int AS>
-__device__ __forceinline__ void relax_pair_pj(const Phys &P, const View &L, const Tile &T, const Rhs &F, double *unew, double *vnew,
-                              int i, int j, int ti, int tj, int hlf, double omega, double pomega)
+__device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, const View &L, const Tile &T, const Rhs &F,
+                                         double *unew, double *vnew, int i, int j, int ti, int tj, int hlf,
+                                         double omega, double pomega)
 {
-    const size_t k = (size_t)j * L.pitch + i;
-    const double ih = L.inv_h, ih2 = ih * ih;
-    const int e = T.idx(ti, tj);
-    const Ax a = make_ax(L, T, i, j, hlf);
-    const bool hlo = a.per || a.ia >= 1, hhi = a.per || a.ia + 1 < a.ma;
-    const int st = T.W * T.H;
+    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf);
+    const Ax &a = b.a;
+    double *const e = T.at(ti, tj);
+    const double *P1 = e + a.dn, *M1 = e - a.dn;
+    const double *fN = face_rhs(F, hlf);
+    const double f_c = F.fc ? lda<AS>(F.fc, b.k) : 0.0, f_mu = F.fc ? lda<AS>(F.fmu, b.k) : 0.0,
+                 f_p = F.fc ? lda<AS>(F.fp, b.k) : 0.0;
+    const double f_lo = F.fc && b.hlo ? lda<AS>(fN, b.k) : 0.0, f_hi = F.fc && b.hhi ? lda<AS>(fN, b.khi) : 0.0;
     // ---- step 1
-    const double ulo0 = face_final(P, T, a, e, ih, hlo, tq(T, a.FN, e));
-    const double uhi0 = face_final(P, T, a, e + a.dn, ih, hhi, tq(T, a.FN, e + a.dn));
-    const PjAx x0 = pj_axis(T, a, e, ih, ulo0, uhi0);
-    const CellAx s = cell_sum(cell_axis(T, a, e, ih));
-    const CellEq q = cell_eq(P, T, e, s);
-    const double adv = x0.adv + other(x0.adv), dadv = x0.dadv + other(x0.dadv);
-    const double c0 = tq(T, T_C, e), m0 = tq(T, T_MU, e), n0 = tq(T, T_CN, e);
-    const double rs = tq(T, T_RS, e), rn = tq(T, T_RN, e), drs = -P.alpha * rs * rs;
-    const double Nc = rn * (c0 - n0) * P.inv_dt + adv - P.inv_Pe * s.Lmu - P.alpha * P.inv_Pe * s.Lp;
-    const double Nmu = q.Nmu - (rs - rn) * m0;
-    const double Jcc = rn * P.inv_dt + dadv, Jcm = q.Jcm, Jmm = rn, Jmc = q.Jmc - drs * m0;
-    const double r1 = ldf<AS>(F.fc, L, i, j) - Nc, r2 = ldf<AS>(F.fmu, L, i, j) - Nmu;
-    const double p0 = tq(T, T_P, e);
-    double cnew, mnew, pnew = p0;
+    double wlo, whi;
+    const double ulo0 = face_final(K, e, a, b.hlo, e[a.fn], wlo);
+    const double uhi0 = face_final(K, P1, a, b.hhi, P1[a.fn], whi);
+    double r, drs;
+    cell_r(K, e, r, drs);
+    const CellSum<double> xo = axis_cell<true>(K, e, a, r, drs, ulo0, uhi0), x = xo + other(xo);
+    CellEq q = cell_eq(K, e, x, r, drs);
+    pj_cell(K, e, x, drs, q);
+    const double dax = K.hih * (M1[T_RS] * ulo0 - P1[T_RS] * uhi0);
+    q.Jcc += dax + other(dax);
+    const double c0 = e[T_C], m0 = e[T_MU], p0 = e[T_P];
+    const double r1 = f_c - q.Nc, r2 = f_mu - q.Nmu;
+    const double Jpm = K.alpha * x.sm;
+    double dc, dm, pnew = p0;
     if (P.coupled) {
         // pbar joins the step with the mass equation: its column lets the
         // velocity of time n+1 follow pbar through (pj-num-pjx) (on the lo
         // face D pbar falls by pbar/h, on the hi face it rises), the c and
         // mubar columns hold it
-        const double dlo = hlo ? -P.dt * P.inv_M * ih * frcp(0.5 * (tq(T, T_RS, e - a.dn) + rs)) : 0.0;
-        const double dhi = hhi ? P.dt * P.inv_M * ih * frcp(0.5 * (rs + tq(T, T_RS, e + a.dn))) : 0.0;
-        const double cl = 0.5 * ih * (tq(T, T_RS, e - a.dn) * (c0 - tq(T, T_C, e - a.dn)) * dlo
-                                      + tq(T, T_RS, e + a.dn) * (tq(T, T_C, e + a.dn) - c0) * dhi);
-        const double jx = ih * (dhi - dlo), dv = x0.div;
-        const double Jcp = cl + other(cl) + P.alpha * P.inv_Pe * s.Sm, Jpm = P.alpha * P.inv_Pe * s.Sm;
-        const double Jpp = jx + other(jx) + q.Jpp;
-        const double Np = dv + other(dv) - P.alpha * P.inv_Pe * s.Lmu - P.alpha * P.alpha * P.inv_Pe * s.Lp;
-        const double r3 = ldf<AS>(F.fp, L, i, j) - Np;
+        const double dlo = b.hlo ? -K.kp * wlo : 0.0, dhi = b.hhi ? K.kp * whi : 0.0;
+        const double cl = K.hih * (M1[T_RS] * (c0 - M1[T_C]) * dlo + P1[T_RS] * (P1[T_C] - c0) * dhi);
+        const double jx = K.ih * (dhi - dlo);
+        const double Jcp = cl + other(cl) + Jpm, Jpp = jx + other(jx) + K.alpha * Jpm;
+        const double r3 = f_p - q.Np;
         // eliminate pbar by the mass row (pivot Jpp), then mubar by the
         // chemical row (pivot Jmm): a 2x2 system in c and mubar remains
         const double ipp = frcp(Jpp);
-        const double kcm = Jcm - Jcp * Jpm * ipp, rc1 = r1 - Jcp * r3 * ipp;
-        const double idet = frcp(Jcc * Jmm - kcm * Jmc);
-        const double dc = (Jmm * rc1 - kcm * r2) * idet;
-        const double dm = (Jcc * r2 - Jmc * rc1) * idet;
-        cnew = c0 + dc;
-        mnew = m0 + dm;
+        const double kcm = q.Jcm - Jcp * Jpm * ipp, rc1 = r1 - Jcp * r3 * ipp;
+        const double idet = frcp(q.Jcc * q.Jmm - kcm * q.Jmc);
+        dc = (q.Jmm * rc1 - kcm * r2) * idet;
+        dm = (q.Jcc * r2 - q.Jmc * rc1) * idet;
         pnew = p0 + (r3 - Jpm * dm) * ipp;
-        T.s[T_P * st + e] = pnew;
+        e[T_P] = pnew;
     } else {
-        const double idet = frcp(Jcc * Jmm - Jcm * Jmc);
-        cnew = c0 + (Jmm * r1 - Jcm * r2) * idet;
-        mnew = m0 + (Jcc * r2 - Jmc * r1) * idet;
+        const double idet = frcp(q.Jcc * q.Jmm - q.Jcm * q.Jmc);
+        dc = (q.Jmm * r1 - q.Jcm * r2) * idet;
+        dm = (q.Jcc * r2 - q.Jmc * r1) * idet;
     }
+    const double cnew = c0 + dc, mnew = m0 + dm;
     if (!TO && hlf == 0) {
-        sta<AS>(L.c, k, cnew);
-        sta<AS>(L.mu, k, mnew);
+        sta<AS>(L.c, b.k, cnew);
+        sta<AS>(L.mu, b.k, mnew);
     }
-    T.s[T_C * st + e] = cnew;
-    T.s[T_MU * st + e] = mnew;
-    T.s[T_RS * st + e] = rho_of(P, cnew);
-    // ---- step 2: the intermediate-velocity box
-    const FaceEq flo = face_eq(P, T, a, e, a.it, ih, true);
-    const FaceEq fhi = face_eq(P, T, a, e + a.dn, a.it, ih, true);
-    const double *fN = face_rhs(F, hlf);
-    const int ihi = hlf ? i : (i + 1 < L.m1 ? i + 1 : 0), jhi = hlf ? (j + 1 < L.m2 ? j + 1 : 0) : j;
-    const size_t khi = (size_t)jhi * L.pitch + ihi;
-    const double blo = hlo ? ldf<AS>(fN, L, i, j) - flo.N : 0.0, dlo = hlo ? flo.diag : 1.0;
-    const double bhi = hhi ? ldf<AS>(fN, L, ihi, jhi) - fhi.N : 0.0, dhi = hhi ? fhi.diag : 1.0;
-    const double w_ax = tq(T, T_RN, e) * 0.5 * (tq(T, a.FNN, e) + tq(T, a.FNN, e + a.dn));
-    const double mv0 = tq(T, T_MV, e);
-    const double vis = (4.0 / 3.0) * P.inv_Re * ih2 * mv0, gd = P.inv_Re * ih2 * mv0 / 3.0;
-    double xlo = 0.0, xhi = 0.0;
-    if (a.per && a.ma == 2) {
-        const double w_o = tq(T, T_RN, e - a.dn) * 0.5 * (tq(T, a.FNN, e) + tq(T, a.FNN, e + a.dn));
-        const double v_o = (4.0 / 3.0) * P.inv_Re * ih2 * tq(T, T_MV, e - a.dn);
-        xlo = -0.5 * ih * w_o - v_o;
-        xhi = 0.5 * ih * w_o - v_o;
-    }
-    // the four faces in the lane's order, its own axis first (as in the box
-    // of the primitive scheme)
-    const double o_blo = other(blo), o_dlo = other(dlo), o_bhi = other(bhi), o_dhi = other(dhi), o_w = other(w_ax);
-    const double o_xlo = other(xlo), o_xhi = other(xhi);
-    const int o_hlo = other((int)hlo), o_hhi = other((int)hhi);
-    double A[4][4], b[4];
-    b[0] = blo; b[1] = bhi; b[2] = o_blo; b[3] = o_bhi;
-    const double m0l = hlo ? 1.0 : 0.0, m0h = hhi ? 1.0 : 0.0, m1l = o_hlo ? 1.0 : 0.0, m1h = o_hhi ? 1.0 : 0.0;
-    A[0][0] = dlo; A[0][1] = m0l * (0.5 * ih * w_ax - vis) + xlo; A[0][2] = m0l * gd; A[0][3] = -m0l * gd;
-    A[1][1] = dhi; A[1][0] = m0h * (-0.5 * ih * w_ax - vis) + xhi; A[1][2] = -m0h * gd; A[1][3] = m0h * gd;
-    A[2][2] = o_dlo; A[2][3] = m1l * (0.5 * ih * o_w - vis) + o_xlo; A[2][0] = m1l * gd; A[2][1] = -m1l * gd;
-    A[3][3] = o_dhi; A[3][2] = m1h * (-0.5 * ih * o_w - vis) + o_xhi; A[3][0] = -m1h * gd; A[3][1] = m1h * gd;
-    double inv[4];
-#pragma unroll
-    for (int c = 0; c < 3; c++) {
-        inv[c] = frcp(A[c][c]);
-#pragma unroll
-        for (int r = c + 1; r < 4; r++) {
-            const double l = A[r][c] * inv[c];
-#pragma unroll
-            for (int t = c + 1; t < 4; t++) A[r][t] -= l * A[c][t];
-            b[r] -= l * b[c];
-        }
-    }
-    inv[3] = frcp(A[3][3]);
-#pragma unroll
-    for (int c = 3; c >= 0; c--) {
-        double acc = b[c];
-#pragma unroll
-        for (int t = c + 1; t < 4; t++) acc -= A[c][t] * b[t];
-        b[c] = acc * inv[c];
-    }
-    const double ulo = tq(T, a.FN, e) + omega * b[0];
-    const double uhi = tq(T, a.FN, e + a.dn) + omega * b[1];
+    e[T_C] = cnew;
+    e[T_MU] = mnew;
+    e[T_RS] = rho_of(P, cnew);
+    // ---- step 2: the intermediate-velocity box; the axes couple through the
+    // viscous terms alone: V x = b + s gd D_o
+    const FaceEq<double> flo = face_eq<double, true, false>(K, e, a), fhi = face_eq<double, true, false>(K, P1, a);
+    double alh, ahl;
+    box_offdiag(K, e, a, b.hlo, b.hhi, alh, ahl);
+    const double gd = K.kv * e[T_MV];
+    const BoxAx<double> X = box_axis(b.hlo ? flo.diag : 1.0, b.hhi ? fhi.diag : 1.0, alh, ahl,
+                                     b.hlo ? f_lo - flo.N : 0.0, b.hhi ? f_hi - fhi.N : 0.0, b.hlo ? 1.0 : 0.0,
+                                     b.hhi ? -1.0 : 0.0, 0.0, 0.0, 0.0, 0.0);
+    const double oDb = other(X.Db), oDs = other(X.Ds);
+    const double gx = gd * X.Ds, gy = gd * oDs;
+    const double t = gd * ((oDb + gy * X.Db) * frcp(1.0 - gx * gy));
+    const double ut0 = e[a.fn], ut1 = P1[a.fn];
+    const double ulo = ut0 + omega * (X.xb[0] + t * X.xs[0]), uhi = ut1 + omega * (X.xb[1] + t * X.xs[1]);
     if (TO) {
-        double *fo = T.s + (T_NF + hlf) * st;
-        if (hlo) fo[e] = ulo;
-        if (hhi) fo[e + a.dn] = uhi;
-    } else if (hlf) {
-        if (hlo) sta<AS>(vnew, k, ulo);
-        if (hhi) sta<AS>(vnew, khi, uhi);
+        if (b.hlo) e[T_U2 + hlf] = ulo;
+        if (b.hhi) e[a.dn + T_U2 + hlf] = uhi;
     } else {
-        if (hlo) sta<AS>(unew, k, ulo);
-        if (hhi) sta<AS>(unew, khi, uhi);
+        double *fo = hlf ? vnew : unew;
+        if (b.hlo) sta<AS>(fo, b.k, ulo);
+        if (b.hhi) sta<AS>(fo, b.khi, uhi);
     }
     // ---- step 3: pbar from the mass equation with the new u~ (passed by
     // value: the tile keeps the snapshot that other boxes of this colour read)
-    const double ulo1 = face_final(P, T, a, e, ih, hlo, ulo), uhi1 = face_final(P, T, a, e + a.dn, ih, hhi, uhi);
-    const double Alo = 0.5 * (tq(T, T_RS, e - a.dn) + tq(T, T_RS, e)), Ahi = 0.5 * (tq(T, T_RS, e) + tq(T, T_RS, e + a.dn));
-    const double jax = P.dt * P.inv_M * ih2 * ((hlo ? frcp(Alo) : 0.0) + (hhi ? frcp(Ahi) : 0.0));
-    const double dv = ih * (uhi1 - ulo1);
-    const double div = dv + other(dv), jp = jax + other(jax);
-    const double Lmu_new = s.Lmu - s.Sm * (mnew - m0), Lp_new = s.Lp - s.Sm * (pnew - p0);
-    const double Np = div - P.alpha * P.inv_Pe * Lmu_new - P.alpha * P.alpha * P.inv_Pe * Lp_new;
-    const double Jp = jp + q.Jpp;
+    const double ulo1 = face_final(K, e, a, b.hlo, ulo, wlo), uhi1 = face_final(K, P1, a, b.hhi, uhi, whi);
+    const double jax = (K.ih * K.kp) * ((b.hlo ? wlo : 0.0) + (b.hhi ? whi : 0.0));
+    const double dv = K.ih * ((uhi1 - ulo1) - (uhi0 - ulo0));
+    const double Np = q.Np + (dv + other(dv)) + Jpm * (dm + K.alpha * (pnew - p0));
+    const double Jp = jax + other(jax) + K.alpha * Jpm;
     if (hlf == 0) {
-        const double pf = pnew + pomega * (ldf<AS>(F.fp, L, i, j) - Np) * frcp(Jp);
-        if (TO) T.s[T_P * st + e] = pf;
-        else sta<AS>(L.p, k, pf);
+        const double pf = pnew + pomega * (f_p - Np) * frcp(Jp);
+        if (TO) e[T_P] = pf;
+        else sta<AS>(L.p, b.k, pf);
     }
-}
-
-// residuals of the projection scheme's five equations attached to cell (i,j)
-// (as resid_pair: rf is the intermediate-velocity momentum residual of this
-// lane's west or south face)
-__device__ __forceinline__ void resid_pair_pj(const Phys &P, const View &L, const Tile &T, const Rhs &F, int i, int j, int hlf,
-                              double &rc, double &rm, double &rp, double &rf)
-{
-    const double ih = L.inv_h;
-    const int e = T.idx(i, j);
-    const Ax a = make_ax(L, T, i, j, hlf);
-    const bool hlo = a.per || a.ia >= 1, hhi = a.per || a.ia + 1 < a.ma;
-    const double ulo = face_final(P, T, a, e, ih, hlo, tq(T, a.FN, e));
-    const double uhi = face_final(P, T, a, e + a.dn, ih, hhi, tq(T, a.FN, e + a.dn));
-    const PjAx x = pj_axis(T, a, e, ih, ulo, uhi);
-    const CellAx s = cell_sum(cell_axis(T, a, e, ih));
-    const CellEq q = cell_eq(P, T, e, s);
-    const double adv = x.adv + other(x.adv), div = x.div + other(x.div);
-    const double c0 = tq(T, T_C, e), m0 = tq(T, T_MU, e), n0 = tq(T, T_CN, e);
-    const double rs = tq(T, T_RS, e), rn = tq(T, T_RN, e);
-    rc = ldf<1>(F.fc, L, i, j) - (rn * (c0 - n0) * P.inv_dt + adv - P.inv_Pe * s.Lmu - P.alpha * P.inv_Pe * s.Lp);
-    rm = ldf<1>(F.fmu, L, i, j) - (q.Nmu - (rs - rn) * m0);
-    rp = ldf<1>(F.fp, L, i, j) - (div - P.alpha * P.inv_Pe * s.Lmu - P.alpha * P.alpha * P.inv_Pe * s.Lp);
-    const FaceEq f = face_eq(P, T, a, e, a.it, ih, true);
-    rf = hlo ? ldf<1>(face_rhs(F, hlf), L, i, j) - f.N : 0.0;
 }
 
 } // namespace qn

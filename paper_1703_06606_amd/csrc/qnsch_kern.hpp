@@ -38,7 +38,8 @@ namespace qn {
 #endif
 #define HS_ATTR __launch_bounds__(TBLK)
 #define FINE_ATTR __launch_bounds__(TBLK) __attribute__((amdgpu_waves_per_eu(QN_FINE_WAVES)))
-#define TILE_DOUBLES (T_NF * (TX + 3) * (TY + 3))
+#define TILE_DOUBLES (T_ES * (TX + 3) * (TY + 3))
+#define TILE_LDS __shared__ __attribute__((aligned(16)))
 #define NXCD 8
 #define MAXITEMS 64
 static_assert(TILE_DOUBLES * 8 + 16 * NRED * 8 <= 65536, "tile exceeds 64 KiB of LDS");
@@ -46,6 +47,7 @@ static_assert(TILE_DOUBLES * 8 + 16 * NRED * 8 <= 65536, "tile exceeds 64 KiB of
 // one level of one simulation, in device memory
 struct Desc {
     Phys P;
+    Kon<double> K;
     double *c, *mu, *p, *ub[2], *vb[2], *cn, *un, *vn; // level arrays (u/v ping-pong)
     double *fc, *fmu, *fp, *fu, *fv;                    // FAS right-hand side (NULL on the finest level)
     double *c0, *mu0, *p0, *u0, *v0;                    // restricted iterate (coarse levels)
@@ -66,12 +68,12 @@ struct Desc {
     // mixed precision: the FP32 correction hierarchy (NULL in FP64 mode; on
     // coarse levels the FP64 arrays above are NULL instead)
     PhysF Pf;
+    Kon<float> Kf;
     float *xc, *xmu, *xu, *xv;                          // linearisation point
     float *dc, *dmu, *dp, *dub[2], *dvb[2];             // correction (u/v ping-pong)
     float *rc, *rmu, *rp, *ru, *rv;                     // right-hand side
     float *dc2, *dmu2, *dp2;                            // second set of cell corrections (fused sweeps)
     float *cnf, *unf, *vnf;                             // time-n data
-    float finv_h;
 };
 
 // (The small entries are 32-bit: a kernel reads them with scalar loads,
@@ -128,14 +130,14 @@ __device__ __forceinline__ Rhs rhs_of(const Desc &d)
 // Items start at multiples of NXCD and their tiles are renumbered so that an
 // XCD gets a contiguous band of tiles: neighbouring tiles, which read each
 // other's halos, share one L2.
-template <typename R, typename IT>
-__device__ __forceinline__ TileT<R> item_tile(R *sm, const IT &it, int k, const Desc &d)
+template <typename TT, typename R, typename IT>
+__device__ __forceinline__ TT item_tile(R *sm, const IT &it, int k, const Desc &d)
 {
     const int tx = it.tx[k];
     const int ty = (d.m2 + TY - 1) / TY;
     const int n = tx * ty, lin = (int)blockIdx.x - it.start[k];
     const int t = (n % NXCD == 0) ? (lin % NXCD) * (n / NXCD) + lin / NXCD : lin;
-    TileT<R> T;
+    TT T;
     T.s = sm;
     T.i0 = (t % tx) * TX;
     T.j0 = (t / tx) * TY;
@@ -151,36 +153,36 @@ template <typename IT> __device__ __forceinline__ bool tile_valid(const IT &it, 
 // --------------------------------------------------------------------------
 // one colour half-sweep (sec. 7.1) on a tile: a lane pair per cell of the
 // colour.  The u/v snapshot is buffer par, the new faces go to buffer par^1.
-template <typename IT> __device__ __forceinline__ void halfsweep_body(const IT &it, int colour, double omega)
+template <bool PJ, typename IT> __device__ __forceinline__ void halfsweep_body(const IT &it, int colour, double omega)
 {
-    __shared__ double sm[TILE_DOUBLES];
+    TILE_LDS double sm[TILE_DOUBLES];
     const int k = find_item(it);
     const Desc &d = *it.d[k];
     if (!tile_valid(it, k, d)) return;
-    // generic accesses and the constants by reference, as in k_hs_fused: the
-    // two kernels then compile the relaxation alike and give bitwise the
-    // same results
-    const Phys &P = d.P;
+    const Phys P = d.P;
+    const Kon<double> K = d.K;
     const int par = it.par[k];
     const View L = view_of(d, par);
-    const Tile T = item_tile(sm, it, k, d);
-    tile_load(P, L, T);
+    const Rhs F = rhs_of(d);
+    double *const un = d.ub[par ^ 1], *const vn = d.vb[par ^ 1];
+    const Tile T = item_tile<Tile>(sm, it, k, d);
+    tile_load<2>(P, L, T);
     __syncthreads();
     const int pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
     const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
     const int j = T.j0 + lj;
     const int i = T.i0 + 2 * kk + ((j + colour) & 1);
-    if (i < L.m1 && j < L.m2) relax_pair<0>(P, L, T, rhs_of(d), d.ub[par ^ 1], d.vb[par ^ 1], i, j, hlf, omega, 1.0);
+    if (i < L.m1 && j < L.m2) relax_cell<PJ, false, 1>(P, K, L, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
 }
-template <typename IT> __global__ HS_ATTR void k_halfsweep(IT it, int colour, double omega)
+template <bool PJ, typename IT> __global__ HS_ATTR void k_halfsweep(IT it, int colour, double omega)
 {
-    halfsweep_body(it, colour, omega);
+    halfsweep_body<PJ>(it, colour, omega);
 }
 // the same kernel under its own name for launches whose items are all finest
 // levels, so that profiles tell the finest level apart
-template <typename IT> __global__ FINE_ATTR void k_halfsweep_fine(IT it, int colour, double omega)
+template <bool PJ, typename IT> __global__ FINE_ATTR void k_halfsweep_fine(IT it, int colour, double omega)
 {
-    halfsweep_body(it, colour, omega);
+    halfsweep_body<PJ>(it, colour, omega);
 }
 
 // --------------------------------------------------------------------------
@@ -195,7 +197,7 @@ template <typename IT> __global__ FINE_ATTR void k_halfsweep_fine(IT it, int col
 #define FUSED_W (TX + 7)
 #define FUSED_H (TY + 7)
 #define FBLK (2 * TBLK)
-#define FUSED_DOUBLES ((T_NF + 2) * FUSED_W * FUSED_H)
+#define FUSED_DOUBLES (T_ES * FUSED_W * FUSED_H)
 static_assert(FUSED_DOUBLES * 8 <= 65536, "fused tile exceeds 64 KiB of LDS");
 static_assert((TX + 4) * (TY + 4) <= FBLK, "widened red region exceeds the workgroup");
 
@@ -290,9 +292,9 @@ __device__ __forceinline__ void fused_load(const Phys &P, const View &L, const T
         if (L.bcx) i = wrapi(i, L.m1);
         if (L.bcy) j = wrapi(j, L.m2);
         const TileSrc q = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        double *s = T.s + e;
+        double *s = T.s + e * T_ES;
         if (q.sc == 0) {
-            for (int f = 0; f < T_NF + 2; f++) s[f * n] = 0.0;
+            tile_zero(T, e);
             continue;
         }
         double v[8] = { lda<1>(L.c, q.c), lda<1>(L.mu, q.c), lda<1>(L.p, q.c), lda<1>(L.u, q.u),
@@ -318,18 +320,9 @@ __device__ __forceinline__ void fused_load(const Phys &P, const View &L, const T
             if (q.su) v[3] += du;
             if (q.sv) v[4] += dv;
         }
-        s[T_C * n] = v[0];
-        s[T_MU * n] = v[1];
-        s[T_P * n] = v[2];
-        s[T_U * n] = s[T_NF * n] = signed_val(q.su, v[3]);
-        s[T_V * n] = s[(T_NF + 1) * n] = signed_val(q.sv, v[4]);
-        s[T_CN * n] = v[5];
-        s[T_UN * n] = signed_val(q.su, v[6]);
-        s[T_VN * n] = signed_val(q.sv, v[7]);
-        s[T_RN * n] = rho_of(P, v[5]);
-        s[T_MV * n] = visc_of(P, v[5]);
-        s[T_MOB * n] = mob_of(P, v[5]);
-        s[T_RS * n] = rho_of(P, v[0]);
+        tile_put(P, s, q.su, q.sv, v);
+        s[T_U2] = s[T_U];
+        s[T_V2] = s[T_V];
     }
 }
 // after the red pass: the new faces become the snapshot of the black pass,
@@ -339,7 +332,6 @@ __device__ __forceinline__ void fused_load(const Phys &P, const View &L, const T
 __device__ __forceinline__ void fused_refresh(const View &L, const Tile &T)
 {
     const int n = T.W * T.H;
-    const double *un = T.s + T_NF * n, *vn = T.s + (T_NF + 1) * n;
     for (int e = threadIdx.x; e < n; e += block_threads()) {
         const int b = e / T.W, a = e - b * T.W;
         const int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
@@ -349,29 +341,28 @@ __device__ __forceinline__ void fused_refresh(const View &L, const Tile &T)
         const int sv = (!L.bcy && (j <= 0 || j >= L.m2)) ? 0 : (gx ? -1 : 1);
         // every value the element may take, before any store (an image's
         // source q is never an image, so no element read here is written)
-        const int q = T.idx(si, sj);
-        const double u = un[T.idx(i, sj)], v = vn[T.idx(si, j)], c = T.s[T_C * n + q], mu = T.s[T_MU * n + q],
-                     p = T.s[T_P * n + q], rs = T.s[T_RS * n + q];
+        const double *q = T.at(si, sj);
+        double *s = T.s + e * T_ES;
+        const double u = T.at(i, sj)[T_U2], v = T.at(si, j)[T_V2], c = q[T_C], mu = q[T_MU], p = q[T_P], rs = q[T_RS];
         __builtin_amdgcn_sched_barrier(0);
-        T.s[T_U * n + e] = signed_val(su, u);
-        T.s[T_V * n + e] = signed_val(sv, v);
+        s[T_U] = signed_val(su, u);
+        s[T_V] = signed_val(sv, v);
         if (gx || gy) {
-            T.s[T_C * n + e] = c;
-            T.s[T_MU * n + e] = mu;
-            T.s[T_P * n + e] = p;
-            T.s[T_RS * n + e] = rs;
+            s[T_C] = c;
+            s[T_MU] = mu;
+            s[T_P] = p;
+            s[T_RS] = rs;
         }
     }
 }
-template <typename IT> __global__ __launch_bounds__(FBLK) void k_hs_fused(IT it, int dir, double omega, int prolong)
+template <bool PJ, typename IT> __global__ __launch_bounds__(FBLK) void k_hs_fused(IT it, int dir, double omega, int prolong)
 {
-    __shared__ double sm[FUSED_DOUBLES];
+    TILE_LDS double sm[FUSED_DOUBLES];
     const int k = find_item(it);
     const Desc &d = *it.d[k];
     if (!tile_valid(it, k, d)) return;
-    // generic accesses and the constants by reference: global-typed accesses
-    // with the constants held by value measured 3 % slower for this kernel
-    const Phys &P = d.P;
+    const Phys P = d.P;
+    const Kon<double> K = d.K;
     const int par = it.par[k];
     View L = view_of(d, par);
     View O = L; // where the sweep's cell results go
@@ -380,21 +371,18 @@ template <typename IT> __global__ __launch_bounds__(FBLK) void k_hs_fused(IT it,
     } else {
         O.c = d.c2; O.mu = d.mu2; O.p = d.p2;
     }
-    const Tile T0 = item_tile(sm, it, k, d);
+    const Tile T0 = item_tile<Tile>(sm, it, k, d);
     Tile T;
     T.s = sm; T.i0 = T0.i0 - 2; T.j0 = T0.j0 - 2; T.W = FUSED_W; T.H = FUSED_H;
-    {
-        // the loader's constants by value (no tile store can change them)
-        const Phys Pv = d.P;
-        if (prolong) {
-            const PSrc ps = psrc_of(d, d.coarse, it.cpar[k]);
-            fused_load(Pv, L, T, &ps);
-        } else {
-            fused_load(Pv, L, T);
-        }
+    const Rhs F = rhs_of(d);
+    double *const un = d.ub[par ^ 1], *const vn = d.vb[par ^ 1];
+    if (prolong) {
+        const PSrc ps = psrc_of(d, d.coarse, it.cpar[k]);
+        fused_load(P, L, T, &ps);
+    } else {
+        fused_load(P, L, T);
     }
     __syncthreads();
-    const Rhs F = rhs_of(d);
     const int pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
     {
         // red: cells with i + j even of i0-2 .. i0+TX+1, j0-2 .. j0+TY+1
@@ -404,7 +392,7 @@ template <typename IT> __global__ __launch_bounds__(FBLK) void k_hs_fused(IT it,
         const bool in = lj < TY + 4 && (L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2));
         if (in) {
             const int i = L.bcx ? wrapi(ti, L.m1) : ti, j = L.bcy ? wrapi(tj, L.m2) : tj;
-            relax_cell<true, 0>(P, L, T, F, nullptr, nullptr, i, j, ti, tj, hlf, omega, 1.0);
+            relax_cell<PJ, true, 1>(P, K, L, T, F, nullptr, nullptr, i, j, ti, tj, hlf, omega, 1.0);
         }
     }
     __syncthreads();
@@ -415,7 +403,7 @@ template <typename IT> __global__ __launch_bounds__(FBLK) void k_hs_fused(IT it,
         const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
         const int j = T0.j0 + lj;
         const int i = T0.i0 + 2 * kk + ((j + 1) & 1);
-        if (i < L.m1 && j < L.m2) relax_cell<false, 0>(P, O, T, F, d.ub[par ^ 1], d.vb[par ^ 1], i, j, i, j, hlf, omega, 1.0);
+        if (i < L.m1 && j < L.m2) relax_cell<PJ, false, 1>(P, K, O, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
     } else {
         // red cells of the tile: their final values
         const int q = pr - TBLK / 2;
@@ -423,10 +411,14 @@ template <typename IT> __global__ __launch_bounds__(FBLK) void k_hs_fused(IT it,
         const int j = T0.j0 + lj;
         const int i = T0.i0 + 2 * kk + (j & 1);
         if (i < L.m1 && j < L.m2) {
-            const int e = T.idx(i, j), n = T.W * T.H;
+            const double *e = T.at(i, j);
             const size_t g = (size_t)j * L.pitch + i;
-            if (hlf == 0) { O.c[g] = T.s[T_C * n + e]; O.mu[g] = T.s[T_MU * n + e]; }
-            else O.p[g] = T.s[T_P * n + e];
+            if (hlf == 0) {
+                sta<1>(O.c, g, e[T_C]);
+                sta<1>(O.mu, g, e[T_MU]);
+            } else {
+                sta<1>(O.p, g, e[T_P]);
+            }
         }
     }
 }
@@ -437,12 +429,11 @@ __global__ __launch_bounds__(BLK) void k_copy_probe(const double *__restrict__ a
     for (size_t q = (size_t)blockIdx.x * BLK + threadIdx.x; q < n; q += (size_t)gridDim.x * BLK) b[q] = a[q];
 }
 
-// LDS doubles of the level-resident solve: 15 per cell (the level arrays and
-// right-hand sides take 12) + one tile + the tile's source map (4 ints per
-// element)
+// LDS doubles of the level-resident solve: 12 per cell (the level arrays and
+// right-hand sides) + one tile + the tile's source map (4 ints per element)
 __host__ __device__ inline size_t coarse_lds_doubles(int m1, int m2)
 {
-    return (size_t)15 * m1 * m2 + (size_t)(T_NF + 2) * (m1 + 3) * (m2 + 3);
+    return (size_t)12 * m1 * m2 + (size_t)(T_ES + 2) * (m1 + 3) * (m2 + 3);
 }
 
 // all sweeps of a level in one workgroup per item, with the whole level
@@ -452,15 +443,16 @@ __host__ __device__ inline size_t coarse_lds_doubles(int m1, int m2)
 // is even, so the result stays in buffer par.  With prolong set the level
 // first takes the coarse-grid correction (k_prolong's arithmetic) as it is
 // loaded.
-template <typename IT>
+template <bool PJ, typename IT>
 __global__ __launch_bounds__(512) void k_coarse_solve(IT it, int sweeps, double omega, double pomega, int prolong)
 {
-    extern __shared__ double sm[];
+    extern __shared__ __attribute__((aligned(16))) double sm[];
     const int k = find_item(it);
     const Desc &d = *it.d[k];
     // the constants by value (no store can change them, so they are not
     // reloaded after one); the relaxation works on LDS arrays (address space 3)
     const Phys P = d.P;
+    const Kon<double> K = d.K;
     const int par = it.par[k];
     const View L = view_of(d, par);
     double *ua = d.ub[par], *va = d.vb[par];
@@ -468,9 +460,9 @@ __global__ __launch_bounds__(512) void k_coarse_solve(IT it, int sweeps, double 
     double *hc = sm, *hmu = sm + n, *hp = sm + 2 * n, *uA = sm + 3 * n, *vA = sm + 4 * n, *uB = sm + 5 * n,
            *vB = sm + 6 * n, *hf = sm + 7 * n;
     Tile T;
-    T.s = sm + 15 * n; T.i0 = 0; T.j0 = 0; T.W = m1 + 3; T.H = m2 + 3;
+    T.s = sm + 12 * n; T.i0 = 0; T.j0 = 0; T.W = m1 + 3; T.H = m2 + 3;
     const int nt = T.W * T.H;
-    int *map = (int *)(T.s + (size_t)T_NF * nt);
+    int *map = (int *)(T.s + (size_t)T_ES * nt);
     // one pass over the tile's elements: each loads its sources from the level
     // arrays (the boundary images of tile_load), adds the coarse-grid
     // correction of each source, and fills the tile (with the cell functions),
@@ -514,22 +506,11 @@ __global__ __launch_bounds__(512) void k_coarse_solve(IT it, int sweeps, double 
         map[4 * e + 1] = q.ju * m1 + q.iu;
         map[4 * e + 2] = q.jv * m1 + q.iv;
         map[4 * e + 3] = (q.su + 1) | ((q.sv + 1) << 2) | (((q.ic + q.jc) & 1) << 5) | (out ? 16 : 0);
-        double *t = T.s + e;
         if (q.sc == 0) {
-            for (int f = 0; f < T_NF; f++) t[f * nt] = 0.0;
+            tile_zero(T, e);
         } else {
-            t[T_C * nt] = c;
-            t[T_MU * nt] = mu;
-            t[T_P * nt] = p;
-            t[T_U * nt] = signed_val(q.su, u);
-            t[T_V * nt] = signed_val(q.sv, v);
-            t[T_CN * nt] = cn;
-            t[T_UN * nt] = signed_val(q.su, un);
-            t[T_VN * nt] = signed_val(q.sv, vn);
-            t[T_RN * nt] = rho_of(P, cn);
-            t[T_MV * nt] = visc_of(P, cn);
-            t[T_MOB * nt] = mob_of(P, cn);
-            t[T_RS * nt] = rho_of(P, c);
+            const double w[8] = { c, mu, p, u, v, cn, un, vn };
+            tile_put(P, T.s + e * T_ES, q.su, q.sv, w);
         }
         if (cell) {
             // a cell of the level: its own source for every field
@@ -560,7 +541,7 @@ __global__ __launch_bounds__(512) void k_coarse_solve(IT it, int sweeps, double 
             const int pr = t >> 1;
             const int j = pr / half;
             const int i = 2 * (pr - j * half) + ((j + colour) & 1);
-            relax_pair<3>(P, H, T, FH, uw, vw, i, j, t & 1, omega, pomega);
+            relax_cell<PJ, false, 3>(P, K, H, T, FH, uw, vw, i, j, i, j, t & 1, omega, pomega);
         }
         __syncthreads();
     }
@@ -586,28 +567,35 @@ __device__ __forceinline__ double rw_mean(double a, double b, double c, double d
 // pair each; N_H is evaluated on a coarse tile whose halo takes R w from the
 // fine arrays directly (the neighbouring workgroups write the coarse iterate
 // meanwhile).
-#define RBLK (2 * TBLK)
-template <typename IT> __global__ __launch_bounds__(RBLK) void k_restrict(IT it)
+//
+// One lane per fine cell (waves 0-3, a coarse cell's children in a quad of
+// lanes, summed by DPP), a fifth wave for the residuals of the tile's 64 coarse
+// cells meanwhile.
+#define RBLK (TBLK + 64)
+static_assert((TX / 2) * (TY / 2) == 64, "k_restrict: one wave of coarse cells");
+// sum over a quad of lanes as (0 + 1) + (2 + 3), the order of rw_mean
+__device__ __forceinline__ double quad_sum(double x)
 {
-    __shared__ double sm[TILE_DOUBLES];
-    __shared__ double smc[T_NF * (TX / 2 + 3) * (TY / 2 + 3)];
-    // sums of the three fine cells of a coarse cell other than its (0, 0)
-    // child: the x lane's residuals and iterate (rc, rm, rp, rf, c, mu, p,
-    // u face), the y lane's face residual and v face
-    __shared__ double part[3][(TX / 2) * (TY / 2)][10];
+    x += other(x);
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffll), 0x4E, 0xF, 0xF, false),
+              hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x4E, 0xF, 0xF, false);
+    return x + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+template <bool PJ, typename IT> __global__ __launch_bounds__(RBLK) void k_restrict(IT it)
+{
+    TILE_LDS double sm[TILE_DOUBLES];
+    TILE_LDS double smc[T_ES * (TX / 2 + 3) * (TY / 2 + 3)];
+    __shared__ double part[5][(TX / 2) * (TY / 2)]; // sums of the fine residuals
     const int k = find_item(it);
     const Desc &d = *it.d[k];
     if (!tile_valid(it, k, d)) return;
     const Desc &C = *d.coarse;
-    // the coarse constants stay by reference: held by value they raised the
-    // kernel from 120 to 143 VGPRs (one workgroup less per compute unit)
     const Phys P = d.P;
-    const Phys &PC = C.P;
     const int cp = it.cpar[k];
     const View Lf = view_of(d, it.par[k]);
     const View Lc = view_of(C, cp);
-    const Tile T = item_tile(sm, it, k, d);
-    tile_load(P, Lf, T);
+    const Tile T = item_tile<Tile>(sm, it, k, d);
     // the coarse tile of R w, from the fine arrays directly (its halo lies
     // in the neighbouring workgroups' tiles), loaded together with the fine
     // tile: cells the mean of the four children, faces the mean of the two
@@ -615,15 +603,11 @@ template <typename IT> __global__ __launch_bounds__(RBLK) void k_restrict(IT it)
     Tile Tc;
     Tc.s = smc; Tc.i0 = T.i0 / 2; Tc.j0 = T.j0 / 2; Tc.W = TX / 2 + 3; Tc.H = TY / 2 + 3;
     {
-        const int n = Tc.W * Tc.H;
-        for (int e = threadIdx.x; e < n; e += block_threads()) {
+        const int n = Tc.W * Tc.H, e = RBLK - 1 - threadIdx.x;
+        const Phys PC = C.P;
+        if (e < n) {
             const int bb = e / Tc.W, aa = e - bb * Tc.W;
             const TileSrc s = tile_src(C.m1, C.m2, C.pitch, C.bcx, C.bcy, Tc.i0 - 1 + aa, Tc.j0 - 1 + bb);
-            double *t = Tc.s + e;
-            if (s.sc == 0) {
-                for (int f = 0; f < T_NF; f++) t[f * n] = 0.0;
-                continue;
-            }
             const int Ic = s.c % C.pitch, Jc = s.c / C.pitch;
             const int Iu = s.u % C.pitch, Ju = s.u / C.pitch, Iv = s.v % C.pitch, Jv = s.v / C.pitch;
             const size_t fu = (size_t)(2 * Ju) * Lf.pitch + 2 * Iu, fv = (size_t)(2 * Jv) * Lf.pitch + 2 * Iv;
@@ -637,97 +621,50 @@ template <typename IT> __global__ __launch_bounds__(RBLK) void k_restrict(IT it)
             const double w0 = lda<1>(Lf.v, fv), w1 = lda<1>(Lf.v, fv + 1);
             const double cn = lda<1>(C.cn, s.c), un = lda<1>(C.un, s.u), vn = lda<1>(C.vn, s.v);
             __builtin_amdgcn_sched_barrier(0);
-            const double c = rw_mean(c4[0], c4[1], c4[2], c4[3]);
-            const double u = s.su ? 0.5 * (u0 + u1) : 0.0;
-            const double w = s.sv ? 0.5 * (w0 + w1) : 0.0;
-            t[T_C * n] = c;
-            t[T_MU * n] = rw_mean(m4[0], m4[1], m4[2], m4[3]);
-            t[T_P * n] = rw_mean(p4[0], p4[1], p4[2], p4[3]);
-            t[T_U * n] = signed_val(s.su, u);
-            t[T_V * n] = signed_val(s.sv, w);
-            t[T_CN * n] = cn;
-            t[T_UN * n] = signed_val(s.su, un);
-            t[T_VN * n] = signed_val(s.sv, vn);
-            t[T_RN * n] = rho_of(PC, cn);
-            t[T_MV * n] = visc_of(PC, cn);
-            t[T_MOB * n] = mob_of(PC, cn);
-            t[T_RS * n] = rho_of(PC, c);
-        }
-    }
-    __syncthreads();
-    // lane pair pr: coarse cell cc of the tile, fine child (a, b) = (ch & 1,
-    // ch >> 1) of it; children other than (0, 0) hand their values to the
-    // (0, 0) pair through LDS
-    const int pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
-    const int NC = (TX / 2) * (TY / 2);
-    const int cc = pr % NC, ch = pr / NC, a = ch & 1, b = ch >> 1;
-    const int I = T.i0 / 2 + cc % (TX / 2), J = T.j0 / 2 + cc / (TX / 2);
-    const bool on = I < C.m1 && J < C.m2;
-    double v[8] = { 0, 0, 0, 0, 0, 0, 0, 0 }; // rc, rm, rp, rf, c, mu, p, face
-    if (on) {
-        const int i = 2 * I + a, j = 2 * J + b;
-        double xc, xm, xp, xf;
-        resid_pair(P, Lf, T, rhs_of(d), i, j, hlf, xc, xm, xp, xf);
-        v[0] = xc; v[1] = xm; v[2] = xp;
-        // the lane's faces of the coarse cell: west faces (a = 0) on the x
-        // lane, south faces (b = 0) on the y lane
-        if ((hlf ? b : a) == 0) { v[3] = xf; v[7] = T.q(hlf ? T_V : T_U, i, j); }
-        v[4] = T.q(T_C, i, j); v[5] = T.q(T_MU, i, j); v[6] = T.q(T_P, i, j);
-        if (ch > 0) {
-            double *o = part[ch - 1][cc];
-            if (hlf == 0) {
-#pragma unroll
-                for (int q = 0; q < 8; q++) o[q] = v[q];
+            if (s.sc == 0) {
+                tile_zero(Tc, e);
             } else {
-                o[8] = v[3];
-                o[9] = v[7];
+                const double w[8] = { rw_mean(c4[0], c4[1], c4[2], c4[3]), rw_mean(m4[0], m4[1], m4[2], m4[3]),
+                                      rw_mean(p4[0], p4[1], p4[2], p4[3]), 0.5 * (u0 + u1), 0.5 * (w0 + w1), cn, un, vn };
+                tile_put(PC, Tc.s + e * T_ES, s.su, s.sv, w);
             }
         }
     }
+    tile_load<2>(P, Lf, T);
     __syncthreads();
-    if (!on || ch != 0) return;
-    // sums over the four children as (0,0) + (1,0) plus (0,1) + (1,1), the
-    // order in which the coarse tile's R w was summed (rw_mean)
-    if (hlf == 0) {
-#pragma unroll
-        for (int q = 0; q < 8; q++) v[q] = (v[q] + part[0][cc][q]) + (part[1][cc][q] + part[2][cc][q]);
-    } else {
-#pragma unroll
-        for (int g = 0; g < 3; g++) {
-            v[3] += part[g][cc][8];
-            v[7] += part[g][cc][9];
+    const bool fine = threadIdx.x < TBLK;
+    const int cc = fine ? (int)threadIdx.x >> 2 : (int)threadIdx.x - TBLK, ch = threadIdx.x & 3;
+    const int I = Tc.i0 + cc % (TX / 2), J = Tc.j0 + cc / (TX / 2);
+    const bool on = I < C.m1 && J < C.m2;
+    Resid r = {};
+    if (fine) {
+        if (on) r = resid_cell<PJ>(d.K, Lf, T, rhs_of(d), 2 * I + (ch & 1), 2 * J + (ch >> 1));
+        // the faces of the coarse cell: west faces of the children (0, .),
+        // south faces of the children (., 0)
+        const double sc = quad_sum(r.c), smu = quad_sum(r.mu), sp = quad_sum(r.p),
+                     su = quad_sum(ch & 1 ? 0.0 : r.u), sv = quad_sum(ch >> 1 ? 0.0 : r.v);
+        if (ch == 0) {
+            part[0][cc] = sc; part[1][cc] = smu; part[2][cc] = sp; part[3][cc] = su; part[4][cc] = sv;
         }
+    } else if (on) {
+        const Rhs Z = { nullptr, nullptr, nullptr, nullptr, nullptr };
+        r = resid_cell<PJ>(C.K, Lc, Tc, Z, I, J); // -N_H(R w)
     }
+    __syncthreads();
+    if (fine || !on) return;
+    // the fifth wave: f_H = N_H(R w) + R r on the coarse cells
     const size_t q = (size_t)J * C.pitch + I;
-    if (hlf == 0) {
-        C.c[q] = C.c0[q] = 0.25 * v[4];
-        C.mu[q] = C.mu0[q] = 0.25 * v[5];
-        C.p[q] = C.p0[q] = 0.25 * v[6];
-        C.ub[cp][q] = C.u0[q] = 0.5 * v[7];
-    } else {
-        C.vb[cp][q] = C.v0[q] = 0.5 * v[7];
-    }
-    // f_H = N_H(R w) + R r on the coarse cell
-    const Rhs Z = { nullptr, nullptr, nullptr, nullptr, nullptr };
-    double rc, rm, rp, rf;
-    resid_pair(PC, Lc, Tc, Z, I, J, hlf, rc, rm, rp, rf); // r = -N_H(R w)
-    if (hlf == 0) {
-        C.fc[q] = 0.25 * v[0] - rc;
-        C.fmu[q] = 0.25 * v[1] - rm;
-        C.fp[q] = 0.25 * v[2] - rp;
-        C.fu[q] = u_unk(Lc, I) ? 0.5 * v[3] - rf : 0.0;
-    } else {
-        C.fv[q] = v_unk(Lc, J) ? 0.5 * v[3] - rf : 0.0;
-    }
-}
-
-// the two cells of a tile handled by lane pair pr: (2k, lj) and (2k+1, lj)
-template <typename TT> __device__ __forceinline__ void pair_cells(const TT &T, int &i, int &j)
-{
-    const int pr = threadIdx.x >> 1;
-    const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
-    i = T.i0 + 2 * kk;
-    j = T.j0 + lj;
+    const double *t = Tc.at(I, J);
+    sta<1>(C.c, q, t[T_C]); sta<1>(C.c0, q, t[T_C]);
+    sta<1>(C.mu, q, t[T_MU]); sta<1>(C.mu0, q, t[T_MU]);
+    sta<1>(C.p, q, t[T_P]); sta<1>(C.p0, q, t[T_P]);
+    sta<1>(C.ub[cp], q, t[T_U]); sta<1>(C.u0, q, t[T_U]);
+    sta<1>(C.vb[cp], q, t[T_V]); sta<1>(C.v0, q, t[T_V]);
+    sta<1>(C.fc, q, 0.25 * part[0][cc] - r.c);
+    sta<1>(C.fmu, q, 0.25 * part[1][cc] - r.mu);
+    sta<1>(C.fp, q, 0.25 * part[2][cc] - r.p);
+    sta<1>(C.fu, q, u_unk(Lc, I) ? 0.5 * part[3][cc] - r.u : 0.0);
+    sta<1>(C.fv, q, v_unk(Lc, J) ? 0.5 * part[4][cc] - r.v : 0.0);
 }
 
 // w_h += P(w_H - R w_h) on the level the item names, one thread per fine cell
@@ -757,18 +694,29 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_prolong(IT it)
     if (ps.bcy || j >= 1) sta<1>(vb, kf, v + dv);
 }
 
-// wave64 + LDS block sum of NRED values (blocks of up to 16 waves)
+// wave64 + LDS block sum of NRED values (blocks of up to 16 waves).  Within a
+// wave each exchange halves the number of slots a lane is responsible for
+// (lane l ends with the sum of slot l / 4): 17 exchanges instead of 6 per slot.
 __device__ __forceinline__ void block_sum_store(double (&v)[NRED], double *out)
 {
+    static_assert(NRED == 16, "block_sum_store");
     __shared__ double sh[16][NRED];
-#pragma unroll
-    for (int q = 0; q < NRED; q++)
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o, 64);
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    if (l == 0)
+    double a[8];
 #pragma unroll
-        for (int q = 0; q < NRED; q++) sh[w][q] = v[q];
+    for (int q = 0; q < 8; q++) {
+        const bool h = l & 32;
+        a[q] = (h ? v[q + 8] : v[q]) + __shfl_xor(h ? v[q] : v[q + 8], 32, 64);
+    }
+#pragma unroll
+    for (int n = 4; n > 0; n >>= 1) {
+        const bool h = l & (4 * n);
+#pragma unroll
+        for (int q = 0; q < n; q++) a[q] = (h ? a[q + n] : a[q]) + __shfl_xor(h ? a[q] : a[q + n], 4 * n, 64);
+    }
+    a[0] += __shfl_xor(a[0], 2, 64);
+    a[0] += __shfl_xor(a[0], 1, 64);
+    if ((l & 3) == 0) sh[w][l >> 2] = a[0];
     __syncthreads();
     if (threadIdx.x < NRED) {
         double s = 0.0;
@@ -778,119 +726,94 @@ __device__ __forceinline__ void block_sum_store(double (&v)[NRED], double *out)
 }
 
 // Acceleration of the cycle iteration, recording of a cycle result in ring
-// slot s: the residual and the iterate of the cell at index w (lane 0: c,
-// mubar, pbar and the west face; lane 1: the south face).
-template <typename TT>
-__device__ __forceinline__ void acc_put(const Desc &d, int s, size_t w, int hlf, double rc, double rm, double rp,
-                                        double rf, const TT &T, int i, int j)
-{
-    const size_t st = (size_t)d.pitch * d.m2;
-    double *ar = d.ar + (size_t)s * 5 * st + w, *aw = d.aw + (size_t)s * 5 * st + w;
-    if (hlf == 0) {
-        ar[0] = rc; ar[st] = rm; ar[2 * st] = rp; ar[3 * st] = rf;
-        aw[0] = T.q(T_C, i, j); aw[st] = T.q(T_MU, i, j); aw[2 * st] = T.q(T_P, i, j); aw[3 * st] = T.q(T_U, i, j);
-    } else {
-        ar[4 * st] = rf;
-        aw[4 * st] = T.q(T_V, i, j);
-    }
-}
-// ... and the lane's share of the normal equations of
+// slot s = ac & 15: the residual and the iterate of the cell at index w and
+// its west and south faces, and the cell's share of the normal equations of
 // min || r + sum_a g_a (r - r_a) ||, r_a the residual a + 1 slots back
-// (a < np): v[7 + b(b+1)/2 + a] += e_a e_b (a <= b), v[13 + a] += e_a r,
-// e_a = r - r_a.  Reads back what acc_put of the same lane wrote (the
-// residuals' registers are free by then), all slots of all the lane's fields
-// (lane 0: four, lane 1: one) before the first product.
-__device__ __forceinline__ void acc_dots(const Desc &d, int ac, size_t w, int hlf, double (&v)[NRED])
+// (a < np = ac >> 4): v[7 + b(b+1)/2 + a] += e_a e_b (a <= b), v[13 + a] += e_a r,
+// e_a = r - r_a.  Every earlier residual is loaded before any store or
+// product.
+__device__ __forceinline__ void acc_record(const Desc &d, int ac, size_t w, const Resid &r, const double *t,
+                                           double (&v)[NRED])
 {
     const int s = ac & 15, np = ac >> 4, R = d.am;
     const size_t st = (size_t)d.pitch * d.m2;
-    const int nf = hlf ? 1 : 4;
-    double x[4], old[4][3];
+    double *const ar = d.ar, *const aw = d.aw;
+    const double x[5] = { r.c, r.mu, r.p, r.u, r.v }, y[5] = { t[T_C], t[T_MU], t[T_P], t[T_U], t[T_V] };
+    double old[3][5];
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const int f = hlf ? 4 : q;
-        x[q] = q < nf ? d.ar[(size_t)(s * 5 + f) * st + w] : 0.0;
+    for (int a = 0; a < 3; a++)
 #pragma unroll
-        for (int a = 0; a < 3; a++)
-            old[q][a] = (q < nf && a < np) ? d.ar[(size_t)(((s - 1 - a + R) % R) * 5 + f) * st + w] : 0.0;
+        for (int f = 0; f < 5; f++)
+            old[a][f] = a < np ? lda<1>(ar, (size_t)(((s - 1 - a + R) % R) * 5 + f) * st + w) : 0.0;
+#pragma unroll
+    for (int f = 0; f < 5; f++) {
+        sta<1>(ar, (size_t)(s * 5 + f) * st + w, x[f]);
+        sta<1>(aw, (size_t)(s * 5 + f) * st + w, y[f]);
     }
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-        if (q >= nf) continue;
-        double e[3] = { 0.0, 0.0, 0.0 };
+    for (int f = 0; f < 5; f++) {
+        double e[3];
 #pragma unroll
-        for (int a = 0; a < 3; a++)
-            if (a < np) e[a] = x[q] - old[q][a];
+        for (int a = 0; a < 3; a++) e[a] = a < np ? x[f] - old[a][f] : 0.0;
 #pragma unroll
         for (int b = 0; b < 3; b++)
 #pragma unroll
             for (int a = 0; a <= b; a++) v[7 + b * (b + 1) / 2 + a] += e[a] * e[b];
 #pragma unroll
-        for (int a = 0; a < 3; a++) v[13 + a] += e[a] * x[q];
+        for (int a = 0; a < 3; a++) v[13 + a] += e[a] * x[f];
     }
 }
 
 // residual norms of a finest level: per tile sums of r^2 for the five
 // equations, the sum of pbar, and the count of cells that are non-finite or
 // past the density pole (partials indexed by the tile's place in the band
-// order); optionally the residual fields themselves
-template <typename IT> __global__ __launch_bounds__(TBLK) void k_resid_norm(IT it)
+// order); optionally the residual fields themselves.  One lane per cell.
+template <bool PJ, typename IT> __global__ __launch_bounds__(TBLK) void k_resid_norm(IT it)
 {
-    __shared__ double sm[TILE_DOUBLES];
+    TILE_LDS double sm[TILE_DOUBLES];
     const int k = find_item(it);
     const Desc &d = *it.d[k];
     if (!tile_valid(it, k, d)) return;
     const Phys P = d.P;
-    const View L = view_of(d, it.par[k]);
-    const Tile T = item_tile(sm, it, k, d);
-    tile_load(P, L, T);
+    const Kon<double> K = d.K;
+    const int par = it.par[k];
+    const View L = view_of(d, par);
+    const Tile T = item_tile<Tile>(sm, it, k, d);
+    tile_load<2>(P, L, T);
     __syncthreads();
     double v[NRED] = {};
     const size_t n = (size_t)L.m1 * L.m2;
-    const int hlf = threadIdx.x & 1;
-    const Rhs F = rhs_of(d);
-    int i, j;
-    pair_cells(T, i, j);
-    for (int a = 0; a < 2; a++, i++) {
-        if (i >= L.m1 || j >= L.m2) continue;
-        double rc, rm, rp, rf;
-        resid_pair(P, L, T, F, i, j, hlf, rc, rm, rp, rf);
-        const size_t q = (size_t)j * L.m1 + i;
-        v[3 + hlf] += rf * rf;
-        if (d.rout) d.rout[(3 + hlf) * n + q] = rf;
+    const int i = T.i0 + (int)threadIdx.x % TX, j = T.j0 + (int)threadIdx.x / TX;
+    if (i < L.m1 && j < L.m2) {
+        const Resid r = resid_cell<PJ>(K, L, T, rhs_of(d), i, j);
+        const double *t = T.at(i, j);
+        const double c = t[T_C], pp = t[T_P];
+        v[0] = r.c * r.c;
+        v[1] = r.mu * r.mu;
+        v[2] = r.p * r.p;
+        v[3] = r.u * r.u;
+        v[4] = r.v * r.v;
+        v[5] = pp;
+        const bool ok = isfinite(c) && isfinite(t[T_MU]) && isfinite(pp) && isfinite(t[T_U]) && isfinite(t[T_V])
+                      && (P.drho * c + P.rho1 > 0.0);
+        v[6] = ok ? 0.0 : 1.0;
+        const size_t q = (size_t)j * L.m1 + i, w = (size_t)j * L.pitch + i;
+        if (d.rout) {
+            d.rout[q] = r.c;
+            d.rout[n + q] = r.mu;
+            d.rout[2 * n + q] = r.p;
+            d.rout[3 * n + q] = r.u;
+            d.rout[4 * n + q] = r.v;
+        }
         if (d.rc) {
             // mixed precision: the right-hand side and linearisation point of
             // the next correction cycle, whose correction starts at zero
-            const size_t w = (size_t)j * L.pitch + i;
-            const int par = it.par[k];
-            if (hlf == 0) {
-                d.rc[w] = (float)rc; d.rmu[w] = (float)rm; d.rp[w] = (float)rp; d.ru[w] = (float)rf;
-                d.xc[w] = (float)T.q(T_C, i, j); d.xmu[w] = (float)T.q(T_MU, i, j);
-                d.xu[w] = (float)T.q(T_U, i, j);
-                d.dc[w] = 0.0f; d.dmu[w] = 0.0f; d.dp[w] = 0.0f; d.dub[par][w] = 0.0f;
-            } else {
-                d.rv[w] = (float)rf;
-                d.xv[w] = (float)T.q(T_V, i, j);
-                d.dvb[par][w] = 0.0f;
-            }
+            d.rc[w] = (float)r.c; d.rmu[w] = (float)r.mu; d.rp[w] = (float)r.p; d.ru[w] = (float)r.u; d.rv[w] = (float)r.v;
+            d.xc[w] = (float)c; d.xmu[w] = (float)t[T_MU]; d.xu[w] = (float)t[T_U]; d.xv[w] = (float)t[T_V];
+            d.dc[w] = 0.0f; d.dmu[w] = 0.0f; d.dp[w] = 0.0f; d.dub[par][w] = 0.0f; d.dvb[par][w] = 0.0f;
         }
-        if (hlf == 0) {
-            v[0] += rc * rc; v[1] += rm * rm; v[2] += rp * rp;
-            const double c = T.q(T_C, i, j), pp = T.q(T_P, i, j);
-            v[5] += pp;
-            const bool ok = isfinite(c) && isfinite(T.q(T_MU, i, j)) && isfinite(pp) && isfinite(T.q(T_U, i, j))
-                          && isfinite(T.q(T_V, i, j)) && (P.drho * c + P.rho1 > 0.0);
-            v[6] += ok ? 0.0 : 1.0;
-            if (d.rout) { d.rout[q] = rc; d.rout[n + q] = rm; d.rout[2 * n + q] = rp; }
-        }
-        if (it.acc[k] >= 0 && d.ar) acc_put(d, it.acc[k] & 15, (size_t)j * L.pitch + i, hlf, rc, rm, rp, rf, T, i, j);
-    }
-    // the normal equations after the residuals, whose registers are free by now
-    if (it.acc[k] >= 0 && d.ar && (it.acc[k] >> 4) > 0) {
-        pair_cells(T, i, j);
-#pragma unroll 1
-        for (int a = 0; a < 2; a++, i++)
-            if (i < L.m1 && j < L.m2) acc_dots(d, it.acc[k], (size_t)j * L.pitch + i, hlf, v);
+        const int ac = it.acc[k];
+        if (ac >= 0 && d.ar) acc_record(d, ac, w, r, t, v);
     }
     const int tl = (T.j0 / TY) * it.tx[k] + T.i0 / TX;
     block_sum_store(v, d.partials + (size_t)tl * NRED);

@@ -545,6 +545,21 @@ static Item1 one_of(const Items &a)
         else hipLaunchKernelGGL(K<Items>, GRID, BLOCK, LDS, ST, (L).it, ##__VA_ARGS__);            \
     } while (0)
 
+// the same for kernels with an instantiation of their own for the projection
+// scheme (PJ, in the calling scope), which runs one simulation per launch
+#define KLAUNCH_PJ(K, L, GRID, BLOCK, LDS, ST, ...)                                                  \
+    do {                                                                                           \
+        if (pj) KLAUNCH1((K<true, Item1>), L, GRID, BLOCK, LDS, ST, ##__VA_ARGS__);                 \
+        else if ((L).it.n == 1) KLAUNCH1((K<false, Item1>), L, GRID, BLOCK, LDS, ST, ##__VA_ARGS__); \
+        else if (e0) hipExtLaunchKernelGGL((K<false, Items>), GRID, BLOCK, LDS, ST, e0, e1, 0, (L).it, ##__VA_ARGS__); \
+        else hipLaunchKernelGGL((K<false, Items>), GRID, BLOCK, LDS, ST, (L).it, ##__VA_ARGS__);     \
+    } while (0)
+#define KLAUNCH1(K1, L, GRID, BLOCK, LDS, ST, ...)                                                   \
+    do {                                                                                           \
+        if (e0) hipExtLaunchKernelGGL(K1, GRID, BLOCK, LDS, ST, e0, e1, 0, one_of((L).it), ##__VA_ARGS__); \
+        else hipLaunchKernelGGL(K1, GRID, BLOCK, LDS, ST, one_of((L).it), ##__VA_ARGS__);            \
+    } while (0)
+
 // Launch one operation for a set of (context, level) entries, in lists of at
 // most MAXITEMS; all entries share the kind and colour.  Errors are reported
 // on the first context.
@@ -558,6 +573,7 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
         ItemList W;
         for (auto &pe : part) add_item(W, pe.first, kind, pe.second);
         const double omega = x0->opt.vanka_omega;
+        const bool pj = x0->opt.scheme == QNSCH_PROJECTION;
         const int tag = prof_tag(kind, part);
         // launches timed in mode 1 take the kernel's own start and end
         // timestamps; other timed launches are bracketed by event records
@@ -579,15 +595,15 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
                     KLAUNCH(k_mx_halfsweep_fine, W, gr, bl, 0, s, colour, (float)omega);
                 else KLAUNCH(k_mx_halfsweep, W, gr, bl, 0, s, colour, (float)omega);
             } else if (W.all_fine) {
-                KLAUNCH(k_halfsweep_fine, W, gr, bl, 0, s, colour, omega);
+                KLAUNCH_PJ(k_halfsweep_fine, W, gr, bl, 0, s, colour, omega);
             } else {
-                KLAUNCH(k_halfsweep, W, gr, bl, 0, s, colour, omega);
+                KLAUNCH_PJ(k_halfsweep, W, gr, bl, 0, s, colour, omega);
             }
             for (auto &pe : part) pe.first->L[pe.second].cur ^= 1;
             break;
         }
         case OP_FUSED: {
-            KLAUNCH(k_hs_fused, W, dim3(W.blocks), dim3(FBLK), 0, s, colour & 1, omega, colour >> 1);
+            KLAUNCH_PJ(k_hs_fused, W, dim3(W.blocks), dim3(FBLK), 0, s, colour & 1, omega, colour >> 1);
             for (auto &pe : part) pe.first->L[pe.second].cur ^= 1;
             break;
         }
@@ -596,7 +612,7 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
             for (auto &pe : part) pe.first->L[pe.second].cur ^= 1;
             break;
         }
-        case OP_RESTRICT: KLAUNCH(k_restrict, W, dim3(W.blocks), dim3(RBLK), 0, s); break;
+        case OP_RESTRICT: KLAUNCH_PJ(k_restrict, W, dim3(W.blocks), dim3(RBLK), 0, s); break;
         case OP_COARSE:
         case OP_SMOOTH: {
             int nmax = 0;
@@ -604,12 +620,12 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
             const unsigned th = (unsigned)(2 * nmax < 512 ? ((2 * nmax + 63) / 64) * 64 : 512);
             // the coarsest level over-relaxes the velocity and pressure
             // updates (the primitive box, the projection pressure step)
-            const bool coarsest = kind == OP_COARSE, pj = x0->opt.scheme == QNSCH_PROJECTION;
+            const bool coarsest = kind == OP_COARSE;
             const int sweeps = coarsest ? x0->opt.nu_coarse : colour % PROLONG_FIRST;
             const int prolong = coarsest ? 0 : colour / PROLONG_FIRST;
             const double om = coarsest && !pj ? x0->opt.coarse_omega : omega;
             const double pom = coarsest && pj ? x0->opt.coarse_omega : 1.0;
-            KLAUNCH(k_coarse_solve, W, dim3(W.blocks), dim3(th), W.lds, s, sweeps, om, pom, prolong);
+            KLAUNCH_PJ(k_coarse_solve, W, dim3(W.blocks), dim3(th), W.lds, s, sweeps, om, pom, prolong);
             break;
         }
         case OP_PROLONG: KLAUNCH(k_prolong, W, dim3(W.blocks), dim3(BLK), 0, s); break;
@@ -637,7 +653,7 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
         case OP_NORMACC: {
             if (kind == OP_NORMACC)
                 for (size_t q = 0; q < part.size(); q++) acc_record_launch(part[q].first, W.it.acc[q]);
-            KLAUNCH(k_resid_norm, W, dim3(W.blocks), dim3(TBLK), 0, s);
+            KLAUNCH_PJ(k_resid_norm, W, dim3(W.blocks), dim3(TBLK), 0, s);
             ItemList F = finalize_list(part, OP_NORM);
             for (size_t q = 0; q < part.size(); q++) F.it.acc[q] = W.it.acc[q];
             KLAUNCH(k_finalize, F, dim3(F.blocks), dim3(BLK), 0, s, 0);
@@ -928,11 +944,39 @@ static PhysF physf_of(const Phys &P)
     PhysF F;
     F.rho1 = (float)P.rho1; F.rho12 = (float)P.rho12; F.drho = (float)P.drho;
     F.visc1 = (float)P.visc1; F.visc12 = (float)P.visc12; F.dvisc = (float)P.dvisc;
-    F.alpha = (float)P.alpha; F.inv_Re = (float)P.inv_Re; F.inv_M = (float)P.inv_M; F.inv_Pe = (float)P.inv_Pe;
-    F.K1 = (float)P.K1; F.K2 = (float)P.K2; F.K3 = (float)P.K3; F.mob_reg = (float)P.mob_reg;
-    F.inv_dt = 0.0f;
+    F.alpha = (float)P.alpha; F.mob_reg = (float)P.mob_reg;
     F.coupled = P.coupled;
     return F;
+}
+
+// coefficients of a level from the physical constants, its 1/h and the step
+// size (0: not known yet)
+template <typename R> static Kon<R> kon_of(const Phys &P, double ih)
+{
+    const double ih2 = ih * ih;
+    Kon<R> K;
+    K.ih = (R)ih; K.hih = (R)(0.5 * ih);
+    K.idt = (R)P.inv_dt; K.hidt = (R)(0.5 * P.inv_dt); K.dt2 = (R)(2.0 * P.dt);
+    K.ka = (R)(ih / 16.0);
+    K.kv = (R)(P.inv_Re * ih2 / 3.0); K.kv34 = (R)(P.inv_Re * ih2 * 0.25);
+    K.kp = (R)(P.inv_M * ih); K.hkp = (R)(0.5 * P.inv_M * ih); K.iM = (R)P.inv_M;
+    K.km = (R)(0.5 * P.inv_Pe * ih2); K.akm = (R)(0.5 * P.alpha * P.inv_Pe * ih2);
+    K.alpha = (R)P.alpha;
+    K.K1 = (R)P.K1; K.kg = (R)(0.25 * P.K2 * ih2); K.kl = (R)(0.125 * P.K3 * ih2);
+    K.inv_Fr = (R)P.inv_Fr; K.rho_ref = (R)P.rho_ref;
+    return K;
+}
+
+// the step size of every level descriptor (host copy)
+static void desc_dt(qnsch_ctx *x, double dt)
+{
+    for (int l = 0; l < x->nlev; l++) {
+        Desc &d = x->hd[l];
+        d.P.inv_dt = 1.0 / dt;
+        d.P.dt = dt;
+        d.K = kon_of<double>(d.P, d.inv_h);
+        d.Kf = kon_of<float>(d.P, d.inv_h);
+    }
 }
 
 static int upload_desc(qnsch_ctx *x)
@@ -1071,8 +1115,9 @@ static size_t device_lds_max()
     int v = 0;
     size_t r = 65536;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 65536
-        && hipFuncSetAttribute((const void *)k_coarse_solve<Items>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
-        && hipFuncSetAttribute((const void *)k_coarse_solve<Item1>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
+        && hipFuncSetAttribute((const void *)k_coarse_solve<false, Items>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
+        && hipFuncSetAttribute((const void *)k_coarse_solve<false, Item1>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
+        && hipFuncSetAttribute((const void *)k_coarse_solve<true, Item1>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
         && hipFuncSetAttribute((const void *)k_mx_coarse_solve<Items>, hipFuncAttributeMaxDynamicSharedMemorySize, v)
                == hipSuccess
         && hipFuncSetAttribute((const void *)k_mx_coarse_solve<Item1>, hipFuncAttributeMaxDynamicSharedMemorySize, v)
@@ -1174,7 +1219,7 @@ static int ctx_init(qnsch_ctx *x, const qnsch_grid *g, const qnsch_params *p, co
         D.h = hx * (double)(1 << l);
         Desc &d = x->hd[l];
         d.m1 = D.m1; d.m2 = D.m2; d.pitch = D.pitch; d.bcx = g->bc_x; d.bcy = g->bc_y;
-        d.h = D.h; d.inv_h = 1.0 / D.h; d.finv_h = (float)d.inv_h;
+        d.h = D.h; d.inv_h = 1.0 / D.h;
         d.coarse = l + 1 < x->nlev ? x->dd + l + 1 : nullptr;
     }
     set_params(x, p);
@@ -1276,11 +1321,7 @@ int qnsch_get_state(qnsch_ctx *x, double *c, double *mu, double *p, double *u, d
 static int set_dt(qnsch_ctx *x, double dt)
 {
     x->dt = dt;
-    for (int l = 0; l < x->nlev; l++) {
-        x->hd[l].P.inv_dt = 1.0 / dt;
-        x->hd[l].P.dt = dt;
-        x->hd[l].Pf.inv_dt = (float)(1.0 / dt);
-    }
+    desc_dt(x, dt);
     return upload_desc(x);
 }
 
@@ -1806,7 +1847,7 @@ int qnsch_residual_noalloc(const qnsch_grid *g, const qnsch_params *prm, double 
     d.m1 = g->m1; d.m2 = g->m2; d.pitch = g->m1; d.bcx = g->bc_x; d.bcy = g->bc_y;
     d.h = g->Lx / g->m1;
     d.inv_h = 1.0 / d.h;
-    d.finv_h = (float)d.inv_h;
+    d.K = kon_of<double>(P, d.inv_h);
     d.partials = (double *)(base + NOALLOC_DESC_BYTES);
     d.red = d.partials + (size_t)NOALLOC_TILES * NRED;
     d.red_host = d.red + NRED;  // the reduced values stay on the device
@@ -1820,7 +1861,7 @@ int qnsch_residual_noalloc(const qnsch_grid *g, const qnsch_params *prm, double 
         it.d[0] = (const Desc *)base;
         it.tx[0] = tx;
         it.acc[0] = -1;
-        hipLaunchKernelGGL(k_resid_norm<Item1>, dim3(tx * ty), dim3(TBLK), 0, s, it);
+        hipLaunchKernelGGL((k_resid_norm<false, Item1>), dim3(tx * ty), dim3(TBLK), 0, s, it);
         Item1 f = it;
         f.start[1] = 1;
         f.tx[0] = tx * ty;
@@ -1995,11 +2036,7 @@ static int admit(qnsch_server *S, Req *r)
     }
     if (!rc) {
         x->dt = r->dt;
-        for (int l = 0; l < x->nlev; l++) {
-            x->hd[l].P.inv_dt = 1.0 / r->dt;
-            x->hd[l].P.dt = r->dt;
-            x->hd[l].Pf.inv_dt = (float)(1.0 / r->dt);
-        }
+        desc_dt(x, r->dt);
         // hd and stage are pinned and not touched again before this
         // context's next admission, long after these copies have run
         rc = upload_desc(x);

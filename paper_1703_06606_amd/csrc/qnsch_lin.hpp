@@ -21,9 +21,10 @@
 // and mass-equation terms) is linear in the unknowns and is applied to delta
 // with the FP64 formulas; gravity and time-n sources drop out.
 //
-// Tile layout: the field indices of the FP64 tile are kept for the fields that
-// play the same role (so the axis descriptor Ax is shared), with the
-// unknowns replaced by their corrections.
+// Tile layout: the element of the FP64 tile (T_C holds c^, the linearisation
+// point; T_MU, T_P, T_U, T_V the corrections dmu, dp, du, dv) with the
+// correction dc and the induced change of density rho'(c^) dc behind it, so
+// that the axis descriptor, the momentum rows and the box solve are shared.
 #pragma once
 #include "qnsch_dev.hpp"
 
@@ -31,7 +32,7 @@ namespace qn {
 
 struct PhysF {
     float rho1, rho12, drho, visc1, visc12, dvisc;
-    float alpha, inv_Re, inv_M, inv_Pe, K1, K2, K3, mob_reg, inv_dt;
+    float alpha, mob_reg;
     int coupled; // smoother as in Phys
 };
 
@@ -43,15 +44,9 @@ struct LView {
     const float *cn, *un, *vn;            // time-n data
     const float *rc, *rmu, *rp, *ru, *rv; // right-hand side
     int m1, m2, pitch, bcx, bcy;
-    float inv_h;
 };
 
-// tile fields: L_C holds c^ (the linearisation point), L_MU, L_P, L_U, L_V
-// the corrections dmu, dp, du, dv; L_DC the correction dc and L_DRS the
-// induced change of density rho'(c^) dc
-enum { L_C = T_C, L_MU = T_MU, L_P = T_P, L_U = T_U, L_V = T_V, L_CN = T_CN, L_UN = T_UN, L_VN = T_VN, L_RN = T_RN,
-       L_MV = T_MV, L_MOB = T_MOB, L_RS = T_RS, L_DC = T_NF, L_DRS, L_NF };
-typedef TileT<float> TileF;
+typedef TileT<float, L_ES> TileF;
 
 __device__ __forceinline__ float frcpf(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ float rhof(const PhysF &P, float c) { return P.rho12 * frcpf(P.drho * c + P.rho1); }
@@ -62,121 +57,75 @@ __device__ __forceinline__ float mobf(const PhysF &P, float c)
     return __builtin_sqrtf(q * q + P.mob_reg);
 }
 
-__device__ __forceinline__ void ltile_load(const PhysF &P, const LView &L, const TileF &T)
+// an element's fields from its nine loaded values (c^, dc, dmu, dp, du, dv,
+// c^n, u^n, v^n) and the signs of its faces
+__device__ __forceinline__ void ltile_put(const PhysF &P, float *t, int su, int sv, const float (&v)[9])
 {
-    const int n = T.W * T.H;
-    if (tile_inner(L.m1, L.m2, T.i0, T.j0, T.W, T.H) && n <= 2 * (int)block_threads()) {
-        // no boundary images: plain strided loads, a thread's two elements
-        // loaded together (see tile_load)
-        const int e0 = threadIdx.x, e1r = threadIdx.x + block_threads(), e1 = e1r < n ? e1r : n - 1;
-        auto at = [&](int e) {
-            const int b = e / T.W, a = e - b * T.W;
-            return (size_t)(T.j0 - 1 + b) * L.pitch + (T.i0 - 1 + a);
-        };
-        const size_t q0 = at(e0 < n ? e0 : n - 1), q1 = at(e1);
-        float v0[9], v1[9];
-        const float *src[9] = { L.c, L.dc, L.dmu, L.dp, L.du, L.dv, L.cn, L.un, L.vn };
+    const float rs = rhof(P, v[0]);
+    t[T_C] = v[0];
+    t[T_CN] = v[6];
+    t[T_MU] = v[2];
+    t[T_P] = v[3];
+    t[T_RN] = rhof(P, v[6]);
+    t[T_MV] = viscf(P, v[6]);
+    t[T_RS] = rs;
+    t[T_MOB] = mobf(P, v[6]);
+    t[T_U] = signed_val(su, v[4]);
+    t[T_V] = signed_val(sv, v[5]);
+    t[T_UN] = signed_val(su, v[7]);
+    t[T_VN] = signed_val(sv, v[8]);
+    t[L_DC] = v[1];
+    t[L_DRS] = -P.alpha * rs * rs * v[1];
+}
+
+// cooperative load of a tile, NE elements per thread (as tile_load)
+template <int NE> __device__ __forceinline__ void ltile_load(const PhysF &P, const LView &L, const TileF &T)
+{
+    const int n = T.W * T.H, nt = block_threads();
+    float v[NE][9];
+    if (tile_inner(L.m1, L.m2, T.i0, T.j0, T.W, T.H)) {
 #pragma unroll
-        for (int f = 0; f < 9; f++) {
-            v0[f] = src[f][q0];
-            v1[f] = src[f][q1];
+        for (int k = 0; k < NE; k++) {
+            const int e = min((int)threadIdx.x + k * nt, n - 1), b = e / T.W, a = e - b * T.W;
+            const size_t q = (size_t)((T.j0 - 1 + b) * L.pitch + (T.i0 - 1 + a));
+            const float *src[9] = { L.c, L.dc, L.dmu, L.dp, L.du, L.dv, L.cn, L.un, L.vn };
+#pragma unroll
+            for (int f = 0; f < 9; f++) v[k][f] = lda<1>(src[f], q);
         }
-        auto put = [&](int e, const float *v) {
-            float *s = T.s + e;
-            s[L_C * n] = v[0];
-            s[L_DC * n] = v[1];
-            s[L_MU * n] = v[2];
-            s[L_P * n] = v[3];
-            s[L_U * n] = v[4];
-            s[L_V * n] = v[5];
-            s[L_CN * n] = v[6];
-            s[L_UN * n] = v[7];
-            s[L_VN * n] = v[8];
-            s[L_RN * n] = rhof(P, v[6]);
-            s[L_MV * n] = viscf(P, v[6]);
-            s[L_MOB * n] = mobf(P, v[6]);
-            const float rs = rhof(P, v[0]);
-            s[L_RS * n] = rs;
-            s[L_DRS * n] = -P.alpha * rs * rs * v[1];
-        };
-        if (e0 < n) put(e0, v0);
-        if (e1r < n) put(e1r, v1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < NE; k++) {
+            const int e = threadIdx.x + k * nt;
+            if (e < n) ltile_put(P, T.s + e * L_ES, 1, 1, v[k]);
+        }
         return;
     }
-    if (n <= 2 * (int)block_threads()) {
-        // boundary images: sources first, then all loads together (see tile_load)
-        const int e0 = threadIdx.x, e1 = threadIdx.x + block_threads();
-        auto src = [&](int e) {
-            const int b = e / T.W, a = e - b * T.W;
-            TileSrc q = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, T.i0 - 1 + a, T.j0 - 1 + b);
-            if (e >= n) q.sc = q.su = q.sv = 0;
-            return q;
-        };
-        const TileSrc s0 = src(e0 < n ? e0 : 0), s1 = src(e1 < n ? e1 : 0);
-        const float v0[9] = { L.c[s0.c], L.dc[s0.c], L.dmu[s0.c], L.dp[s0.c], L.du[s0.u], L.dv[s0.v],
-                              L.cn[s0.c], L.un[s0.u], L.vn[s0.v] };
-        const float v1[9] = { L.c[s1.c], L.dc[s1.c], L.dmu[s1.c], L.dp[s1.c], L.du[s1.u], L.dv[s1.v],
-                              L.cn[s1.c], L.un[s1.u], L.vn[s1.v] };
-        auto put = [&](int e, const TileSrc &q, const float *v) {
-            float *s = T.s + e;
-            if (q.sc == 0) {
-                for (int f = 0; f < L_NF; f++) s[f * n] = 0.0f;
-                return;
-            }
-            s[L_C * n] = v[0];
-            s[L_DC * n] = v[1];
-            s[L_MU * n] = v[2];
-            s[L_P * n] = v[3];
-            s[L_U * n] = signed_val(q.su, v[4]);
-            s[L_V * n] = signed_val(q.sv, v[5]);
-            s[L_CN * n] = v[6];
-            s[L_UN * n] = signed_val(q.su, v[7]);
-            s[L_VN * n] = signed_val(q.sv, v[8]);
-            s[L_RN * n] = rhof(P, v[6]);
-            s[L_MV * n] = viscf(P, v[6]);
-            s[L_MOB * n] = mobf(P, v[6]);
-            const float rs = rhof(P, v[0]);
-            s[L_RS * n] = rs;
-            s[L_DRS * n] = -P.alpha * rs * rs * v[1];
-        };
-        if (e0 < n) put(e0, s0, v0);
-        if (e1 < n) put(e1, s1, v1);
-        return;
+    TileSrc s[NE];
+#pragma unroll
+    for (int k = 0; k < NE; k++) {
+        const int e = min((int)threadIdx.x + k * nt, n - 1), b = e / T.W, a = e - b * T.W;
+        s[k] = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, T.i0 - 1 + a, T.j0 - 1 + b);
+        const float w[9] = { lda<1>(L.c, s[k].c), lda<1>(L.dc, s[k].c), lda<1>(L.dmu, s[k].c), lda<1>(L.dp, s[k].c),
+                             lda<1>(L.du, s[k].u), lda<1>(L.dv, s[k].v), lda<1>(L.cn, s[k].c), lda<1>(L.un, s[k].u),
+                             lda<1>(L.vn, s[k].v) };
+#pragma unroll
+        for (int f = 0; f < 9; f++) v[k][f] = w[f];
     }
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
-        const int b = e / T.W, a = e - b * T.W;
-        const int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
-        float *s = T.s + e;
-        if (i > L.m1 + 1 || j > L.m2 + 1) {
-            for (int f = 0; f < L_NF; f++) s[f * n] = 0.0f;
-            continue;
-        }
-        const float c = ldc(L.c, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        const float cn = ldc(L.cn, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        const float dc = ldc(L.dc, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[L_C * n] = c;
-        s[L_DC * n] = dc;
-        s[L_MU * n] = ldc(L.dmu, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[L_P * n] = ldc(L.dp, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[L_U * n] = ldu(L.du, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[L_V * n] = ldv(L.dv, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[L_CN * n] = cn;
-        s[L_UN * n] = ldu(L.un, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[L_VN * n] = ldv(L.vn, L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        s[L_RN * n] = rhof(P, cn);
-        s[L_MV * n] = viscf(P, cn);
-        s[L_MOB * n] = mobf(P, cn);
-        const float rs = rhof(P, c);
-        s[L_RS * n] = rs;
-        s[L_DRS * n] = -P.alpha * rs * rs * dc;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < NE; k++) {
+        const int e = threadIdx.x + k * nt;
+        if (e >= n) continue;
+        if (s[k].sc == 0) tile_zero(T, e);
+        else ltile_put(P, T.s + e * L_ES, s[k].su, s[k].sv, v[k]);
     }
 }
 
-// reload of the corrections into a tile that ltile_load filled before, after
-// a half-sweep of the given colour, with the sources computed once
-// (tile_map_build): all face corrections, and the cell corrections and the
-// density change of the elements whose source cell has that colour (the
-// linearisation point and time-n fields stay)
+// reload of the corrections into a tile filled before, after a half-sweep of
+// the given colour, with the sources computed once (tile_map_build): all face
+// corrections, and the cell corrections and the density change of the
+// elements whose source cell has that colour (the linearisation point and
+// time-n fields stay)
 __device__ __forceinline__ void ltile_refresh_map(const PhysF &P, const LView &L, const TileF &T, const int *map,
                                                   int colour)
 {
@@ -185,349 +134,207 @@ __device__ __forceinline__ void ltile_refresh_map(const PhysF &P, const LView &L
         // the map entry, then every value the element may take, before any
         // use (as tile_refresh_map)
         const int q = map[4 * e], qu = map[4 * e + 1], qv = map[4 * e + 2], fl = map[4 * e + 3];
-        float *s = T.s + e;
-        const float du = L.du[qu], dv = L.dv[qv], dc = L.dc[q], dmu = L.dmu[q], dp = L.dp[q], rs = s[L_RS * n];
+        float *s = T.s + e * L_ES;
+        const float du = L.du[qu], dv = L.dv[qv], dc = L.dc[q], dmu = L.dmu[q], dp = L.dp[q], rs = s[T_RS];
         __builtin_amdgcn_sched_barrier(0);
         if (fl & 16) continue;
-        s[L_U * n] = signed_val((fl & 3) - 1, du);
-        s[L_V * n] = signed_val(((fl >> 2) & 3) - 1, dv);
+        s[T_U] = signed_val((fl & 3) - 1, du);
+        s[T_V] = signed_val(((fl >> 2) & 3) - 1, dv);
         if (((fl >> 5) & 1) != colour) continue;
-        s[L_DC * n] = dc;
-        s[L_MU * n] = dmu;
-        s[L_P * n] = dp;
-        s[L_DRS * n] = -P.alpha * rs * rs * dc;
+        s[L_DC] = dc;
+        s[T_MU] = dmu;
+        s[T_P] = dp;
+        s[L_DRS] = -P.alpha * rs * rs * dc;
     }
 }
 
-// one axis of the linearised cell equations at element e: the linear terms
-// applied to the corrections, the linearised gradient-energy and
-// capillary-divergence terms (dG, dL), and the values at c^ that the local
-// Jacobian needs
-struct LCellAx {
-    float adv, div, Lmu, Lp, Sm, Gc, Gn, dG, dL, dGc, dLra, dLrb;
-};
-
-__device__ __forceinline__ LCellAx lcell_axis(const TileF &T, const Ax &a, int e, float ih)
+// one axis of the linearised cell equations at element s: as axis_cell on the
+// corrections, with lr the linearised gradient-energy and capillary terms of
+// the chemical row beside the pointwise ones (across a wall the mirrored
+// ghost makes both the difference of c^ and that of dc vanish)
+__device__ __forceinline__ CellSum<float> laxis_cell(const Kon<float> &K, const float *s, const Ax &a, float r,
+                                                     float drs)
 {
-    const float ih2 = ih * ih;
-    const float wP = (a.per || a.ia < a.ma - 1) ? 1.0f : 0.0f, wM = (a.per || a.ia > 0) ? 1.0f : 0.0f;
-    const int eP = e + a.dn, eM = e - a.dn;
-    const float c = tq(T, L_C, e), cP = tq(T, L_C, eP), cM = tq(T, L_C, eM);
-    const float n = tq(T, L_CN, e), nP = tq(T, L_CN, eP), nM = tq(T, L_CN, eM);
-    const float dc = tq(T, L_DC, e), dcP = tq(T, L_DC, eP), dcM = tq(T, L_DC, eM);
-    const float mu = tq(T, L_MU, e), p = tq(T, L_P, e);
-    const float rnP = tq(T, L_RN, eP), rnM = tq(T, L_RN, eM), rn = tq(T, L_RN, e);
-    const float rs = tq(T, L_RS, e);
-    const float m0 = tq(T, L_MOB, e);
-    const float mP = 0.5f * (tq(T, L_MOB, eP) + m0) * wP, mM = 0.5f * (tq(T, L_MOB, eM) + m0) * wM;
-    const float uP = tq(T, a.FN, eP), u0 = tq(T, a.FN, e);
-    LCellAx x;
-    x.adv = 0.5f * ih * (rnP * (nP - n) * uP + rnM * (n - nM) * u0);
-    x.div = ih * (uP - u0);
-    x.Lmu = ih2 * (mP * (tq(T, L_MU, eP) - mu) - mM * (mu - tq(T, L_MU, eM)));
-    x.Lp = ih2 * (mP * (tq(T, L_P, eP) - p) - mM * (p - tq(T, L_P, eM)));
-    x.Sm = ih2 * (mP + mM);
-    const float dP = cP - c, dM = c - cM, gP = nP - n, gM = n - nM;
-    x.Gc = 0.5f * ih2 * (dP * dP + dM * dM);
-    x.Gn = 0.5f * ih2 * (gP * gP + gM * gM);
-    // d(Gc) = ih2 (dP d(dP) + dM d(dM)); across a wall the mirrored ghost
-    // makes both dP and d(dP) vanish
-    x.dG = ih2 * (dP * (dcP - dc) + dM * (dc - dcM));
-    const float rh = 0.5f * (rs + rn);
-    const float kP = 0.5f * (0.5f * (tq(T, L_RS, eP) + rnP) + rh) * wP;
-    const float kM = 0.5f * (0.5f * (tq(T, L_RS, eM) + rnM) + rh) * wM;
-    const float hP = 0.5f * (dP + gP), hM = 0.5f * (dM + gM);
-    const float drs = tq(T, L_DRS, e);
-    const float dkP = 0.25f * (tq(T, L_DRS, eP) + drs) * wP, dkM = 0.25f * (tq(T, L_DRS, eM) + drs) * wM;
-    x.dL = ih2 * (dkP * hP + kP * 0.5f * (dcP - dc) - dkM * hM - kM * 0.5f * (dc - dcM));
-    x.dGc = ih2 * (wP * (-dP) + wM * dM);
-    x.dLra = ih2 * (wP * hP - wM * hM);
-    x.dLrb = ih2 * (kP + kM);
+    const bool wP = a.per || a.ia < a.ma - 1, wM = a.per || a.ia > 0;
+    const float *sP = s + a.dn, *sM = s - a.dn;
+    const float mP = sP[T_MOB] + s[T_MOB], mM = sM[T_MOB] + s[T_MOB];
+    const float S = s[T_MU] + K.alpha * s[T_P];
+    const float fP = (sP[T_MU] + K.alpha * sP[T_P]) - S, fM = S - (sM[T_MU] + K.alpha * sM[T_P]);
+    const float flux = mP * fP - mM * fM;
+    const float gP = sP[T_CN] - s[T_CN], gM = s[T_CN] - sM[T_CN], dP = sP[T_C] - s[T_C], dM = s[T_C] - sM[T_C];
+    const float eP = sP[L_DC] - s[L_DC], eM = s[L_DC] - sM[L_DC];
+    const float uP = sP[a.fn], u0 = s[a.fn];
+    CellSum<float> x;
+    const float adv = (sP[T_RN] * gP) * uP + (sM[T_RN] * gM) * u0;
+    x.s1 = K.hih * adv - K.km * flux;
+    x.s2 = K.ih * (uP - u0) - K.akm * flux;
+    x.sm = K.km * ((wP ? mP : 0.0f) + (wM ? mM : 0.0f));
+    x.g = (dP * dP + dM * dM) + (gP * gP + gM * gM);
+    const float hP = dP + gP, hM = dM + gM;
+    const float R0 = s[T_RS] + s[T_RN];
+    const float RP = (sP[T_RS] + sP[T_RN]) + R0, RM = (sM[T_RS] + sM[T_RN]) + R0;
+    const float dL = ((sP[L_DRS] + s[L_DRS]) * hP - (sM[L_DRS] + s[L_DRS]) * hM) + (RP * eP - RM * eM);
+    const float k2 = 2.0f * K.kg * r;
+    x.lr = K.kl * dL - k2 * (dP * eP + dM * eM);
+    const float w = (wP ? RP : 0.0f) + (wM ? RM : 0.0f);
+    x.j = K.kl * (drs * (hP - hM) - w) - k2 * (dM - dP);
     return x;
-}
-
-__device__ __forceinline__ LCellAx lcell_sum(const LCellAx &x)
-{
-    LCellAx s;
-    s.adv = x.adv + other(x.adv);
-    s.div = x.div + other(x.div);
-    s.Lmu = x.Lmu + other(x.Lmu);
-    s.Lp = x.Lp + other(x.Lp);
-    s.Sm = x.Sm + other(x.Sm);
-    s.Gc = x.Gc + other(x.Gc);
-    s.Gn = x.Gn + other(x.Gn);
-    s.dG = x.dG + other(x.dG);
-    s.dL = x.dL + other(x.dL);
-    s.dGc = x.dGc + other(x.dGc);
-    s.dLra = x.dLra + other(x.dLra);
-    s.dLrb = x.dLrb + other(x.dLrb);
-    return s;
 }
 
 // J delta for the three cell equations and the local 2x2 Jacobian in
 // (c_ij, mubar_ij) at c^ (the matrix of the FP64 point smoother)
 struct LCellEq {
     float Nc, Nmu, Np;
-    float Jcc, Jcm, Jmc, Jmm, Jpp;
+    float Jcc, Jcm, Jmc, Jmm;
 };
-
-__device__ __forceinline__ LCellEq lcell_eq(const PhysF &P, const TileF &T, int e, const LCellAx &s, float muh)
+__device__ __forceinline__ void lcell_r(const Kon<float> &K, const float *s, float &r, float &drs)
 {
-    const float c = tq(T, L_C, e), n = tq(T, L_CN, e);
-    const float rs = tq(T, L_RS, e), rn = tq(T, L_RN, e);
-    const float dc = tq(T, L_DC, e), dmu = tq(T, L_MU, e);
-    const float drs = -P.alpha * rs * rs;
+    const float t = -K.alpha * s[T_RS];
+    r = t * s[T_RN];
+    drs = t * s[T_RS];
+}
+__device__ __forceinline__ LCellEq lcell_eq(const Kon<float> &K, const float *s, const CellSum<float> &x, float r,
+                                            float drs, float muh)
+{
+    const float c = s[T_C], n = s[T_CN], rs = s[T_RS], rn = s[T_RN], dc = s[L_DC], dmu = s[T_MU];
     LCellEq q;
-    q.Jcc = (drs * (c - n) + rs) * P.inv_dt;
-    q.Nc = q.Jcc * dc + s.adv - P.inv_Pe * s.Lmu - P.alpha * P.inv_Pe * s.Lp;
-    q.Np = s.div - P.alpha * P.inv_Pe * s.Lmu - P.alpha * P.alpha * P.inv_Pe * s.Lp;
+    q.Jcc = K.idt * (drs * (c - n) + rs);
+    q.Nc = q.Jcc * dc + x.s1;
+    q.Np = x.s2;
     const float rh = 0.5f * (rs + rn);
-    const float q1 = c * (c - 1.0f), q0 = n * (n - 1.0f);
-    const float g = 0.25f * (q1 + q0) * (c + n - 1.0f);
-    const float Fh = 0.5f * (0.25f * q1 * q1 + 0.25f * q0 * q0);
-    const float r = -P.alpha * rs * rn;
-    const float Gh = 0.5f * (s.Gc + s.Gn);
-    const float dg = 0.25f * ((2.0f * c - 1.0f) * (c + n - 1.0f) + q1 + q0);
+    const float q1 = c * (c - 1.0f), q0 = n * (n - 1.0f), t = c + n - 1.0f, qs = q1 + q0;
+    const float g = 0.25f * qs * t;
+    const float Fh = 0.125f * (q1 * q1 + q0 * q0);
+    const float G = K.kg * x.g + K.K1 * Fh;
+    const float dg = 0.25f * ((2.0f * c - 1.0f) * t + qs);
     const float f1 = q1 * (c - 0.5f);
-    const float dr = P.alpha * P.alpha * rs * rs * rn;
+    const float dr = -K.alpha * rs * r;
     // derivative in the cell's own c of every term that is pointwise in it
-    const float Jpw = drs * muh - P.K1 * (0.5f * drs * g + rh * dg + 0.5f * f1 * r + Fh * dr) - P.K2 * Gh * dr;
-    q.Nmu = rs * dmu + Jpw * dc - P.K2 * 0.5f * s.dG * r + P.K3 * s.dL;
-    q.Jcm = P.inv_Pe * s.Sm;
+    const float Jpw = drs * muh - K.K1 * (0.5f * (drs * g + f1 * r) + rh * dg) - G * dr;
+    q.Nmu = rs * dmu + Jpw * dc + x.lr;
+    q.Jcm = x.sm;
     q.Jmm = rs;
-    const float dLr = 0.25f * drs * s.dLra - 0.5f * s.dLrb;
-    q.Jmc = Jpw - P.K2 * 0.5f * s.dGc * r + P.K3 * dLr;
-    q.Jpp = P.alpha * P.alpha * P.inv_Pe * s.Sm;
+    q.Jmc = Jpw + x.j;
     return q;
 }
-
-struct FaceEqF {
-    float N, diag;
-};
-
-// J delta for the momentum equation on the face at element ef, and the
-// derivative in the face's own velocity at w^ (uh = that face's velocity at
-// w^, which multiplies the change of the density average)
-__device__ __forceinline__ FaceEqF lface_eq(const PhysF &P, const TileF &T, const Ax &a, int ef, int it, float ih,
-                                            float uh)
-{
-    const float ih2 = ih * ih;
-    const int eL = ef - a.dn, eR = ef, dt = a.dt;
-    const float rL = tq(T, L_RN, eL), rR = tq(T, L_RN, eR);
-    const float Rt = 0.25f * (rL + rR + tq(T, L_RN, eL + dt) + tq(T, L_RN, eR + dt));
-    const float Rb = 0.25f * (rL + rR + tq(T, L_RN, eL - dt) + tq(T, L_RN, eR - dt));
-    const float mvL = tq(T, L_MV, eL), mvR = tq(T, L_MV, eR);
-    const float nut = 0.25f * (mvL + mvR + tq(T, L_MV, eL + dt) + tq(T, L_MV, eR + dt));
-    const float nub = 0.25f * (mvL + mvR + tq(T, L_MV, eL - dt) + tq(T, L_MV, eR - dt));
-    const float Arn = 0.5f * (rL + rR);
-    const float Ars = 0.5f * (tq(T, L_RS, eL) + tq(T, L_RS, eR));
-    const float dArs = 0.5f * (tq(T, L_DRS, eL) + tq(T, L_DRS, eR));
-    const float un0 = tq(T, a.FNN, ef);
-    const float wL = rL * 0.5f * (tq(T, a.FNN, ef - a.dn) + un0);
-    const float wR = rR * 0.5f * (un0 + tq(T, a.FNN, ef + a.dn));
-    const float Vt = 0.5f * (tq(T, a.FTN, eL + dt) + tq(T, a.FTN, eR + dt));
-    const float Vb = 0.5f * (tq(T, a.FTN, eL) + tq(T, a.FTN, eR));
-    const float u0 = tq(T, a.FN, ef), uE = tq(T, a.FN, ef + a.dn), uW = tq(T, a.FN, ef - a.dn);
-    const float uN = tq(T, a.FN, ef + dt), uS = tq(T, a.FN, ef - dt);
-    const float thR = ih * (uE - u0 + tq(T, a.FT, eR + dt) - tq(T, a.FT, eR));
-    const float thL = ih * (u0 - uW + tq(T, a.FT, eL + dt) - tq(T, a.FT, eL));
-    const float nL = tq(T, L_CN, eL), nR = tq(T, L_CN, eR);
-    FaceEqF q;
-    q.N = Arn * u0 * P.inv_dt
-        + 0.5f * ih * (wR * uE - wL * uW + Rt * Vt * uN - Rb * Vb * uS)
-        + 0.5f * (Ars - Arn) * P.inv_dt * u0 + 0.5f * dArs * P.inv_dt * uh
-        + P.inv_M * ih * (tq(T, L_P, eR) - tq(T, L_P, eL))
-        - P.inv_M * ih * 0.5f * (rR * tq(T, L_MU, eL) + rL * tq(T, L_MU, eR)) * (nR - nL)
-        - P.inv_Re * ih2 * (mvR * (uE - u0) - mvL * (u0 - uW) + nut * (uN - u0) - nub * (u0 - uS))
-        - (P.inv_Re / 3.0f) * ih * (mvR * thR - mvL * thL);
-    const float gt = (!a.pert && it == a.mt - 1) ? 1.0f : 0.0f, gb = (!a.pert && it == 0) ? 1.0f : 0.0f;
-    q.diag = 0.5f * (Arn + Ars) * P.inv_dt + (4.0f / 3.0f) * P.inv_Re * ih2 * (mvL + mvR)
-           + P.inv_Re * ih2 * (nut * (1.0f + gt) + nub * (1.0f + gb)) + 0.5f * ih * (gb * Rb * Vb - gt * Rt * Vt);
-    return q;
-}
-
 
 // one cell of the current colour: the FP64 smoother applied to the
 // correction equation J(w^) delta = r.  Segregated: step 1 is a 2x2 solve for
 // (dc, dmu) of the cell, step 2 the 5x5 Vanka box for its four faces and dp.
 // Coupled: the seven-unknown box of the FP64 smoother with the entries of J at
-// w^ (the face rows' dc entry multiplies the face velocity at w^), eliminated
-// the same way.
+// w^ (the face rows' dc entry multiplies the face velocity at w^), solved the
+// same way.
 // With TO set, as relax_cell: the cell at tile position (ti, tj), results
 // kept in the tile (dc, dmu, dp and the density change in place, the face
-// corrections in the fields L_NF (u) and L_NF + 1 (v)).
-template <bool TO, int AS = 0>
-__device__ __forceinline__ void lrelax_cell(const PhysF &P, const LView &L, const TileF &T, float *dunew,
-                                            float *dvnew, int i, int j, int ti, int tj, int hlf, float omega)
+// corrections in the fields T_U2, T_V2).
+template <bool TO, int AS>
+__device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K, const LView &L, const TileF &T,
+                                            float *dunew, float *dvnew, int i, int j, int ti, int tj, int hlf,
+                                            float omega)
 {
-    const size_t k = (size_t)j * L.pitch + i;
-    const float ih = L.inv_h, ih2 = ih * ih;
-    const int e = T.idx(ti, tj);
-    const Ax a = make_ax(L, T, i, j, hlf);
+    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf);
+    const Ax &a = b.a;
+    float *const e = T.at(ti, tj);
     const bool cpl = P.coupled;
-    const LCellAx s = lcell_sum(lcell_axis(T, a, e, ih));
-    const LCellEq q = lcell_eq(P, T, e, s, lda<AS>(L.mu, k));
-    const float r1 = lda<AS>(L.rc, k) - q.Nc, r2 = lda<AS>(L.rmu, k) - q.Nmu;
-    const float c0 = tq(T, L_DC, e), m0 = tq(T, L_MU, e);
-    const int st = T.W * T.H;
-    const float rs = tq(T, L_RS, e);
-    float mnew = m0;
-    if (!cpl) {
+    const float muh = lda<AS>(L.mu, b.k), f_c = lda<AS>(L.rc, b.k), f_mu = lda<AS>(L.rmu, b.k),
+                f_p = lda<AS>(L.rp, b.k);
+    // the velocity at w^ and the right-hand sides on the lane's two faces
+    // (west and east, or south and north, of the cell)
+    const float *fw = hlf ? L.v : L.u, *fN = hlf ? L.rv : L.ru;
+    const float uhlo = lda<AS>(fw, b.k), uhhi = lda<AS>(fw, b.khi);
+    const float f_lo = lda<AS>(fN, b.k), f_hi = lda<AS>(fN, b.khi);
+    float r, drs;
+    lcell_r(K, e, r, drs);
+    const CellSum<float> xo = laxis_cell(K, e, a, r, drs), x = xo + other(xo);
+    const LCellEq q = lcell_eq(K, e, x, r, drs, muh);
+    const float r1 = f_c - q.Nc, r2 = f_mu - q.Nmu;
+    const float c0 = e[L_DC], m0 = e[T_MU], p0 = e[T_P], rs = e[T_RS];
+    const float Jcp = K.alpha * x.sm;
+    float bp = f_p - q.Np;
+    float kmc = 0.0f, kbm = 0.0f, Jc = 0.0f, bc = 0.0f, gc = 0.0f;
+    if (cpl) {
+        const float imm = frcpf(q.Jmm);
+        kmc = q.Jmc * imm;
+        kbm = r2 * imm;
+        Jc = q.Jcc - q.Jcm * kmc;
+        bc = r1 - q.Jcm * kbm;
+        gc = 0.5f * K.hidt * drs;
+    } else {
         // ---- step 1
         const float idet = frcpf(q.Jcc * q.Jmm - q.Jcm * q.Jmc);
         const float cnew = c0 + (q.Jmm * r1 - q.Jcm * r2) * idet;
-        mnew = m0 + (q.Jcc * r2 - q.Jmc * r1) * idet;
+        const float dm = (q.Jcc * r2 - q.Jmc * r1) * idet, mnew = m0 + dm;
         if (!TO && hlf == 0) {
-            sta<AS>(L.dc, k, cnew);
-            sta<AS>(L.dmu, k, mnew);
+            sta<AS>(L.dc, b.k, cnew);
+            sta<AS>(L.dmu, b.k, mnew);
         }
-        T.s[L_DC * st + e] = cnew;
-        T.s[L_MU * st + e] = mnew;
-        T.s[L_DRS * st + e] = -P.alpha * rs * rs * cnew;
+        e[L_DC] = cnew;
+        e[T_MU] = mnew;
+        e[L_DRS] = -P.alpha * rs * rs * cnew;
+        bp -= Jcp * dm;
     }
     // ---- the box
-    const bool hlo = a.per || a.ia >= 1, hhi = a.per || a.ia + 1 < a.ma;
-    const int ihi = hlf ? i : (i + 1 < L.m1 ? i + 1 : 0), jhi = hlf ? (j + 1 < L.m2 ? j + 1 : 0) : j;
-    const size_t khi = (size_t)jhi * L.pitch + ihi;
-    // the velocity at w^ on the lane's two faces (west and east, or south and
-    // north, of the cell)
-    const float uhlo = lda<AS>(hlf ? L.v : L.u, k), uhhi = lda<AS>(hlf ? L.v : L.u, khi);
-    const FaceEqF flo = lface_eq(P, T, a, e, a.it, ih, uhlo);
-    const FaceEqF fhi = lface_eq(P, T, a, e + a.dn, a.it, ih, uhhi);
-    const float *rN = hlf ? L.rv : L.ru;
-    const float blo = hlo ? lda<AS>(rN, k) - flo.N : 0.0f, dlo = hlo ? flo.diag : 1.0f;
-    const float bhi = hhi ? lda<AS>(rN, khi) - fhi.N : 0.0f, dhi = hhi ? fhi.diag : 1.0f;
-    const float Lmu_new = s.Lmu - s.Sm * (mnew - m0);
-    const float bp = lda<AS>(L.rp, k) - (s.div - P.alpha * P.inv_Pe * Lmu_new - P.alpha * P.alpha * P.inv_Pe * s.Lp);
-    const float w_ax = tq(T, L_RN, e) * 0.5f * (tq(T, a.FNN, e) + tq(T, a.FNN, e + a.dn));
-    const float mv0 = tq(T, L_MV, e);
-    const float vis = (4.0f / 3.0f) * P.inv_Re * ih2 * mv0, gd = P.inv_Re * ih2 * mv0 / 3.0f;
-    const float gp = P.inv_M * ih;
-    // periodic axis of two cells: the box faces meet twice (as in relax_pair)
-    float xlo = 0.0f, xhi = 0.0f;
-    if (a.per && a.ma == 2) {
-        const float w_o = tq(T, L_RN, e - a.dn) * 0.5f * (tq(T, a.FNN, e) + tq(T, a.FNN, e + a.dn));
-        const float v_o = (4.0f / 3.0f) * P.inv_Re * ih2 * tq(T, L_MV, e - a.dn);
-        xlo = -0.5f * ih * w_o - v_o;
-        xhi = 0.5f * ih * w_o - v_o;
-    }
-    // the box's unknowns in the lane's order, its own axis first (as in the
-    // FP64 box)
-    const float o_blo = other(blo), o_dlo = other(dlo), o_bhi = other(bhi), o_dhi = other(dhi), o_w = other(w_ax);
-    const float o_xlo = other(xlo), o_xhi = other(xhi);
-    const int o_hlo = other((int)hlo), o_hhi = other((int)hhi);
-    float A[5][5], b[5];
-    b[0] = blo; b[1] = bhi; b[2] = o_blo; b[3] = o_bhi; b[4] = bp;
-    const float m0l = hlo ? 1.0f : 0.0f, m0h = hhi ? 1.0f : 0.0f, m1l = o_hlo ? 1.0f : 0.0f, m1h = o_hhi ? 1.0f : 0.0f;
-    A[0][0] = dlo; A[0][1] = m0l * (0.5f * ih * w_ax - vis) + xlo; A[0][2] = m0l * gd; A[0][3] = -m0l * gd; A[0][4] = m0l * gp;
-    A[1][1] = dhi; A[1][0] = m0h * (-0.5f * ih * w_ax - vis) + xhi; A[1][2] = -m0h * gd; A[1][3] = m0h * gd; A[1][4] = -m0h * gp;
-    A[2][2] = o_dlo; A[2][3] = m1l * (0.5f * ih * o_w - vis) + o_xlo; A[2][0] = m1l * gd; A[2][1] = -m1l * gd; A[2][4] = m1l * gp;
-    A[3][3] = o_dhi; A[3][2] = m1h * (-0.5f * ih * o_w - vis) + o_xhi; A[3][0] = -m1h * gd; A[3][1] = m1h * gd; A[3][4] = -m1h * gp;
-    A[4][0] = -m0l * ih; A[4][1] = m0h * ih; A[4][2] = -m1l * ih; A[4][3] = m1h * ih; A[4][4] = q.Jpp;
-    float ac[5] = { 0.0f, 0.0f, 0.0f, 0.0f, 0.0f }, icc = 0.0f, bc = 0.0f, imm = 0.0f;
-    if (cpl) {
-        const int e1 = e + a.dn;
-        const float alo = hlo ? 0.5f * ih * tq(T, L_RN, e - a.dn) * (tq(T, L_CN, e) - tq(T, L_CN, e - a.dn)) : 0.0f;
-        const float ahi = hhi ? 0.5f * ih * tq(T, L_RN, e1) * (tq(T, L_CN, e1) - tq(T, L_CN, e)) : 0.0f;
-        const float ulo = hlo ? uhlo : 0.0f, uhi = hhi ? uhhi : 0.0f;
-        ac[0] = alo; ac[1] = ahi; ac[2] = other(alo); ac[3] = other(ahi);
-        const float uf[4] = { ulo, uhi, other(ulo), other(uhi) };
-        const float gc = 0.25f * (-P.alpha * rs * rs) * P.inv_dt;
-        const float Jcp = P.alpha * P.inv_Pe * s.Sm;
-        ac[4] = Jcp;
-        imm = frcpf(q.Jmm);
-        const float kmc = q.Jmc * imm, kbm = r2 * imm;
-        icc = frcpf(q.Jcc - q.Jcm * kmc);
-        bc = r1 - q.Jcm * kbm;
-        float gam[5];
-#pragma unroll
-        for (int f = 0; f < 4; f++) {
-            const float lam = -P.inv_M * ac[f];
-            gam[f] = gc * uf[f] - lam * kmc;
-            b[f] -= lam * kbm;
-        }
-        gam[4] = -Jcp * kmc;
-        b[4] -= Jcp * kbm;
-#pragma unroll
-        for (int r = 0; r < 5; r++) {
-            const float t = gam[r] * icc;
-#pragma unroll
-            for (int cc = 0; cc < 5; cc++) A[r][cc] -= t * ac[cc];
-            b[r] -= t * bc;
-        }
-    }
-    float inv[5];
-#pragma unroll
-    for (int cc = 0; cc < 4; cc++) {
-        inv[cc] = frcpf(A[cc][cc]);
-#pragma unroll
-        for (int r = cc + 1; r < 5; r++) {
-            const float l = A[r][cc] * inv[cc];
-#pragma unroll
-            for (int t = cc + 1; t < 5; t++) A[r][t] -= l * A[cc][t];
-            b[r] -= l * b[cc];
-        }
-    }
-    inv[4] = frcpf(A[4][4]);
-#pragma unroll
-    for (int cc = 4; cc >= 0; cc--) {
-        float acc = b[cc];
-#pragma unroll
-        for (int t = cc + 1; t < 5; t++) acc -= A[cc][t] * b[t];
-        b[cc] = acc * inv[cc];
-    }
-    if (cpl && hlf == 0) {
-        float acc = bc;
-#pragma unroll
-        for (int t = 0; t < 5; t++) acc -= ac[t] * b[t];
-        const float dc = acc * icc;
-        if (TO) {
-            T.s[L_DC * st + e] = c0 + dc;
-            T.s[L_MU * st + e] = m0 + (r2 - q.Jmc * dc) * imm;
-            T.s[L_DRS * st + e] = -P.alpha * rs * rs * (c0 + dc);
-        } else {
-            sta<AS>(L.dc, k, c0 + dc);
-            sta<AS>(L.dmu, k, m0 + (r2 - q.Jmc * dc) * imm);
-        }
-    }
-    const float dl = b[0], dh = b[1];
+    const FaceEq<float> flo = face_eq<float, false, true>(K, e, a, uhlo), fhi = face_eq<float, false, true>(K, e + a.dn, a, uhhi);
+    const float *P1 = e + a.dn, *M1 = e - a.dn;
+    const float alo = b.hlo ? K.hih * (M1[T_RN] * (e[T_CN] - M1[T_CN])) : 0.0f;
+    const float ahi = b.hhi ? K.hih * (P1[T_RN] * (P1[T_CN] - e[T_CN])) : 0.0f;
+    float alh, ahl;
+    box_offdiag(K, e, a, b.hlo, b.hhi, alh, ahl);
+    const float sb = kbm * K.iM, sc = kmc * K.iM;
+    const float blo = b.hlo ? (f_lo - flo.N) + sb * alo : 0.0f, bhi = b.hhi ? (f_hi - fhi.N) + sb * ahi : 0.0f;
+    const float qlo = b.hlo ? gc * uhlo + sc * alo : 0.0f, qhi = b.hhi ? gc * uhhi + sc * ahi : 0.0f;
+    const BoxAx<float> X = box_axis(b.hlo ? flo.diag : 1.0f, b.hhi ? fhi.diag : 1.0f, alh, ahl, blo, bhi,
+                                    b.hlo ? 1.0f : 0.0f, b.hhi ? -1.0f : 0.0f, qlo, qhi, alo, ahi);
+    float dp, dc, t, tt;
+    box_solve(X, box_other(X), cpl, K.kv * e[T_MV], K.kp, K.ih, K.alpha * Jcp, Jcp, kmc, kbm, Jc, bp, bc, dp, dc, t, tt);
+    const float nlo = e[a.fn] + omega * ((X.xb[0] + t * X.xs[0]) - dc * X.xq[0]);
+    const float nhi = P1[a.fn] + omega * ((X.xb[1] + t * X.xs[1]) - dc * X.xq[1]);
+    const float np = p0 + omega * dp;
     if (TO) {
-        float *fo = T.s + (L_NF + hlf) * st;
-        if (hlo) fo[e] = tq(T, a.FN, e) + omega * dl;
-        if (hhi) fo[e + a.dn] = tq(T, a.FN, e + a.dn) + omega * dh;
-        if (hlf == 0) T.s[L_P * st + e] = tq(T, L_P, e) + omega * b[4];
+        if (b.hlo) e[T_U2 + hlf] = nlo;
+        if (b.hhi) e[a.dn + T_U2 + hlf] = nhi;
+        if (hlf == 0) {
+            e[T_P] = np;
+            if (cpl) {
+                e[L_DC] = c0 + dc;
+                e[T_MU] = m0 + (kbm - kmc * dc);
+                e[L_DRS] = -P.alpha * rs * rs * (c0 + dc);
+            }
+        }
         return;
     }
-    float *dst = hlf ? dvnew : dunew;
-    if (hlo) sta<AS>(dst, k, tq(T, a.FN, e) + omega * dl);
-    if (hhi) sta<AS>(dst, khi, tq(T, a.FN, e + a.dn) + omega * dh);
-    if (hlf == 0) sta<AS>(L.dp, k, tq(T, L_P, e) + omega * b[4]);
-}
-template <int AS = 0>
-__device__ __forceinline__ void lrelax_pair(const PhysF &P, const LView &L, const TileF &T, float *dunew,
-                                            float *dvnew, int i, int j, int hlf, float omega)
-{
-    lrelax_cell<false, AS>(P, L, T, dunew, dvnew, i, j, i, j, hlf, omega);
+    float *fo = hlf ? dvnew : dunew;
+    if (b.hlo) sta<AS>(fo, b.k, nlo);
+    if (b.hhi) sta<AS>(fo, b.khi, nhi);
+    if (hlf == 0) {
+        sta<AS>(L.dp, b.k, np);
+        if (cpl) {
+            sta<AS>(L.dc, b.k, c0 + dc);
+            sta<AS>(L.dmu, b.k, m0 + (kbm - kmc * dc));
+        }
+    }
 }
 
 // residual of the correction equation r - J(w^) delta for the five equations
-// attached to cell (i, j) (cell equations; west face on lane 0, south face on
-// lane 1, zero for a face on a wall); the level is in global memory
-__device__ __forceinline__ void lresid_pair(const PhysF &P, const LView &L, const TileF &T, int i, int j, int hlf,
-                                            float &rc, float &rm, float &rp, float &rf)
+// attached to cell (i, j) (cell equations, west and south face, zero for a
+// face on a wall), by one lane; the level is in global memory
+struct ResidF {
+    float c, mu, p, u, v;
+};
+__device__ __forceinline__ ResidF lresid_cell(const Kon<float> &K, const LView &L, const TileF &T, int i, int j)
 {
     const size_t k = (size_t)j * L.pitch + i;
-    const int e = T.idx(i, j);
-    const Ax a = make_ax(L, T, i, j, hlf);
-    const LCellAx s = lcell_sum(lcell_axis(T, a, e, L.inv_h));
-    const LCellEq q = lcell_eq(P, T, e, s, lda<1>(L.mu, k));
-    rc = lda<1>(L.rc, k) - q.Nc;
-    rm = lda<1>(L.rmu, k) - q.Nmu;
-    rp = lda<1>(L.rp, k) - q.Np;
-    const bool hlo = a.per || a.ia >= 1;
-    // (the velocity at w^ on the lane's face)
-    const FaceEqF f = lface_eq(P, T, a, e, a.it, L.inv_h, lda<1>(hlf ? L.v : L.u, k));
-    rf = hlo ? lda<1>(hlf ? L.rv : L.ru, k) - f.N : 0.0f;
+    const float *e = T.at(i, j);
+    const Ax ax = make_ax(L, T, i, j, 0), ay = make_ax(L, T, i, j, 1);
+    const ResidF f = { lda<1>(L.rc, k), lda<1>(L.rmu, k), lda<1>(L.rp, k), lda<1>(L.ru, k), lda<1>(L.rv, k) };
+    const float muh = lda<1>(L.mu, k), uh = lda<1>(L.u, k), vh = lda<1>(L.v, k);
+    float r, drs;
+    lcell_r(K, e, r, drs);
+    const CellSum<float> x = laxis_cell(K, e, ax, r, drs) + laxis_cell(K, e, ay, r, drs);
+    const LCellEq q = lcell_eq(K, e, x, r, drs, muh);
+    const FaceEq<float> fu = face_eq<float, false, true>(K, e, ax, uh), fv = face_eq<float, false, true>(K, e, ay, vh);
+    return { f.c - q.Nc, f.mu - q.Nmu, f.p - q.Np, ax.per || i >= 1 ? f.u - fu.N : 0.0f,
+             ay.per || j >= 1 ? f.v - fv.N : 0.0f };
 }
 
 } // namespace qn

@@ -15,7 +15,7 @@
 
 namespace qn {
 
-#define LTILE_FLOATS (L_NF * (TX + 3) * (TY + 3))
+#define LTILE_FLOATS (L_ES * (TX + 3) * (TY + 3))
 static_assert(LTILE_FLOATS * 4 <= 65536, "FP32 tile exceeds 64 KiB of LDS");
 
 __device__ __forceinline__ LView lview_of(const Desc &d, int par)
@@ -28,7 +28,6 @@ __device__ __forceinline__ LView lview_of(const Desc &d, int par)
     V.rc = d.rc; V.rmu = d.rmu; V.rp = d.rp; V.ru = d.ru; V.rv = d.rv;
     V.m1 = d.m1; V.m2 = d.m2; V.pitch = d.pitch;
     V.bcx = d.bcx; V.bcy = d.bcy;
-    V.inv_h = d.finv_h;
     return V;
 }
 
@@ -36,20 +35,20 @@ __device__ __forceinline__ LView lview_of(const Desc &d, int par)
 // read from buffer par and written to par^1
 template <typename IT> __device__ __forceinline__ void mx_halfsweep_body(const IT &it, int colour, float omega)
 {
-    __shared__ float sm[LTILE_FLOATS];
+    TILE_LDS float sm[LTILE_FLOATS];
     const int k = find_item(it);
     const Desc &d = *it.d[k];
     if (!tile_valid(it, k, d)) return;
     const int par = it.par[k];
     const LView L = lview_of(d, par);
-    const TileF T = item_tile(sm, it, k, d);
-    ltile_load(d.Pf, L, T);
+    const TileF T = item_tile<TileF>(sm, it, k, d);
+    ltile_load<2>(d.Pf, L, T);
     __syncthreads();
     const int pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
     const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
     const int j = T.j0 + lj;
     const int i = T.i0 + 2 * kk + ((j + colour) & 1);
-    if (i < L.m1 && j < L.m2) lrelax_pair<1>(d.Pf, L, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, hlf, omega);
+    if (i < L.m1 && j < L.m2) lrelax_cell<false, 1>(d.Pf, d.Kf, L, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
 }
 template <typename IT> __global__ HS_ATTR void k_mx_halfsweep(IT it, int colour, float omega)
 {
@@ -64,7 +63,7 @@ template <typename IT> __global__ HS_ATTR void k_mx_halfsweep_fine(IT it, int co
 // temporal blocking of the correction smoother: one red + black sweep per
 // launch, as k_hs_fused (the widened tile in LDS, the cell corrections from
 // one set to the other, the face corrections from buffer par to par ^ 1)
-#define MX_FUSED_FLOATS ((L_NF + 2) * FUSED_W * FUSED_H)
+#define MX_FUSED_FLOATS (L_ES * FUSED_W * FUSED_H)
 static_assert(MX_FUSED_FLOATS * 4 <= 65536, "fused FP32 tile exceeds 64 KiB of LDS");
 
 __device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, const TileF &T)
@@ -76,9 +75,9 @@ __device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, co
         if (L.bcx) i = wrapi(i, L.m1);
         if (L.bcy) j = wrapi(j, L.m2);
         const TileSrc q = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        float *s = T.s + e;
+        float *s = T.s + e * L_ES;
         if (q.sc == 0) {
-            for (int f = 0; f < L_NF + 2; f++) s[f * n] = 0.0f;
+            tile_zero(T, e);
             continue;
         }
         // the level is in global memory; every load before any use
@@ -86,21 +85,9 @@ __device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, co
                              lda<1>(L.du, q.u), lda<1>(L.dv, q.v), lda<1>(L.cn, q.c), lda<1>(L.un, q.u),
                              lda<1>(L.vn, q.v) };
         __builtin_amdgcn_sched_barrier(0);
-        s[L_C * n] = v[0];
-        s[L_DC * n] = v[1];
-        s[L_MU * n] = v[2];
-        s[L_P * n] = v[3];
-        s[L_U * n] = s[L_NF * n] = signed_val(q.su, v[4]);
-        s[L_V * n] = s[(L_NF + 1) * n] = signed_val(q.sv, v[5]);
-        s[L_CN * n] = v[6];
-        s[L_UN * n] = signed_val(q.su, v[7]);
-        s[L_VN * n] = signed_val(q.sv, v[8]);
-        s[L_RN * n] = rhof(P, v[6]);
-        s[L_MV * n] = viscf(P, v[6]);
-        s[L_MOB * n] = mobf(P, v[6]);
-        const float rs = rhof(P, v[0]);
-        s[L_RS * n] = rs;
-        s[L_DRS * n] = -P.alpha * rs * rs * v[1];
+        ltile_put(P, s, q.su, q.sv, v);
+        s[T_U2] = s[T_U];
+        s[T_V2] = s[T_V];
     }
 }
 // after the red pass (as fused_refresh): the new face corrections become the
@@ -108,7 +95,6 @@ __device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, co
 __device__ __forceinline__ void mx_fused_refresh(const LView &L, const TileF &T)
 {
     const int n = T.W * T.H;
-    const float *un = T.s + L_NF * n, *vn = T.s + (L_NF + 1) * n;
     for (int e = threadIdx.x; e < n; e += block_threads()) {
         const int b = e / T.W, a = e - b * T.W;
         const int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
@@ -118,23 +104,23 @@ __device__ __forceinline__ void mx_fused_refresh(const LView &L, const TileF &T)
         const int sv = (!L.bcy && (j <= 0 || j >= L.m2)) ? 0 : (gx ? -1 : 1);
         // every value the element may take, before any store (as
         // fused_refresh)
-        const int q = T.idx(si, sj);
-        const float u = un[T.idx(i, sj)], v = vn[T.idx(si, j)], dc = T.s[L_DC * n + q], mu = T.s[L_MU * n + q],
-                    p = T.s[L_P * n + q], drs = T.s[L_DRS * n + q];
+        const float *q = T.at(si, sj);
+        float *s = T.s + e * L_ES;
+        const float u = T.at(i, sj)[T_U2], v = T.at(si, j)[T_V2], dc = q[L_DC], mu = q[T_MU], p = q[T_P], drs = q[L_DRS];
         __builtin_amdgcn_sched_barrier(0);
-        T.s[L_U * n + e] = signed_val(su, u);
-        T.s[L_V * n + e] = signed_val(sv, v);
+        s[T_U] = signed_val(su, u);
+        s[T_V] = signed_val(sv, v);
         if (gx || gy) {
-            T.s[L_DC * n + e] = dc;
-            T.s[L_MU * n + e] = mu;
-            T.s[L_P * n + e] = p;
-            T.s[L_DRS * n + e] = drs;
+            s[L_DC] = dc;
+            s[T_MU] = mu;
+            s[T_P] = p;
+            s[L_DRS] = drs;
         }
     }
 }
 template <typename IT> __global__ __launch_bounds__(FBLK) void k_mx_fused(IT it, int dir, float omega)
 {
-    __shared__ float sm[MX_FUSED_FLOATS];
+    TILE_LDS float sm[MX_FUSED_FLOATS];
     const int k = find_item(it);
     const Desc &d = *it.d[k];
     if (!tile_valid(it, k, d)) return;
@@ -146,7 +132,7 @@ template <typename IT> __global__ __launch_bounds__(FBLK) void k_mx_fused(IT it,
     } else {
         O.dc = d.dc2; O.dmu = d.dmu2; O.dp = d.dp2;
     }
-    const TileF T0 = item_tile(sm, it, k, d);
+    const TileF T0 = item_tile<TileF>(sm, it, k, d);
     TileF T;
     T.s = sm; T.i0 = T0.i0 - 2; T.j0 = T0.j0 - 2; T.W = FUSED_W; T.H = FUSED_H;
     mx_fused_load(d.Pf, L, T);
@@ -159,7 +145,7 @@ template <typename IT> __global__ __launch_bounds__(FBLK) void k_mx_fused(IT it,
         const bool in = lj < TY + 4 && (L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2));
         if (in) {
             const int i = L.bcx ? wrapi(ti, L.m1) : ti, j = L.bcy ? wrapi(tj, L.m2) : tj;
-            lrelax_cell<true, 1>(d.Pf, L, T, nullptr, nullptr, i, j, ti, tj, hlf, omega);
+            lrelax_cell<true, 1>(d.Pf, d.Kf, L, T, nullptr, nullptr, i, j, ti, tj, hlf, omega);
         }
     }
     __syncthreads();
@@ -169,17 +155,17 @@ template <typename IT> __global__ __launch_bounds__(FBLK) void k_mx_fused(IT it,
         const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
         const int j = T0.j0 + lj;
         const int i = T0.i0 + 2 * kk + ((j + 1) & 1);
-        if (i < L.m1 && j < L.m2) lrelax_cell<false, 1>(d.Pf, O, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
+        if (i < L.m1 && j < L.m2) lrelax_cell<false, 1>(d.Pf, d.Kf, O, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
     } else {
         const int q = pr - TBLK / 2;
         const int lj = q / (TX / 2), kk = q - lj * (TX / 2);
         const int j = T0.j0 + lj;
         const int i = T0.i0 + 2 * kk + (j & 1);
         if (i < L.m1 && j < L.m2) {
-            const int e = T.idx(i, j), n = T.W * T.H;
+            const float *e = T.at(i, j);
             const size_t g = (size_t)j * L.pitch + i;
-            if (hlf == 0) { O.dc[g] = T.s[L_DC * n + e]; O.dmu[g] = T.s[L_MU * n + e]; }
-            else O.dp[g] = T.s[L_P * n + e];
+            if (hlf == 0) { O.dc[g] = e[L_DC]; O.dmu[g] = e[T_MU]; }
+            else O.dp[g] = e[T_P];
         }
     }
 }
@@ -187,50 +173,55 @@ template <typename IT> __global__ __launch_bounds__(FBLK) void k_mx_fused(IT it,
 // r - J delta on the item's level, restricted to the next coarser level
 // (cells: mean of four; faces: mean of the two coincident fine faces),
 // together with the linearisation point; the coarse correction starts at 0
+// (one lane per fine cell, a coarse cell's children in a quad of lanes)
+__device__ __forceinline__ float quad_sum(float x)
+{
+    x += other(x);
+    return x + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false));
+}
 template <typename IT> __global__ __launch_bounds__(TBLK) void k_mx_restrict(IT it)
 {
-    __shared__ float sm[LTILE_FLOATS];
+    TILE_LDS float sm[LTILE_FLOATS];
     const int k = find_item(it);
     const Desc &d = *it.d[k];
     if (!tile_valid(it, k, d)) return;
     const Desc &C = *d.coarse;
     const LView Lf = lview_of(d, it.par[k]);
-    const TileF T = item_tile(sm, it, k, d);
-    ltile_load(d.Pf, Lf, T);
+    const TileF T = item_tile<TileF>(sm, it, k, d);
+    ltile_load<2>(d.Pf, Lf, T);
     __syncthreads();
-    const int pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
-    if (pr >= (TX / 2) * (TY / 2)) return;
-    const int I = T.i0 / 2 + pr % (TX / 2), J = T.j0 / 2 + pr / (TX / 2);
-    if (I >= C.m1 || J >= C.m2) return;
-    float rc = 0, rm = 0, rp = 0, rf = 0, sc = 0, smu = 0, sf = 0;
-#pragma unroll
-    for (int b = 0; b < 2; b++)
-#pragma unroll
-        for (int a = 0; a < 2; a++) {
-            const int i = 2 * I + a, j = 2 * J + b;
-            const size_t q = (size_t)j * Lf.pitch + i;
-            float xc, xm, xp, xf;
-            lresid_pair(d.Pf, Lf, T, i, j, hlf, xc, xm, xp, xf);
-            rc += xc; rm += xm; rp += xp;
-            if ((hlf ? b : a) == 0) { rf += xf; sf += lda<1>(hlf ? Lf.v : Lf.u, q); }
-            sc += T.q(L_C, i, j); smu += lda<1>(Lf.mu, q);
-        }
+    const int cc = threadIdx.x >> 2, ch = threadIdx.x & 3;
+    const int I = T.i0 / 2 + cc % (TX / 2), J = T.j0 / 2 + cc / (TX / 2);
+    const int i = 2 * I + (ch & 1), j = 2 * J + (ch >> 1);
+    if (I >= C.m1 || J >= C.m2) return; // a quad's lanes share I, J
+    const size_t w = (size_t)j * Lf.pitch + i;
+    const float xmu = lda<1>(Lf.mu, w), xu = lda<1>(Lf.u, w), xv = lda<1>(Lf.v, w);
+    const ResidF r = lresid_cell(d.Kf, Lf, T, i, j);
+    const bool wu = (ch & 1) == 0, wv = (ch >> 1) == 0; // faces of the coarse cell
+    const float rc = quad_sum(r.c), rm = quad_sum(r.mu), rp = quad_sum(r.p), ru = quad_sum(wu ? r.u : 0.0f),
+                rv = quad_sum(wv ? r.v : 0.0f);
+    const float sc = quad_sum(T.q(T_C, i, j)), smu = quad_sum(xmu), su = quad_sum(wu ? xu : 0.0f),
+                sv = quad_sum(wv ? xv : 0.0f);
     const size_t q = (size_t)J * C.pitch + I;
     const int cp = it.cpar[k];
-    if (hlf == 0) {
-        C.xc[q] = 0.25f * sc;
-        C.xmu[q] = 0.25f * smu;
-        C.xu[q] = 0.5f * sf;
-        C.rc[q] = 0.25f * rc;
-        C.rmu[q] = 0.25f * rm;
-        C.rp[q] = 0.25f * rp;
-        C.ru[q] = 0.5f * rf;
-        C.dc[q] = 0.0f; C.dmu[q] = 0.0f; C.dp[q] = 0.0f;
-        C.dub[cp][q] = 0.0f;
+    if (ch == 0) {
+        sta<1>(C.xc, q, 0.25f * sc);
+        sta<1>(C.xmu, q, 0.25f * smu);
+        sta<1>(C.xu, q, 0.5f * su);
+        sta<1>(C.xv, q, 0.5f * sv);
+    } else if (ch == 1) {
+        sta<1>(C.rc, q, 0.25f * rc);
+        sta<1>(C.rmu, q, 0.25f * rm);
+        sta<1>(C.rp, q, 0.25f * rp);
+        sta<1>(C.ru, q, 0.5f * ru);
+        sta<1>(C.rv, q, 0.5f * rv);
+    } else if (ch == 2) {
+        sta<1>(C.dc, q, 0.0f);
+        sta<1>(C.dmu, q, 0.0f);
+        sta<1>(C.dp, q, 0.0f);
     } else {
-        C.xv[q] = 0.5f * sf;
-        C.rv[q] = 0.5f * rf;
-        C.dvb[cp][q] = 0.0f;
+        sta<1>(C.dub[cp], q, 0.0f);
+        sta<1>(C.dvb[cp], q, 0.0f);
     }
 }
 
@@ -317,7 +308,21 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_mx_prolong(IT it
 // + the tile's source map (4 ints per element)
 __host__ __device__ inline size_t mx_coarse_lds_floats(int m1, int m2)
 {
-    return (size_t)19 * m1 * m2 + (size_t)(L_NF + 4) * (m1 + 3) * (m2 + 3);
+    return (size_t)19 * m1 * m2 + (size_t)(L_ES + 4) * (m1 + 3) * (m2 + 3) + 4;
+}
+
+// the tile of a level whose arrays are in LDS
+__device__ __forceinline__ void ltile_fill(const PhysF &P, const LView &L, const TileF &T)
+{
+    const int n = T.W * T.H;
+    for (int e = threadIdx.x; e < n; e += block_threads()) {
+        const int b = e / T.W, a = e - b * T.W;
+        const TileSrc q = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, T.i0 - 1 + a, T.j0 - 1 + b);
+        const float v[9] = { L.c[q.c], L.dc[q.c], L.dmu[q.c], L.dp[q.c], L.du[q.u], L.dv[q.v], L.cn[q.c], L.un[q.u],
+                             L.vn[q.v] };
+        if (q.sc == 0) tile_zero(T, e);
+        else ltile_put(P, T.s + e * L_ES, q.su, q.sv, v);
+    }
 }
 
 // all correction sweeps of a level in one workgroup per item, the level
@@ -326,7 +331,7 @@ __host__ __device__ inline size_t mx_coarse_lds_floats(int m1, int m2)
 template <typename IT>
 __global__ __launch_bounds__(512) void k_mx_coarse_solve(IT it, int sweeps, float omega, int prolong)
 {
-    extern __shared__ float smf[];
+    extern __shared__ __attribute__((aligned(16))) float smf[];
     const int k = find_item(it);
     const Desc &d = *it.d[k];
     const int par = it.par[k];
@@ -372,8 +377,8 @@ __global__ __launch_bounds__(512) void k_mx_coarse_solve(IT it, int sweeps, floa
     H.rc = hr; H.rmu = hr + n; H.rp = hr + 2 * n; H.ru = hr + 3 * n; H.rv = hr + 4 * n;
     H.pitch = m1;
     TileF T;
-    T.s = smf + 19 * n; T.i0 = 0; T.j0 = 0; T.W = m1 + 3; T.H = m2 + 3;
-    int *map = (int *)(T.s + (size_t)L_NF * T.W * T.H);
+    T.s = smf + ((19 * n + 3) & ~3); T.i0 = 0; T.j0 = 0; T.W = m1 + 3; T.H = m2 + 3;
+    int *map = (int *)(T.s + (size_t)L_ES * T.W * T.H);
     tile_map_build(H, T, map);
     const int half = m1 >> 1;
     for (int s = 0; s < 2 * sweeps; s++) {
@@ -381,14 +386,14 @@ __global__ __launch_bounds__(512) void k_mx_coarse_solve(IT it, int sweeps, floa
         float *uw, *vw;
         if (s & 1) { H.du = uB; H.dv = vB; uw = uA; vw = vA; }
         else { H.du = uA; H.dv = vA; uw = uB; vw = vB; }
-        if (s == 0) ltile_load(d.Pf, H, T);
+        if (s == 0) ltile_fill(d.Pf, H, T);
         else ltile_refresh_map(d.Pf, H, T, map, colour ^ 1);
         __syncthreads();
         for (int t = threadIdx.x; t < 2 * half * m2; t += block_threads()) {
             const int pr = t >> 1;
             const int j = pr / half;
             const int i = 2 * (pr - j * half) + ((j + colour) & 1);
-            lrelax_pair<3>(d.Pf, H, T, uw, vw, i, j, t & 1, omega);
+            lrelax_cell<false, 3>(d.Pf, d.Kf, H, T, uw, vw, i, j, i, j, t & 1, omega);
         }
         __syncthreads();
     }
@@ -436,26 +441,24 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_mx_restrict_n(IT
 // field, packed), for checking the linearisation
 template <typename IT> __global__ __launch_bounds__(TBLK) void k_mx_linresid(IT it)
 {
-    __shared__ float sm[LTILE_FLOATS];
+    TILE_LDS float sm[LTILE_FLOATS];
     const int k = find_item(it);
     const Desc &d = *it.d[k];
     if (!tile_valid(it, k, d)) return;
     const LView L = lview_of(d, it.par[k]);
-    const TileF T = item_tile(sm, it, k, d);
-    ltile_load(d.Pf, L, T);
+    const TileF T = item_tile<TileF>(sm, it, k, d);
+    ltile_load<2>(d.Pf, L, T);
     __syncthreads();
     const size_t n = (size_t)L.m1 * L.m2;
-    const int hlf = threadIdx.x & 1;
-    int i, j;
-    pair_cells(T, i, j);
-    for (int a = 0; a < 2; a++, i++) {
-        if (i >= L.m1 || j >= L.m2) continue;
-        float rc, rm, rp, rf;
-        lresid_pair(d.Pf, L, T, i, j, hlf, rc, rm, rp, rf);
-        const size_t q = (size_t)j * L.m1 + i;
-        d.rout[(3 + hlf) * n + q] = rf;
-        if (hlf == 0) { d.rout[q] = rc; d.rout[n + q] = rm; d.rout[2 * n + q] = rp; }
-    }
+    const int i = T.i0 + (int)threadIdx.x % TX, j = T.j0 + (int)threadIdx.x / TX;
+    if (i >= L.m1 || j >= L.m2) return;
+    const ResidF r = lresid_cell(d.Kf, L, T, i, j);
+    const size_t q = (size_t)j * L.m1 + i;
+    d.rout[q] = r.c;
+    d.rout[n + q] = r.mu;
+    d.rout[2 * n + q] = r.p;
+    d.rout[3 * n + q] = r.u;
+    d.rout[4 * n + q] = r.v;
 }
 
 } // namespace qn
