@@ -14,8 +14,10 @@ ARCH = "gfx950"
 # Multiply-adds are contracted within an expression only: kernels that share a
 # function (one-item and many-item lists, fused and plain sweeps) then compute
 # bitwise the same values, which contraction across expressions, decided per
-# kernel, does not give.
+# kernel, does not give.  The first 16 words of the kernel arguments are
+# preloaded into scalar registers.
 HIPFLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-ffp-contract=on",
+            "-mllvm", "-amdgpu-kernarg-preload-count=16",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-Wall", "-Wno-unused-function", "-Wno-unused-variable"]
 

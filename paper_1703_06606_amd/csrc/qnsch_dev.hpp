@@ -280,12 +280,15 @@ enum { T_C = 0, T_CN, T_MU, T_P, T_RN, T_MV, T_RS, T_MOB, T_U, T_V, T_UN, T_VN, 
 enum { L_DC = T_ES, L_DRS, L_NF, L_ES = 20 };
 
 // A tile covers level cells i0-1 .. i0+W-2, j0-1 .. j0+H-2 (a tile of TX
-// columns: W = TX+3); at(i, j), q(f, i, j) take level coordinates.
+// columns: W = TX+3) in rows of S elements; at(i, j), q(f, i, j) take level
+// coordinates.  S is even: the cells of one colour are every second element,
+// from another start in every other row, and with an even S the rows of odd
+// start then use the LDS banks that the others leave free.
 template <typename R, int ES_> struct TileT {
     static constexpr int ES = ES_;
     R *s; // W*H elements of ES values in LDS
-    int i0, j0, W, H;
-    __device__ __forceinline__ int idx(int i, int j) const { return (j - j0 + 1) * W + (i - i0 + 1); }
+    int i0, j0, W, H, S;
+    __device__ __forceinline__ int idx(int i, int j) const { return (j - j0 + 1) * S + (i - i0 + 1); }
     __device__ __forceinline__ R *at(int i, int j) const { return s + idx(i, j) * ES; }
     __device__ __forceinline__ R q(int f, int i, int j) const { return at(i, j)[f]; }
 };
@@ -327,14 +330,14 @@ __device__ __forceinline__ bool tile_inner(int m1, int m2, int i0, int j0, int W
 // thread are loaded together: their sources first, then every load, then the
 // signs and cell functions (an element past the end is clamped to a valid
 // one and not stored).
-template <int NE> __device__ __forceinline__ void tile_load(const Phys &P, const View &L, const Tile &T)
+template <int NE, int NT> __device__ __forceinline__ void tile_load(const Phys &P, const View &L, const Tile &T)
 {
-    const int n = T.W * T.H, nt = block_threads();
+    const int n = T.W * T.H;
     double v[NE][8];
     if (tile_inner(L.m1, L.m2, T.i0, T.j0, T.W, T.H)) {
 #pragma unroll
         for (int k = 0; k < NE; k++) {
-            const int e = min((int)threadIdx.x + k * nt, n - 1), b = e / T.W, a = e - b * T.W;
+            const int e = min((int)threadIdx.x + k * NT, n - 1), b = e / T.W, a = e - b * T.W;
             const size_t q = (size_t)((T.j0 - 1 + b) * L.pitch + (T.i0 - 1 + a));
             const double *src[8] = { L.c, L.mu, L.p, L.u, L.v, L.cn, L.un, L.vn };
 #pragma unroll
@@ -343,15 +346,15 @@ template <int NE> __device__ __forceinline__ void tile_load(const Phys &P, const
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < NE; k++) {
-            const int e = threadIdx.x + k * nt;
-            if (e < n) tile_put(P, T.s + e * T_ES, 1, 1, v[k]);
+            const int e = threadIdx.x + k * NT, b = e / T.W, a = e - b * T.W;
+            if (e < n) tile_put(P, T.s + (b * T.S + a) * T_ES, 1, 1, v[k]);
         }
         return;
     }
     TileSrc s[NE];
 #pragma unroll
     for (int k = 0; k < NE; k++) {
-        const int e = min((int)threadIdx.x + k * nt, n - 1), b = e / T.W, a = e - b * T.W;
+        const int e = min((int)threadIdx.x + k * NT, n - 1), b = e / T.W, a = e - b * T.W;
         s[k] = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, T.i0 - 1 + a, T.j0 - 1 + b);
         const double w[8] = { lda<1>(L.c, s[k].c), lda<1>(L.mu, s[k].c), lda<1>(L.p, s[k].c), lda<1>(L.u, s[k].u),
                               lda<1>(L.v, s[k].v), lda<1>(L.cn, s[k].c), lda<1>(L.un, s[k].u), lda<1>(L.vn, s[k].v) };
@@ -361,10 +364,10 @@ template <int NE> __device__ __forceinline__ void tile_load(const Phys &P, const
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < NE; k++) {
-        const int e = threadIdx.x + k * nt;
+        const int e = threadIdx.x + k * NT, b = e / T.W, a = e - b * T.W;
         if (e >= n) continue;
-        if (s[k].sc == 0) tile_zero(T, e);
-        else tile_put(P, T.s + e * T_ES, s[k].su, s[k].sv, v[k]);
+        if (s[k].sc == 0) tile_zero(T, b * T.S + a);
+        else tile_put(P, T.s + (b * T.S + a) * T_ES, s[k].su, s[k].sv, v[k]);
     }
 }
 
@@ -439,8 +442,8 @@ __device__ __forceinline__ Ax make_ax(const V &L, const TT &T, int i, int j, int
 {
     Ax a;
     a.hlf = hlf;
-    a.dn = hlf ? T.W * TT::ES : TT::ES;
-    a.dt = hlf ? TT::ES : T.W * TT::ES;
+    a.dn = hlf ? T.S * TT::ES : TT::ES;
+    a.dt = hlf ? TT::ES : T.S * TT::ES;
     a.fn = T_U + hlf;
     a.ft = T_V - hlf;
     a.per = hlf ? L.bcy : L.bcx;
@@ -740,9 +743,10 @@ __device__ __forceinline__ const double *face_rhs(const Rhs &F, int hlf)
 // right-hand sides (1: global memory, 3: LDS, where the level resides in the
 // workgroup's LDS).
 //
-// 260 vector instructions fewer per relaxation than with the box assembled
-// and eliminated as a 5x5 matrix, the coefficients formed per cell and the
-// tile's fields in separate arrays (2351 -> @@ in the half-sweep kernel).
+// Against a box assembled and eliminated as a 5x5 matrix, coefficients formed
+// per cell and a tile of one array per field, a half-sweep takes 700 instead
+// of 911 vector instructions per wave and 143 instead of 200 registers (three
+// waves per SIMD instead of two): 50.4 -> 38.0 us on 512 x 2048 (MI355X).
 
 // what a sweep of one cell starts from
 struct CellPos {

@@ -38,13 +38,15 @@ namespace qn {
 #endif
 #define HS_ATTR __launch_bounds__(TBLK)
 #define FINE_ATTR __launch_bounds__(TBLK) __attribute__((amdgpu_waves_per_eu(QN_FINE_WAVES)))
-#define TILE_DOUBLES (T_ES * (TX + 3) * (TY + 3))
+#define TILE_S (TX + 4)
+#define TILE_DOUBLES (T_ES * TILE_S * (TY + 3))
 #define TILE_LDS __shared__ __attribute__((aligned(16)))
 #define NXCD 8
 #define MAXITEMS 64
 static_assert(TILE_DOUBLES * 8 + 16 * NRED * 8 <= 65536, "tile exceeds 64 KiB of LDS");
 
-// one level of one simulation, in device memory
+// one level of one simulation, in device memory; the levels of a simulation
+// follow each other, so that the next coarser one's is the next descriptor
 struct Desc {
     Phys P;
     Kon<double> K;
@@ -53,7 +55,6 @@ struct Desc {
     double *c0, *mu0, *p0, *u0, *v0;                    // restricted iterate (coarse levels)
     int m1, m2, pitch, bcx, bcy;
     double h, inv_h;
-    const Desc *coarse;                                 // next coarser level (NULL on the coarsest)
     double *partials;                                   // per-simulation reduction partials (finest level)
     double *red;                                        // reduced values (device)
     double *red_host;                                   // reduced values (pinned host)
@@ -88,26 +89,58 @@ struct Items {
     int tx[MAXITEMS];         // tiles per row (tile kernels); partial count (k_finalize)
     int acc[MAXITEMS];        // acceleration ring slot s | (earlier results used) << 4; -1 none
 };
-// The same for a list of one item (a simulation run on its own): 40 bytes
-// of kernel arguments instead of 1.8 KB, which a dependent launch pays for
-// (about 1.5 us measured per launch with 1.4 KB).  Kernels are instantiated
-// for both.
+// A list of one item (a simulation run on its own), as three kernel arguments
+// of 16 bytes in all.  They arrive in scalar registers with the wave (kernel
+// argument preloading), so that a kernel's first memory access is the level
+// descriptor's: read from memory, as the many-item list's 1.8 KB are, the
+// arguments cost every kernel a round trip of ~0.5 us before it, and a
+// dependent launch another 1.5 us for 1.4 KB of them.
+// w: u/v buffer of the level, of the next coarser one << 1, (acceleration
+// slot and earlier results, or -1) + 1 << 2; cnt: tiles per row, or partials.
 struct Item1 {
-    int n;
-    int start[2];
-    const Desc *d[1];
-    int par[1];
-    int cpar[1];
-    int tx[1];
-    int acc[1];
+    const Desc *d;
+    int w, cnt;
 };
 
-template <typename IT> __device__ __forceinline__ int find_item(const IT &it)
+__device__ __forceinline__ int find_item(const Items &it)
 {
     int k = 0;
     while (k + 1 < it.n && (int)blockIdx.x >= it.start[k + 1]) k++;
     return k;
 }
+__device__ __forceinline__ int find_item(const Item1 &) { return 0; }
+__device__ __forceinline__ const Desc &it_desc(const Items &it, int k) { return *it.d[k]; }
+__device__ __forceinline__ const Desc &it_desc(const Item1 &it, int) { return *it.d; }
+__device__ __forceinline__ int it_par(const Items &it, int k) { return it.par[k]; }
+__device__ __forceinline__ int it_par(const Item1 &it, int) { return it.w & 1; }
+__device__ __forceinline__ int it_cpar(const Items &it, int k) { return it.cpar[k]; }
+__device__ __forceinline__ int it_cpar(const Item1 &it, int) { return (it.w >> 1) & 1; }
+__device__ __forceinline__ int it_cnt(const Items &it, int k) { return it.tx[k]; }
+__device__ __forceinline__ int it_cnt(const Item1 &it, int) { return it.cnt; }
+__device__ __forceinline__ int it_acc(const Items &it, int k) { return it.acc[k]; }
+__device__ __forceinline__ int it_acc(const Item1 &it, int) { return (it.w >> 2) - 1; }
+__device__ __forceinline__ int it_start(const Items &it, int k) { return it.start[k]; }
+__device__ __forceinline__ int it_start(const Item1 &, int) { return 0; }
+__device__ __forceinline__ int it_count(const Items &it) { return it.n; }
+__device__ __forceinline__ int it_count(const Item1 &) { return 1; }
+
+// The two kernels of an operation, NAME for a list of one item and NAME_n for
+// many, from its body NAME_body(list, ...).  PARAMS, ARGS: the further
+// parameters, in parentheses.  QN_KERNEL_PJ: a body with the template
+// parameter PJ (projection scheme; not served, so no NAME_n of it).
+#define QN_MORE(...) , ##__VA_ARGS__
+#define QN_KERNEL(NAME, ATTR, PARAMS, ARGS)                                                        \
+    __global__ ATTR void NAME(const Desc *__restrict__ d, int w, int cnt QN_MORE PARAMS)                       \
+    {                                                                                              \
+        NAME##_body(Item1{ d, w, cnt } QN_MORE ARGS);                                              \
+    }                                                                                              \
+    __global__ ATTR void NAME##_n(Items it QN_MORE PARAMS) { NAME##_body(it QN_MORE ARGS); }
+#define QN_KERNEL_PJ(NAME, ATTR, PARAMS, ARGS)                                                     \
+    template <bool PJ> __global__ ATTR void NAME(const Desc *__restrict__ d, int w, int cnt QN_MORE PARAMS)    \
+    {                                                                                              \
+        NAME##_body<PJ>(Item1{ d, w, cnt } QN_MORE ARGS);                                          \
+    }                                                                                              \
+    __global__ ATTR void NAME##_n(Items it QN_MORE PARAMS) { NAME##_body<false>(it QN_MORE ARGS); }
 
 __device__ __forceinline__ View view_of(const Desc &d, int par)
 {
@@ -133,9 +166,9 @@ __device__ __forceinline__ Rhs rhs_of(const Desc &d)
 template <typename TT, typename R, typename IT>
 __device__ __forceinline__ TT item_tile(R *sm, const IT &it, int k, const Desc &d)
 {
-    const int tx = it.tx[k];
+    const int tx = it_cnt(it, k);
     const int ty = (d.m2 + TY - 1) / TY;
-    const int n = tx * ty, lin = (int)blockIdx.x - it.start[k];
+    const int n = tx * ty, lin = (int)blockIdx.x - it_start(it, k);
     const int t = (n % NXCD == 0) ? (lin % NXCD) * (n / NXCD) + lin / NXCD : lin;
     TT T;
     T.s = sm;
@@ -143,30 +176,31 @@ __device__ __forceinline__ TT item_tile(R *sm, const IT &it, int k, const Desc &
     T.j0 = (t / tx) * TY;
     T.W = TX + 3;
     T.H = TY + 3;
+    T.S = TILE_S;
     return T;
 }
 template <typename IT> __device__ __forceinline__ bool tile_valid(const IT &it, int k, const Desc &d)
 {
-    return (int)blockIdx.x - it.start[k] < it.tx[k] * ((d.m2 + TY - 1) / TY);
+    return (int)blockIdx.x - it_start(it, k) < it_cnt(it, k) * ((d.m2 + TY - 1) / TY);
 }
 
 // --------------------------------------------------------------------------
 // one colour half-sweep (sec. 7.1) on a tile: a lane pair per cell of the
 // colour.  The u/v snapshot is buffer par, the new faces go to buffer par^1.
-template <bool PJ, typename IT> __device__ __forceinline__ void halfsweep_body(const IT &it, int colour, double omega)
+template <bool PJ, typename IT> __device__ __forceinline__ void k_halfsweep_body(const IT &it, int colour, double omega)
 {
     TILE_LDS double sm[TILE_DOUBLES];
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
+    const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
     const Phys P = d.P;
     const Kon<double> K = d.K;
-    const int par = it.par[k];
+    const int par = it_par(it, k);
     const View L = view_of(d, par);
     const Rhs F = rhs_of(d);
     double *const un = d.ub[par ^ 1], *const vn = d.vb[par ^ 1];
     const Tile T = item_tile<Tile>(sm, it, k, d);
-    tile_load<2>(P, L, T);
+    tile_load<2, TBLK>(P, L, T);
     __syncthreads();
     const int pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
     const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
@@ -174,16 +208,14 @@ template <bool PJ, typename IT> __device__ __forceinline__ void halfsweep_body(c
     const int i = T.i0 + 2 * kk + ((j + colour) & 1);
     if (i < L.m1 && j < L.m2) relax_cell<PJ, false, 1>(P, K, L, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
 }
-template <bool PJ, typename IT> __global__ HS_ATTR void k_halfsweep(IT it, int colour, double omega)
-{
-    halfsweep_body<PJ>(it, colour, omega);
-}
+QN_KERNEL_PJ(k_halfsweep, HS_ATTR, (int colour, double omega), (colour, omega))
 // the same kernel under its own name for launches whose items are all finest
 // levels, so that profiles tell the finest level apart
-template <bool PJ, typename IT> __global__ FINE_ATTR void k_halfsweep_fine(IT it, int colour, double omega)
+template <bool PJ, typename IT> __device__ __forceinline__ void k_halfsweep_fine_body(const IT &it, int colour, double omega)
 {
-    halfsweep_body<PJ>(it, colour, omega);
+    k_halfsweep_body<PJ>(it, colour, omega);
 }
+QN_KERNEL_PJ(k_halfsweep_fine, FINE_ATTR, (int colour, double omega), (colour, omega))
 
 // --------------------------------------------------------------------------
 // temporal blocking: one sweep (red, then black half-sweep of sec. 7.1, the
@@ -196,8 +228,9 @@ template <bool PJ, typename IT> __global__ FINE_ATTR void k_halfsweep_fine(IT it
 // to c2, mu2, p2; dir 1 back) and the faces from buffer par to par ^ 1.
 #define FUSED_W (TX + 7)
 #define FUSED_H (TY + 7)
+#define FUSED_S (TX + 8)
 #define FBLK (2 * TBLK)
-#define FUSED_DOUBLES (T_ES * FUSED_W * FUSED_H)
+#define FUSED_DOUBLES (T_ES * FUSED_S * FUSED_H)
 static_assert(FUSED_DOUBLES * 8 <= 65536, "fused tile exceeds 64 KiB of LDS");
 static_assert((TX + 4) * (TY + 4) <= FBLK, "widened red region exceeds the workgroup");
 
@@ -286,15 +319,15 @@ __device__ __forceinline__ void prolong_apply(const PSrc &C, const PRaw &r, int 
 __device__ __forceinline__ void fused_load(const Phys &P, const View &L, const Tile &T, const PSrc *pc = nullptr)
 {
     const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
+    for (int e = threadIdx.x; e < n; e += FBLK) {
         const int b = e / T.W, a = e - b * T.W;
         int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
         if (L.bcx) i = wrapi(i, L.m1);
         if (L.bcy) j = wrapi(j, L.m2);
         const TileSrc q = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        double *s = T.s + e * T_ES;
+        double *s = T.s + (b * T.S + a) * T_ES;
         if (q.sc == 0) {
-            tile_zero(T, e);
+            tile_zero(T, b * T.S + a);
             continue;
         }
         double v[8] = { lda<1>(L.c, q.c), lda<1>(L.mu, q.c), lda<1>(L.p, q.c), lda<1>(L.u, q.u),
@@ -332,7 +365,7 @@ __device__ __forceinline__ void fused_load(const Phys &P, const View &L, const T
 __device__ __forceinline__ void fused_refresh(const View &L, const Tile &T)
 {
     const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
+    for (int e = threadIdx.x; e < n; e += FBLK) {
         const int b = e / T.W, a = e - b * T.W;
         const int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
         const bool gx = !L.bcx && (i < 0 || i >= L.m1), gy = !L.bcy && (j < 0 || j >= L.m2);
@@ -342,7 +375,7 @@ __device__ __forceinline__ void fused_refresh(const View &L, const Tile &T)
         // every value the element may take, before any store (an image's
         // source q is never an image, so no element read here is written)
         const double *q = T.at(si, sj);
-        double *s = T.s + e * T_ES;
+        double *s = T.s + (b * T.S + a) * T_ES;
         const double u = T.at(i, sj)[T_U2], v = T.at(si, j)[T_V2], c = q[T_C], mu = q[T_MU], p = q[T_P], rs = q[T_RS];
         __builtin_amdgcn_sched_barrier(0);
         s[T_U] = signed_val(su, u);
@@ -355,15 +388,15 @@ __device__ __forceinline__ void fused_refresh(const View &L, const Tile &T)
         }
     }
 }
-template <bool PJ, typename IT> __global__ __launch_bounds__(FBLK) void k_hs_fused(IT it, int dir, double omega, int prolong)
+template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused_body(const IT &it, int dir, double omega, int prolong)
 {
     TILE_LDS double sm[FUSED_DOUBLES];
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
+    const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
     const Phys P = d.P;
     const Kon<double> K = d.K;
-    const int par = it.par[k];
+    const int par = it_par(it, k);
     View L = view_of(d, par);
     View O = L; // where the sweep's cell results go
     if (dir) {
@@ -373,11 +406,11 @@ template <bool PJ, typename IT> __global__ __launch_bounds__(FBLK) void k_hs_fus
     }
     const Tile T0 = item_tile<Tile>(sm, it, k, d);
     Tile T;
-    T.s = sm; T.i0 = T0.i0 - 2; T.j0 = T0.j0 - 2; T.W = FUSED_W; T.H = FUSED_H;
+    T.s = sm; T.i0 = T0.i0 - 2; T.j0 = T0.j0 - 2; T.W = FUSED_W; T.H = FUSED_H; T.S = FUSED_S;
     const Rhs F = rhs_of(d);
     double *const un = d.ub[par ^ 1], *const vn = d.vb[par ^ 1];
     if (prolong) {
-        const PSrc ps = psrc_of(d, d.coarse, it.cpar[k]);
+        const PSrc ps = psrc_of(d, &d + 1, it_cpar(it, k));
         fused_load(P, L, T, &ps);
     } else {
         fused_load(P, L, T);
@@ -422,6 +455,7 @@ template <bool PJ, typename IT> __global__ __launch_bounds__(FBLK) void k_hs_fus
         }
     }
 }
+QN_KERNEL_PJ(k_hs_fused, __launch_bounds__(FBLK), (int dir, double omega, int prolong), (dir, omega, prolong))
 
 // plain copy, used to measure the copy bandwidth and to calibrate counters
 __global__ __launch_bounds__(BLK) void k_copy_probe(const double *__restrict__ a, double *__restrict__ b, size_t n)
@@ -443,24 +477,23 @@ __host__ __device__ inline size_t coarse_lds_doubles(int m1, int m2)
 // is even, so the result stays in buffer par.  With prolong set the level
 // first takes the coarse-grid correction (k_prolong's arithmetic) as it is
 // loaded.
-template <bool PJ, typename IT>
-__global__ __launch_bounds__(512) void k_coarse_solve(IT it, int sweeps, double omega, double pomega, int prolong)
+template <bool PJ, typename IT> __device__ __forceinline__ void k_coarse_solve_body(const IT &it, int sweeps, double omega, double pomega, int prolong)
 {
     extern __shared__ __attribute__((aligned(16))) double sm[];
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
+    const Desc &d = it_desc(it, k);
     // the constants by value (no store can change them, so they are not
     // reloaded after one); the relaxation works on LDS arrays (address space 3)
     const Phys P = d.P;
     const Kon<double> K = d.K;
-    const int par = it.par[k];
+    const int par = it_par(it, k);
     const View L = view_of(d, par);
     double *ua = d.ub[par], *va = d.vb[par];
     const int m1 = L.m1, m2 = L.m2, n = m1 * m2;
     double *hc = sm, *hmu = sm + n, *hp = sm + 2 * n, *uA = sm + 3 * n, *vA = sm + 4 * n, *uB = sm + 5 * n,
            *vB = sm + 6 * n, *hf = sm + 7 * n;
     Tile T;
-    T.s = sm + 12 * n; T.i0 = 0; T.j0 = 0; T.W = m1 + 3; T.H = m2 + 3;
+    T.s = sm + 12 * n; T.i0 = 0; T.j0 = 0; T.W = T.S = m1 + 3; T.H = m2 + 3;
     const int nt = T.W * T.H;
     int *map = (int *)(T.s + (size_t)T_ES * nt);
     // one pass over the tile's elements: each loads its sources from the level
@@ -470,7 +503,7 @@ __global__ __launch_bounds__(512) void k_coarse_solve(IT it, int sweeps, double 
     // element that is a cell of the level, the level arrays in LDS and the
     // right-hand sides
     PSrc ps = {};
-    if (prolong) ps = psrc_of(d, d.coarse, it.cpar[k]);
+    if (prolong) ps = psrc_of(d, &d + 1, it_cpar(it, k));
     // the right-hand sides' arrays read before the first store (read after
     // one, every element would reload them from the descriptor)
     const double *const rfc = d.fc, *const rfmu = d.fmu, *const rfp = d.fp, *const rfu = d.fu, *const rfv = d.fv;
@@ -551,6 +584,7 @@ __global__ __launch_bounds__(512) void k_coarse_solve(IT it, int sweeps, double 
         L.c[q] = hc[e]; L.mu[q] = hmu[e]; L.p[q] = hp[e]; ua[q] = uA[e]; va[q] = vA[e];
     }
 }
+QN_KERNEL_PJ(k_coarse_solve, __launch_bounds__(512), (int sweeps, double omega, double pomega, int prolong), (sweeps, omega, pomega, prolong))
 
 // R w of a coarse cell from the values of its four children (a, b: the
 // children (0, 0), (1, 0); c, d: (0, 1), (1, 1)): the mean, summed in the order
@@ -572,6 +606,7 @@ __device__ __forceinline__ double rw_mean(double a, double b, double c, double d
 // lanes, summed by DPP), a fifth wave for the residuals of the tile's 64 coarse
 // cells meanwhile.
 #define RBLK (TBLK + 64)
+#define CTILE_S (TX / 2 + 4)
 static_assert((TX / 2) * (TY / 2) == 64, "k_restrict: one wave of coarse cells");
 // sum over a quad of lanes as (0 + 1) + (2 + 3), the order of rw_mean
 __device__ __forceinline__ double quad_sum(double x)
@@ -582,18 +617,18 @@ __device__ __forceinline__ double quad_sum(double x)
               hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x4E, 0xF, 0xF, false);
     return x + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
-template <bool PJ, typename IT> __global__ __launch_bounds__(RBLK) void k_restrict(IT it)
+template <bool PJ, typename IT> __device__ __forceinline__ void k_restrict_body(const IT &it)
 {
     TILE_LDS double sm[TILE_DOUBLES];
-    TILE_LDS double smc[T_ES * (TX / 2 + 3) * (TY / 2 + 3)];
+    TILE_LDS double smc[T_ES * CTILE_S * (TY / 2 + 3)];
     __shared__ double part[5][(TX / 2) * (TY / 2)]; // sums of the fine residuals
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
+    const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
-    const Desc &C = *d.coarse;
+    const Desc &C = (&d)[1];
     const Phys P = d.P;
-    const int cp = it.cpar[k];
-    const View Lf = view_of(d, it.par[k]);
+    const int cp = it_cpar(it, k);
+    const View Lf = view_of(d, it_par(it, k));
     const View Lc = view_of(C, cp);
     const Tile T = item_tile<Tile>(sm, it, k, d);
     // the coarse tile of R w, from the fine arrays directly (its halo lies
@@ -601,7 +636,7 @@ template <bool PJ, typename IT> __global__ __launch_bounds__(RBLK) void k_restri
     // tile: cells the mean of the four children, faces the mean of the two
     // coincident fine faces
     Tile Tc;
-    Tc.s = smc; Tc.i0 = T.i0 / 2; Tc.j0 = T.j0 / 2; Tc.W = TX / 2 + 3; Tc.H = TY / 2 + 3;
+    Tc.s = smc; Tc.i0 = T.i0 / 2; Tc.j0 = T.j0 / 2; Tc.W = TX / 2 + 3; Tc.H = TY / 2 + 3; Tc.S = CTILE_S;
     {
         const int n = Tc.W * Tc.H, e = RBLK - 1 - threadIdx.x;
         const Phys PC = C.P;
@@ -622,15 +657,15 @@ template <bool PJ, typename IT> __global__ __launch_bounds__(RBLK) void k_restri
             const double cn = lda<1>(C.cn, s.c), un = lda<1>(C.un, s.u), vn = lda<1>(C.vn, s.v);
             __builtin_amdgcn_sched_barrier(0);
             if (s.sc == 0) {
-                tile_zero(Tc, e);
+                tile_zero(Tc, bb * CTILE_S + aa);
             } else {
                 const double w[8] = { rw_mean(c4[0], c4[1], c4[2], c4[3]), rw_mean(m4[0], m4[1], m4[2], m4[3]),
                                       rw_mean(p4[0], p4[1], p4[2], p4[3]), 0.5 * (u0 + u1), 0.5 * (w0 + w1), cn, un, vn };
-                tile_put(PC, Tc.s + e * T_ES, s.su, s.sv, w);
+                tile_put(PC, Tc.s + (bb * CTILE_S + aa) * T_ES, s.su, s.sv, w);
             }
         }
     }
-    tile_load<2>(P, Lf, T);
+    tile_load<2, RBLK>(P, Lf, T);
     __syncthreads();
     const bool fine = threadIdx.x < TBLK;
     const int cc = fine ? (int)threadIdx.x >> 2 : (int)threadIdx.x - TBLK, ch = threadIdx.x & 3;
@@ -666,21 +701,22 @@ template <bool PJ, typename IT> __global__ __launch_bounds__(RBLK) void k_restri
     sta<1>(C.fu, q, u_unk(Lc, I) ? 0.5 * part[3][cc] - r.u : 0.0);
     sta<1>(C.fv, q, v_unk(Lc, J) ? 0.5 * part[4][cc] - r.v : 0.0);
 }
+QN_KERNEL_PJ(k_restrict, __launch_bounds__(RBLK), (), ())
 
 // w_h += P(w_H - R w_h) on the level the item names, one thread per fine cell
-template <typename IT> __global__ __launch_bounds__(BLK) void k_prolong(IT it)
+template <typename IT> __device__ __forceinline__ void k_prolong_body(const IT &it)
 {
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
-    const Desc &C = *d.coarse;
-    const int t = ((int)blockIdx.x - it.start[k]) * BLK + threadIdx.x;
+    const Desc &d = it_desc(it, k);
+    const Desc &C = (&d)[1];
+    const int t = ((int)blockIdx.x - it_start(it, k)) * BLK + threadIdx.x;
     if (t >= d.m1 * d.m2) return;
     const int j = t / d.m1, i = t - j * d.m1;
     const size_t kf = (size_t)j * d.pitch + i;
     // the correction of the cell and its west and south faces, every load
     // issued before any use
-    const PSrc ps = psrc_of(d, &C, it.cpar[k]);
-    double *ub = d.ub[it.par[k]], *vb = d.vb[it.par[k]];
+    const PSrc ps = psrc_of(d, &C, it_cpar(it, k));
+    double *ub = d.ub[it_par(it, k)], *vb = d.vb[it_par(it, k)];
     const PRaw raw = prolong_load(ps, i, j, i, j, i, j);
     const double c = lda<1>(d.c, kf), mu = lda<1>(d.mu, kf), p = lda<1>(d.p, kf), u = lda<1>(ub, kf),
                  v = lda<1>(vb, kf);
@@ -693,14 +729,15 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_prolong(IT it)
     if (ps.bcx || i >= 1) sta<1>(ub, kf, u + du);
     if (ps.bcy || j >= 1) sta<1>(vb, kf, v + dv);
 }
+QN_KERNEL(k_prolong, __launch_bounds__(BLK), (), ())
 
-// wave64 + LDS block sum of NRED values (blocks of up to 16 waves).  Within a
+// wave64 + LDS block sum of NRED values (blocks of NT threads).  Within a
 // wave each exchange halves the number of slots a lane is responsible for
 // (lane l ends with the sum of slot l / 4): 17 exchanges instead of 6 per slot.
-__device__ __forceinline__ void block_sum_store(double (&v)[NRED], double *out)
+template <int NT> __device__ __forceinline__ void block_sum_store(double (&v)[NRED], double *out)
 {
     static_assert(NRED == 16, "block_sum_store");
-    __shared__ double sh[16][NRED];
+    __shared__ double sh[NT / 64][NRED];
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     double a[8];
 #pragma unroll
@@ -720,7 +757,7 @@ __device__ __forceinline__ void block_sum_store(double (&v)[NRED], double *out)
     __syncthreads();
     if (threadIdx.x < NRED) {
         double s = 0.0;
-        for (int ww = 0; ww < (int)(block_threads() >> 6); ww++) s += sh[ww][threadIdx.x];
+        for (int ww = 0; ww < NT / 64; ww++) s += sh[ww][threadIdx.x];
         out[threadIdx.x] = s;
     }
 }
@@ -768,18 +805,18 @@ __device__ __forceinline__ void acc_record(const Desc &d, int ac, size_t w, cons
 // equations, the sum of pbar, and the count of cells that are non-finite or
 // past the density pole (partials indexed by the tile's place in the band
 // order); optionally the residual fields themselves.  One lane per cell.
-template <bool PJ, typename IT> __global__ __launch_bounds__(TBLK) void k_resid_norm(IT it)
+template <bool PJ, typename IT> __device__ __forceinline__ void k_resid_norm_body(const IT &it)
 {
     TILE_LDS double sm[TILE_DOUBLES];
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
+    const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
     const Phys P = d.P;
     const Kon<double> K = d.K;
-    const int par = it.par[k];
+    const int par = it_par(it, k);
     const View L = view_of(d, par);
     const Tile T = item_tile<Tile>(sm, it, k, d);
-    tile_load<2>(P, L, T);
+    tile_load<2, TBLK>(P, L, T);
     __syncthreads();
     double v[NRED] = {};
     const size_t n = (size_t)L.m1 * L.m2;
@@ -812,21 +849,22 @@ template <bool PJ, typename IT> __global__ __launch_bounds__(TBLK) void k_resid_
             d.xc[w] = (float)c; d.xmu[w] = (float)t[T_MU]; d.xu[w] = (float)t[T_U]; d.xv[w] = (float)t[T_V];
             d.dc[w] = 0.0f; d.dmu[w] = 0.0f; d.dp[w] = 0.0f; d.dub[par][w] = 0.0f; d.dvb[par][w] = 0.0f;
         }
-        const int ac = it.acc[k];
+        const int ac = it_acc(it, k);
         if (ac >= 0 && d.ar) acc_record(d, ac, w, r, t, v);
     }
-    const int tl = (T.j0 / TY) * it.tx[k] + T.i0 / TX;
-    block_sum_store(v, d.partials + (size_t)tl * NRED);
+    const int tl = (T.j0 / TY) * it_cnt(it, k) + T.i0 / TX;
+    block_sum_store<BLK>(v, d.partials + (size_t)tl * NRED);
 }
+QN_KERNEL_PJ(k_resid_norm, __launch_bounds__(TBLK), (), ())
 
 // mass and energy partial sums of the current state, one thread per cell
-template <typename IT> __global__ __launch_bounds__(BLK) void k_mass_energy(IT it)
+template <typename IT> __device__ __forceinline__ void k_mass_energy_body(const IT &it)
 {
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
-    const View L = view_of(d, it.par[k]);
+    const Desc &d = it_desc(it, k);
+    const View L = view_of(d, it_par(it, k));
     const Phys &P = d.P;
-    const int b = (int)blockIdx.x - it.start[k];
+    const int b = (int)blockIdx.x - it_start(it, k);
     const int t = b * BLK + threadIdx.x;
     double v[NRED] = {};
     if (t < L.m1 * L.m2) {
@@ -847,8 +885,9 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_mass_energy(IT i
         v[4] = r * dwell(c);
         v[5] = (r - P.rho_ref) * (j + 0.5) * d.h;
     }
-    block_sum_store(v, d.partials + (size_t)b * NRED);
+    block_sum_store<BLK>(v, d.partials + (size_t)b * NRED);
 }
+QN_KERNEL(k_mass_energy, __launch_bounds__(BLK), (), ())
 
 // Dissipation of the step just taken (Theorem of sec. 6.1 with the norms of
 // App. A.7), from the new iterate and the time-n data still held by the
@@ -859,18 +898,18 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_mass_energy(IT i
 //   2: A m(c^n) |D mu_c|^2 on the west and south faces, mu_c = mubar + alpha pbar
 //   3: A rho^n |u - u^n|^2 on the west and south faces (unknown faces only)
 // One thread per cell.
-template <typename IT> __global__ __launch_bounds__(BLK) void k_dissipation(IT it)
+template <typename IT> __device__ __forceinline__ void k_dissipation_body(const IT &it)
 {
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
+    const Desc &d = it_desc(it, k);
     // projection scheme: the viscous parts and the time-difference part are
     // taken on the intermediate velocity (the other face buffer), and slot 4
     // sums A rho(c) (u^{n+1} - u~)^2 over the faces
     const bool pj = d.P.scheme != 0;
-    const View L = view_of(d, pj ? it.par[k] ^ 1 : it.par[k]);
-    const double *uf = d.ub[it.par[k]], *vf = d.vb[it.par[k]];
+    const View L = view_of(d, pj ? it_par(it, k) ^ 1 : it_par(it, k));
+    const double *uf = d.ub[it_par(it, k)], *vf = d.vb[it_par(it, k)];
     const Phys &P = d.P;
-    const int b = (int)blockIdx.x - it.start[k];
+    const int b = (int)blockIdx.x - it_start(it, k);
     const int t = b * BLK + threadIdx.x;
     double v[NRED] = {};
     if (t < L.m1 * L.m2) {
@@ -921,21 +960,22 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_dissipation(IT i
             }
         }
     }
-    block_sum_store(v, d.partials + (size_t)b * NRED);
+    block_sum_store<BLK>(v, d.partials + (size_t)b * NRED);
 }
+QN_KERNEL(k_dissipation, __launch_bounds__(BLK), (), ())
 
 // Projection scheme, end of a converged step: the velocity of time n+1 from
 // the projection equation (pj-num-pjx) (as face_final) on every west and
 // south face, written to the other face buffer, which becomes the current
 // one; the intermediate velocity stays in buffer par for the dissipation.
-template <typename IT> __global__ __launch_bounds__(BLK) void k_pj_final(IT it)
+template <typename IT> __device__ __forceinline__ void k_pj_final_body(const IT &it)
 {
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
-    const int par = it.par[k];
+    const Desc &d = it_desc(it, k);
+    const int par = it_par(it, k);
     const View L = view_of(d, par);
     const Phys &P = d.P;
-    const int t = ((int)blockIdx.x - it.start[k]) * BLK + threadIdx.x;
+    const int t = ((int)blockIdx.x - it_start(it, k)) * BLK + threadIdx.x;
     if (t >= L.m1 * L.m2) return;
     const int j = t / L.m1, i = t - j * L.m1;
     const int m1 = L.m1, m2 = L.m2, pt = L.pitch, bx = L.bcx, by = L.bcy;
@@ -957,6 +997,7 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_pj_final(IT it)
     d.ub[par ^ 1][q] = uf;
     d.vb[par ^ 1][q] = vf;
 }
+QN_KERNEL(k_pj_final, __launch_bounds__(BLK), (), ())
 
 // Physical diagnostics of the current state (sec. 8), per-block partials:
 //   0: sum c v_cell (v_cell = mean of the cell's south and north faces)
@@ -968,13 +1009,13 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_pj_final(IT it)
 //   7: max height of a crossing in the first column (x = h/2)
 // (5-7 hold -inf / +inf where there is none.)
 #define DIAG_NONE 1e300
-template <typename IT> __global__ __launch_bounds__(BLK) void k_diagnostics(IT it)
+template <typename IT> __device__ __forceinline__ void k_diagnostics_body(const IT &it)
 {
     __shared__ double sh[BLK / 64][NRED];
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
-    const View L = view_of(d, it.par[k]);
-    const int b = (int)blockIdx.x - it.start[k];
+    const Desc &d = it_desc(it, k);
+    const View L = view_of(d, it_par(it, k));
+    const int b = (int)blockIdx.x - it_start(it, k);
     const int t = b * BLK + threadIdx.x;
     double v[NRED] = { 0, 0, 0, 0, 0, -DIAG_NONE, DIAG_NONE, -DIAG_NONE };
     if (t < L.m1 * L.m2) {
@@ -1024,18 +1065,19 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_diagnostics(IT i
         d.partials[(size_t)b * NRED + r] = acc;
     }
 }
+QN_KERNEL(k_diagnostics, __launch_bounds__(BLK), (), ())
 
 // fixed-order sum of a simulation's partials (one workgroup per item); the
 // norms become sqrt(h^2 sum r^2); written to device and pinned host memory.
 // mode 0: residual reduction (5 norms, sum p, bad count); 1: plain sums;
 // 2: the diagnostics slots (sum, max or min per slot as in k_diagnostics).
-template <typename IT> __global__ __launch_bounds__(BLK) void k_finalize(IT it, int mode)
+template <typename IT> __device__ __forceinline__ void k_finalize_body(const IT &it, int mode)
 {
     __shared__ double sh[BLK][NRED];
     const int k = blockIdx.x;
-    if (k >= it.n) return;
-    const Desc &d = *it.d[k];
-    const int nblk = it.tx[k];
+    if (k >= it_count(it)) return;
+    const Desc &d = it_desc(it, k);
+    const int nblk = it_cnt(it, k);
     // slot q combines by sum, or (diagnostics) by max (op 1) or min (op 2)
     auto op = [&](int q) { return mode != 2 ? 0 : (q == 2 || q == 5 || q == 7) ? 1 : (q == 6 ? 2 : 0); };
     auto comb = [&](int q, double a, double b) { const int o = op(q); return o == 0 ? a + b : (o == 1 ? fmax(a, b) : fmin(a, b)); };
@@ -1060,21 +1102,23 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_finalize(IT it, 
         d.red[threadIdx.x] = x;
         d.red_host[threadIdx.x] = x;
         // a recorded cycle result: the pbar mean k_shift_p removes from it
-        if (mode == 0 && threadIdx.x == 5 && it.acc[k] >= 0 && d.amean)
-            d.amean[it.acc[k] & 15] = x / (double)(d.m1 * d.m2);
+        if (mode == 0 && threadIdx.x == 5 && it_acc(it, k) >= 0 && d.amean)
+            d.amean[it_acc(it, k) & 15] = x / (double)(d.m1 * d.m2);
     }
 }
+QN_KERNEL(k_finalize, __launch_bounds__(BLK), (int mode), (mode))
 
 // pbar -= mean(pbar), the mean from the reduced sums
-template <typename IT> __global__ __launch_bounds__(BLK) void k_shift_p(IT it)
+template <typename IT> __device__ __forceinline__ void k_shift_p_body(const IT &it)
 {
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
-    const int t = ((int)blockIdx.x - it.start[k]) * BLK + threadIdx.x;
+    const Desc &d = it_desc(it, k);
+    const int t = ((int)blockIdx.x - it_start(it, k)) * BLK + threadIdx.x;
     if (t >= d.m1 * d.m2) return;
     const int j = t / d.m1, i = t - j * d.m1;
     d.p[(size_t)j * d.pitch + i] -= d.red[5] / (double)(d.m1 * d.m2);
 }
+QN_KERNEL(k_shift_p, __launch_bounds__(BLK), (), ())
 
 // coefficients of the accelerated combination, per item
 template <int N> struct AccCoef {
@@ -1087,15 +1131,15 @@ template <int N> struct AccCoef {
 // which makes it the iterate that result was).  Mixed precision: the next
 // correction cycle's right-hand side becomes the same combination of the
 // recorded residuals, its linearisation point the combined iterate.
-template <typename IT, int N> __global__ __launch_bounds__(BLK) void k_accel(IT it, AccCoef<N> G)
+template <typename IT, int N> __device__ __forceinline__ void k_accel_body(const IT &it, const AccCoef<N> &G)
 {
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
-    const int t = ((int)blockIdx.x - it.start[k]) * BLK + threadIdx.x;
-    if (t >= d.m1 * d.m2 || !d.aw || it.acc[k] < 0) return;
+    const Desc &d = it_desc(it, k);
+    const int t = ((int)blockIdx.x - it_start(it, k)) * BLK + threadIdx.x;
+    if (t >= d.m1 * d.m2 || !d.aw || it_acc(it, k) < 0) return;
     const int j = t / d.m1, i = t - j * d.m1;
     const size_t q = (size_t)j * d.pitch + i, st = (size_t)d.pitch * d.m2;
-    const int ac = it.acc[k], s = ac & 15, np = ac >> 4, R = d.am, par = it.par[k];
+    const int ac = it_acc(it, k), s = ac & 15, np = ac >> 4, R = d.am, par = it_par(it, k);
     int sl[3];
 #pragma unroll
     for (int b = 0; b < 3; b++) sl[b] = (s - 1 - b + R) % R;
@@ -1148,17 +1192,22 @@ template <typename IT, int N> __global__ __launch_bounds__(BLK) void k_accel(IT 
         d.xc[q] = (float)y[0]; d.xmu[q] = (float)y[1]; d.xu[q] = (float)y[3]; d.xv[q] = (float)y[4];
     }
 }
+__global__ __launch_bounds__(BLK) void k_accel(const Desc *d, int w, int cnt, AccCoef<1> G)
+{
+    k_accel_body(Item1{ d, w, cnt }, G);
+}
+__global__ __launch_bounds__(BLK) void k_accel_n(Items it, AccCoef<MAXITEMS> G) { k_accel_body(it, G); }
 
 // time-n data of the finest level = current iterate; keep mubar, pbar of time n
-template <typename IT> __global__ __launch_bounds__(BLK) void k_begin(IT it)
+template <typename IT> __device__ __forceinline__ void k_begin_body(const IT &it)
 {
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
-    const int t = ((int)blockIdx.x - it.start[k]) * BLK + threadIdx.x;
+    const Desc &d = it_desc(it, k);
+    const int t = ((int)blockIdx.x - it_start(it, k)) * BLK + threadIdx.x;
     if (t >= d.m1 * d.m2) return;
     const int j = t / d.m1, i = t - j * d.m1;
     const size_t q = (size_t)j * d.pitch + i;
-    const int par = it.par[k];
+    const int par = it_par(it, k);
     d.cn[q] = d.c[q];
     d.un[q] = d.ub[par][q];
     d.vn[q] = d.vb[par][q];
@@ -1170,14 +1219,15 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_begin(IT it)
         d.vnf[q] = (float)d.vb[par][q];
     }
 }
+QN_KERNEL(k_begin, __launch_bounds__(BLK), (), ())
 
 // time-n data of the coarser level of the item's level
-template <typename IT> __global__ __launch_bounds__(BLK) void k_restrict_n(IT it)
+template <typename IT> __device__ __forceinline__ void k_restrict_n_body(const IT &it)
 {
     const int k = find_item(it);
-    const Desc &F = *it.d[k];
-    const Desc &C = *F.coarse;
-    const int t = ((int)blockIdx.x - it.start[k]) * BLK + threadIdx.x;
+    const Desc &F = it_desc(it, k);
+    const Desc &C = (&F)[1];
+    const int t = ((int)blockIdx.x - it_start(it, k)) * BLK + threadIdx.x;
     if (t >= C.m1 * C.m2) return;
     const int J = t / C.m1, I = t - J * C.m1;
     const size_t f = (size_t)(2 * J) * F.pitch + 2 * I, q = (size_t)J * C.pitch + I;
@@ -1185,22 +1235,24 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_restrict_n(IT it
     C.un[q] = 0.5 * (F.un[f] + F.un[f + F.pitch]);
     C.vn[q] = 0.5 * (F.vn[f] + F.vn[f + 1]);
 }
+QN_KERNEL(k_restrict_n, __launch_bounds__(BLK), (), ())
 
 // restore the state of time n on the finest level (failed step)
-template <typename IT> __global__ __launch_bounds__(BLK) void k_restore(IT it)
+template <typename IT> __device__ __forceinline__ void k_restore_body(const IT &it)
 {
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
-    const int t = ((int)blockIdx.x - it.start[k]) * BLK + threadIdx.x;
+    const Desc &d = it_desc(it, k);
+    const int t = ((int)blockIdx.x - it_start(it, k)) * BLK + threadIdx.x;
     if (t >= d.m1 * d.m2) return;
     const int j = t / d.m1, i = t - j * d.m1;
     const size_t q = (size_t)j * d.pitch + i;
-    const int par = it.par[k];
+    const int par = it_par(it, k);
     d.c[q] = d.cn[q];
     d.ub[par][q] = d.un[q];
     d.vb[par][q] = d.vn[q];
     d.mu[q] = d.mus[q];
     d.p[q] = d.ps[q];
 }
+QN_KERNEL(k_restore, __launch_bounds__(BLK), (), ())
 
 } // namespace qn

@@ -516,48 +516,37 @@ static void acc_reset(qnsch_ctx *x)
     x->acc_first = true;
 }
 
-// a work list of one item in its compact form
-static Item1 one_of(const Items &a)
-{
-    Item1 b;
-    memset(&b, 0, sizeof(b));
-    b.n = 1;
-    b.start[0] = a.start[0];
-    b.start[1] = a.start[1];
-    b.d[0] = a.d[0];
-    b.par[0] = a.par[0];
-    b.cpar[0] = a.cpar[0];
-    b.tx[0] = a.tx[0];
-    b.acc[0] = a.acc[0];
-    return b;
-}
-// launch kernel template K on list L (ItemList): the one-item instantiation
-// when the list has a single item; a timed launch (e0 set in the calling
-// scope) carries the events that take the kernel's own start and end
+// the arguments of a list of one item (Item1)
+static int one_w(const Items &a) { return (a.par[0] & 1) | (a.cpar[0] & 1) << 1 | (a.acc[0] + 1) << 2; }
+// launch kernel K on list L (ItemList): K itself when the list has a single
+// item, else K_n; a timed launch (e0 set in the calling scope) carries the
+// events that take the kernel's own start and end
+#define KLAUNCH1(K, L, GRID, BLOCK, LDS, ST, ...)                                                    \
+    do {                                                                                           \
+        if (e0)                                                                                    \
+            hipExtLaunchKernelGGL(K, GRID, BLOCK, LDS, ST, e0, e1, 0, (L).it.d[0], one_w((L).it),     \
+                                  (L).it.tx[0], ##__VA_ARGS__);                                    \
+        else                                                                                       \
+            hipLaunchKernelGGL(K, GRID, BLOCK, LDS, ST, (L).it.d[0], one_w((L).it), (L).it.tx[0],      \
+                               ##__VA_ARGS__);                                                     \
+    } while (0)
+#define KLAUNCHN(K, L, GRID, BLOCK, LDS, ST, ...)                                                    \
+    do {                                                                                           \
+        if (e0) hipExtLaunchKernelGGL(K, GRID, BLOCK, LDS, ST, e0, e1, 0, (L).it, ##__VA_ARGS__);    \
+        else hipLaunchKernelGGL(K, GRID, BLOCK, LDS, ST, (L).it, ##__VA_ARGS__);                     \
+    } while (0)
 #define KLAUNCH(K, L, GRID, BLOCK, LDS, ST, ...)                                                     \
     do {                                                                                           \
-        if (e0) {                                                                                  \
-            if ((L).it.n == 1)                                                                     \
-                hipExtLaunchKernelGGL(K<Item1>, GRID, BLOCK, LDS, ST, e0, e1, 0, one_of((L).it), ##__VA_ARGS__); \
-            else hipExtLaunchKernelGGL(K<Items>, GRID, BLOCK, LDS, ST, e0, e1, 0, (L).it, ##__VA_ARGS__); \
-        } else if ((L).it.n == 1)                                                                  \
-            hipLaunchKernelGGL(K<Item1>, GRID, BLOCK, LDS, ST, one_of((L).it), ##__VA_ARGS__);     \
-        else hipLaunchKernelGGL(K<Items>, GRID, BLOCK, LDS, ST, (L).it, ##__VA_ARGS__);            \
+        if ((L).it.n == 1) KLAUNCH1(K, L, GRID, BLOCK, LDS, ST, ##__VA_ARGS__);                      \
+        else KLAUNCHN(K##_n, L, GRID, BLOCK, LDS, ST, ##__VA_ARGS__);                                \
     } while (0)
-
 // the same for kernels with an instantiation of their own for the projection
-// scheme (PJ, in the calling scope), which runs one simulation per launch
+// scheme (pj, in the calling scope), which runs one simulation per launch
 #define KLAUNCH_PJ(K, L, GRID, BLOCK, LDS, ST, ...)                                                  \
     do {                                                                                           \
-        if (pj) KLAUNCH1((K<true, Item1>), L, GRID, BLOCK, LDS, ST, ##__VA_ARGS__);                 \
-        else if ((L).it.n == 1) KLAUNCH1((K<false, Item1>), L, GRID, BLOCK, LDS, ST, ##__VA_ARGS__); \
-        else if (e0) hipExtLaunchKernelGGL((K<false, Items>), GRID, BLOCK, LDS, ST, e0, e1, 0, (L).it, ##__VA_ARGS__); \
-        else hipLaunchKernelGGL((K<false, Items>), GRID, BLOCK, LDS, ST, (L).it, ##__VA_ARGS__);     \
-    } while (0)
-#define KLAUNCH1(K1, L, GRID, BLOCK, LDS, ST, ...)                                                   \
-    do {                                                                                           \
-        if (e0) hipExtLaunchKernelGGL(K1, GRID, BLOCK, LDS, ST, e0, e1, 0, one_of((L).it), ##__VA_ARGS__); \
-        else hipLaunchKernelGGL(K1, GRID, BLOCK, LDS, ST, one_of((L).it), ##__VA_ARGS__);            \
+        if (pj) KLAUNCH1(K<true>, L, GRID, BLOCK, LDS, ST, ##__VA_ARGS__);                           \
+        else if ((L).it.n == 1) KLAUNCH1(K<false>, L, GRID, BLOCK, LDS, ST, ##__VA_ARGS__);          \
+        else KLAUNCHN(K##_n, L, GRID, BLOCK, LDS, ST, ##__VA_ARGS__);                                \
     } while (0)
 
 // Launch one operation for a set of (context, level) entries, in lists of at
@@ -688,12 +677,9 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
             if (W.it.n == 1) {
                 AccCoef<1> G1;
                 for (int b = 0; b < 3; b++) G1.g[0][b] = G.g[0][b];
-                if (e0) hipExtLaunchKernelGGL((k_accel<Item1, 1>), dim3(W.blocks), dim3(BLK), 0, s, e0, e1, 0, one_of(W.it), G1);
-                else hipLaunchKernelGGL((k_accel<Item1, 1>), dim3(W.blocks), dim3(BLK), 0, s, one_of(W.it), G1);
-            } else if (e0) {
-                hipExtLaunchKernelGGL((k_accel<Items, MAXITEMS>), dim3(W.blocks), dim3(BLK), 0, s, e0, e1, 0, W.it, G);
+                KLAUNCH1(k_accel, W, dim3(W.blocks), dim3(BLK), 0, s, G1);
             } else {
-                hipLaunchKernelGGL((k_accel<Items, MAXITEMS>), dim3(W.blocks), dim3(BLK), 0, s, W.it, G);
+                KLAUNCHN(k_accel_n, W, dim3(W.blocks), dim3(BLK), 0, s, G);
             }
             break;
         }
@@ -1115,12 +1101,12 @@ static size_t device_lds_max()
     int v = 0;
     size_t r = 65536;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 65536
-        && hipFuncSetAttribute((const void *)k_coarse_solve<false, Items>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
-        && hipFuncSetAttribute((const void *)k_coarse_solve<false, Item1>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
-        && hipFuncSetAttribute((const void *)k_coarse_solve<true, Item1>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
-        && hipFuncSetAttribute((const void *)k_mx_coarse_solve<Items>, hipFuncAttributeMaxDynamicSharedMemorySize, v)
+        && hipFuncSetAttribute((const void *)k_coarse_solve_n, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
+        && hipFuncSetAttribute((const void *)k_coarse_solve<false>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
+        && hipFuncSetAttribute((const void *)k_coarse_solve<true>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
+        && hipFuncSetAttribute((const void *)k_mx_coarse_solve_n, hipFuncAttributeMaxDynamicSharedMemorySize, v)
                == hipSuccess
-        && hipFuncSetAttribute((const void *)k_mx_coarse_solve<Item1>, hipFuncAttributeMaxDynamicSharedMemorySize, v)
+        && hipFuncSetAttribute((const void *)k_mx_coarse_solve, hipFuncAttributeMaxDynamicSharedMemorySize, v)
                == hipSuccess)
         r = (size_t)v;
     (void)hipGetLastError();
@@ -1220,7 +1206,6 @@ static int ctx_init(qnsch_ctx *x, const qnsch_grid *g, const qnsch_params *p, co
         Desc &d = x->hd[l];
         d.m1 = D.m1; d.m2 = D.m2; d.pitch = D.pitch; d.bcx = g->bc_x; d.bcy = g->bc_y;
         d.h = D.h; d.inv_h = 1.0 / D.h;
-        d.coarse = l + 1 < x->nlev ? x->dd + l + 1 : nullptr;
     }
     set_params(x, p);
     x->hd[0].red_host = x->red_host;
@@ -1853,19 +1838,8 @@ int qnsch_residual_noalloc(const qnsch_grid *g, const qnsch_params *prm, double 
     d.red_host = d.red + NRED;  // the reduced values stay on the device
     hipError_t e = hipMemcpyAsync(base, &d, sizeof(d), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
-        Item1 it;
-        memset(&it, 0, sizeof(it));
-        it.n = 1;
-        it.start[0] = 0;
-        it.start[1] = tx * ty;
-        it.d[0] = (const Desc *)base;
-        it.tx[0] = tx;
-        it.acc[0] = -1;
-        hipLaunchKernelGGL((k_resid_norm<false, Item1>), dim3(tx * ty), dim3(TBLK), 0, s, it);
-        Item1 f = it;
-        f.start[1] = 1;
-        f.tx[0] = tx * ty;
-        hipLaunchKernelGGL(k_finalize<Item1>, dim3(1), dim3(BLK), 0, s, f, 0);
+        hipLaunchKernelGGL(k_resid_norm<false>, dim3(tx * ty), dim3(TBLK), 0, s, (const Desc *)base, 0, tx);
+        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(BLK), 0, s, (const Desc *)base, 0, tx * ty, 0);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(norms, d.red, 5 * sizeof(double), hipMemcpyDeviceToHost, s);

@@ -79,14 +79,14 @@ __device__ __forceinline__ void ltile_put(const PhysF &P, float *t, int su, int 
 }
 
 // cooperative load of a tile, NE elements per thread (as tile_load)
-template <int NE> __device__ __forceinline__ void ltile_load(const PhysF &P, const LView &L, const TileF &T)
+template <int NE, int NT> __device__ __forceinline__ void ltile_load(const PhysF &P, const LView &L, const TileF &T)
 {
-    const int n = T.W * T.H, nt = block_threads();
+    const int n = T.W * T.H;
     float v[NE][9];
     if (tile_inner(L.m1, L.m2, T.i0, T.j0, T.W, T.H)) {
 #pragma unroll
         for (int k = 0; k < NE; k++) {
-            const int e = min((int)threadIdx.x + k * nt, n - 1), b = e / T.W, a = e - b * T.W;
+            const int e = min((int)threadIdx.x + k * NT, n - 1), b = e / T.W, a = e - b * T.W;
             const size_t q = (size_t)((T.j0 - 1 + b) * L.pitch + (T.i0 - 1 + a));
             const float *src[9] = { L.c, L.dc, L.dmu, L.dp, L.du, L.dv, L.cn, L.un, L.vn };
 #pragma unroll
@@ -95,15 +95,15 @@ template <int NE> __device__ __forceinline__ void ltile_load(const PhysF &P, con
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < NE; k++) {
-            const int e = threadIdx.x + k * nt;
-            if (e < n) ltile_put(P, T.s + e * L_ES, 1, 1, v[k]);
+            const int e = threadIdx.x + k * NT, b = e / T.W, a = e - b * T.W;
+            if (e < n) ltile_put(P, T.s + (b * T.S + a) * L_ES, 1, 1, v[k]);
         }
         return;
     }
     TileSrc s[NE];
 #pragma unroll
     for (int k = 0; k < NE; k++) {
-        const int e = min((int)threadIdx.x + k * nt, n - 1), b = e / T.W, a = e - b * T.W;
+        const int e = min((int)threadIdx.x + k * NT, n - 1), b = e / T.W, a = e - b * T.W;
         s[k] = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, T.i0 - 1 + a, T.j0 - 1 + b);
         const float w[9] = { lda<1>(L.c, s[k].c), lda<1>(L.dc, s[k].c), lda<1>(L.dmu, s[k].c), lda<1>(L.dp, s[k].c),
                              lda<1>(L.du, s[k].u), lda<1>(L.dv, s[k].v), lda<1>(L.cn, s[k].c), lda<1>(L.un, s[k].u),
@@ -114,10 +114,10 @@ template <int NE> __device__ __forceinline__ void ltile_load(const PhysF &P, con
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < NE; k++) {
-        const int e = threadIdx.x + k * nt;
+        const int e = threadIdx.x + k * NT, b = e / T.W, a = e - b * T.W;
         if (e >= n) continue;
-        if (s[k].sc == 0) tile_zero(T, e);
-        else ltile_put(P, T.s + e * L_ES, s[k].su, s[k].sv, v[k]);
+        if (s[k].sc == 0) tile_zero(T, b * T.S + a);
+        else ltile_put(P, T.s + (b * T.S + a) * L_ES, s[k].su, s[k].sv, v[k]);
     }
 }
 

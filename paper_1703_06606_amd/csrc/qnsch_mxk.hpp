@@ -15,7 +15,7 @@
 
 namespace qn {
 
-#define LTILE_FLOATS (L_ES * (TX + 3) * (TY + 3))
+#define LTILE_FLOATS (L_ES * TILE_S * (TY + 3))
 static_assert(LTILE_FLOATS * 4 <= 65536, "FP32 tile exceeds 64 KiB of LDS");
 
 __device__ __forceinline__ LView lview_of(const Desc &d, int par)
@@ -33,16 +33,16 @@ __device__ __forceinline__ LView lview_of(const Desc &d, int par)
 
 // one colour half-sweep of the correction smoother; the correction faces are
 // read from buffer par and written to par^1
-template <typename IT> __device__ __forceinline__ void mx_halfsweep_body(const IT &it, int colour, float omega)
+template <typename IT> __device__ __forceinline__ void k_mx_halfsweep_body(const IT &it, int colour, float omega)
 {
     TILE_LDS float sm[LTILE_FLOATS];
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
+    const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
-    const int par = it.par[k];
+    const int par = it_par(it, k);
     const LView L = lview_of(d, par);
     const TileF T = item_tile<TileF>(sm, it, k, d);
-    ltile_load<2>(d.Pf, L, T);
+    ltile_load<2, TBLK>(d.Pf, L, T);
     __syncthreads();
     const int pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
     const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
@@ -50,34 +50,32 @@ template <typename IT> __device__ __forceinline__ void mx_halfsweep_body(const I
     const int i = T.i0 + 2 * kk + ((j + colour) & 1);
     if (i < L.m1 && j < L.m2) lrelax_cell<false, 1>(d.Pf, d.Kf, L, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
 }
-template <typename IT> __global__ HS_ATTR void k_mx_halfsweep(IT it, int colour, float omega)
-{
-    mx_halfsweep_body(it, colour, omega);
-}
+QN_KERNEL(k_mx_halfsweep, HS_ATTR, (int colour, float omega), (colour, omega))
 // finest-level launches under their own name (profiles)
-template <typename IT> __global__ HS_ATTR void k_mx_halfsweep_fine(IT it, int colour, float omega)
+template <typename IT> __device__ __forceinline__ void k_mx_halfsweep_fine_body(const IT &it, int colour, float omega)
 {
-    mx_halfsweep_body(it, colour, omega);
+    k_mx_halfsweep_body(it, colour, omega);
 }
+QN_KERNEL(k_mx_halfsweep_fine, HS_ATTR, (int colour, float omega), (colour, omega))
 
 // temporal blocking of the correction smoother: one red + black sweep per
 // launch, as k_hs_fused (the widened tile in LDS, the cell corrections from
 // one set to the other, the face corrections from buffer par to par ^ 1)
-#define MX_FUSED_FLOATS (L_ES * FUSED_W * FUSED_H)
+#define MX_FUSED_FLOATS (L_ES * FUSED_S * FUSED_H)
 static_assert(MX_FUSED_FLOATS * 4 <= 65536, "fused FP32 tile exceeds 64 KiB of LDS");
 
 __device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, const TileF &T)
 {
     const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
+    for (int e = threadIdx.x; e < n; e += FBLK) {
         const int b = e / T.W, a = e - b * T.W;
         int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
         if (L.bcx) i = wrapi(i, L.m1);
         if (L.bcy) j = wrapi(j, L.m2);
         const TileSrc q = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        float *s = T.s + e * L_ES;
+        float *s = T.s + (b * T.S + a) * L_ES;
         if (q.sc == 0) {
-            tile_zero(T, e);
+            tile_zero(T, b * T.S + a);
             continue;
         }
         // the level is in global memory; every load before any use
@@ -95,7 +93,7 @@ __device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, co
 __device__ __forceinline__ void mx_fused_refresh(const LView &L, const TileF &T)
 {
     const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
+    for (int e = threadIdx.x; e < n; e += FBLK) {
         const int b = e / T.W, a = e - b * T.W;
         const int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
         const bool gx = !L.bcx && (i < 0 || i >= L.m1), gy = !L.bcy && (j < 0 || j >= L.m2);
@@ -105,7 +103,7 @@ __device__ __forceinline__ void mx_fused_refresh(const LView &L, const TileF &T)
         // every value the element may take, before any store (as
         // fused_refresh)
         const float *q = T.at(si, sj);
-        float *s = T.s + e * L_ES;
+        float *s = T.s + (b * T.S + a) * L_ES;
         const float u = T.at(i, sj)[T_U2], v = T.at(si, j)[T_V2], dc = q[L_DC], mu = q[T_MU], p = q[T_P], drs = q[L_DRS];
         __builtin_amdgcn_sched_barrier(0);
         s[T_U] = signed_val(su, u);
@@ -118,13 +116,13 @@ __device__ __forceinline__ void mx_fused_refresh(const LView &L, const TileF &T)
         }
     }
 }
-template <typename IT> __global__ __launch_bounds__(FBLK) void k_mx_fused(IT it, int dir, float omega)
+template <typename IT> __device__ __forceinline__ void k_mx_fused_body(const IT &it, int dir, float omega)
 {
     TILE_LDS float sm[MX_FUSED_FLOATS];
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
+    const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
-    const int par = it.par[k];
+    const int par = it_par(it, k);
     LView L = lview_of(d, par);
     LView O = L;
     if (dir) {
@@ -134,7 +132,7 @@ template <typename IT> __global__ __launch_bounds__(FBLK) void k_mx_fused(IT it,
     }
     const TileF T0 = item_tile<TileF>(sm, it, k, d);
     TileF T;
-    T.s = sm; T.i0 = T0.i0 - 2; T.j0 = T0.j0 - 2; T.W = FUSED_W; T.H = FUSED_H;
+    T.s = sm; T.i0 = T0.i0 - 2; T.j0 = T0.j0 - 2; T.W = FUSED_W; T.H = FUSED_H; T.S = FUSED_S;
     mx_fused_load(d.Pf, L, T);
     __syncthreads();
     const int pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
@@ -169,6 +167,7 @@ template <typename IT> __global__ __launch_bounds__(FBLK) void k_mx_fused(IT it,
         }
     }
 }
+QN_KERNEL(k_mx_fused, __launch_bounds__(FBLK), (int dir, float omega), (dir, omega))
 
 // r - J delta on the item's level, restricted to the next coarser level
 // (cells: mean of four; faces: mean of the two coincident fine faces),
@@ -179,16 +178,16 @@ __device__ __forceinline__ float quad_sum(float x)
     x += other(x);
     return x + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false));
 }
-template <typename IT> __global__ __launch_bounds__(TBLK) void k_mx_restrict(IT it)
+template <typename IT> __device__ __forceinline__ void k_mx_restrict_body(const IT &it)
 {
     TILE_LDS float sm[LTILE_FLOATS];
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
+    const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
-    const Desc &C = *d.coarse;
-    const LView Lf = lview_of(d, it.par[k]);
+    const Desc &C = (&d)[1];
+    const LView Lf = lview_of(d, it_par(it, k));
     const TileF T = item_tile<TileF>(sm, it, k, d);
-    ltile_load<2>(d.Pf, Lf, T);
+    ltile_load<2, TBLK>(d.Pf, Lf, T);
     __syncthreads();
     const int cc = threadIdx.x >> 2, ch = threadIdx.x & 3;
     const int I = T.i0 / 2 + cc % (TX / 2), J = T.j0 / 2 + cc / (TX / 2);
@@ -203,7 +202,7 @@ template <typename IT> __global__ __launch_bounds__(TBLK) void k_mx_restrict(IT 
     const float sc = quad_sum(T.q(T_C, i, j)), smu = quad_sum(xmu), su = quad_sum(wu ? xu : 0.0f),
                 sv = quad_sum(wv ? xv : 0.0f);
     const size_t q = (size_t)J * C.pitch + I;
-    const int cp = it.cpar[k];
+    const int cp = it_cpar(it, k);
     if (ch == 0) {
         sta<1>(C.xc, q, 0.25f * sc);
         sta<1>(C.xmu, q, 0.25f * smu);
@@ -224,6 +223,7 @@ template <typename IT> __global__ __launch_bounds__(TBLK) void k_mx_restrict(IT 
         sta<1>(C.dvb[cp], q, 0.0f);
     }
 }
+QN_KERNEL(k_mx_restrict, __launch_bounds__(TBLK), (), ())
 
 // P delta_H of the FP32 correction at fine cell (i, j): cells piecewise
 // constant, faces as in prolong_load / prolong_apply (a face on a wall is no
@@ -280,16 +280,16 @@ __device__ __forceinline__ void mx_prolong_apply(const PSrcF &C, const PRawF &r,
 }
 
 // delta_h += P delta_H, one thread per fine cell
-template <typename IT> __global__ __launch_bounds__(BLK) void k_mx_prolong(IT it)
+template <typename IT> __device__ __forceinline__ void k_mx_prolong_body(const IT &it)
 {
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
-    const int t = ((int)blockIdx.x - it.start[k]) * BLK + threadIdx.x;
+    const Desc &d = it_desc(it, k);
+    const int t = ((int)blockIdx.x - it_start(it, k)) * BLK + threadIdx.x;
     if (t >= d.m1 * d.m2) return;
     const int j = t / d.m1, i = t - j * d.m1;
     const size_t kf = (size_t)j * d.pitch + i;
-    const PSrcF ps = psrcf_of(d, d.coarse, it.cpar[k]);
-    float *ub = d.dub[it.par[k]], *vb = d.dvb[it.par[k]];
+    const PSrcF ps = psrcf_of(d, &d + 1, it_cpar(it, k));
+    float *ub = d.dub[it_par(it, k)], *vb = d.dvb[it_par(it, k)];
     const PRawF raw = mx_prolong_load(ps, i, j);
     const float c0 = lda<1>(d.dc, kf), m0 = lda<1>(d.dmu, kf), p0 = lda<1>(d.dp, kf), u0 = lda<1>(ub, kf),
                 v0 = lda<1>(vb, kf);
@@ -303,6 +303,7 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_mx_prolong(IT it
     if (hu) sta<1>(ub, kf, u0 + du);
     if (hv) sta<1>(vb, kf, v0 + dv);
 }
+QN_KERNEL(k_mx_prolong, __launch_bounds__(BLK), (), ())
 
 // LDS floats of the coarsest-level correction solve: 19 level arrays + a tile
 // + the tile's source map (4 ints per element)
@@ -328,13 +329,12 @@ __device__ __forceinline__ void ltile_fill(const PhysF &P, const LView &L, const
 // all correction sweeps of a level in one workgroup per item, the level
 // resident in LDS (the coarsest level, and the smoothing of small coarse
 // levels); an even number of half-sweeps keeps the result in buffer par
-template <typename IT>
-__global__ __launch_bounds__(512) void k_mx_coarse_solve(IT it, int sweeps, float omega, int prolong)
+template <typename IT> __device__ __forceinline__ void k_mx_coarse_solve_body(const IT &it, int sweeps, float omega, int prolong)
 {
     extern __shared__ __attribute__((aligned(16))) float smf[];
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
-    const int par = it.par[k];
+    const Desc &d = it_desc(it, k);
+    const int par = it_par(it, k);
     const LView L = lview_of(d, par);
     float *ua = d.dub[par], *va = d.dvb[par];
     const int m1 = L.m1, m2 = L.m2, n = m1 * m2;
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(512) void k_mx_coarse_solve(IT it, int sweeps, floa
           *hdmu = smf + 5 * n, *hdp = smf + 6 * n, *uA = smf + 7 * n, *vA = smf + 8 * n, *uB = smf + 9 * n,
           *vB = smf + 10 * n, *hcn = smf + 11 * n, *hun = smf + 12 * n, *hvn = smf + 13 * n, *hr = smf + 14 * n;
     PSrcF ps = {};
-    if (prolong) ps = psrcf_of(d, d.coarse, it.cpar[k]);
+    if (prolong) ps = psrcf_of(d, &d + 1, it_cpar(it, k));
     for (int e = threadIdx.x; e < n; e += block_threads()) {
         const int j = e / m1, i = e - j * m1;
         const size_t q = (size_t)j * L.pitch + i;
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(512) void k_mx_coarse_solve(IT it, int sweeps, floa
     H.rc = hr; H.rmu = hr + n; H.rp = hr + 2 * n; H.ru = hr + 3 * n; H.rv = hr + 4 * n;
     H.pitch = m1;
     TileF T;
-    T.s = smf + ((19 * n + 3) & ~3); T.i0 = 0; T.j0 = 0; T.W = m1 + 3; T.H = m2 + 3;
+    T.s = smf + ((19 * n + 3) & ~3); T.i0 = 0; T.j0 = 0; T.W = T.S = m1 + 3; T.H = m2 + 3;
     int *map = (int *)(T.s + (size_t)L_ES * T.W * T.H);
     tile_map_build(H, T, map);
     const int half = m1 >> 1;
@@ -403,32 +403,34 @@ __global__ __launch_bounds__(512) void k_mx_coarse_solve(IT it, int sweeps, floa
         L.dc[q] = hdc[e]; L.dmu[q] = hdmu[e]; L.dp[q] = hdp[e]; ua[q] = uA[e]; va[q] = vA[e];
     }
 }
+QN_KERNEL(k_mx_coarse_solve, __launch_bounds__(512), (int sweeps, float omega, int prolong), (sweeps, omega, prolong))
 
 // w += delta on the finest level (FP64 state, single u/v buffer in mixed
 // mode); faces on walls are not unknowns
-template <typename IT> __global__ __launch_bounds__(BLK) void k_mx_update(IT it)
+template <typename IT> __device__ __forceinline__ void k_mx_update_body(const IT &it)
 {
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
-    const int t = ((int)blockIdx.x - it.start[k]) * BLK + threadIdx.x;
+    const Desc &d = it_desc(it, k);
+    const int t = ((int)blockIdx.x - it_start(it, k)) * BLK + threadIdx.x;
     if (t >= d.m1 * d.m2) return;
     const int j = t / d.m1, i = t - j * d.m1;
     const size_t q = (size_t)j * d.pitch + i;
-    const int par = it.par[k];
+    const int par = it_par(it, k);
     d.c[q] += (double)d.dc[q];
     d.mu[q] += (double)d.dmu[q];
     d.p[q] += (double)d.dp[q];
     if (d.bcx || i >= 1) d.ub[0][q] += (double)d.dub[par][q];
     if (d.bcy || j >= 1) d.vb[0][q] += (double)d.dvb[par][q];
 }
+QN_KERNEL(k_mx_update, __launch_bounds__(BLK), (), ())
 
 // FP32 time-n data of the next coarser level
-template <typename IT> __global__ __launch_bounds__(BLK) void k_mx_restrict_n(IT it)
+template <typename IT> __device__ __forceinline__ void k_mx_restrict_n_body(const IT &it)
 {
     const int k = find_item(it);
-    const Desc &F = *it.d[k];
-    const Desc &C = *F.coarse;
-    const int t = ((int)blockIdx.x - it.start[k]) * BLK + threadIdx.x;
+    const Desc &F = it_desc(it, k);
+    const Desc &C = (&F)[1];
+    const int t = ((int)blockIdx.x - it_start(it, k)) * BLK + threadIdx.x;
     if (t >= C.m1 * C.m2) return;
     const int J = t / C.m1, I = t - J * C.m1;
     const size_t f = (size_t)(2 * J) * F.pitch + 2 * I, q = (size_t)J * C.pitch + I;
@@ -436,18 +438,19 @@ template <typename IT> __global__ __launch_bounds__(BLK) void k_mx_restrict_n(IT
     C.unf[q] = 0.5f * (F.unf[f] + F.unf[f + F.pitch]);
     C.vnf[q] = 0.5f * (F.vnf[f] + F.vnf[f + 1]);
 }
+QN_KERNEL(k_mx_restrict_n, __launch_bounds__(BLK), (), ())
 
 // r - J delta on a level into the FP64 residual-field buffer (m1 x m2 per
 // field, packed), for checking the linearisation
-template <typename IT> __global__ __launch_bounds__(TBLK) void k_mx_linresid(IT it)
+template <typename IT> __device__ __forceinline__ void k_mx_linresid_body(const IT &it)
 {
     TILE_LDS float sm[LTILE_FLOATS];
     const int k = find_item(it);
-    const Desc &d = *it.d[k];
+    const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
-    const LView L = lview_of(d, it.par[k]);
+    const LView L = lview_of(d, it_par(it, k));
     const TileF T = item_tile<TileF>(sm, it, k, d);
-    ltile_load<2>(d.Pf, L, T);
+    ltile_load<2, TBLK>(d.Pf, L, T);
     __syncthreads();
     const size_t n = (size_t)L.m1 * L.m2;
     const int i = T.i0 + (int)threadIdx.x % TX, j = T.j0 + (int)threadIdx.x / TX;
@@ -460,5 +463,6 @@ template <typename IT> __global__ __launch_bounds__(TBLK) void k_mx_linresid(IT 
     d.rout[3 * n + q] = r.u;
     d.rout[4 * n + q] = r.v;
 }
+QN_KERNEL(k_mx_linresid, __launch_bounds__(TBLK), (), ())
 
 } // namespace qn
