@@ -81,13 +81,12 @@ FP64_PEAK_TFLOPS = 78.6
 # reduction's finalisation and, after a cycle, the pbar shift)
 OP_KERNEL = {
     "halfsweep": ("k_halfsweep_fine", "k_halfsweep"), "fused_sweep": ("k_hs_fused", "k_hs_fused"),
-    "smooth": ("k_coarse_solve", "k_coarse_solve"), "coarse_solve": ("k_coarse_solve", "k_coarse_solve"),
+    "coarse_solve": ("k_bottom", "k_bottom"),
     "restrict": ("k_restrict", "k_restrict"),
     "prolong": ("k_prolong", "k_prolong"), "residual": ("k_resid_norm",) * 2, "residual0": ("k_resid_norm",) * 2,
     "residual_acc": ("k_resid_norm",) * 2, "accelerate": ("k_accel",) * 2, "begin": ("k_begin",) * 2,
     "restrict_n": ("k_restrict_n",) * 2, "mx_halfsweep": ("k_mx_halfsweep_fine", "k_mx_halfsweep"),
-    "mx_fused_sweep": ("k_mx_fused",) * 2, "mx_smooth": ("k_mx_coarse_solve",) * 2,
-    "mx_coarse_solve": ("k_mx_coarse_solve",) * 2, "mx_restrict": ("k_mx_restrict",) * 2,
+    "mx_fused_sweep": ("k_mx_fused",) * 2, "mx_coarse_solve": ("k_mx_bottom",) * 2, "mx_restrict": ("k_mx_restrict",) * 2,
     "mx_prolong": ("k_mx_prolong",) * 2, "mx_update": ("k_mx_update",) * 2, "mx_restrict_n": ("k_mx_restrict_n",) * 2,
     "pj_final": ("k_pj_final",) * 2,
 }

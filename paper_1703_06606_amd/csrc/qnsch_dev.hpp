@@ -23,19 +23,6 @@
 
 namespace qn {
 
-// threads of the workgroup.  Every launch of this library has whole
-// workgroups, so this is the dispatch's group size: the 16-bit field at byte
-// 12 of the implicit kernel arguments (code object v5), read with a scalar
-// load of its 32-bit word.  blockDim.x also allows for a partial last
-// workgroup and reads the field with a vector load, one memory latency at the
-// start of every kernel that uses it.
-__device__ __forceinline__ int block_threads()
-{
-    const __attribute__((address_space(4))) unsigned int *p =
-        (const __attribute__((address_space(4))) unsigned int *)__builtin_amdgcn_implicitarg_ptr();
-    return (int)(p[3] & 0xffffu);
-}
-
 struct Phys {
     double rho1, rho2, rho12, drho;  // rho(c) = rho12 / (drho c + rho1)
     double visc1, visc2, visc12, dvisc;
@@ -371,51 +358,38 @@ template <int NE, int NT> __device__ __forceinline__ void tile_load(const Phys &
     }
 }
 
-// A level resident in LDS is refreshed into its tile after every half-sweep.
-// Where each element comes from is fixed, so it is computed once (4 ints per
-// element: the cell, u and v source indices as tile_src gives them, and a
-// word with the u and v signs, a beyond-reach flag (such elements keep their
-// loaded values) and the colour of the source cell).
-template <typename V, typename TT> __device__ __forceinline__ void tile_map_build(const V &L, const TT &T, int *map)
+// Images of a level that is resident in its tile: the elements outside
+// the level, [-1, m+1] on each axis without [0, m-1], in the order the ring is
+// walked; for each its element and those of its sources (a cell, a u face, a v
+// face of the level) with the signs of the faces, as tile_src_ij gives them.
+struct alignas(16) Image {
+    int e, c, u, v; // element; elements of the sources, faces' signs + 1 in the low two bits
+};
+__host__ __device__ __forceinline__ int ring_size(int m1, int m2) { return (m1 + 3) * (m2 + 3) - m1 * m2; }
+// build the ring's entries (thread t of NT)
+template <typename TT>
+__device__ __forceinline__ void ring_build(const TT &T, int m1, int m2, int bcx, int bcy, Image *ring, int t, int NT)
 {
-    const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
-        const int b = e / T.W, a = e - b * T.W;
-        const int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
-        const TileSrc q = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        const int ic = q.c % L.pitch, jc = q.c / L.pitch;
-        int fl = (q.su + 1) | ((q.sv + 1) << 2) | (((ic + jc) & 1) << 5);
-        if (i > L.m1 + 1 || j > L.m2 + 1) fl |= 16;
-        map[4 * e] = q.c;
-        map[4 * e + 1] = q.u;
-        map[4 * e + 2] = q.v;
-        map[4 * e + 3] = fl;
-    }
-}
-// the refresh after a half-sweep of the given colour: all face velocities
-// (the new buffer), and c, mubar, pbar, rho(c) of the elements whose source
-// cell has that colour (the others did not change), with the boundary images
-// of ldc, ldu, ldv
-__device__ __forceinline__ void tile_refresh_map(const Phys &P, const View &L, const Tile &T, const int *map,
-                                                 int colour)
-{
-    const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
-        // the map entry, then every value the element may take (the indices
-        // are valid in any case), before any use: two round trips to LDS
-        // instead of one per dependent step
-        const int q = map[4 * e], qu = map[4 * e + 1], qv = map[4 * e + 2], fl = map[4 * e + 3];
-        const double u = L.u[qu], v = L.v[qv], c = L.c[q], mu = L.mu[q], p = L.p[q];
-        __builtin_amdgcn_sched_barrier(0);
-        if (fl & 16) continue;
-        double *s = T.s + e * T_ES;
-        s[T_U] = signed_val((fl & 3) - 1, u);
-        s[T_V] = signed_val(((fl >> 2) & 3) - 1, v);
-        if (((fl >> 5) & 1) != colour) continue;
-        s[T_C] = c;
-        s[T_MU] = mu;
-        s[T_P] = p;
-        s[T_RS] = rho_of(P, c);
+    const int n = ring_size(m1, m2);
+    for (int k = t; k < n; k += NT) {
+        int i, j;
+        // rows -1, m2, m2 + 1, then columns -1, m1, m1 + 1 of the other rows
+        if (k < 3 * (m1 + 3)) {
+            const int r = k / (m1 + 3);
+            i = k - r * (m1 + 3) - 1;
+            j = r == 0 ? -1 : m2 + r - 1;
+        } else {
+            const int q = k - 3 * (m1 + 3), r = q / 3, s = q - 3 * r;
+            j = r;
+            i = s == 0 ? -1 : m1 + s - 1;
+        }
+        const TileSrcIJ q = tile_src_ij(m1, m2, bcx, bcy, i, j);
+        Image g;
+        g.e = T.idx(i, j);
+        g.c = T.idx(q.ic, q.jc);
+        g.u = T.idx(q.iu, q.ju) * 4 + q.su + 1;
+        g.v = T.idx(q.iv, q.jv) * 4 + q.sv + 1;
+        ring[k] = g;
     }
 }
 
@@ -431,21 +405,24 @@ __device__ __forceinline__ void tile_refresh_map(const Phys &P, const View &L, c
 
 struct Ax {
     int dn, dt;          // offsets of the next element along the normal / tangential axis
-    int fn, ft;          // own velocity (T_U or T_V), other velocity
+    int fn, ft, fo;      // own velocity (T_U or T_V, or T_U2, T_V2), other velocity, new own velocity
     bool per, pert;      // periodic along the axis / the other one
     int ia, ma, it, mt;  // cell index and count along the axis / the other one
     int hlf;             // 0 x, 1 y
 };
 
+// slot: the faces are in T_U, T_V and a sweep that stays in the tile puts the
+// new ones into T_U2, T_V2 (0), or the other way round (1)
 template <typename V, typename TT>
-__device__ __forceinline__ Ax make_ax(const V &L, const TT &T, int i, int j, int hlf)
+__device__ __forceinline__ Ax make_ax(const V &L, const TT &T, int i, int j, int hlf, int slot = 0)
 {
     Ax a;
     a.hlf = hlf;
     a.dn = hlf ? T.S * TT::ES : TT::ES;
     a.dt = hlf ? TT::ES : T.S * TT::ES;
-    a.fn = T_U + hlf;
-    a.ft = T_V - hlf;
+    a.fn = T_U + hlf + slot * (T_U2 - T_U);
+    a.ft = T_V - hlf + slot * (T_U2 - T_U);
+    a.fo = T_U2 + hlf - slot * (T_U2 - T_U);
     a.per = hlf ? L.bcy : L.bcx;
     a.pert = hlf ? L.bcx : L.bcy;
     a.ia = hlf ? j : i;
@@ -580,7 +557,7 @@ template <typename R> struct FaceEq {
 template <typename R, bool PJ, bool LIN>
 __device__ __forceinline__ FaceEq<R> face_eq(const Kon<R> &K, const R *s, const Ax &a, R uh = R(0))
 {
-    const int dn = a.dn, dt = a.dt, fn = a.fn, ft = a.ft, fnn = fn + (T_UN - T_U), ftn = ft + (T_UN - T_U);
+    const int dn = a.dn, dt = a.dt, fn = a.fn, ft = a.ft, fnn = T_UN + a.hlf, ftn = T_VN - a.hlf;
     const R *L = s - dn;
     const R rL = L[T_RN], rR = s[T_RN], mL = L[T_MV], mR = s[T_MV];
     const R a1 = rL + rR, b1 = mL + mR;
@@ -735,11 +712,13 @@ __device__ __forceinline__ const double *face_rhs(const Rhs &F, int hlf)
 //
 // omega relaxes the box's velocity and pressure updates; pomega the
 // projection scheme's separate pressure step.
-// With TO set, the cell sits at tile position (ti, tj), which differs from
-// its level position (i, j) at a periodic image, and the results stay in the
-// tile: c, mubar, pbar and rho(c) in place (no other cell of the colour reads
-// them), the box faces in the fields T_U2, T_V2, whose elements only this
-// cell's box writes.  AS is the address space of the level arrays and
+// TO: 0 the results go to the level arrays.  1: the cell sits at tile position
+// (ti, tj), which differs from its level position (i, j) at a periodic image,
+// and the results stay in the tile; 2: the same in a tile that holds the whole
+// level, where the high face of the last cell of a periodic axis is the first
+// cell's low face.  In the tile go c, mubar, pbar and rho(c) in place (no other cell of the colour reads
+// them), the box faces in the fields T_U2, T_V2 (slot 0; from them to T_U, T_V:
+// slot 1), whose elements only this cell's box writes.  AS is the address space of the level arrays and
 // right-hand sides (1: global memory, 3: LDS, where the level resides in the
 // workgroup's LDS).
 //
@@ -753,12 +732,17 @@ struct CellPos {
     Ax a;
     bool hlo, hhi;    // the lane's faces are unknowns
     size_t k, khi;    // level index of the cell (and its low faces), of the lane's high face
+    // where the new high face goes in the tile, from the cell's element
+    template <int TO> __device__ __forceinline__ int hi() const
+    {
+        return TO == 2 && a.ia + 1 == a.ma ? a.dn - a.ma * a.dn : a.dn;
+    }
 };
 template <typename V, typename TT>
-__device__ __forceinline__ CellPos cell_pos(const V &L, const TT &T, int i, int j, int ti, int tj, int hlf)
+__device__ __forceinline__ CellPos cell_pos(const V &L, const TT &T, int i, int j, int ti, int tj, int hlf, int slot)
 {
     CellPos c;
-    c.a = make_ax(L, T, i, j, hlf);
+    c.a = make_ax(L, T, i, j, hlf, slot);
     c.hlo = c.a.per || c.a.ia >= 1;
     c.hhi = c.a.per || c.a.ia + 1 < c.a.ma;
     c.k = (size_t)j * L.pitch + i;
@@ -773,7 +757,7 @@ __device__ __forceinline__ CellPos cell_pos(const V &L, const TT &T, int i, int 
 template <typename R>
 __device__ __forceinline__ void box_offdiag(const Kon<R> &K, const R *s, const Ax &a, bool hlo, bool hhi, R &alh, R &ahl)
 {
-    const int fnn = a.fn + (T_UN - T_U);
+    const int fnn = T_UN + a.hlf;
     const R un = s[fnn] + s[a.dn + fnn];
     const R w = R(4) * (K.ka * (s[T_RN] * un)), vis = R(4) * (K.kv * s[T_MV]);
     alh = hlo ? w - vis : R(0);
@@ -786,21 +770,21 @@ __device__ __forceinline__ void box_offdiag(const Kon<R> &K, const R *s, const A
     }
 }
 
-template <bool TO, int AS>
+template <int TO, int AS>
 __device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, const View &L, const Tile &T, const Rhs &F,
                                          double *unew, double *vnew, int i, int j, int ti, int tj, int hlf,
-                                         double omega, double pomega);
+                                         double omega, double pomega, int slot);
 
-template <bool PJ, bool TO, int AS>
+template <bool PJ, int TO, int AS>
 __device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, const View &L, const Tile &T,
                                            const Rhs &F, double *unew, double *vnew, int i, int j, int ti, int tj,
-                                           int hlf, double omega, double pomega)
+                                           int hlf, double omega, double pomega, int slot = 0)
 {
     if (PJ) {
-        relax_pj<TO, AS>(P, K, L, T, F, unew, vnew, i, j, ti, tj, hlf, omega, pomega);
+        relax_pj<TO, AS>(P, K, L, T, F, unew, vnew, i, j, ti, tj, hlf, omega, pomega, slot);
         return;
     }
-    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf);
+    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
     const Ax &a = b.a;
     double *const e = T.at(ti, tj);
     const bool cpl = P.coupled;
@@ -861,8 +845,8 @@ __device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, 
     const double nhi = uhi + omega * ((X.xb[1] + t * X.xs[1]) - dc * X.xq[1]);
     const double np = p0 + omega * dp;
     if (TO) {
-        if (b.hlo) e[T_U2 + hlf] = nlo;
-        if (b.hhi) e[a.dn + T_U2 + hlf] = nhi;
+        if (b.hlo) e[a.fo] = nlo;
+        if (b.hhi) e[b.hi<TO>() + a.fo] = nhi;
         if (hlf == 0) {
             e[T_P] = np;
             if (cpl) {
@@ -923,7 +907,7 @@ __device__ __forceinline__ double face_final(const Kon<double> &K, const double 
     return unk ? ut + w * f : 0.0;
 }
 
-template <bool PJ>
+template <bool PJ, int AS = 1>
 __device__ __forceinline__ Resid resid_cell(const Kon<double> &K, const View &L, const Tile &T, const Rhs &F, int i,
                                             int j)
 {
@@ -931,7 +915,7 @@ __device__ __forceinline__ Resid resid_cell(const Kon<double> &K, const View &L,
     const Ax ax = make_ax(L, T, i, j, 0), ay = make_ax(L, T, i, j, 1);
     const size_t k = (size_t)j * L.pitch + i;
     Resid f = {};
-    if (F.fc) f = { lda<1>(F.fc, k), lda<1>(F.fmu, k), lda<1>(F.fp, k), lda<1>(F.fu, k), lda<1>(F.fv, k) };
+    if (F.fc) f = { lda<AS>(F.fc, k), lda<AS>(F.fmu, k), lda<AS>(F.fp, k), lda<AS>(F.fu, k), lda<AS>(F.fv, k) };
     const bool hu = ax.per || i >= 1, hv = ay.per || j >= 1;
     double ulo = e[T_U], uhi = e[ax.dn + T_U], vlo = e[T_V], vhi = e[ay.dn + T_V];
     if (PJ) {
@@ -969,12 +953,12 @@ __device__ __forceinline__ Resid resid_cell(const Kon<double> &K, const View &L,
 //  4. the velocity of time n+1 is never stored, so nothing is left to update.
 // The tile entries of the cell (c, mubar, rho(c)) are updated after step 1; no
 // other pair of this colour reads them.
-template <bool TO, int AS>
+template <int TO, int AS>
 __device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, const View &L, const Tile &T, const Rhs &F,
                                          double *unew, double *vnew, int i, int j, int ti, int tj, int hlf,
-                                         double omega, double pomega)
+                                         double omega, double pomega, int slot)
 {
-    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf);
+    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
     const Ax &a = b.a;
     double *const e = T.at(ti, tj);
     const double *P1 = e + a.dn, *M1 = e - a.dn;
@@ -1044,8 +1028,8 @@ __device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, co
     const double ut0 = e[a.fn], ut1 = P1[a.fn];
     const double ulo = ut0 + omega * (X.xb[0] + t * X.xs[0]), uhi = ut1 + omega * (X.xb[1] + t * X.xs[1]);
     if (TO) {
-        if (b.hlo) e[T_U2 + hlf] = ulo;
-        if (b.hhi) e[a.dn + T_U2 + hlf] = uhi;
+        if (b.hlo) e[a.fo] = ulo;
+        if (b.hhi) e[b.hi<TO>() + a.fo] = uhi;
     } else {
         double *fo = hlf ? vnew : unew;
         if (b.hlo) sta<AS>(fo, b.k, ulo);

@@ -54,6 +54,7 @@ struct Desc {
     double *fc, *fmu, *fp, *fu, *fv;                    // FAS right-hand side (NULL on the finest level)
     double *c0, *mu0, *p0, *u0, *v0;                    // restricted iterate (coarse levels)
     int m1, m2, pitch, bcx, bcy;
+    int depth;                                          // levels from this one to the coarsest, both included
     double h, inv_h;
     double *partials;                                   // per-simulation reduction partials (finest level)
     double *red;                                        // reduced values (device)
@@ -206,7 +207,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_halfsweep_body
     const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
     const int j = T.j0 + lj;
     const int i = T.i0 + 2 * kk + ((j + colour) & 1);
-    if (i < L.m1 && j < L.m2) relax_cell<PJ, false, 1>(P, K, L, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
+    if (i < L.m1 && j < L.m2) relax_cell<PJ, 0, 1>(P, K, L, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
 }
 QN_KERNEL_PJ(k_halfsweep, HS_ATTR, (int colour, double omega), (colour, omega))
 // the same kernel under its own name for launches whose items are all finest
@@ -425,7 +426,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused_body(
         const bool in = lj < TY + 4 && (L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2));
         if (in) {
             const int i = L.bcx ? wrapi(ti, L.m1) : ti, j = L.bcy ? wrapi(tj, L.m2) : tj;
-            relax_cell<PJ, true, 1>(P, K, L, T, F, nullptr, nullptr, i, j, ti, tj, hlf, omega, 1.0);
+            relax_cell<PJ, 1, 1>(P, K, L, T, F, nullptr, nullptr, i, j, ti, tj, hlf, omega, 1.0);
         }
     }
     __syncthreads();
@@ -436,7 +437,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused_body(
         const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
         const int j = T0.j0 + lj;
         const int i = T0.i0 + 2 * kk + ((j + 1) & 1);
-        if (i < L.m1 && j < L.m2) relax_cell<PJ, false, 1>(P, K, O, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
+        if (i < L.m1 && j < L.m2) relax_cell<PJ, 0, 1>(P, K, O, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
     } else {
         // red cells of the tile: their final values
         const int q = pr - TBLK / 2;
@@ -462,129 +463,6 @@ __global__ __launch_bounds__(BLK) void k_copy_probe(const double *__restrict__ a
 {
     for (size_t q = (size_t)blockIdx.x * BLK + threadIdx.x; q < n; q += (size_t)gridDim.x * BLK) b[q] = a[q];
 }
-
-// LDS doubles of the level-resident solve: 12 per cell (the level arrays and
-// right-hand sides) + one tile + the tile's source map (4 ints per element)
-__host__ __device__ inline size_t coarse_lds_doubles(int m1, int m2)
-{
-    return (size_t)12 * m1 * m2 + (size_t)(T_ES + 2) * (m1 + 3) * (m2 + 3);
-}
-
-// all sweeps of a level in one workgroup per item, with the whole level
-// resident in LDS: the solve of the coarsest level, and the pre- and
-// post-smoothing of coarse levels small enough (the same arithmetic as the
-// half-sweep launches); the u/v buffers alternate, the number of half-sweeps
-// is even, so the result stays in buffer par.  With prolong set the level
-// first takes the coarse-grid correction (k_prolong's arithmetic) as it is
-// loaded.
-template <bool PJ, typename IT> __device__ __forceinline__ void k_coarse_solve_body(const IT &it, int sweeps, double omega, double pomega, int prolong)
-{
-    extern __shared__ __attribute__((aligned(16))) double sm[];
-    const int k = find_item(it);
-    const Desc &d = it_desc(it, k);
-    // the constants by value (no store can change them, so they are not
-    // reloaded after one); the relaxation works on LDS arrays (address space 3)
-    const Phys P = d.P;
-    const Kon<double> K = d.K;
-    const int par = it_par(it, k);
-    const View L = view_of(d, par);
-    double *ua = d.ub[par], *va = d.vb[par];
-    const int m1 = L.m1, m2 = L.m2, n = m1 * m2;
-    double *hc = sm, *hmu = sm + n, *hp = sm + 2 * n, *uA = sm + 3 * n, *vA = sm + 4 * n, *uB = sm + 5 * n,
-           *vB = sm + 6 * n, *hf = sm + 7 * n;
-    Tile T;
-    T.s = sm + 12 * n; T.i0 = 0; T.j0 = 0; T.W = T.S = m1 + 3; T.H = m2 + 3;
-    const int nt = T.W * T.H;
-    int *map = (int *)(T.s + (size_t)T_ES * nt);
-    // one pass over the tile's elements: each loads its sources from the level
-    // arrays (the boundary images of tile_load), adds the coarse-grid
-    // correction of each source, and fills the tile (with the cell functions),
-    // the refresh map (level indices in LDS, as tile_map_build) and, for an
-    // element that is a cell of the level, the level arrays in LDS and the
-    // right-hand sides
-    PSrc ps = {};
-    if (prolong) ps = psrc_of(d, &d + 1, it_cpar(it, k));
-    // the right-hand sides' arrays read before the first store (read after
-    // one, every element would reload them from the descriptor)
-    const double *const rfc = d.fc, *const rfmu = d.fmu, *const rfp = d.fp, *const rfu = d.fu, *const rfv = d.fv;
-    for (int e = threadIdx.x; e < nt; e += block_threads()) {
-        const int b = e / T.W, a = e - b * T.W;
-        const int i = a - 1, j = b - 1;
-        const TileSrcIJ q = tile_src_ij(m1, m2, L.bcx, L.bcy, i, j);
-        const size_t kc = (size_t)q.jc * L.pitch + q.ic, ku = (size_t)q.ju * L.pitch + q.iu,
-                     kv = (size_t)q.jv * L.pitch + q.iv;
-        const bool cell = i >= 0 && i < m1 && j >= 0 && j < m2;
-        const size_t ql = cell ? (size_t)j * L.pitch + i : 0;
-        // every load of the element before any use: its sources, the
-        // right-hand sides (a cell of the level; index 0 otherwise, not used)
-        // and the coarse values of the correction at each source
-        double c = lda<1>(L.c, kc), mu = lda<1>(L.mu, kc), p = lda<1>(L.p, kc), u = lda<1>(ua, ku),
-               v = lda<1>(va, kv);
-        const double cn = lda<1>(L.cn, kc), un = lda<1>(L.un, ku), vn = lda<1>(L.vn, kv);
-        const double f0 = rfc ? lda<1>(rfc, ql) : 0.0, f1 = rfmu ? lda<1>(rfmu, ql) : 0.0,
-                     f2 = rfp ? lda<1>(rfp, ql) : 0.0, f3 = rfu ? lda<1>(rfu, ql) : 0.0,
-                     f4 = rfv ? lda<1>(rfv, ql) : 0.0;
-        PRaw raw = {};
-        if (prolong) raw = prolong_load(ps, q.ic, q.jc, q.iu, q.ju, q.iv, q.jv);
-        __builtin_amdgcn_sched_barrier(0);
-        if (prolong) {
-            double rc, rm, rp, du, dv;
-            prolong_apply(ps, raw, q.iu, q.iv, q.jv, rc, rm, rp, du, dv);
-            c += rc; mu += rm; p += rp;
-            if (ps.bcx || q.iu >= 1) u += du;
-            if (ps.bcy || q.jv >= 1) v += dv;
-        }
-        const bool out = i > m1 + 1 || j > m2 + 1;
-        map[4 * e] = q.jc * m1 + q.ic;
-        map[4 * e + 1] = q.ju * m1 + q.iu;
-        map[4 * e + 2] = q.jv * m1 + q.iv;
-        map[4 * e + 3] = (q.su + 1) | ((q.sv + 1) << 2) | (((q.ic + q.jc) & 1) << 5) | (out ? 16 : 0);
-        if (q.sc == 0) {
-            tile_zero(T, e);
-        } else {
-            const double w[8] = { c, mu, p, u, v, cn, un, vn };
-            tile_put(P, T.s + e * T_ES, q.su, q.sv, w);
-        }
-        if (cell) {
-            // a cell of the level: its own source for every field
-            const int el = j * m1 + i;
-            hc[el] = c; hmu[el] = mu; hp[el] = p; uA[el] = u; vA[el] = v;
-            hf[el] = f0;
-            hf[n + el] = f1;
-            hf[2 * n + el] = f2;
-            hf[3 * n + el] = f3;
-            hf[4 * n + el] = f4;
-        }
-    }
-    __syncthreads();
-    View H = L;
-    H.c = hc; H.mu = hmu; H.p = hp; H.pitch = m1;
-    const Rhs FH = { hf, hf + n, hf + 2 * n, hf + 3 * n, hf + 4 * n };
-    const int half = m1 >> 1;
-    for (int s = 0; s < 2 * sweeps; s++) {
-        const int colour = s & 1;
-        double *uw, *vw;
-        if (s & 1) { H.u = uB; H.v = vB; uw = uA; vw = vA; }
-        else { H.u = uA; H.v = vA; uw = uB; vw = vB; }
-        if (s > 0) {
-            tile_refresh_map(P, H, T, map, colour ^ 1);
-            __syncthreads();
-        }
-        for (int t = threadIdx.x; t < 2 * half * m2; t += block_threads()) {
-            const int pr = t >> 1;
-            const int j = pr / half;
-            const int i = 2 * (pr - j * half) + ((j + colour) & 1);
-            relax_cell<PJ, false, 3>(P, K, H, T, FH, uw, vw, i, j, i, j, t & 1, omega, pomega);
-        }
-        __syncthreads();
-    }
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
-        const int j = e / m1, i = e - j * m1;
-        const size_t q = (size_t)j * L.pitch + i;
-        L.c[q] = hc[e]; L.mu[q] = hmu[e]; L.p[q] = hp[e]; ua[q] = uA[e]; va[q] = vA[e];
-    }
-}
-QN_KERNEL_PJ(k_coarse_solve, __launch_bounds__(512), (int sweeps, double omega, double pomega, int prolong), (sweeps, omega, pomega, prolong))
 
 // R w of a coarse cell from the values of its four children (a, b: the
 // children (0, 0), (1, 0); c, d: (0, 1), (1, 1)): the mean, summed in the order
@@ -702,6 +580,273 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_restrict_body(
     sta<1>(C.fv, q, v_unk(Lc, J) ? 0.5 * part[4][cc] - r.v : 0.0);
 }
 QN_KERNEL_PJ(k_restrict, __launch_bounds__(RBLK), (), ())
+
+// --------------------------------------------------------------------------
+// The bottom of a V-cycle: a level and every coarser one in one workgroup per
+// item, resident in LDS: pre-smoothing and restriction down to the coarsest
+// level, its solve, prolongation and post-smoothing back up, with the
+// arithmetic of the kernels that do the same level by level.  Such levels have
+// fewer cells of a colour than a workgroup has lane pairs, so a launch lasts as
+// long as its dependent chain; a launch per step also paid for its start (two
+// memory round trips), for the level's way from and to memory and for an
+// image map of the whole tile.  Per cycle of the 256 x 512 droplet (16 x 32, 8 x 16,
+// 4 x 8 cells: 24 half-sweeps), seven launches of 20.8 and 6.4 us, @@ us in all,
+// became one of @@ us (MI355X).
+//
+// LDS of a level: its tile (rows of an even number of elements), the
+// right-hand sides, the restricted iterate (coarser levels), the images.
+#define BOT 512
+struct BotLev {
+    double *f, *w0; // 5 fields of m1*m2
+    Image *ring;
+    Tile T;
+    int m1, m2;
+};
+__host__ __device__ inline int bot_stride(int m1) { return (m1 + 4) & ~1; }
+__host__ __device__ inline size_t bot_tile(int m1, int m2, int es) { return (size_t)es * bot_stride(m1) * (m2 + 3); }
+__host__ __device__ inline size_t bot_doubles(int m1, int m2)
+{
+    return bot_tile(m1, m2, T_ES) + (size_t)10 * m1 * m2 + 2 * (size_t)ring_size(m1, m2);
+}
+// level l below the m1 x m2 one whose LDS starts at sm
+__device__ __forceinline__ BotLev bot_lev(double *sm, int m1, int m2, int l)
+{
+    for (; l > 0; l--) {
+        sm += bot_doubles(m1, m2);
+        m1 >>= 1;
+        m2 >>= 1;
+    }
+    BotLev B;
+    B.m1 = m1; B.m2 = m2;
+    B.T.s = sm; B.T.i0 = 0; B.T.j0 = 0; B.T.W = m1 + 3; B.T.H = m2 + 3; B.T.S = bot_stride(m1);
+    B.f = sm + bot_tile(m1, m2, T_ES);
+    B.w0 = B.f + 5 * m1 * m2;
+    B.ring = (Image *)(B.w0 + 5 * m1 * m2);
+    return B;
+}
+__device__ __forceinline__ View bot_view(const BotLev &B, const Desc &d)
+{
+    View L = {};
+    L.m1 = B.m1; L.m2 = B.m2; L.pitch = B.m1;
+    L.bcx = d.bcx; L.bcy = d.bcy;
+    return L;
+}
+__device__ __forceinline__ Rhs bot_rhs(const BotLev &B)
+{
+    const int n = B.m1 * B.m2;
+    const Rhs F = { B.f, B.f + n, B.f + 2 * n, B.f + 3 * n, B.f + 4 * n };
+    return F;
+}
+// the images follow their sources; the faces are in slot `slot`
+__device__ __forceinline__ void bot_images(const BotLev &B, int slot)
+{
+    const int n = ring_size(B.m1, B.m2), fu = T_U + slot * (T_U2 - T_U);
+    for (int k = threadIdx.x; k < n; k += BOT) {
+        const Image g = B.ring[k];
+        const double *s = B.T.s + g.c * T_ES;
+        const double c = s[T_C], mu = s[T_MU], p = s[T_P], rs = s[T_RS];
+        const double u = B.T.s[(g.u >> 2) * T_ES + fu], v = B.T.s[(g.v >> 2) * T_ES + fu + 1];
+        double *t = B.T.s + g.e * T_ES;
+        t[T_C] = c;
+        t[T_MU] = mu;
+        t[T_P] = p;
+        t[T_RS] = rs;
+        t[fu] = signed_val((g.u & 3) - 1, u);
+        t[fu + 1] = signed_val((g.v & 3) - 1, v);
+    }
+}
+// sweeps of a level (an even number of half-sweeps: the faces end in slot 0)
+template <bool PJ>
+__device__ __forceinline__ void bot_smooth(const Phys &P, const Desc &d, const BotLev &B, int sweeps, double omega, double pomega)
+{
+    const Kon<double> K = d.K;
+    const View L = bot_view(B, d);
+    const Rhs F = bot_rhs(B);
+    const int half = B.m1 >> 1;
+    for (int s = 0; s < 2 * sweeps; s++) {
+        const int colour = s & 1;
+        for (int t = threadIdx.x; t < 2 * half * B.m2; t += BOT) {
+            const int pr = t >> 1, j = pr / half;
+            const int i = 2 * (pr - j * half) + ((j + colour) & 1);
+            relax_cell<PJ, 2, 3>(P, K, L, B.T, F, nullptr, nullptr, i, j, i, j, t & 1, omega, pomega, colour);
+        }
+        __syncthreads();
+        bot_images(B, colour ^ 1);
+        __syncthreads();
+    }
+}
+// residual of level A, restricted with the iterate to the next level C, whose
+// right-hand side becomes N_H(R w) + R r
+template <bool PJ>
+__device__ __forceinline__ void bot_restrict(const Phys &P, const Desc &d, const BotLev &A, const BotLev &C)
+{
+    const int nc = C.m1 * C.m2;
+    {
+        const Kon<double> K = d.K;
+        const View L = bot_view(A, d);
+        const Rhs F = bot_rhs(A);
+        for (int t = threadIdx.x; t < 4 * nc; t += BOT) {
+            const int cc = t >> 2, ch = t & 3;
+            const int J = cc / C.m1, I = cc - J * C.m1, i = 2 * I + (ch & 1), j = 2 * J + (ch >> 1);
+            const Resid r = resid_cell<PJ, 3>(K, L, A.T, F, i, j);
+            const double *e = A.T.at(i, j);
+            const bool wu = (ch & 1) == 0, wv = (ch >> 1) == 0; // faces of the coarse cell
+            const double c = 0.25 * quad_sum(e[T_C]), mu = 0.25 * quad_sum(e[T_MU]), p = 0.25 * quad_sum(e[T_P]),
+                         u = 0.5 * quad_sum(wu ? e[T_U] : 0.0), v = 0.5 * quad_sum(wv ? e[T_V] : 0.0);
+            const double f[5] = { 0.25 * quad_sum(r.c), 0.25 * quad_sum(r.mu), 0.25 * quad_sum(r.p),
+                                  0.5 * quad_sum(wu ? r.u : 0.0), 0.5 * quad_sum(wv ? r.v : 0.0) };
+            if (ch == 0) {
+                double *o = C.T.at(I, J);
+                const double w[5] = { c, mu, p, u, v };
+                o[T_C] = c;
+                o[T_MU] = mu;
+                o[T_P] = p;
+                o[T_RS] = rho_of(P, c);
+                o[T_U] = o[T_U2] = u;
+                o[T_V] = o[T_V2] = v;
+#pragma unroll
+                for (int q = 0; q < 5; q++) {
+                    C.w0[q * nc + cc] = w[q];
+                    C.f[q * nc + cc] = f[q];
+                }
+            }
+        }
+    }
+    __syncthreads();
+    bot_images(C, 0);
+    __syncthreads();
+    {
+        const Desc &dc = (&d)[1];
+        const Kon<double> K = dc.K;
+        const View L = bot_view(C, dc);
+        const Rhs Z = { nullptr, nullptr, nullptr, nullptr, nullptr };
+        for (int t = threadIdx.x; t < nc; t += BOT) {
+            const int J = t / C.m1, I = t - J * C.m1;
+            const Resid r = resid_cell<PJ, 3>(K, L, C.T, Z, I, J); // -N_H(R w)
+            C.f[t] -= r.c;
+            C.f[nc + t] -= r.mu;
+            C.f[2 * nc + t] -= r.p;
+            C.f[3 * nc + t] -= r.u;
+            C.f[4 * nc + t] -= r.v;
+        }
+    }
+    __syncthreads();
+}
+// the coarse-grid correction (k_prolong's arithmetic) from level C to A
+__device__ __forceinline__ void bot_prolong(const Phys &P, const Desc &d, const BotLev &A, const BotLev &C)
+{
+    const int na = A.m1 * A.m2, nc = C.m1 * C.m2;
+    const bool bx = d.bcx, by = d.bcy;
+    for (int t = threadIdx.x; t < na; t += BOT) {
+        const int j = t / A.m1, i = t - j * A.m1, I = i >> 1, J = j >> 1;
+        auto corr = [&](int f, int a, int b) { return C.T.at(a, b)[f] - C.w0[(f == T_C ? 0 : f == T_MU ? 1 : f == T_P ? 2 : f == T_U ? 3 : 4) * nc + b * C.m1 + a]; };
+        double du = corr(T_U, I, J), dv = corr(T_V, I, J);
+        if (i & 1) {
+            const bool in = I + 1 < C.m1;
+            const double e = in || bx ? corr(T_U, in ? I + 1 : 0, J) : 0.0;
+            du = 0.5 * (du + e);
+        }
+        if (j & 1) {
+            const bool in = J + 1 < C.m2;
+            const double e = in || by ? corr(T_V, I, in ? J + 1 : 0) : 0.0;
+            dv = 0.5 * (dv + e);
+        }
+        double *o = A.T.at(i, j);
+        const double c = o[T_C] + corr(T_C, I, J);
+        o[T_C] = c;
+        o[T_MU] += corr(T_MU, I, J);
+        o[T_P] += corr(T_P, I, J);
+        o[T_RS] = rho_of(P, c);
+        if (bx || i >= 1) o[T_U] += du;
+        if (by || j >= 1) o[T_V] += dv;
+    }
+    __syncthreads();
+    bot_images(A, 0);
+    __syncthreads();
+}
+template <bool PJ, typename IT>
+__device__ __forceinline__ void k_bottom_body(const IT &it, int nu1, int nu2, int nuc, double omega, double comega)
+{
+    extern __shared__ __attribute__((aligned(16))) double sm[];
+    const int k = find_item(it);
+    const Desc &d = it_desc(it, k);
+    const Phys P = d.P;
+    const int par = it_par(it, k), m1 = d.m1, m2 = d.m2, depth = d.depth;
+    const View L = view_of(d, par);
+    double *const ua = d.ub[par], *const va = d.vb[par];
+    // the top level with its images and right-hand sides, and the time-n data
+    // of the coarser ones; every load of an element before any use
+    {
+        const Rhs F = rhs_of(d);
+        const BotLev B = bot_lev(sm, m1, m2, 0);
+        const int n = m1 * m2;
+        for (int e = threadIdx.x; e < B.T.W * B.T.H; e += BOT) {
+            const int b = e / B.T.W, a = e - b * B.T.W, i = a - 1, j = b - 1;
+            const TileSrc q = tile_src(m1, m2, L.pitch, L.bcx, L.bcy, i, j);
+            const bool cell = i >= 0 && i < m1 && j >= 0 && j < m2;
+            const double v[8] = { lda<1>(L.c, q.c), lda<1>(L.mu, q.c), lda<1>(L.p, q.c), lda<1>(L.u, q.u),
+                                  lda<1>(L.v, q.v), lda<1>(L.cn, q.c), lda<1>(L.un, q.u), lda<1>(L.vn, q.v) };
+            double f[5] = { 0.0, 0.0, 0.0, 0.0, 0.0 };
+            if (F.fc && cell) {
+                f[0] = lda<1>(F.fc, q.c); f[1] = lda<1>(F.fmu, q.c); f[2] = lda<1>(F.fp, q.c);
+                f[3] = lda<1>(F.fu, q.c); f[4] = lda<1>(F.fv, q.c);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            double *t = B.T.s + (b * B.T.S + a) * T_ES;
+            tile_put(P, t, q.su, q.sv, v);
+            t[T_U2] = t[T_U];
+            t[T_V2] = t[T_V];
+            if (cell)
+#pragma unroll
+                for (int g = 0; g < 5; g++) B.f[g * n + j * m1 + i] = f[g];
+        }
+        ring_build(B.T, m1, m2, L.bcx, L.bcy, B.ring, threadIdx.x, BOT);
+    }
+    for (int l = 1; l < depth; l++) {
+        const BotLev B = bot_lev(sm, m1, m2, l);
+        const Desc &c = (&d)[l];
+        const double *const cn = c.cn, *const un = c.un, *const vn = c.vn;
+        for (int e = threadIdx.x; e < B.T.W * B.T.H; e += BOT) {
+            const int b = e / B.T.W, a = e - b * B.T.W;
+            const TileSrc q = tile_src(B.m1, B.m2, B.m1, L.bcx, L.bcy, a - 1, b - 1);
+            const double n = lda<1>(cn, q.c), u = lda<1>(un, q.u), v = lda<1>(vn, q.v);
+            double *t = B.T.s + (b * B.T.S + a) * T_ES;
+            t[T_CN] = n;
+            t[T_RN] = rho_of(P, n);
+            t[T_MV] = visc_of(P, n);
+            t[T_MOB] = mob_of(P, n);
+            t[T_UN] = signed_val(q.su, u);
+            t[T_VN] = signed_val(q.sv, v);
+        }
+        ring_build(B.T, B.m1, B.m2, L.bcx, L.bcy, B.ring, threadIdx.x, BOT);
+    }
+    __syncthreads();
+    for (int l = 0; l + 1 < depth; l++) {
+        const BotLev A = bot_lev(sm, m1, m2, l), C = bot_lev(sm, m1, m2, l + 1);
+        bot_smooth<PJ>(P, (&d)[l], A, nu1, omega, 1.0);
+        bot_restrict<PJ>(P, (&d)[l], A, C);
+    }
+    // the coarsest level over-relaxes the velocity and pressure updates (the
+    // primitive box, the projection pressure step)
+    bot_smooth<PJ>(P, (&d)[depth - 1], bot_lev(sm, m1, m2, depth - 1), nuc, PJ ? omega : comega, PJ ? comega : 1.0);
+    for (int l = depth - 2; l >= 0; l--) {
+        const BotLev A = bot_lev(sm, m1, m2, l), C = bot_lev(sm, m1, m2, l + 1);
+        bot_prolong(P, d, A, C);
+        bot_smooth<PJ>(P, (&d)[l], A, nu2, omega, 1.0);
+    }
+    const BotLev B = bot_lev(sm, m1, m2, 0);
+    for (int e = threadIdx.x; e < m1 * m2; e += BOT) {
+        const int j = e / m1, i = e - j * m1;
+        const size_t q = (size_t)j * L.pitch + i;
+        const double *t = B.T.at(i, j);
+        sta<1>(L.c, q, t[T_C]);
+        sta<1>(L.mu, q, t[T_MU]);
+        sta<1>(L.p, q, t[T_P]);
+        sta<1>(ua, q, t[T_U]);
+        sta<1>(va, q, t[T_V]);
+    }
+}
+QN_KERNEL_PJ(k_bottom, __launch_bounds__(BOT), (int nu1, int nu2, int nuc, double omega, double comega), (nu1, nu2, nuc, omega, comega))
 
 // w_h += P(w_H - R w_h) on the level the item names, one thread per fine cell
 template <typename IT> __device__ __forceinline__ void k_prolong_body(const IT &it)
@@ -1197,6 +1342,14 @@ __global__ __launch_bounds__(BLK) void k_accel(const Desc *d, int w, int cnt, Ac
     k_accel_body(Item1{ d, w, cnt }, G);
 }
 __global__ __launch_bounds__(BLK) void k_accel_n(Items it, AccCoef<MAXITEMS> G) { k_accel_body(it, G); }
+
+// the faces on walls of the level, whose values are zero, in buffer par
+__global__ __launch_bounds__(BLK) void k_wall_faces(const Desc *__restrict__ d, int par)
+{
+    const int t = blockIdx.x * BLK + threadIdx.x;
+    if (!d->bcx && t < d->m2) d->ub[par][(size_t)t * d->pitch] = 0.0;
+    if (!d->bcy && t < d->m1) d->vb[par][t] = 0.0;
+}
 
 // time-n data of the finest level = current iterate; keep mubar, pbar of time n
 template <typename IT> __device__ __forceinline__ void k_begin_body(const IT &it)

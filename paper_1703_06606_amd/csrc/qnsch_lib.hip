@@ -32,12 +32,13 @@ using namespace qn;
 
 enum OpKind { OP_BEGIN, OP_RN, OP_NORM0, OP_NORM, OP_HS, OP_RESTRICT, OP_COARSE, OP_PROLONG, OP_STEPEND,
               OP_RESTORE,
+              // (OP_COARSE, OP_MXCOARSE: the cycle on this level and every
+              // coarser one, in one workgroup; colour field = nu1 + 16 nu2)
               // mixed precision: FP32 correction cycle, FP64 update
               OP_MXRN, OP_MXHS, OP_MXRESTRICT, OP_MXCOARSE, OP_MXPROLONG, OP_MXUPDATE,
               // diagnostics of the current state
               OP_DISSIP, OP_DIAG, OP_PJFINAL,
-              // colour field = number of sweeps: all sweeps of a small level
-              // in one workgroup with the level resident in LDS
+              // (numbers of operations that are no longer issued)
               OP_SMOOTH, OP_MXSMOOTH,
               // acceleration of the cycle iteration: residual norms that also
               // record the result, and the combination before the next cycle
@@ -59,19 +60,13 @@ static bool single_kernel_op(int kind)
              || kind == OP_DIAG);
 }
 
-// nu sweeps of level l: one launch per colour half-sweep, or, on a coarse
-// level that fits in LDS (l >= small), all of them in one workgroup, or, on a
-// level marked in fuse, one launch per sweep (an even number of them, so that
-// the cell unknowns end in the set they started in; an odd last sweep takes
-// two half-sweeps), all with the same arithmetic in the same order
-static void smooth_ops(int l, int nu, int small, int hs_kind, int lds_kind, unsigned fuse, std::vector<Op> &out)
+// nu sweeps of level l: one launch per colour half-sweep or, on a level marked
+// in fuse, one launch per sweep (an even number of them, so that the cell
+// unknowns end in the set they started in; an odd last sweep takes two
+// half-sweeps), with the same arithmetic in the same order
+static void smooth_ops(int l, int nu, int hs_kind, unsigned fuse, std::vector<Op> &out)
 {
     const int fused_kind = hs_kind == OP_MXHS ? OP_MXFUSED : OP_FUSED;
-    if (nu <= 0) return;
-    if (l > 0 && l >= small) {
-        out.push_back({ lds_kind, l, nu });
-        return;
-    }
     int s = 0;
     if ((fuse >> l) & 1)
         for (; s + 1 < nu; s += 2) {
@@ -83,53 +78,46 @@ static void smooth_ops(int l, int nu, int small, int hs_kind, int lds_kind, unsi
         out.push_back({ hs_kind, l, 1 });
     }
 }
-// prolongation onto level l, then its post-smoothing; a level-resident
-// smoothing takes the correction as it loads the level (colour field
-// nu + PROLONG_FIRST), and so does the first fused sweep of an FP64 level
-// (colour field 2 + direction 0), which saves the prolongation launch
-#define PROLONG_FIRST 16
+// prolongation onto level l, then its post-smoothing; the first fused sweep of
+// an FP64 level takes the correction as it loads the level (colour field 2 +
+// direction 0), which saves the prolongation launch
+#define MAX_SWEEPS 16
 #define FUSED_PROLONG 2
-static void prolong_smooth_ops(int l, int nu, int small, int pr_kind, int hs_kind, int lds_kind, unsigned fuse,
-                               std::vector<Op> &out)
+static void prolong_smooth_ops(int l, int nu, int pr_kind, int hs_kind, unsigned fuse, std::vector<Op> &out)
 {
-    if (nu > 0 && nu < PROLONG_FIRST && l > 0 && l >= small) {
-        out.push_back({ lds_kind, l, nu + PROLONG_FIRST });
-        return;
-    }
-    if (pr_kind == OP_PROLONG && nu >= 2 && !(l > 0 && l >= small) && ((fuse >> l) & 1)) {
+    if (pr_kind == OP_PROLONG && nu >= 2 && ((fuse >> l) & 1)) {
         const size_t first = out.size();
-        smooth_ops(l, nu, small, hs_kind, lds_kind, fuse, out);
+        smooth_ops(l, nu, hs_kind, fuse, out);
         out[first].colour |= FUSED_PROLONG;
         return;
     }
     out.push_back({ pr_kind, l, 0 });
-    smooth_ops(l, nu, small, hs_kind, lds_kind, fuse, out);
+    smooth_ops(l, nu, hs_kind, fuse, out);
 }
 
-// one V-cycle of a hierarchy of L levels, ending with the residual norms and
-// the pbar mean removal
-static void vcycle_program(int L, int nu1, int nu2, int small, unsigned fuse, bool acc, std::vector<Op> &out)
+// one V-cycle whose levels from `bottom` on run in one workgroup, ending with
+// the residual norms and the pbar mean removal
+static void vcycle_program(int bottom, int nu1, int nu2, unsigned fuse, bool acc, std::vector<Op> &out)
 {
-    for (int l = 0; l + 1 < L; l++) {
-        smooth_ops(l, nu1, small, OP_HS, OP_SMOOTH, fuse, out);
+    for (int l = 0; l < bottom; l++) {
+        smooth_ops(l, nu1, OP_HS, fuse, out);
         out.push_back({ OP_RESTRICT, l, 0 }); // with the coarse FAS right-hand side
     }
-    out.push_back({ OP_COARSE, L - 1, 0 });
-    for (int l = L - 2; l >= 0; l--) prolong_smooth_ops(l, nu2, small, OP_PROLONG, OP_HS, OP_SMOOTH, fuse, out);
+    out.push_back({ OP_COARSE, bottom, nu1 + MAX_SWEEPS * nu2 });
+    for (int l = bottom - 1; l >= 0; l--) prolong_smooth_ops(l, nu2, OP_PROLONG, OP_HS, fuse, out);
     out.push_back({ acc ? OP_NORMACC : OP_NORM, 0, 0 });
 }
 // one outer iteration of the mixed-precision step: an FP32 correction
 // V-cycle on J(w^) delta = r, w += delta in FP64, then the FP64 residual
 // (which also prepares the next cycle) and the pbar mean removal
-static void mixed_program(int L, int nu1, int nu2, int small, unsigned fuse, bool acc, std::vector<Op> &out)
+static void mixed_program(int bottom, int nu1, int nu2, unsigned fuse, bool acc, std::vector<Op> &out)
 {
-    for (int l = 0; l + 1 < L; l++) {
-        smooth_ops(l, nu1, small, OP_MXHS, OP_MXSMOOTH, fuse, out);
+    for (int l = 0; l < bottom; l++) {
+        smooth_ops(l, nu1, OP_MXHS, fuse, out);
         out.push_back({ OP_MXRESTRICT, l, 0 });
     }
-    out.push_back({ OP_MXCOARSE, L - 1, 0 });
-    for (int l = L - 2; l >= 0; l--)
-        prolong_smooth_ops(l, nu2, small, OP_MXPROLONG, OP_MXHS, OP_MXSMOOTH, fuse, out);
+    out.push_back({ OP_MXCOARSE, bottom, nu1 + MAX_SWEEPS * nu2 });
+    for (int l = bottom - 1; l >= 0; l--) prolong_smooth_ops(l, nu2, OP_MXPROLONG, OP_MXHS, fuse, out);
     out.push_back({ OP_MXUPDATE, 0, 0 });
     out.push_back({ acc ? OP_NORMACC : OP_NORM, 0, 0 });
 }
@@ -230,25 +218,32 @@ struct qnsch_ctx {
 
 static bool is_mixed(const qnsch_ctx *x) { return x->opt.precision == QNSCH_MIXED; }
 static void step_begin_program(const qnsch_ctx *x, std::vector<Op> &out) { begin_program(x->nlev, is_mixed(x), out); }
-// first level from which every coarser level fits in LDS for the
-// level-resident smoothing (nlev if none); lds_max is set at context creation
-static int small_level(const qnsch_ctx *x)
+// LDS of the kernel that runs the cycle from level l on (k_bottom, k_mx_bottom)
+static size_t bottom_lds(const qnsch_ctx *x, int l)
 {
-    int small = x->nlev;
-    for (int l = x->nlev - 1; l >= 1; l--) {
-        const int m1 = x->L[l].m1, m2 = x->L[l].m2;
-        const size_t b = is_mixed(x) ? mx_coarse_lds_floats(m1, m2) * sizeof(float)
-                                     : coarse_lds_doubles(m1, m2) * sizeof(double);
-        if (b > x->lds_max) break;
-        small = l;
-    }
-    return small;
+    size_t b = 0;
+    for (; l < x->nlev; l++)
+        b += is_mixed(x) ? bot_floats(x->L[l].m1, x->L[l].m2) * sizeof(float)
+                         : bot_doubles(x->L[l].m1, x->L[l].m2) * sizeof(double);
+    return b;
+}
+// the first level from which every level fits in the LDS of a workgroup
+// together (never the finest one, unless it is the coarsest too) and has at
+// most 512 cells of a colour; lds_max is set at context creation.  16 x 32 and
+// below in FP64: 148 KiB.  (The LDS is the tighter limit but for FP32 levels
+// of 24 x 48: 576 cells of a colour take three passes of a workgroup's lane
+// pairs per half-sweep, @@.)
+static int bottom_level(const qnsch_ctx *x)
+{
+    int l = x->nlev - 1;
+    while (l > 1 && bottom_lds(x, l - 1) <= x->lds_max && x->L[l - 1].m1 * x->L[l - 1].m2 <= 2 * BOT) l--;
+    return l;
 }
 // whether the opts give the levels a second set of cell unknowns (FP64) or
 // cell corrections (mixed precision)
 static bool two_sets(const qnsch_opts &o) { return o.blocking > 0; }
 // levels whose sweeps run fused (bit l): those smoothed by half-sweep
-// launches (below small) with a periodic axis at least TX + 3 (TY + 3) cells
+// launches (finer than the bottom levels) with a periodic axis at least TX + 3 (TY + 3) cells
 // long (the widened tile wraps once) and few enough tiles: coarse levels with
 // at most two tiles per compute unit; the finest level with at most one
 // (blocking 1), or two (blocking 2).  A fused sweep pays for its redundant red
@@ -264,8 +259,8 @@ static unsigned fused_levels(const qnsch_ctx *x)
 {
     if (!two_sets(x->opt)) return 0u;
     unsigned m = 0;
-    const int small = small_level(x);
-    for (int l = 0; l < small && l < x->nlev; l++) {
+    const int bottom = bottom_level(x);
+    for (int l = 0; l < bottom; l++) {
         const DLev &D = x->L[l];
         if ((x->g.bc_x == QNSCH_BC_PERIODIC && D.m1 < TX + 3) || (x->g.bc_y == QNSCH_BC_PERIODIC && D.m2 < TY + 3))
             continue;
@@ -284,8 +279,8 @@ static unsigned fused_levels(const qnsch_ctx *x)
 static void cycle_program(const qnsch_ctx *x, std::vector<Op> &out)
 {
     const bool rec = x->opt.accel > 0;
-    if (is_mixed(x)) mixed_program(x->nlev, x->opt.nu1, x->opt.nu2, small_level(x), fused_levels(x), rec, out);
-    else vcycle_program(x->nlev, x->opt.nu1, x->opt.nu2, small_level(x), fused_levels(x), rec, out);
+    if (is_mixed(x)) mixed_program(bottom_level(x), x->opt.nu1, x->opt.nu2, fused_levels(x), rec, out);
+    else vcycle_program(bottom_level(x), x->opt.nu1, x->opt.nu2, fused_levels(x), rec, out);
 }
 
 #define HIPCHK(ctx, x)                                                                        \
@@ -320,7 +315,7 @@ static int op_blocks(const qnsch_ctx *x, int kind, int l)
     case OP_HS: case OP_RESTRICT: case OP_NORM: case OP_NORM0: case OP_NORMACC: case OP_MXHS:
     case OP_MXRESTRICT: case OP_FUSED: case OP_MXFUSED:
         return tiles_x(D.m1) * tiles_y(D.m2);
-    case OP_COARSE: case OP_MXCOARSE: case OP_SMOOTH: case OP_MXSMOOTH: return 1;
+    case OP_COARSE: case OP_MXCOARSE: return 1;
     case OP_RN: case OP_MXRN: return (int)nblocks((size_t)x->L[l + 1].m1 * x->L[l + 1].m2);
     default: return (int)nblocks((size_t)D.m1 * D.m2);
     }
@@ -341,10 +336,7 @@ static void add_item(ItemList &W, const qnsch_ctx *x, int kind, int l)
     it.n = k + 1;
     it.start[k + 1] = W.blocks;
     if (l != 0) W.all_fine = false;
-    if (kind == OP_COARSE || kind == OP_SMOOTH)
-        W.lds = std::max(W.lds, coarse_lds_doubles(x->L[l].m1, x->L[l].m2) * sizeof(double));
-    if (kind == OP_MXCOARSE || kind == OP_MXSMOOTH)
-        W.lds = std::max(W.lds, mx_coarse_lds_floats(x->L[l].m1, x->L[l].m2) * sizeof(float));
+    if (kind == OP_COARSE || kind == OP_MXCOARSE) W.lds = std::max(W.lds, bottom_lds(x, l));
 }
 
 // finalize list: one workgroup per simulation, tx = number of partials
@@ -603,34 +595,15 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
         }
         case OP_RESTRICT: KLAUNCH_PJ(k_restrict, W, dim3(W.blocks), dim3(RBLK), 0, s); break;
         case OP_COARSE:
-        case OP_SMOOTH: {
-            int nmax = 0;
-            for (auto &pe : part) nmax = std::max(nmax, pe.first->L[pe.second].m1 * pe.first->L[pe.second].m2 / 2);
-            const unsigned th = (unsigned)(2 * nmax < 512 ? ((2 * nmax + 63) / 64) * 64 : 512);
-            // the coarsest level over-relaxes the velocity and pressure
-            // updates (the primitive box, the projection pressure step)
-            const bool coarsest = kind == OP_COARSE;
-            const int sweeps = coarsest ? x0->opt.nu_coarse : colour % PROLONG_FIRST;
-            const int prolong = coarsest ? 0 : colour / PROLONG_FIRST;
-            const double om = coarsest && !pj ? x0->opt.coarse_omega : omega;
-            const double pom = coarsest && pj ? x0->opt.coarse_omega : 1.0;
-            KLAUNCH_PJ(k_coarse_solve, W, dim3(W.blocks), dim3(th), W.lds, s, sweeps, om, pom, prolong);
+            KLAUNCH_PJ(k_bottom, W, dim3(W.blocks), dim3(BOT), W.lds, s, colour % MAX_SWEEPS, colour / MAX_SWEEPS,
+                       x0->opt.nu_coarse, omega, x0->opt.coarse_omega);
             break;
-        }
         case OP_PROLONG: KLAUNCH(k_prolong, W, dim3(W.blocks), dim3(BLK), 0, s); break;
         case OP_MXRESTRICT: KLAUNCH(k_mx_restrict, W, dim3(W.blocks), dim3(TBLK), 0, s); break;
         case OP_MXCOARSE:
-        case OP_MXSMOOTH: {
-            int nmax = 0;
-            for (auto &pe : part) nmax = std::max(nmax, pe.first->L[pe.second].m1 * pe.first->L[pe.second].m2 / 2);
-            const unsigned th = (unsigned)(2 * nmax < 512 ? ((2 * nmax + 63) / 64) * 64 : 512);
-            const bool coarsest = kind == OP_MXCOARSE;
-            const int sweeps = coarsest ? x0->opt.nu_coarse : colour % PROLONG_FIRST;
-            const int prolong = coarsest ? 0 : colour / PROLONG_FIRST;
-            const double om = coarsest ? x0->opt.coarse_omega : omega;
-            KLAUNCH(k_mx_coarse_solve, W, dim3(W.blocks), dim3(th), W.lds, s, sweeps, (float)om, prolong);
+            KLAUNCH(k_mx_bottom, W, dim3(W.blocks), dim3(BOT), W.lds, s, colour % MAX_SWEEPS, colour / MAX_SWEEPS,
+                    x0->opt.nu_coarse, (float)omega, (float)x0->opt.coarse_omega);
             break;
-        }
         case OP_MXPROLONG: KLAUNCH(k_mx_prolong, W, dim3(W.blocks), dim3(BLK), 0, s); break;
         case OP_MXUPDATE: KLAUNCH(k_mx_update, W, dim3(W.blocks), dim3(BLK), 0, s); break;
         case OP_MXRN: KLAUNCH(k_mx_restrict_n, W, dim3(W.blocks), dim3(BLK), 0, s); break;
@@ -841,7 +814,10 @@ static int level_count(const qnsch_grid *g)
             nl++;
     }
     if (nl > 16 || g->m1 % (1 << nl) != 0 || g->m2 % (1 << nl) != 0) return -1;
-    if (coarse_lds_doubles(g->m1 >> (nl - 1), g->m2 >> (nl - 1)) * sizeof(double) > 65536) return -1;
+    // (15 doubles per cell and 14 per element of its tile in 64 KiB bound the
+    // coarsest level)
+    const size_t c1 = g->m1 >> (nl - 1), c2 = g->m2 >> (nl - 1);
+    if ((15 * c1 * c2 + 14 * (c1 + 3) * (c2 + 3)) * sizeof(double) > 65536) return -1;
     return nl;
 }
 
@@ -1043,7 +1019,7 @@ static qnsch_params resolve_params(const qnsch_params &p)
 static int validate(const qnsch_grid *g, const qnsch_params *p, const qnsch_opts *o)
 {
     if (validate_grid_params(g, p)) return QNSCH_EINVAL;
-    if (o && (o->nu1 < 0 || o->nu2 < 0 || o->nu1 >= PROLONG_FIRST || o->nu2 >= PROLONG_FIRST || o->nu_coarse < 0
+    if (o && (o->nu1 < 0 || o->nu2 < 0 || o->nu1 >= MAX_SWEEPS || o->nu2 >= MAX_SWEEPS || o->nu_coarse < 0
               || o->max_vcycles < 0
               || (o->precision != QNSCH_FP64 && o->precision != QNSCH_MIXED)
               || (o->smoother != QNSCH_SMOOTH_SEGREGATED && o->smoother != QNSCH_SMOOTH_COUPLED)
@@ -1101,55 +1077,15 @@ static size_t device_lds_max()
     int v = 0;
     size_t r = 65536;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 65536
-        && hipFuncSetAttribute((const void *)k_coarse_solve_n, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
-        && hipFuncSetAttribute((const void *)k_coarse_solve<false>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
-        && hipFuncSetAttribute((const void *)k_coarse_solve<true>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
-        && hipFuncSetAttribute((const void *)k_mx_coarse_solve_n, hipFuncAttributeMaxDynamicSharedMemorySize, v)
-               == hipSuccess
-        && hipFuncSetAttribute((const void *)k_mx_coarse_solve, hipFuncAttributeMaxDynamicSharedMemorySize, v)
-               == hipSuccess)
+        && hipFuncSetAttribute((const void *)k_bottom_n, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
+        && hipFuncSetAttribute((const void *)k_bottom<false>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
+        && hipFuncSetAttribute((const void *)k_bottom<true>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
+        && hipFuncSetAttribute((const void *)k_mx_bottom_n, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
+        && hipFuncSetAttribute((const void *)k_mx_bottom, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess)
         r = (size_t)v;
     (void)hipGetLastError();
     cache[dev] = r;
     return r;
-}
-
-// the workgroup size as block_threads() reads it, written by the first thread
-// of a one-workgroup launch of BLK threads, for group_size_check below
-static __device__ int g_group_size;
-__global__ __launch_bounds__(BLK) void k_group_size_check()
-{
-    if (threadIdx.x == 0) g_group_size = block_threads();
-}
-
-// The kernels read their workgroup size from a fixed place of the dispatch's
-// implicit kernel arguments (block_threads: code object versions 5 and 6); a
-// build for another layout must not run.  One check per device, before the
-// first kernel there: QNSCH_OK, or QNSCH_EDEVICE with the reason in err.
-static int group_size_check(std::string &err)
-{
-    static std::mutex mu;
-    static int state[64] = {}; // 0 unchecked, 1 passed, -1 failed
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
-        err = "no current HIP device";
-        return QNSCH_EDEVICE;
-    }
-    std::lock_guard<std::mutex> lock(mu);
-    if (state[dev] == 0) {
-        hipLaunchKernelGGL(k_group_size_check, dim3(1), dim3(BLK), 0, nullptr);
-        int h = 0;
-        const hipError_t e = hipMemcpyFromSymbol(&h, HIP_SYMBOL(g_group_size), sizeof(h));
-        state[dev] = (e == hipSuccess && h == BLK) ? 1 : -1;
-        if (state[dev] < 0) {
-            char b[160];
-            snprintf(b, sizeof(b), "workgroup size check: %d read from the dispatch for %d threads (%s)", h, BLK,
-                     hipGetErrorString(e));
-            err = b;
-        }
-    }
-    if (state[dev] < 0 && err.empty()) err = "workgroup size check failed on this device";
-    return state[dev] > 0 ? QNSCH_OK : QNSCH_EDEVICE;
 }
 
 static int ctx_init(qnsch_ctx *x, const qnsch_grid *g, const qnsch_params *p, const qnsch_opts *o, void *stream)
@@ -1167,10 +1103,6 @@ static int ctx_init(qnsch_ctx *x, const qnsch_grid *g, const qnsch_params *p, co
     if (o) x->opt = *o;
     resolve_opts(x->opt, x->nlev);
     x->lds_max = device_lds_max();
-    if ((rc = group_size_check(x->err))) {
-        fprintf(stderr, "qnsch: %s\n", x->err.c_str());
-        return rc;
-    }
     {
         int dev = 0, v = 0;
         if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess
@@ -1201,11 +1133,12 @@ static int ctx_init(qnsch_ctx *x, const qnsch_grid *g, const qnsch_params *p, co
         DLev &D = x->L[l];
         D.m1 = g->m1 >> l;
         D.m2 = g->m2 >> l;
-        D.pitch = D.m1;
+        D.pitch = D.m1; // rows follow each other (put, get copy a field at once)
         D.h = hx * (double)(1 << l);
         Desc &d = x->hd[l];
         d.m1 = D.m1; d.m2 = D.m2; d.pitch = D.pitch; d.bcx = g->bc_x; d.bcy = g->bc_y;
         d.h = D.h; d.inv_h = 1.0 / D.h;
+        d.depth = x->nlev - l;
     }
     set_params(x, p);
     x->hd[0].red_host = x->red_host;
@@ -1232,40 +1165,38 @@ int qnsch_create(const qnsch_grid *g, const qnsch_params *p, const qnsch_opts *o
     return QNSCH_OK;
 }
 
-// host (m1*m2, packed) <-> device (pitch) copies
+// host <-> device copies of a field of the finest level, whose rows follow
+// each other without padding.  (One copy per field: as a pitched copy of
+// pageable memory a field goes row by row, ~9 us each; 256 x 512: set_state
+// 24.3 -> 0.08 ms, get_state 18.2 -> 0.43, MI355X host.)
 static int put(qnsch_ctx *x, double *dst, const double *src)
 {
-    DLev &D = x->L[0];
-    HIPCHK(x, hipMemcpy2DAsync(dst, D.pitch * sizeof(double), src, D.m1 * sizeof(double), D.m1 * sizeof(double), D.m2,
-                               hipMemcpyHostToDevice, x->s));
+    HIPCHK(x, hipMemcpyAsync(dst, src, x->L[0].n() * sizeof(double), hipMemcpyHostToDevice, x->s));
     return QNSCH_OK;
 }
 static int get(qnsch_ctx *x, double *dst, const double *src)
 {
-    DLev &D = x->L[0];
-    HIPCHK(x, hipMemcpy2DAsync(dst, D.m1 * sizeof(double), src, D.pitch * sizeof(double), D.m1 * sizeof(double), D.m2,
-                               hipMemcpyDeviceToHost, x->s));
+    HIPCHK(x, hipMemcpyAsync(dst, src, x->L[0].n() * sizeof(double), hipMemcpyDeviceToHost, x->s));
     return QNSCH_OK;
 }
 
 static int upload(qnsch_ctx *x, const double *c, const double *mu, const double *p, const double *u, const double *v)
 {
-    DLev &D = x->L[0];
-    Desc &d = x->hd[0];
-    const size_t n = (size_t)D.m1 * D.m2;
-    std::vector<double> z(n, 0.0), uu(n, 0.0), vv(n, 0.0);
-    if (u) memcpy(uu.data(), u, n * sizeof(double));
-    if (v) memcpy(vv.data(), v, n * sizeof(double));
-    if (x->g.bc_x == QNSCH_BC_WALL)
-        for (int j = 0; j < D.m2; j++) uu[(size_t)j * D.m1] = 0.0;
-    if (x->g.bc_y == QNSCH_BC_WALL)
-        for (int i = 0; i < D.m1; i++) vv[i] = 0.0;
+    const DLev &D = x->L[0];
+    const Desc &d = x->hd[0];
+    double *const dst[5] = { d.c, d.mu, d.p, d.ub[D.cur], d.vb[D.cur] };
+    const double *const src[5] = { c, mu, p, u, v };
     int rc;
-    if ((rc = put(x, d.c, c))) return rc;
-    if ((rc = put(x, d.mu, mu ? mu : z.data()))) return rc;
-    if ((rc = put(x, d.p, p ? p : z.data()))) return rc;
-    if ((rc = put(x, d.ub[D.cur], uu.data()))) return rc;
-    if ((rc = put(x, d.vb[D.cur], vv.data()))) return rc;
+    for (int f = 0; f < 5; f++) {
+        if (!src[f]) HIPCHK(x, hipMemsetAsync(dst[f], 0, D.n() * sizeof(double), x->s));
+        else if ((rc = put(x, dst[f], src[f]))) return rc;
+    }
+    // faces on walls are no unknowns
+    if ((u && x->g.bc_x == QNSCH_BC_WALL) || (v && x->g.bc_y == QNSCH_BC_WALL)) {
+        const int n = std::max(D.m1, D.m2);
+        hipLaunchKernelGGL(k_wall_faces, dim3(nblocks(n)), dim3(BLK), 0, x->s, (const Desc *)x->dd, D.cur);
+        HIPCHK(x, hipGetLastError());
+    }
     HIPCHK(x, hipStreamSynchronize(x->s));
     return QNSCH_OK;
 }
@@ -1406,8 +1337,7 @@ int qnsch_lin_apply(qnsch_ctx *x, const double *dw, double *out)
     float *dst[5] = { d.dc, d.dmu, d.dp, d.dub[D.cur], d.dvb[D.cur] };
     for (int q = 0; q < 5; q++) {
         for (size_t k = 0; k < n; k++) f[k] = (float)dw[q * n + k];
-        HIPCHK(x, hipMemcpy2DAsync(dst[q], D.pitch * sizeof(float), f.data(), D.m1 * sizeof(float),
-                                   D.m1 * sizeof(float), D.m2, hipMemcpyHostToDevice, x->s));
+        HIPCHK(x, hipMemcpyAsync(dst[q], f.data(), n * sizeof(float), hipMemcpyHostToDevice, x->s));
         HIPCHK(x, hipStreamSynchronize(x->s)); // f is reused
     }
     ItemList W;
@@ -1805,15 +1735,6 @@ int qnsch_residual_noalloc(const qnsch_grid *g, const qnsch_params *prm, double 
     }
     char *base = noalloc_scratch(noalloc_err);
     if (!base) return QNSCH_EDEVICE;
-    {
-        // the workgroup-size check (a launch and a synchronous copy), unless
-        // the stream is being captured: then it waits for a call outside a
-        // capture or a context creation on this device
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing((hipStream_t)stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone
-            && group_size_check(noalloc_err))
-            return QNSCH_EDEVICE;
-    }
     hipStream_t s = (hipStream_t)stream;
     const int tx = tiles_x(g->m1), ty = tiles_y(g->m2);
     Desc d;
@@ -2018,8 +1939,7 @@ static int admit(qnsch_server *S, Req *r)
     if (!rc) {
         const DLev &D = x->L[0];
         memcpy(x->stage, r->c0.data(), (size_t)D.m1 * D.m2 * sizeof(double));
-        if (hipMemcpy2DAsync(x->hd[0].c, D.pitch * sizeof(double), x->stage, D.m1 * sizeof(double),
-                             D.m1 * sizeof(double), D.m2, hipMemcpyHostToDevice, st) != hipSuccess)
+        if (hipMemcpyAsync(x->hd[0].c, x->stage, D.n() * sizeof(double), hipMemcpyHostToDevice, st) != hipSuccess)
             rc = QNSCH_EDEVICE;
     }
     r->x = x;
@@ -2042,8 +1962,7 @@ static void begin_finish(qnsch_server *S, Req *r, int status)
     const double *src[5] = { d.c, d.mu, d.p, d.ub[D.cur], d.vb[D.cur] };
     bool ok = true;
     for (int q = 0; q < 5; q++)
-        ok = ok && hipMemcpy2DAsync(x->stage + q * n, D.m1 * sizeof(double), src[q], D.pitch * sizeof(double),
-                                    D.m1 * sizeof(double), D.m2, hipMemcpyDeviceToHost, x->s) == hipSuccess;
+        ok = ok && hipMemcpyAsync(x->stage + q * n, src[q], n * sizeof(double), hipMemcpyDeviceToHost, x->s) == hipSuccess;
     ok = ok && hipEventRecord(x->ev, x->s) == hipSuccess;
     if (!ok && r->status == QNSCH_OK) r->status = QNSCH_EDEVICE;
     r->wait = W_DOWNLOAD;

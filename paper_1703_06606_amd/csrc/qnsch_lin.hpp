@@ -121,33 +121,6 @@ template <int NE, int NT> __device__ __forceinline__ void ltile_load(const PhysF
     }
 }
 
-// reload of the corrections into a tile filled before, after a half-sweep of
-// the given colour, with the sources computed once (tile_map_build): all face
-// corrections, and the cell corrections and the density change of the
-// elements whose source cell has that colour (the linearisation point and
-// time-n fields stay)
-__device__ __forceinline__ void ltile_refresh_map(const PhysF &P, const LView &L, const TileF &T, const int *map,
-                                                  int colour)
-{
-    const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
-        // the map entry, then every value the element may take, before any
-        // use (as tile_refresh_map)
-        const int q = map[4 * e], qu = map[4 * e + 1], qv = map[4 * e + 2], fl = map[4 * e + 3];
-        float *s = T.s + e * L_ES;
-        const float du = L.du[qu], dv = L.dv[qv], dc = L.dc[q], dmu = L.dmu[q], dp = L.dp[q], rs = s[T_RS];
-        __builtin_amdgcn_sched_barrier(0);
-        if (fl & 16) continue;
-        s[T_U] = signed_val((fl & 3) - 1, du);
-        s[T_V] = signed_val(((fl >> 2) & 3) - 1, dv);
-        if (((fl >> 5) & 1) != colour) continue;
-        s[L_DC] = dc;
-        s[T_MU] = dmu;
-        s[T_P] = dp;
-        s[L_DRS] = -P.alpha * rs * rs * dc;
-    }
-}
-
 // one axis of the linearised cell equations at element s: as axis_cell on the
 // corrections, with lr the linearised gradient-energy and capillary terms of
 // the chemical row beside the pointwise ones (across a wall the mirrored
@@ -227,12 +200,12 @@ __device__ __forceinline__ LCellEq lcell_eq(const Kon<float> &K, const float *s,
 // With TO set, as relax_cell: the cell at tile position (ti, tj), results
 // kept in the tile (dc, dmu, dp and the density change in place, the face
 // corrections in the fields T_U2, T_V2).
-template <bool TO, int AS>
+template <int TO, int AS>
 __device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K, const LView &L, const TileF &T,
                                             float *dunew, float *dvnew, int i, int j, int ti, int tj, int hlf,
-                                            float omega)
+                                            float omega, int slot = 0)
 {
-    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf);
+    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
     const Ax &a = b.a;
     float *const e = T.at(ti, tj);
     const bool cpl = P.coupled;
@@ -291,8 +264,8 @@ __device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K,
     const float nhi = P1[a.fn] + omega * ((X.xb[1] + t * X.xs[1]) - dc * X.xq[1]);
     const float np = p0 + omega * dp;
     if (TO) {
-        if (b.hlo) e[T_U2 + hlf] = nlo;
-        if (b.hhi) e[a.dn + T_U2 + hlf] = nhi;
+        if (b.hlo) e[a.fo] = nlo;
+        if (b.hhi) e[b.hi<TO>() + a.fo] = nhi;
         if (hlf == 0) {
             e[T_P] = np;
             if (cpl) {
@@ -321,13 +294,14 @@ __device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K,
 struct ResidF {
     float c, mu, p, u, v;
 };
+template <int AS = 1>
 __device__ __forceinline__ ResidF lresid_cell(const Kon<float> &K, const LView &L, const TileF &T, int i, int j)
 {
     const size_t k = (size_t)j * L.pitch + i;
     const float *e = T.at(i, j);
     const Ax ax = make_ax(L, T, i, j, 0), ay = make_ax(L, T, i, j, 1);
-    const ResidF f = { lda<1>(L.rc, k), lda<1>(L.rmu, k), lda<1>(L.rp, k), lda<1>(L.ru, k), lda<1>(L.rv, k) };
-    const float muh = lda<1>(L.mu, k), uh = lda<1>(L.u, k), vh = lda<1>(L.v, k);
+    const ResidF f = { lda<AS>(L.rc, k), lda<AS>(L.rmu, k), lda<AS>(L.rp, k), lda<AS>(L.ru, k), lda<AS>(L.rv, k) };
+    const float muh = lda<AS>(L.mu, k), uh = lda<AS>(L.u, k), vh = lda<AS>(L.v, k);
     float r, drs;
     lcell_r(K, e, r, drs);
     const CellSum<float> x = laxis_cell(K, e, ax, r, drs) + laxis_cell(K, e, ay, r, drs);

@@ -48,7 +48,7 @@ template <typename IT> __device__ __forceinline__ void k_mx_halfsweep_body(const
     const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
     const int j = T.j0 + lj;
     const int i = T.i0 + 2 * kk + ((j + colour) & 1);
-    if (i < L.m1 && j < L.m2) lrelax_cell<false, 1>(d.Pf, d.Kf, L, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
+    if (i < L.m1 && j < L.m2) lrelax_cell<0, 1>(d.Pf, d.Kf, L, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
 }
 QN_KERNEL(k_mx_halfsweep, HS_ATTR, (int colour, float omega), (colour, omega))
 // finest-level launches under their own name (profiles)
@@ -143,7 +143,7 @@ template <typename IT> __device__ __forceinline__ void k_mx_fused_body(const IT 
         const bool in = lj < TY + 4 && (L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2));
         if (in) {
             const int i = L.bcx ? wrapi(ti, L.m1) : ti, j = L.bcy ? wrapi(tj, L.m2) : tj;
-            lrelax_cell<true, 1>(d.Pf, d.Kf, L, T, nullptr, nullptr, i, j, ti, tj, hlf, omega);
+            lrelax_cell<1, 1>(d.Pf, d.Kf, L, T, nullptr, nullptr, i, j, ti, tj, hlf, omega);
         }
     }
     __syncthreads();
@@ -153,7 +153,7 @@ template <typename IT> __device__ __forceinline__ void k_mx_fused_body(const IT 
         const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
         const int j = T0.j0 + lj;
         const int i = T0.i0 + 2 * kk + ((j + 1) & 1);
-        if (i < L.m1 && j < L.m2) lrelax_cell<false, 1>(d.Pf, d.Kf, O, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
+        if (i < L.m1 && j < L.m2) lrelax_cell<0, 1>(d.Pf, d.Kf, O, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
     } else {
         const int q = pr - TBLK / 2;
         const int lj = q / (TX / 2), kk = q - lj * (TX / 2);
@@ -305,105 +305,234 @@ template <typename IT> __device__ __forceinline__ void k_mx_prolong_body(const I
 }
 QN_KERNEL(k_mx_prolong, __launch_bounds__(BLK), (), ())
 
-// LDS floats of the coarsest-level correction solve: 19 level arrays + a tile
-// + the tile's source map (4 ints per element)
-__host__ __device__ inline size_t mx_coarse_lds_floats(int m1, int m2)
+// The bottom of the correction cycle, as k_bottom: a level and every coarser
+// one resident in LDS in one workgroup per item (the correction and the
+// linearisation point of the coarser levels never leave it).  LDS of a level:
+// its tile, the right-hand sides and the linearisation point's mubar, u, v,
+// the images.
+struct BotLevF {
+    float *r, *x; // 5 and 3 fields of m1*m2
+    Image *ring;
+    TileF T;
+    int m1, m2;
+};
+__host__ __device__ inline size_t bot_floats(int m1, int m2)
 {
-    return (size_t)19 * m1 * m2 + (size_t)(L_ES + 4) * (m1 + 3) * (m2 + 3) + 4;
+    return bot_tile(m1, m2, L_ES) + (size_t)8 * m1 * m2 + 4 * (size_t)ring_size(m1, m2);
 }
-
-// the tile of a level whose arrays are in LDS
-__device__ __forceinline__ void ltile_fill(const PhysF &P, const LView &L, const TileF &T)
+__device__ __forceinline__ BotLevF bot_lev(float *sm, int m1, int m2, int l)
 {
-    const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
-        const int b = e / T.W, a = e - b * T.W;
-        const TileSrc q = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, T.i0 - 1 + a, T.j0 - 1 + b);
-        const float v[9] = { L.c[q.c], L.dc[q.c], L.dmu[q.c], L.dp[q.c], L.du[q.u], L.dv[q.v], L.cn[q.c], L.un[q.u],
-                             L.vn[q.v] };
-        if (q.sc == 0) tile_zero(T, e);
-        else ltile_put(P, T.s + e * L_ES, q.su, q.sv, v);
+    for (; l > 0; l--) {
+        sm += bot_floats(m1, m2);
+        m1 >>= 1;
+        m2 >>= 1;
+    }
+    BotLevF B;
+    B.m1 = m1; B.m2 = m2;
+    B.T.s = sm; B.T.i0 = 0; B.T.j0 = 0; B.T.W = m1 + 3; B.T.H = m2 + 3; B.T.S = bot_stride(m1);
+    B.r = sm + bot_tile(m1, m2, L_ES);
+    B.x = B.r + 5 * m1 * m2;
+    B.ring = (Image *)(B.x + 3 * m1 * m2);
+    return B;
+}
+__device__ __forceinline__ LView bot_view(const BotLevF &B, const Desc &d)
+{
+    const int n = B.m1 * B.m2;
+    LView L = {};
+    L.m1 = B.m1; L.m2 = B.m2; L.pitch = B.m1;
+    L.bcx = d.bcx; L.bcy = d.bcy;
+    L.mu = B.x; L.u = B.x + n; L.v = B.x + 2 * n;
+    L.rc = B.r; L.rmu = B.r + n; L.rp = B.r + 2 * n; L.ru = B.r + 3 * n; L.rv = B.r + 4 * n;
+    return L;
+}
+__device__ __forceinline__ void bot_images(const BotLevF &B, int slot)
+{
+    const int n = ring_size(B.m1, B.m2), fu = T_U + slot * (T_U2 - T_U);
+    for (int k = threadIdx.x; k < n; k += BOT) {
+        const Image g = B.ring[k];
+        const float *s = B.T.s + g.c * L_ES;
+        const float dc = s[L_DC], mu = s[T_MU], p = s[T_P], drs = s[L_DRS];
+        const float u = B.T.s[(g.u >> 2) * L_ES + fu], v = B.T.s[(g.v >> 2) * L_ES + fu + 1];
+        float *t = B.T.s + g.e * L_ES;
+        t[L_DC] = dc;
+        t[T_MU] = mu;
+        t[T_P] = p;
+        t[L_DRS] = drs;
+        t[fu] = signed_val((g.u & 3) - 1, u);
+        t[fu + 1] = signed_val((g.v & 3) - 1, v);
     }
 }
-
-// all correction sweeps of a level in one workgroup per item, the level
-// resident in LDS (the coarsest level, and the smoothing of small coarse
-// levels); an even number of half-sweeps keeps the result in buffer par
-template <typename IT> __device__ __forceinline__ void k_mx_coarse_solve_body(const IT &it, int sweeps, float omega, int prolong)
+__device__ __forceinline__ void bot_smooth(const PhysF &P, const Desc &d, const BotLevF &B, int sweeps, float omega)
+{
+    const Kon<float> K = d.Kf;
+    const LView L = bot_view(B, d);
+    const int half = B.m1 >> 1;
+    for (int s = 0; s < 2 * sweeps; s++) {
+        const int colour = s & 1;
+        for (int t = threadIdx.x; t < 2 * half * B.m2; t += BOT) {
+            const int pr = t >> 1, j = pr / half;
+            const int i = 2 * (pr - j * half) + ((j + colour) & 1);
+            lrelax_cell<2, 3>(P, K, L, B.T, nullptr, nullptr, i, j, i, j, t & 1, omega, colour);
+        }
+        __syncthreads();
+        bot_images(B, colour ^ 1);
+        __syncthreads();
+    }
+}
+// residual of level A and the linearisation point restricted to the next level
+// C, whose correction starts at zero (its time-n fields are in the tile)
+__device__ __forceinline__ void bot_restrict(const PhysF &P, const Desc &d, const BotLevF &A, const BotLevF &C)
+{
+    const int nc = C.m1 * C.m2, na = A.m1 * A.m2;
+    const Kon<float> K = d.Kf;
+    const LView L = bot_view(A, d);
+    for (int t = threadIdx.x; t < 4 * nc; t += BOT) {
+        const int cc = t >> 2, ch = t & 3;
+        const int J = cc / C.m1, I = cc - J * C.m1, i = 2 * I + (ch & 1), j = 2 * J + (ch >> 1), w = j * A.m1 + i;
+        const ResidF r = lresid_cell<3>(K, L, A.T, i, j);
+        const bool wu = (ch & 1) == 0, wv = (ch >> 1) == 0; // faces of the coarse cell
+        const float f[5] = { 0.25f * quad_sum(r.c), 0.25f * quad_sum(r.mu), 0.25f * quad_sum(r.p),
+                             0.5f * quad_sum(wu ? r.u : 0.0f), 0.5f * quad_sum(wv ? r.v : 0.0f) };
+        const float x[3] = { 0.25f * quad_sum(A.x[w]), 0.5f * quad_sum(wu ? A.x[na + w] : 0.0f),
+                             0.5f * quad_sum(wv ? A.x[2 * na + w] : 0.0f) };
+        const float c = 0.25f * quad_sum(A.T.at(i, j)[T_C]);
+        if (ch == 0) {
+            float *o = C.T.at(I, J);
+            o[T_C] = c;
+            o[T_RS] = rhof(P, c);
+            o[T_MU] = o[T_P] = o[L_DC] = o[L_DRS] = 0.0f;
+            o[T_U] = o[T_U2] = o[T_V] = o[T_V2] = 0.0f;
+#pragma unroll
+            for (int q = 0; q < 5; q++) C.r[q * nc + cc] = f[q];
+#pragma unroll
+            for (int q = 0; q < 3; q++) C.x[q * nc + cc] = x[q];
+        }
+    }
+    __syncthreads();
+    // images: also of the linearisation point's c and rho, once
+    const int n = ring_size(C.m1, C.m2);
+    for (int k = threadIdx.x; k < n; k += BOT) {
+        const Image g = C.ring[k];
+        const float *s = C.T.s + g.c * L_ES;
+        float *t = C.T.s + g.e * L_ES;
+        t[T_C] = s[T_C];
+        t[T_RS] = s[T_RS];
+    }
+    bot_images(C, 0);
+    __syncthreads();
+}
+// delta_A += P delta_C (k_mx_prolong's arithmetic)
+__device__ __forceinline__ void bot_prolong(const PhysF &P, const Desc &d, const BotLevF &A, const BotLevF &C)
+{
+    const int na = A.m1 * A.m2;
+    const bool bx = d.bcx, by = d.bcy;
+    for (int t = threadIdx.x; t < na; t += BOT) {
+        const int j = t / A.m1, i = t - j * A.m1, I = i >> 1, J = j >> 1;
+        const float *s = C.T.at(I, J);
+        float du = s[T_U], dv = s[T_V];
+        if (i & 1) {
+            const bool in = I + 1 < C.m1;
+            const float e = in || bx ? C.T.at(in ? I + 1 : 0, J)[T_U] : 0.0f;
+            du = 0.5f * (du + e);
+        }
+        if (j & 1) {
+            const bool in = J + 1 < C.m2;
+            const float e = in || by ? C.T.at(I, in ? J + 1 : 0)[T_V] : 0.0f;
+            dv = 0.5f * (dv + e);
+        }
+        float *o = A.T.at(i, j);
+        const float dc = o[L_DC] + s[L_DC], rs = o[T_RS];
+        o[L_DC] = dc;
+        o[L_DRS] = -P.alpha * rs * rs * dc;
+        o[T_MU] += s[T_MU];
+        o[T_P] += s[T_P];
+        if (bx || i >= 1) o[T_U] += du;
+        if (by || j >= 1) o[T_V] += dv;
+    }
+    __syncthreads();
+    bot_images(A, 0);
+    __syncthreads();
+}
+template <typename IT>
+__device__ __forceinline__ void k_mx_bottom_body(const IT &it, int nu1, int nu2, int nuc, float omega, float comega)
 {
     extern __shared__ __attribute__((aligned(16))) float smf[];
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
-    const int par = it_par(it, k);
+    const PhysF P = d.Pf;
+    const int par = it_par(it, k), m1 = d.m1, m2 = d.m2, depth = d.depth;
     const LView L = lview_of(d, par);
-    float *ua = d.dub[par], *va = d.dvb[par];
-    const int m1 = L.m1, m2 = L.m2, n = m1 * m2;
-    float *hxc = smf, *hxmu = smf + n, *hxu = smf + 2 * n, *hxv = smf + 3 * n, *hdc = smf + 4 * n,
-          *hdmu = smf + 5 * n, *hdp = smf + 6 * n, *uA = smf + 7 * n, *vA = smf + 8 * n, *uB = smf + 9 * n,
-          *vB = smf + 10 * n, *hcn = smf + 11 * n, *hun = smf + 12 * n, *hvn = smf + 13 * n, *hr = smf + 14 * n;
-    PSrcF ps = {};
-    if (prolong) ps = psrcf_of(d, &d + 1, it_cpar(it, k));
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
-        const int j = e / m1, i = e - j * m1;
-        const size_t q = (size_t)j * L.pitch + i;
-        // every load of the element before any use
-        const float xc = lda<1>(L.c, q), xmu = lda<1>(L.mu, q), xu = lda<1>(L.u, q), xv = lda<1>(L.v, q);
-        float dc = lda<1>(L.dc, q), dmu = lda<1>(L.dmu, q), dp = lda<1>(L.dp, q), du = lda<1>(ua, q),
-              dv = lda<1>(va, q);
-        const float cn = lda<1>(L.cn, q), un = lda<1>(L.un, q), vn = lda<1>(L.vn, q);
-        const float r0 = lda<1>(L.rc, q), r1 = lda<1>(L.rmu, q), r2 = lda<1>(L.rp, q), r3 = lda<1>(L.ru, q),
-                    r4 = lda<1>(L.rv, q);
-        PRawF raw = {};
-        if (prolong) raw = mx_prolong_load(ps, i, j);
-        __builtin_amdgcn_sched_barrier(0);
-        if (prolong) {
-            float c, mu, p, pu, pv;
-            bool hu, hv;
-            mx_prolong_apply(ps, raw, i, j, c, mu, p, pu, pv, hu, hv);
-            dc += c; dmu += mu; dp += p;
-            if (hu) du += pu;
-            if (hv) dv += pv;
+    float *const ua = d.dub[par], *const va = d.dvb[par];
+    {
+        const BotLevF B = bot_lev(smf, m1, m2, 0);
+        const int n = m1 * m2;
+        for (int e = threadIdx.x; e < B.T.W * B.T.H; e += BOT) {
+            const int b = e / B.T.W, a = e - b * B.T.W, i = a - 1, j = b - 1;
+            const TileSrc q = tile_src(m1, m2, L.pitch, L.bcx, L.bcy, i, j);
+            const bool cell = i >= 0 && i < m1 && j >= 0 && j < m2;
+            const float v[9] = { lda<1>(L.c, q.c), lda<1>(L.dc, q.c), lda<1>(L.dmu, q.c), lda<1>(L.dp, q.c),
+                                 lda<1>(L.du, q.u), lda<1>(L.dv, q.v), lda<1>(L.cn, q.c), lda<1>(L.un, q.u),
+                                 lda<1>(L.vn, q.v) };
+            float f[8] = {};
+            if (cell) {
+                f[0] = lda<1>(L.rc, q.c); f[1] = lda<1>(L.rmu, q.c); f[2] = lda<1>(L.rp, q.c);
+                f[3] = lda<1>(L.ru, q.c); f[4] = lda<1>(L.rv, q.c);
+                f[5] = lda<1>(L.mu, q.c); f[6] = lda<1>(L.u, q.c); f[7] = lda<1>(L.v, q.c);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            float *t = B.T.s + (b * B.T.S + a) * L_ES;
+            ltile_put(P, t, q.su, q.sv, v);
+            t[T_U2] = t[T_U];
+            t[T_V2] = t[T_V];
+            if (cell)
+#pragma unroll
+                for (int g = 0; g < 8; g++) B.r[g * n + j * m1 + i] = f[g]; // r, then x
         }
-        hxc[e] = xc; hxmu[e] = xmu; hxu[e] = xu; hxv[e] = xv;
-        hdc[e] = dc; hdmu[e] = dmu; hdp[e] = dp; uA[e] = du; vA[e] = dv;
-        hcn[e] = cn; hun[e] = un; hvn[e] = vn;
-        hr[e] = r0; hr[n + e] = r1; hr[2 * n + e] = r2; hr[3 * n + e] = r3;
-        hr[4 * n + e] = r4;
+        ring_build(B.T, m1, m2, L.bcx, L.bcy, B.ring, threadIdx.x, BOT);
+    }
+    for (int l = 1; l < depth; l++) {
+        const BotLevF B = bot_lev(smf, m1, m2, l);
+        const Desc &c = (&d)[l];
+        const float *const cn = c.cnf, *const un = c.unf, *const vn = c.vnf;
+        for (int e = threadIdx.x; e < B.T.W * B.T.H; e += BOT) {
+            const int b = e / B.T.W, a = e - b * B.T.W;
+            const TileSrc q = tile_src(B.m1, B.m2, B.m1, L.bcx, L.bcy, a - 1, b - 1);
+            const float n = lda<1>(cn, q.c), u = lda<1>(un, q.u), v = lda<1>(vn, q.v);
+            float *t = B.T.s + (b * B.T.S + a) * L_ES;
+            t[T_CN] = n;
+            t[T_RN] = rhof(P, n);
+            t[T_MV] = viscf(P, n);
+            t[T_MOB] = mobf(P, n);
+            t[T_UN] = signed_val(q.su, u);
+            t[T_VN] = signed_val(q.sv, v);
+        }
+        ring_build(B.T, B.m1, B.m2, L.bcx, L.bcy, B.ring, threadIdx.x, BOT);
     }
     __syncthreads();
-    LView H = L;
-    H.c = hxc; H.mu = hxmu; H.u = hxu; H.v = hxv; H.dc = hdc; H.dmu = hdmu; H.dp = hdp;
-    H.cn = hcn; H.un = hun; H.vn = hvn;
-    H.rc = hr; H.rmu = hr + n; H.rp = hr + 2 * n; H.ru = hr + 3 * n; H.rv = hr + 4 * n;
-    H.pitch = m1;
-    TileF T;
-    T.s = smf + ((19 * n + 3) & ~3); T.i0 = 0; T.j0 = 0; T.W = T.S = m1 + 3; T.H = m2 + 3;
-    int *map = (int *)(T.s + (size_t)L_ES * T.W * T.H);
-    tile_map_build(H, T, map);
-    const int half = m1 >> 1;
-    for (int s = 0; s < 2 * sweeps; s++) {
-        const int colour = s & 1;
-        float *uw, *vw;
-        if (s & 1) { H.du = uB; H.dv = vB; uw = uA; vw = vA; }
-        else { H.du = uA; H.dv = vA; uw = uB; vw = vB; }
-        if (s == 0) ltile_fill(d.Pf, H, T);
-        else ltile_refresh_map(d.Pf, H, T, map, colour ^ 1);
-        __syncthreads();
-        for (int t = threadIdx.x; t < 2 * half * m2; t += block_threads()) {
-            const int pr = t >> 1;
-            const int j = pr / half;
-            const int i = 2 * (pr - j * half) + ((j + colour) & 1);
-            lrelax_cell<false, 3>(d.Pf, d.Kf, H, T, uw, vw, i, j, i, j, t & 1, omega);
-        }
-        __syncthreads();
+    for (int l = 0; l + 1 < depth; l++) {
+        const BotLevF A = bot_lev(smf, m1, m2, l), C = bot_lev(smf, m1, m2, l + 1);
+        bot_smooth(P, (&d)[l], A, nu1, omega);
+        bot_restrict(P, (&d)[l], A, C);
     }
-    for (int e = threadIdx.x; e < n; e += block_threads()) {
+    bot_smooth(P, (&d)[depth - 1], bot_lev(smf, m1, m2, depth - 1), nuc, comega);
+    for (int l = depth - 2; l >= 0; l--) {
+        const BotLevF A = bot_lev(smf, m1, m2, l), C = bot_lev(smf, m1, m2, l + 1);
+        bot_prolong(P, d, A, C);
+        bot_smooth(P, (&d)[l], A, nu2, omega);
+    }
+    const BotLevF B = bot_lev(smf, m1, m2, 0);
+    for (int e = threadIdx.x; e < m1 * m2; e += BOT) {
         const int j = e / m1, i = e - j * m1;
         const size_t q = (size_t)j * L.pitch + i;
-        L.dc[q] = hdc[e]; L.dmu[q] = hdmu[e]; L.dp[q] = hdp[e]; ua[q] = uA[e]; va[q] = vA[e];
+        const float *t = B.T.at(i, j);
+        sta<1>(L.dc, q, t[L_DC]);
+        sta<1>(L.dmu, q, t[T_MU]);
+        sta<1>(L.dp, q, t[T_P]);
+        sta<1>(ua, q, t[T_U]);
+        sta<1>(va, q, t[T_V]);
     }
 }
-QN_KERNEL(k_mx_coarse_solve, __launch_bounds__(512), (int sweeps, float omega, int prolong), (sweeps, omega, prolong))
+QN_KERNEL(k_mx_bottom, __launch_bounds__(BOT), (int nu1, int nu2, int nuc, float omega, float comega), (nu1, nu2, nuc, omega, comega))
 
 // w += delta on the finest level (FP64 state, single u/v buffer in mixed
 // mode); faces on walls are not unknowns
