@@ -261,7 +261,7 @@ __device__ __forceinline__ double dwell(double c)
 // bytes; with one array per field every access of a relaxation needed an
 // address of its own.  The element of 14 doubles spreads the cells of a
 // colour (every second element) over half of the LDS banks.
-enum { T_C = 0, T_CN, T_MU, T_P, T_RN, T_MV, T_RS, T_MOB, T_U, T_V, T_UN, T_VN, T_NF, T_U2 = T_NF, T_V2, T_ES };
+enum { T_C = 0, T_CN, T_MU, T_P, T_RN, T_MV, T_RS, T_MOB, T_U, T_UN, T_V, T_VN, T_NF, T_U2 = T_NF, T_V2, T_ES };
 // the correction smoother's further fields (its T_MU, T_P, T_U, T_V hold
 // corrections): the correction of c and the change of density it induces
 enum { L_DC = T_ES, L_DRS, L_NF, L_ES = 20 };
@@ -281,6 +281,18 @@ template <typename R, int ES_> struct TileT {
 };
 typedef TileT<double, T_ES> Tile;
 
+// values per element of a tile
+template <typename R> struct Elem;
+template <> struct Elem<double> { static constexpr int N = T_ES; };
+template <> struct Elem<float> { static constexpr int N = L_ES; };
+// the element n elements from s (a row is S of them).  The offset is a
+// multiple of the element's size in the code, too: the compiler then knows the
+// element to be aligned to 16 bytes and loads a pair of fields as one
+// ds_read_b128; otherwise it makes a ds_read2_b64 of it, which takes the LDS
+// 15.5 cycles per wave instead of 4.5 (MI355X).
+template <typename R> __device__ __forceinline__ R *el(R *s, int n) { return s + n * Elem<R>::N; }
+template <typename R> __device__ __forceinline__ const R *el(const R *s, int n) { return s + n * Elem<R>::N; }
+
 // an element's fields from its eight loaded values (c, mubar, pbar, u, v, c^n,
 // u^n, v^n) and the signs of its faces
 __device__ __forceinline__ void tile_put(const Phys &P, double *t, int su, int sv, const double (&v)[8])
@@ -294,8 +306,8 @@ __device__ __forceinline__ void tile_put(const Phys &P, double *t, int su, int s
     t[T_RS] = rho_of(P, v[0]);
     t[T_MOB] = mob_of(P, v[5]);
     t[T_U] = signed_val(su, v[3]);
-    t[T_V] = signed_val(sv, v[4]);
     t[T_UN] = signed_val(su, v[6]);
+    t[T_V] = signed_val(sv, v[4]);
     t[T_VN] = signed_val(sv, v[7]);
 }
 template <typename TT> __device__ __forceinline__ void tile_zero(const TT &T, int e)
@@ -404,8 +416,9 @@ __device__ __forceinline__ void ring_build(const TT &T, int m1, int m2, int bcx,
 // the same values.
 
 struct Ax {
-    int dn, dt;          // offsets of the next element along the normal / tangential axis
+    int dn, dt;          // elements to the next one along the normal / tangential axis
     int fn, ft, fo;      // own velocity (T_U or T_V, or T_U2, T_V2), other velocity, new own velocity
+    int fnn, ftn;        // own and other velocity of time n
     bool per, pert;      // periodic along the axis / the other one
     int ia, ma, it, mt;  // cell index and count along the axis / the other one
     int hlf;             // 0 x, 1 y
@@ -418,11 +431,13 @@ __device__ __forceinline__ Ax make_ax(const V &L, const TT &T, int i, int j, int
 {
     Ax a;
     a.hlf = hlf;
-    a.dn = hlf ? T.S * TT::ES : TT::ES;
-    a.dt = hlf ? TT::ES : T.S * TT::ES;
-    a.fn = T_U + hlf + slot * (T_U2 - T_U);
-    a.ft = T_V - hlf + slot * (T_U2 - T_U);
-    a.fo = T_U2 + hlf - slot * (T_U2 - T_U);
+    a.dn = hlf ? T.S : 1;
+    a.dt = hlf ? 1 : T.S;
+    a.fn = slot ? T_U2 + hlf : T_U + 2 * hlf;
+    a.ft = slot ? T_V2 - hlf : T_V - 2 * hlf;
+    a.fo = slot ? T_U + 2 * hlf : T_U2 + hlf;
+    a.fnn = T_UN + 2 * hlf;
+    a.ftn = T_VN - 2 * hlf;
     a.per = hlf ? L.bcy : L.bcx;
     a.pert = hlf ? L.bcx : L.bcy;
     a.ia = hlf ? j : i;
@@ -465,7 +480,7 @@ __device__ __forceinline__ CellSum<double> axis_cell(const Kon<double> &K, const
                                                      double drs, double u0, double uP)
 {
     const bool wP = a.per || a.ia < a.ma - 1, wM = a.per || a.ia > 0;
-    const double *sP = s + a.dn, *sM = s - a.dn;
+    const double *sP = el(s, a.dn), *sM = el(s, -a.dn);
     const double mP = sP[T_MOB] + s[T_MOB], mM = sM[T_MOB] + s[T_MOB];
     const double S = s[T_MU] + K.alpha * s[T_P];
     const double fP = (sP[T_MU] + K.alpha * sP[T_P]) - S, fM = S - (sM[T_MU] + K.alpha * sM[T_P]);
@@ -557,19 +572,19 @@ template <typename R> struct FaceEq {
 template <typename R, bool PJ, bool LIN>
 __device__ __forceinline__ FaceEq<R> face_eq(const Kon<R> &K, const R *s, const Ax &a, R uh = R(0))
 {
-    const int dn = a.dn, dt = a.dt, fn = a.fn, ft = a.ft, fnn = T_UN + a.hlf, ftn = T_VN - a.hlf;
-    const R *L = s - dn;
+    const int dn = a.dn, dt = a.dt, fn = a.fn, ft = a.ft, fnn = a.fnn, ftn = a.ftn;
+    const R *L = el(s, -dn), *Rn = el(s, dn), *Lt = el(L, dt), *Lb = el(L, -dt), *St = el(s, dt), *Sb = el(s, -dt);
     const R rL = L[T_RN], rR = s[T_RN], mL = L[T_MV], mR = s[T_MV];
     const R a1 = rL + rR, b1 = mL + mR;
-    const R At = (L[dt + T_RN] + s[dt + T_RN]) + a1, Ab = (L[T_RN - dt] + s[T_RN - dt]) + a1;
-    const R mt = (L[dt + T_MV] + s[dt + T_MV]) + b1, mb = (L[T_MV - dt] + s[T_MV - dt]) + b1;
+    const R At = (Lt[T_RN] + St[T_RN]) + a1, Ab = (Lb[T_RN] + Sb[T_RN]) + a1;
+    const R mt = (Lt[T_MV] + St[T_MV]) + b1, mb = (Lb[T_MV] + Sb[T_MV]) + b1;
     const R hA = R(0.5) * ((L[T_RS] + s[T_RS]) - a1);
     const R un0 = s[fnn];
-    const R wL = rL * (L[fnn] + un0), wR = rR * (un0 + s[dn + fnn]);
-    const R Ct = At * (L[dt + ftn] + s[dt + ftn]), Cb = Ab * (L[ftn] + s[ftn]);
-    const R u0 = s[fn], uE = s[dn + fn], uW = L[fn], uN = s[dt + fn], uS = s[fn - dt];
+    const R wL = rL * (L[fnn] + un0), wR = rR * (un0 + Rn[fnn]);
+    const R Ct = At * (Lt[ftn] + St[ftn]), Cb = Ab * (L[ftn] + s[ftn]);
+    const R u0 = s[fn], uE = Rn[fn], uW = L[fn], uN = St[fn], uS = Sb[fn];
     // (4 d_n u + d_t v) h of the cells on both sides
-    const R thR = R(4) * (uE - u0) + (s[dt + ft] - s[ft]), thL = R(4) * (u0 - uW) + (L[dt + ft] - L[ft]);
+    const R thR = R(4) * (uE - u0) + (St[ft] - s[ft]), thL = R(4) * (u0 - uW) + (Lt[ft] - L[ft]);
     const R advn = wR * uE - wL * uW;
     const R adv = R(4) * advn + (Ct * uN - Cb * uS);
     const R v1 = mR * thR - mL * thL, v2 = mt * (uN - u0) - mb * (u0 - uS);
@@ -691,6 +706,67 @@ __device__ __forceinline__ const double *face_rhs(const Rhs &F, int hlf)
 }
 
 // --------------------------------------------------------------------------
+// The neighbourhood of a cell that a lane's part of its relaxation reads,
+// copied into registers: elements n = -1 .. 2 along the lane's axis, t = -1 ..
+// 1 across it, at h[((n + 1) * 3 + t + 1) * ES], with the velocities in the
+// lane's order (own: T_U, T_UN).  All loads are issued before anything uses
+// one.  Where a launch lasts as long as the chain of its relaxations (few
+// waves, registers to spare), reading the tile at each use instead waits for
+// LDS some twenty times per relaxation: @@.
+template <typename TT, typename R> struct Hood {
+    R h[12 * TT::ES];
+    __device__ __forceinline__ R *centre() { return h + 4 * TT::ES; }
+    template <bool LIN> __device__ __forceinline__ Ax load(const R *e, const Ax &a)
+    {
+        auto get = [&](int n, int t, int f, int g) {
+            h[((n + 1) * 3 + t + 1) * TT::ES + f] = el(e, n * a.dn + t * a.dt)[g];
+        };
+#pragma unroll
+        for (int n = -1; n <= 1; n++) {
+#pragma unroll
+            for (int f = T_C; f <= T_MOB; f++) get(n, 0, f, f);
+            if (LIN) {
+                get(n, 0, L_DC, L_DC);
+                get(n, 0, L_DRS, L_DRS);
+            }
+        }
+#pragma unroll
+        for (int n = -1; n <= 1; n++)
+#pragma unroll
+            for (int t = -1; t <= 1; t += 2) {
+                get(n, t, T_RN, T_RN);
+                get(n, t, T_MV, T_MV);
+            }
+#pragma unroll
+        for (int n = -1; n <= 2; n++) {
+            get(n, 0, T_U, a.fn);
+            get(n, 0, T_UN, a.fnn);
+        }
+#pragma unroll
+        for (int n = 0; n <= 1; n++) {
+            get(n, -1, T_U, a.fn);
+            get(n, 1, T_U, a.fn);
+        }
+#pragma unroll
+        for (int n = -1; n <= 1; n++)
+#pragma unroll
+            for (int t = 0; t <= 1; t++) {
+                get(n, t, T_V, a.ft);
+                get(n, t, T_VN, a.ftn);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+        Ax b = a;
+        b.dn = 3;
+        b.dt = 1;
+        b.fn = T_U;
+        b.ft = T_V;
+        b.fnn = T_UN;
+        b.ftn = T_VN;
+        return b;
+    }
+};
+
+// --------------------------------------------------------------------------
 // smoother for one cell of the current colour (sec. 7.1), run by a lane pair.
 // Segregated (P.coupled = 0): step 1 is Newton on (N_c, N_mu) in (c_ij,
 // mubar_ij); step 2 the Vanka box on (uW, uE, vS, vN, p).  Coupled: one Newton
@@ -720,7 +796,7 @@ __device__ __forceinline__ const double *face_rhs(const Rhs &F, int hlf)
 // them), the box faces in the fields T_U2, T_V2 (slot 0; from them to T_U, T_V:
 // slot 1), whose elements only this cell's box writes.  AS is the address space of the level arrays and
 // right-hand sides (1: global memory, 3: LDS, where the level resides in the
-// workgroup's LDS).
+// workgroup's LDS).  HOOD: the neighbourhood is read into registers first.
 //
 // Against a box assembled and eliminated as a 5x5 matrix, coefficients formed
 // per cell and a tile of one array per field, a half-sweep takes 700 instead
@@ -757,50 +833,62 @@ __device__ __forceinline__ CellPos cell_pos(const V &L, const TT &T, int i, int 
 template <typename R>
 __device__ __forceinline__ void box_offdiag(const Kon<R> &K, const R *s, const Ax &a, bool hlo, bool hhi, R &alh, R &ahl)
 {
-    const int fnn = T_UN + a.hlf;
-    const R un = s[fnn] + s[a.dn + fnn];
+    const int fnn = a.fnn;
+    const R un = s[fnn] + el(s, a.dn)[fnn];
     const R w = R(4) * (K.ka * (s[T_RN] * un)), vis = R(4) * (K.kv * s[T_MV]);
     alh = hlo ? w - vis : R(0);
     ahl = hhi ? -w - vis : R(0);
     if (a.per && a.ma == 2) {
-        const R *o = s - a.dn;
+        const R *o = el(s, -a.dn);
         const R wo = R(4) * (K.ka * (o[T_RN] * un)), vo = R(4) * (K.kv * o[T_MV]);
         alh = alh - (wo + vo);
         ahl = ahl + (wo - vo);
     }
 }
 
-template <int TO, int AS>
+template <int TO, int AS, bool HOOD>
 __device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, const View &L, const Tile &T, const Rhs &F,
                                          double *unew, double *vnew, int i, int j, int ti, int tj, int hlf,
                                          double omega, double pomega, int slot);
 
-template <bool PJ, int TO, int AS>
+template <bool PJ, int TO, int AS, bool HOOD>
 __device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, const View &L, const Tile &T,
                                            const Rhs &F, double *unew, double *vnew, int i, int j, int ti, int tj,
                                            int hlf, double omega, double pomega, int slot = 0)
 {
     if (PJ) {
-        relax_pj<TO, AS>(P, K, L, T, F, unew, vnew, i, j, ti, tj, hlf, omega, pomega, slot);
+        relax_pj<TO, AS, HOOD>(P, K, L, T, F, unew, vnew, i, j, ti, tj, hlf, omega, pomega, slot);
         return;
     }
     const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
-    const Ax &a = b.a;
-    double *const e = T.at(ti, tj);
+    double *const e = T.at(ti, tj); // results go here, everything is read at s
+    Hood<Tile, double> H;
+    const double *s = e;
+    Ax a = b.a;
     const bool cpl = P.coupled;
     // the right-hand sides first: their loads are then in flight during the
     // cell equations
     const double *fN = face_rhs(F, hlf);
-    const double f_c = F.fc ? lda<AS>(F.fc, b.k) : 0.0, f_mu = F.fc ? lda<AS>(F.fmu, b.k) : 0.0,
-                 f_p = F.fc ? lda<AS>(F.fp, b.k) : 0.0;
-    const double f_lo = F.fc && b.hlo ? lda<AS>(fN, b.k) : 0.0, f_hi = F.fc && b.hhi ? lda<AS>(fN, b.khi) : 0.0;
+    // (a level in LDS has them; the high face of a wall: loaded, not used)
+    double f_c = 0.0, f_mu = 0.0, f_p = 0.0, f_lo = 0.0, f_hi = 0.0;
+    if (AS == 3 || F.fc) {
+        f_c = lda<AS>(F.fc, b.k);
+        f_mu = lda<AS>(F.fmu, b.k);
+        f_p = lda<AS>(F.fp, b.k);
+        f_lo = lda<AS>(fN, b.k);
+        f_hi = lda<AS>(fN, b.khi);
+    }
+    if (HOOD) {
+        a = H.template load<false>(e, b.a);
+        s = H.centre();
+    }
     double r, drs;
-    cell_r(K, e, r, drs);
-    const double ulo = e[a.fn], uhi = e[a.dn + a.fn];
-    const CellSum<double> xo = axis_cell<false>(K, e, a, r, drs, ulo, uhi), x = xo + other(xo);
-    const CellEq q = cell_eq(K, e, x, r, drs);
+    cell_r(K, s, r, drs);
+    const double ulo = s[a.fn], uhi = el(s, a.dn)[a.fn];
+    const CellSum<double> xo = axis_cell<false>(K, s, a, r, drs, ulo, uhi), x = xo + other(xo);
+    const CellEq q = cell_eq(K, s, x, r, drs);
     const double r1 = f_c - q.Nc, r2 = f_mu - q.Nmu;
-    const double c0 = e[T_C], m0 = e[T_MU], p0 = e[T_P];
+    const double c0 = s[T_C], m0 = s[T_MU], p0 = s[T_P];
     const double Jcp = K.alpha * x.sm; // dN_c/dpbar = dN_p/dmubar
     double bp = f_p - q.Np;
     // coupled box: mubar eliminated by N_mu (pivot Jmm)
@@ -821,32 +909,41 @@ __device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, 
             sta<AS>(L.c, b.k, cnew);
             sta<AS>(L.mu, b.k, mnew);
         }
-        e[T_C] = cnew;
-        e[T_MU] = mnew;
-        e[T_RS] = rho_of(P, cnew);
+        const double rnew = rho_of(P, cnew);
+        if (HOOD) {
+            double *o = H.centre();
+            o[T_C] = cnew;
+            o[T_MU] = mnew;
+            o[T_RS] = rnew;
+        }
+        if (TO || !HOOD) {
+            e[T_C] = cnew;
+            e[T_MU] = mnew;
+            e[T_RS] = rnew;
+        }
         // mass equation with the new mubar of the cell
         bp -= Jcp * dm;
     }
     // ---- the box: this lane's two faces along its axis
-    const FaceEq<double> flo = face_eq<double, false, false>(K, e, a), fhi = face_eq<double, false, false>(K, e + a.dn, a);
-    const double *P1 = e + a.dn, *M1 = e - a.dn;
-    const double alo = b.hlo ? K.hih * (M1[T_RN] * (e[T_CN] - M1[T_CN])) : 0.0;
-    const double ahi = b.hhi ? K.hih * (P1[T_RN] * (P1[T_CN] - e[T_CN])) : 0.0;
+    const FaceEq<double> flo = face_eq<double, false, false>(K, s, a), fhi = face_eq<double, false, false>(K, el(s, a.dn), a);
+    const double *P1 = el(s, a.dn), *M1 = el(s, -a.dn);
+    const double alo = b.hlo ? K.hih * (M1[T_RN] * (s[T_CN] - M1[T_CN])) : 0.0;
+    const double ahi = b.hhi ? K.hih * (P1[T_RN] * (P1[T_CN] - s[T_CN])) : 0.0;
     double alh, ahl;
-    box_offdiag(K, e, a, b.hlo, b.hhi, alh, ahl);
+    box_offdiag(K, s, a, b.hlo, b.hhi, alh, ahl);
     const double sb = kbm * K.iM, sc = kmc * K.iM;
     const double blo = b.hlo ? (f_lo - flo.N) + sb * alo : 0.0, bhi = b.hhi ? (f_hi - fhi.N) + sb * ahi : 0.0;
     const double qlo = b.hlo ? gc * ulo + sc * alo : 0.0, qhi = b.hhi ? gc * uhi + sc * ahi : 0.0;
     const BoxAx<double> X = box_axis(b.hlo ? flo.diag : 1.0, b.hhi ? fhi.diag : 1.0, alh, ahl, blo, bhi,
                                      b.hlo ? 1.0 : 0.0, b.hhi ? -1.0 : 0.0, qlo, qhi, alo, ahi);
     double dp, dc, t, tt;
-    box_solve(X, box_other(X), cpl, K.kv * e[T_MV], K.kp, K.ih, K.alpha * Jcp, Jcp, kmc, kbm, Jc, bp, bc, dp, dc, t, tt);
+    box_solve(X, box_other(X), cpl, K.kv * s[T_MV], K.kp, K.ih, K.alpha * Jcp, Jcp, kmc, kbm, Jc, bp, bc, dp, dc, t, tt);
     const double nlo = ulo + omega * ((X.xb[0] + t * X.xs[0]) - dc * X.xq[0]);
     const double nhi = uhi + omega * ((X.xb[1] + t * X.xs[1]) - dc * X.xq[1]);
     const double np = p0 + omega * dp;
     if (TO) {
-        if (b.hlo) e[a.fo] = nlo;
-        if (b.hhi) e[b.hi<TO>() + a.fo] = nhi;
+        if (b.hlo) e[b.a.fo] = nlo;
+        if (b.hhi) el(e, b.hi<TO>())[b.a.fo] = nhi;
         if (hlf == 0) {
             e[T_P] = np;
             if (cpl) {
@@ -898,7 +995,7 @@ struct Resid {
 __device__ __forceinline__ double face_final(const Kon<double> &K, const double *s, const Ax &a, bool unk, double ut,
                                              double &w)
 {
-    const double *L = s - a.dn;
+    const double *L = el(s, -a.dn);
     const double rL = L[T_RS], rR = s[T_RS], A2 = rL + rR;
     const double st = 0.5 * (rR * L[T_MU] + rL * s[T_MU]) * (s[T_C] - L[T_C]);
     double f = K.kp * (st - (s[T_P] - L[T_P]));
@@ -917,13 +1014,13 @@ __device__ __forceinline__ Resid resid_cell(const Kon<double> &K, const View &L,
     Resid f = {};
     if (F.fc) f = { lda<AS>(F.fc, k), lda<AS>(F.fmu, k), lda<AS>(F.fp, k), lda<AS>(F.fu, k), lda<AS>(F.fv, k) };
     const bool hu = ax.per || i >= 1, hv = ay.per || j >= 1;
-    double ulo = e[T_U], uhi = e[ax.dn + T_U], vlo = e[T_V], vhi = e[ay.dn + T_V];
+    double ulo = e[T_U], uhi = el(e, ax.dn)[T_U], vlo = e[T_V], vhi = el(e, ay.dn)[T_V];
     if (PJ) {
         double w;
         ulo = face_final(K, e, ax, hu, ulo, w);
-        uhi = face_final(K, e + ax.dn, ax, ax.per || i + 1 < L.m1, uhi, w);
+        uhi = face_final(K, el(e, ax.dn), ax, ax.per || i + 1 < L.m1, uhi, w);
         vlo = face_final(K, e, ay, hv, vlo, w);
-        vhi = face_final(K, e + ay.dn, ay, ay.per || j + 1 < L.m2, vhi, w);
+        vhi = face_final(K, el(e, ay.dn), ay, ay.per || j + 1 < L.m2, vhi, w);
     }
     double r, drs;
     cell_r(K, e, r, drs);
@@ -953,31 +1050,43 @@ __device__ __forceinline__ Resid resid_cell(const Kon<double> &K, const View &L,
 //  4. the velocity of time n+1 is never stored, so nothing is left to update.
 // The tile entries of the cell (c, mubar, rho(c)) are updated after step 1; no
 // other pair of this colour reads them.
-template <int TO, int AS>
+template <int TO, int AS, bool HOOD>
 __device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, const View &L, const Tile &T, const Rhs &F,
                                          double *unew, double *vnew, int i, int j, int ti, int tj, int hlf,
                                          double omega, double pomega, int slot)
 {
     const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
-    const Ax &a = b.a;
-    double *const e = T.at(ti, tj);
-    const double *P1 = e + a.dn, *M1 = e - a.dn;
+    double *const e = T.at(ti, tj); // results go here, everything is read at s
+    Hood<Tile, double> H;
+    double *s = e;
+    Ax a = b.a;
     const double *fN = face_rhs(F, hlf);
-    const double f_c = F.fc ? lda<AS>(F.fc, b.k) : 0.0, f_mu = F.fc ? lda<AS>(F.fmu, b.k) : 0.0,
-                 f_p = F.fc ? lda<AS>(F.fp, b.k) : 0.0;
-    const double f_lo = F.fc && b.hlo ? lda<AS>(fN, b.k) : 0.0, f_hi = F.fc && b.hhi ? lda<AS>(fN, b.khi) : 0.0;
+    // (a level in LDS has them; the high face of a wall: loaded, not used)
+    double f_c = 0.0, f_mu = 0.0, f_p = 0.0, f_lo = 0.0, f_hi = 0.0;
+    if (AS == 3 || F.fc) {
+        f_c = lda<AS>(F.fc, b.k);
+        f_mu = lda<AS>(F.fmu, b.k);
+        f_p = lda<AS>(F.fp, b.k);
+        f_lo = lda<AS>(fN, b.k);
+        f_hi = lda<AS>(fN, b.khi);
+    }
+    if (HOOD) {
+        a = H.template load<false>(e, b.a);
+        s = H.centre();
+    }
+    const double *P1 = el(s, a.dn), *M1 = el(s, -a.dn);
     // ---- step 1
     double wlo, whi;
-    const double ulo0 = face_final(K, e, a, b.hlo, e[a.fn], wlo);
+    const double ulo0 = face_final(K, s, a, b.hlo, s[a.fn], wlo);
     const double uhi0 = face_final(K, P1, a, b.hhi, P1[a.fn], whi);
     double r, drs;
-    cell_r(K, e, r, drs);
-    const CellSum<double> xo = axis_cell<true>(K, e, a, r, drs, ulo0, uhi0), x = xo + other(xo);
-    CellEq q = cell_eq(K, e, x, r, drs);
-    pj_cell(K, e, x, drs, q);
+    cell_r(K, s, r, drs);
+    const CellSum<double> xo = axis_cell<true>(K, s, a, r, drs, ulo0, uhi0), x = xo + other(xo);
+    CellEq q = cell_eq(K, s, x, r, drs);
+    pj_cell(K, s, x, drs, q);
     const double dax = K.hih * (M1[T_RS] * ulo0 - P1[T_RS] * uhi0);
     q.Jcc += dax + other(dax);
-    const double c0 = e[T_C], m0 = e[T_MU], p0 = e[T_P];
+    const double c0 = s[T_C], m0 = s[T_MU], p0 = s[T_P];
     const double r1 = f_c - q.Nc, r2 = f_mu - q.Nmu;
     const double Jpm = K.alpha * x.sm;
     double dc, dm, pnew = p0;
@@ -999,7 +1108,7 @@ __device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, co
         dc = (q.Jmm * rc1 - kcm * r2) * idet;
         dm = (q.Jcc * r2 - q.Jmc * rc1) * idet;
         pnew = p0 + (r3 - Jpm * dm) * ipp;
-        e[T_P] = pnew;
+        s[T_P] = pnew;
     } else {
         const double idet = frcp(q.Jcc * q.Jmm - q.Jcm * q.Jmc);
         dc = (q.Jmm * r1 - q.Jcm * r2) * idet;
@@ -1010,26 +1119,32 @@ __device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, co
         sta<AS>(L.c, b.k, cnew);
         sta<AS>(L.mu, b.k, mnew);
     }
-    e[T_C] = cnew;
-    e[T_MU] = mnew;
-    e[T_RS] = rho_of(P, cnew);
+    // (with the neighbourhood in registers, s is not the tile's element)
+    s[T_C] = cnew;
+    s[T_MU] = mnew;
+    s[T_RS] = rho_of(P, cnew);
+    if (HOOD && TO) {
+        e[T_C] = cnew;
+        e[T_MU] = mnew;
+        e[T_RS] = s[T_RS];
+    }
     // ---- step 2: the intermediate-velocity box; the axes couple through the
     // viscous terms alone: V x = b + s gd D_o
-    const FaceEq<double> flo = face_eq<double, true, false>(K, e, a), fhi = face_eq<double, true, false>(K, P1, a);
+    const FaceEq<double> flo = face_eq<double, true, false>(K, s, a), fhi = face_eq<double, true, false>(K, P1, a);
     double alh, ahl;
-    box_offdiag(K, e, a, b.hlo, b.hhi, alh, ahl);
-    const double gd = K.kv * e[T_MV];
+    box_offdiag(K, s, a, b.hlo, b.hhi, alh, ahl);
+    const double gd = K.kv * s[T_MV];
     const BoxAx<double> X = box_axis(b.hlo ? flo.diag : 1.0, b.hhi ? fhi.diag : 1.0, alh, ahl,
                                      b.hlo ? f_lo - flo.N : 0.0, b.hhi ? f_hi - fhi.N : 0.0, b.hlo ? 1.0 : 0.0,
                                      b.hhi ? -1.0 : 0.0, 0.0, 0.0, 0.0, 0.0);
     const double oDb = other(X.Db), oDs = other(X.Ds);
     const double gx = gd * X.Ds, gy = gd * oDs;
     const double t = gd * ((oDb + gy * X.Db) * frcp(1.0 - gx * gy));
-    const double ut0 = e[a.fn], ut1 = P1[a.fn];
+    const double ut0 = s[a.fn], ut1 = P1[a.fn];
     const double ulo = ut0 + omega * (X.xb[0] + t * X.xs[0]), uhi = ut1 + omega * (X.xb[1] + t * X.xs[1]);
     if (TO) {
-        if (b.hlo) e[a.fo] = ulo;
-        if (b.hhi) e[b.hi<TO>() + a.fo] = uhi;
+        if (b.hlo) e[b.a.fo] = ulo;
+        if (b.hhi) el(e, b.hi<TO>())[b.a.fo] = uhi;
     } else {
         double *fo = hlf ? vnew : unew;
         if (b.hlo) sta<AS>(fo, b.k, ulo);
@@ -1037,7 +1152,7 @@ __device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, co
     }
     // ---- step 3: pbar from the mass equation with the new u~ (passed by
     // value: the tile keeps the snapshot that other boxes of this colour read)
-    const double ulo1 = face_final(K, e, a, b.hlo, ulo, wlo), uhi1 = face_final(K, P1, a, b.hhi, uhi, whi);
+    const double ulo1 = face_final(K, s, a, b.hlo, ulo, wlo), uhi1 = face_final(K, P1, a, b.hhi, uhi, whi);
     const double jax = (K.ih * K.kp) * ((b.hlo ? wlo : 0.0) + (b.hhi ? whi : 0.0));
     const double dv = K.ih * ((uhi1 - ulo1) - (uhi0 - ulo0));
     const double Np = q.Np + (dv + other(dv)) + Jpm * (dm + K.alpha * (pnew - p0));

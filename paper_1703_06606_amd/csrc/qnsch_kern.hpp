@@ -8,6 +8,8 @@
 // work of a workgroup depends only on its item, so a simulation's results do
 // not depend on what else shares the launch.
 #pragma once
+#include <type_traits>
+
 #include "qnsch_dev.hpp"
 #include "qnsch_lin.hpp"
 
@@ -207,7 +209,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_halfsweep_body
     const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
     const int j = T.j0 + lj;
     const int i = T.i0 + 2 * kk + ((j + colour) & 1);
-    if (i < L.m1 && j < L.m2) relax_cell<PJ, 0, 1>(P, K, L, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
+    if (i < L.m1 && j < L.m2) relax_cell<PJ, 0, 1, false>(P, K, L, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
 }
 QN_KERNEL_PJ(k_halfsweep, HS_ATTR, (int colour, double omega), (colour, omega))
 // the same kernel under its own name for launches whose items are all finest
@@ -426,7 +428,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused_body(
         const bool in = lj < TY + 4 && (L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2));
         if (in) {
             const int i = L.bcx ? wrapi(ti, L.m1) : ti, j = L.bcy ? wrapi(tj, L.m2) : tj;
-            relax_cell<PJ, 1, 1>(P, K, L, T, F, nullptr, nullptr, i, j, ti, tj, hlf, omega, 1.0);
+            relax_cell<PJ, 1, 1, true>(P, K, L, T, F, nullptr, nullptr, i, j, ti, tj, hlf, omega, 1.0);
         }
     }
     __syncthreads();
@@ -437,7 +439,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused_body(
         const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
         const int j = T0.j0 + lj;
         const int i = T0.i0 + 2 * kk + ((j + 1) & 1);
-        if (i < L.m1 && j < L.m2) relax_cell<PJ, 0, 1>(P, K, O, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
+        if (i < L.m1 && j < L.m2) relax_cell<PJ, 0, 1, true>(P, K, O, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
     } else {
         // red cells of the tile: their final values
         const int q = pr - TBLK / 2;
@@ -608,20 +610,26 @@ __host__ __device__ inline size_t bot_doubles(int m1, int m2)
 {
     return bot_tile(m1, m2, T_ES) + (size_t)10 * m1 * m2 + 2 * (size_t)ring_size(m1, m2);
 }
+// (the top level has no restricted iterate: the levels' LDS starts that much
+// before it)
+__host__ __device__ inline size_t bot_skip(int m1, int m2) { return (size_t)5 * m1 * m2; }
 // level l below the m1 x m2 one whose LDS starts at sm
 __device__ __forceinline__ BotLev bot_lev(double *sm, int m1, int m2, int l)
 {
+    const bool top = l == 0;
+    int off = top ? 0 : -(int)(bot_skip(m1, m2) / 2); // in 16 bytes (el)
     for (; l > 0; l--) {
-        sm += bot_doubles(m1, m2);
+        off += (int)(bot_doubles(m1, m2) / 2);
         m1 >>= 1;
         m2 >>= 1;
     }
+    sm += 2 * off;
     BotLev B;
     B.m1 = m1; B.m2 = m2;
     B.T.s = sm; B.T.i0 = 0; B.T.j0 = 0; B.T.W = m1 + 3; B.T.H = m2 + 3; B.T.S = bot_stride(m1);
     B.f = sm + bot_tile(m1, m2, T_ES);
     B.w0 = B.f + 5 * m1 * m2;
-    B.ring = (Image *)(B.w0 + 5 * m1 * m2);
+    B.ring = (Image *)(top ? B.w0 : B.w0 + 5 * m1 * m2);
     return B;
 }
 __device__ __forceinline__ View bot_view(const BotLev &B, const Desc &d)
@@ -640,19 +648,19 @@ __device__ __forceinline__ Rhs bot_rhs(const BotLev &B)
 // the images follow their sources; the faces are in slot `slot`
 __device__ __forceinline__ void bot_images(const BotLev &B, int slot)
 {
-    const int n = ring_size(B.m1, B.m2), fu = T_U + slot * (T_U2 - T_U);
+    const int n = ring_size(B.m1, B.m2), fu = slot ? T_U2 : T_U, fv = slot ? T_V2 : T_V;
     for (int k = threadIdx.x; k < n; k += BOT) {
         const Image g = B.ring[k];
         const double *s = B.T.s + g.c * T_ES;
         const double c = s[T_C], mu = s[T_MU], p = s[T_P], rs = s[T_RS];
-        const double u = B.T.s[(g.u >> 2) * T_ES + fu], v = B.T.s[(g.v >> 2) * T_ES + fu + 1];
+        const double u = B.T.s[(g.u >> 2) * T_ES + fu], v = B.T.s[(g.v >> 2) * T_ES + fv];
         double *t = B.T.s + g.e * T_ES;
         t[T_C] = c;
         t[T_MU] = mu;
         t[T_P] = p;
         t[T_RS] = rs;
         t[fu] = signed_val((g.u & 3) - 1, u);
-        t[fu + 1] = signed_val((g.v & 3) - 1, v);
+        t[fv] = signed_val((g.v & 3) - 1, v);
     }
 }
 // sweeps of a level (an even number of half-sweeps: the faces end in slot 0)
@@ -662,17 +670,26 @@ __device__ __forceinline__ void bot_smooth(const Phys &P, const Desc &d, const B
     const Kon<double> K = d.K;
     const View L = bot_view(B, d);
     const Rhs F = bot_rhs(B);
-    const int half = B.m1 >> 1;
-    for (int s = 0; s < 2 * sweeps; s++) {
-        const int colour = s & 1;
-        for (int t = threadIdx.x; t < 2 * half * B.m2; t += BOT) {
-            const int pr = t >> 1, j = pr / half;
-            const int i = 2 * (pr - j * half) + ((j + colour) & 1);
-            relax_cell<PJ, 2, 3>(P, K, L, B.T, F, nullptr, nullptr, i, j, i, j, t & 1, omega, pomega, colour);
+    // a thread's first cell of a sweep (a level of more cells of a colour
+    // than lane pairs takes several passes)
+    const int half = B.m1 >> 1, n2 = 2 * half * B.m2, pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
+    const int j0 = pr / half, i0 = 2 * (pr - j0 * half), dj = (BOT / 2) / half, di = 2 * ((BOT / 2) - dj * half);
+    auto sweep = [&](auto colour) {
+        int i = i0, j = j0;
+        for (int t = threadIdx.x; t < n2; t += BOT) {
+            const int ic = i + ((j + colour.value) & 1);
+            relax_cell<PJ, 2, 3, true>(P, K, L, B.T, F, nullptr, nullptr, ic, j, ic, j, hlf, omega, pomega, colour.value);
+            i += di;
+            j += dj;
+            if (i >= B.m1) { i -= B.m1; j++; }
         }
         __syncthreads();
-        bot_images(B, colour ^ 1);
+        bot_images(B, colour.value ^ 1);
         __syncthreads();
+    };
+    for (int s = 0; s < sweeps; s++) {
+        sweep(std::integral_constant<int, 0>());
+        sweep(std::integral_constant<int, 1>());
     }
 }
 // residual of level A, restricted with the iterate to the next level C, whose
@@ -821,18 +838,16 @@ __device__ __forceinline__ void k_bottom_body(const IT &it, int nu1, int nu2, in
         ring_build(B.T, B.m1, B.m2, L.bcx, L.bcy, B.ring, threadIdx.x, BOT);
     }
     __syncthreads();
-    for (int l = 0; l + 1 < depth; l++) {
-        const BotLev A = bot_lev(sm, m1, m2, l), C = bot_lev(sm, m1, m2, l + 1);
-        bot_smooth<PJ>(P, (&d)[l], A, nu1, omega, 1.0);
-        bot_restrict<PJ>(P, (&d)[l], A, C);
-    }
-    // the coarsest level over-relaxes the velocity and pressure updates (the
-    // primitive box, the projection pressure step)
-    bot_smooth<PJ>(P, (&d)[depth - 1], bot_lev(sm, m1, m2, depth - 1), nuc, PJ ? omega : comega, PJ ? comega : 1.0);
-    for (int l = depth - 2; l >= 0; l--) {
-        const BotLev A = bot_lev(sm, m1, m2, l), C = bot_lev(sm, m1, m2, l + 1);
-        bot_prolong(P, d, A, C);
-        bot_smooth<PJ>(P, (&d)[l], A, nu2, omega, 1.0);
+    // down to the coarsest level and back up (one copy of the code of each
+    // phase: it is fetched once).  The coarsest level over-relaxes the velocity
+    // and pressure updates (the primitive box, the projection pressure step).
+    for (int p = 0; p < 2 * depth - 1; p++) {
+        const int l = p < depth ? p : 2 * depth - 2 - p;
+        const BotLev B = bot_lev(sm, m1, m2, l);
+        if (p > 0 && p < depth) bot_restrict<PJ>(P, (&d)[l - 1], bot_lev(sm, m1, m2, l - 1), B);
+        if (p >= depth) bot_prolong(P, d, B, bot_lev(sm, m1, m2, l + 1));
+        const bool last = p == depth - 1;
+        bot_smooth<PJ>(P, (&d)[l], B, last ? nuc : p < depth ? nu1 : nu2, last && !PJ ? comega : omega, last && PJ ? comega : 1.0);
     }
     const BotLev B = bot_lev(sm, m1, m2, 0);
     for (int e = threadIdx.x; e < m1 * m2; e += BOT) {

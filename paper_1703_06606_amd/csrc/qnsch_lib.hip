@@ -221,7 +221,7 @@ static void step_begin_program(const qnsch_ctx *x, std::vector<Op> &out) { begin
 // LDS of the kernel that runs the cycle from level l on (k_bottom, k_mx_bottom)
 static size_t bottom_lds(const qnsch_ctx *x, int l)
 {
-    size_t b = 0;
+    size_t b = is_mixed(x) ? 0 : 0 - bot_skip(x->L[l].m1, x->L[l].m2) * sizeof(double);
     for (; l < x->nlev; l++)
         b += is_mixed(x) ? bot_floats(x->L[l].m1, x->L[l].m2) * sizeof(float)
                          : bot_doubles(x->L[l].m1, x->L[l].m2) * sizeof(double);

@@ -71,8 +71,8 @@ __device__ __forceinline__ void ltile_put(const PhysF &P, float *t, int su, int 
     t[T_RS] = rs;
     t[T_MOB] = mobf(P, v[6]);
     t[T_U] = signed_val(su, v[4]);
-    t[T_V] = signed_val(sv, v[5]);
     t[T_UN] = signed_val(su, v[7]);
+    t[T_V] = signed_val(sv, v[5]);
     t[T_VN] = signed_val(sv, v[8]);
     t[L_DC] = v[1];
     t[L_DRS] = -P.alpha * rs * rs * v[1];
@@ -129,7 +129,7 @@ __device__ __forceinline__ CellSum<float> laxis_cell(const Kon<float> &K, const 
                                                      float drs)
 {
     const bool wP = a.per || a.ia < a.ma - 1, wM = a.per || a.ia > 0;
-    const float *sP = s + a.dn, *sM = s - a.dn;
+    const float *sP = el(s, a.dn), *sM = el(s, -a.dn);
     const float mP = sP[T_MOB] + s[T_MOB], mM = sM[T_MOB] + s[T_MOB];
     const float S = s[T_MU] + K.alpha * s[T_P];
     const float fP = (sP[T_MU] + K.alpha * sP[T_P]) - S, fM = S - (sM[T_MU] + K.alpha * sM[T_P]);
@@ -200,14 +200,16 @@ __device__ __forceinline__ LCellEq lcell_eq(const Kon<float> &K, const float *s,
 // With TO set, as relax_cell: the cell at tile position (ti, tj), results
 // kept in the tile (dc, dmu, dp and the density change in place, the face
 // corrections in the fields T_U2, T_V2).
-template <int TO, int AS>
+template <int TO, int AS, bool HOOD>
 __device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K, const LView &L, const TileF &T,
                                             float *dunew, float *dvnew, int i, int j, int ti, int tj, int hlf,
                                             float omega, int slot = 0)
 {
     const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
-    const Ax &a = b.a;
-    float *const e = T.at(ti, tj);
+    float *const e = T.at(ti, tj); // results go here, everything is read at s
+    Hood<TileF, float> H;
+    const float *s = e;
+    Ax a = b.a;
     const bool cpl = P.coupled;
     const float muh = lda<AS>(L.mu, b.k), f_c = lda<AS>(L.rc, b.k), f_mu = lda<AS>(L.rmu, b.k),
                 f_p = lda<AS>(L.rp, b.k);
@@ -216,12 +218,16 @@ __device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K,
     const float *fw = hlf ? L.v : L.u, *fN = hlf ? L.rv : L.ru;
     const float uhlo = lda<AS>(fw, b.k), uhhi = lda<AS>(fw, b.khi);
     const float f_lo = lda<AS>(fN, b.k), f_hi = lda<AS>(fN, b.khi);
+    if (HOOD) {
+        a = H.template load<true>(e, b.a);
+        s = H.centre();
+    }
     float r, drs;
-    lcell_r(K, e, r, drs);
-    const CellSum<float> xo = laxis_cell(K, e, a, r, drs), x = xo + other(xo);
-    const LCellEq q = lcell_eq(K, e, x, r, drs, muh);
+    lcell_r(K, s, r, drs);
+    const CellSum<float> xo = laxis_cell(K, s, a, r, drs), x = xo + other(xo);
+    const LCellEq q = lcell_eq(K, s, x, r, drs, muh);
     const float r1 = f_c - q.Nc, r2 = f_mu - q.Nmu;
-    const float c0 = e[L_DC], m0 = e[T_MU], p0 = e[T_P], rs = e[T_RS];
+    const float c0 = s[L_DC], m0 = s[T_MU], p0 = s[T_P], rs = s[T_RS];
     const float Jcp = K.alpha * x.sm;
     float bp = f_p - q.Np;
     float kmc = 0.0f, kbm = 0.0f, Jc = 0.0f, bc = 0.0f, gc = 0.0f;
@@ -241,31 +247,40 @@ __device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K,
             sta<AS>(L.dc, b.k, cnew);
             sta<AS>(L.dmu, b.k, mnew);
         }
-        e[L_DC] = cnew;
-        e[T_MU] = mnew;
-        e[L_DRS] = -P.alpha * rs * rs * cnew;
+        const float drnew = -P.alpha * rs * rs * cnew;
+        if (HOOD) {
+            float *o = H.centre();
+            o[L_DC] = cnew;
+            o[T_MU] = mnew;
+            o[L_DRS] = drnew;
+        }
+        if (TO || !HOOD) {
+            e[L_DC] = cnew;
+            e[T_MU] = mnew;
+            e[L_DRS] = drnew;
+        }
         bp -= Jcp * dm;
     }
     // ---- the box
-    const FaceEq<float> flo = face_eq<float, false, true>(K, e, a, uhlo), fhi = face_eq<float, false, true>(K, e + a.dn, a, uhhi);
-    const float *P1 = e + a.dn, *M1 = e - a.dn;
-    const float alo = b.hlo ? K.hih * (M1[T_RN] * (e[T_CN] - M1[T_CN])) : 0.0f;
-    const float ahi = b.hhi ? K.hih * (P1[T_RN] * (P1[T_CN] - e[T_CN])) : 0.0f;
+    const FaceEq<float> flo = face_eq<float, false, true>(K, s, a, uhlo), fhi = face_eq<float, false, true>(K, el(s, a.dn), a, uhhi);
+    const float *P1 = el(s, a.dn), *M1 = el(s, -a.dn);
+    const float alo = b.hlo ? K.hih * (M1[T_RN] * (s[T_CN] - M1[T_CN])) : 0.0f;
+    const float ahi = b.hhi ? K.hih * (P1[T_RN] * (P1[T_CN] - s[T_CN])) : 0.0f;
     float alh, ahl;
-    box_offdiag(K, e, a, b.hlo, b.hhi, alh, ahl);
+    box_offdiag(K, s, a, b.hlo, b.hhi, alh, ahl);
     const float sb = kbm * K.iM, sc = kmc * K.iM;
     const float blo = b.hlo ? (f_lo - flo.N) + sb * alo : 0.0f, bhi = b.hhi ? (f_hi - fhi.N) + sb * ahi : 0.0f;
     const float qlo = b.hlo ? gc * uhlo + sc * alo : 0.0f, qhi = b.hhi ? gc * uhhi + sc * ahi : 0.0f;
     const BoxAx<float> X = box_axis(b.hlo ? flo.diag : 1.0f, b.hhi ? fhi.diag : 1.0f, alh, ahl, blo, bhi,
                                     b.hlo ? 1.0f : 0.0f, b.hhi ? -1.0f : 0.0f, qlo, qhi, alo, ahi);
     float dp, dc, t, tt;
-    box_solve(X, box_other(X), cpl, K.kv * e[T_MV], K.kp, K.ih, K.alpha * Jcp, Jcp, kmc, kbm, Jc, bp, bc, dp, dc, t, tt);
-    const float nlo = e[a.fn] + omega * ((X.xb[0] + t * X.xs[0]) - dc * X.xq[0]);
+    box_solve(X, box_other(X), cpl, K.kv * s[T_MV], K.kp, K.ih, K.alpha * Jcp, Jcp, kmc, kbm, Jc, bp, bc, dp, dc, t, tt);
+    const float nlo = s[a.fn] + omega * ((X.xb[0] + t * X.xs[0]) - dc * X.xq[0]);
     const float nhi = P1[a.fn] + omega * ((X.xb[1] + t * X.xs[1]) - dc * X.xq[1]);
     const float np = p0 + omega * dp;
     if (TO) {
-        if (b.hlo) e[a.fo] = nlo;
-        if (b.hhi) e[b.hi<TO>() + a.fo] = nhi;
+        if (b.hlo) e[b.a.fo] = nlo;
+        if (b.hhi) el(e, b.hi<TO>())[b.a.fo] = nhi;
         if (hlf == 0) {
             e[T_P] = np;
             if (cpl) {

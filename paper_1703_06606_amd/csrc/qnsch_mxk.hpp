@@ -48,7 +48,7 @@ template <typename IT> __device__ __forceinline__ void k_mx_halfsweep_body(const
     const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
     const int j = T.j0 + lj;
     const int i = T.i0 + 2 * kk + ((j + colour) & 1);
-    if (i < L.m1 && j < L.m2) lrelax_cell<0, 1>(d.Pf, d.Kf, L, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
+    if (i < L.m1 && j < L.m2) lrelax_cell<0, 1, false>(d.Pf, d.Kf, L, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
 }
 QN_KERNEL(k_mx_halfsweep, HS_ATTR, (int colour, float omega), (colour, omega))
 // finest-level launches under their own name (profiles)
@@ -143,7 +143,7 @@ template <typename IT> __device__ __forceinline__ void k_mx_fused_body(const IT 
         const bool in = lj < TY + 4 && (L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2));
         if (in) {
             const int i = L.bcx ? wrapi(ti, L.m1) : ti, j = L.bcy ? wrapi(tj, L.m2) : tj;
-            lrelax_cell<1, 1>(d.Pf, d.Kf, L, T, nullptr, nullptr, i, j, ti, tj, hlf, omega);
+            lrelax_cell<1, 1, true>(d.Pf, d.Kf, L, T, nullptr, nullptr, i, j, ti, tj, hlf, omega);
         }
     }
     __syncthreads();
@@ -153,7 +153,7 @@ template <typename IT> __device__ __forceinline__ void k_mx_fused_body(const IT 
         const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
         const int j = T0.j0 + lj;
         const int i = T0.i0 + 2 * kk + ((j + 1) & 1);
-        if (i < L.m1 && j < L.m2) lrelax_cell<0, 1>(d.Pf, d.Kf, O, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
+        if (i < L.m1 && j < L.m2) lrelax_cell<0, 1, true>(d.Pf, d.Kf, O, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
     } else {
         const int q = pr - TBLK / 2;
         const int lj = q / (TX / 2), kk = q - lj * (TX / 2);
@@ -322,11 +322,13 @@ __host__ __device__ inline size_t bot_floats(int m1, int m2)
 }
 __device__ __forceinline__ BotLevF bot_lev(float *sm, int m1, int m2, int l)
 {
+    int off = 0; // in 16 bytes
     for (; l > 0; l--) {
-        sm += bot_floats(m1, m2);
+        off += (int)(bot_floats(m1, m2) / 4);
         m1 >>= 1;
         m2 >>= 1;
     }
+    sm += 4 * off;
     BotLevF B;
     B.m1 = m1; B.m2 = m2;
     B.T.s = sm; B.T.i0 = 0; B.T.j0 = 0; B.T.W = m1 + 3; B.T.H = m2 + 3; B.T.S = bot_stride(m1);
@@ -347,36 +349,43 @@ __device__ __forceinline__ LView bot_view(const BotLevF &B, const Desc &d)
 }
 __device__ __forceinline__ void bot_images(const BotLevF &B, int slot)
 {
-    const int n = ring_size(B.m1, B.m2), fu = T_U + slot * (T_U2 - T_U);
+    const int n = ring_size(B.m1, B.m2), fu = slot ? T_U2 : T_U, fv = slot ? T_V2 : T_V;
     for (int k = threadIdx.x; k < n; k += BOT) {
         const Image g = B.ring[k];
         const float *s = B.T.s + g.c * L_ES;
         const float dc = s[L_DC], mu = s[T_MU], p = s[T_P], drs = s[L_DRS];
-        const float u = B.T.s[(g.u >> 2) * L_ES + fu], v = B.T.s[(g.v >> 2) * L_ES + fu + 1];
+        const float u = B.T.s[(g.u >> 2) * L_ES + fu], v = B.T.s[(g.v >> 2) * L_ES + fv];
         float *t = B.T.s + g.e * L_ES;
         t[L_DC] = dc;
         t[T_MU] = mu;
         t[T_P] = p;
         t[L_DRS] = drs;
         t[fu] = signed_val((g.u & 3) - 1, u);
-        t[fu + 1] = signed_val((g.v & 3) - 1, v);
+        t[fv] = signed_val((g.v & 3) - 1, v);
     }
 }
 __device__ __forceinline__ void bot_smooth(const PhysF &P, const Desc &d, const BotLevF &B, int sweeps, float omega)
 {
     const Kon<float> K = d.Kf;
     const LView L = bot_view(B, d);
-    const int half = B.m1 >> 1;
-    for (int s = 0; s < 2 * sweeps; s++) {
-        const int colour = s & 1;
-        for (int t = threadIdx.x; t < 2 * half * B.m2; t += BOT) {
-            const int pr = t >> 1, j = pr / half;
-            const int i = 2 * (pr - j * half) + ((j + colour) & 1);
-            lrelax_cell<2, 3>(P, K, L, B.T, nullptr, nullptr, i, j, i, j, t & 1, omega, colour);
+    const int half = B.m1 >> 1, n2 = 2 * half * B.m2, pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
+    const int j0 = pr / half, i0 = 2 * (pr - j0 * half), dj = (BOT / 2) / half, di = 2 * ((BOT / 2) - dj * half);
+    auto sweep = [&](auto colour) {
+        int i = i0, j = j0;
+        for (int t = threadIdx.x; t < n2; t += BOT) {
+            const int ic = i + ((j + colour.value) & 1);
+            lrelax_cell<2, 3, true>(P, K, L, B.T, nullptr, nullptr, ic, j, ic, j, hlf, omega, colour.value);
+            i += di;
+            j += dj;
+            if (i >= B.m1) { i -= B.m1; j++; }
         }
         __syncthreads();
-        bot_images(B, colour ^ 1);
+        bot_images(B, colour.value ^ 1);
         __syncthreads();
+    };
+    for (int s = 0; s < sweeps; s++) {
+        sweep(std::integral_constant<int, 0>());
+        sweep(std::integral_constant<int, 1>());
     }
 }
 // residual of level A and the linearisation point restricted to the next level
@@ -509,16 +518,13 @@ __device__ __forceinline__ void k_mx_bottom_body(const IT &it, int nu1, int nu2,
         ring_build(B.T, B.m1, B.m2, L.bcx, L.bcy, B.ring, threadIdx.x, BOT);
     }
     __syncthreads();
-    for (int l = 0; l + 1 < depth; l++) {
-        const BotLevF A = bot_lev(smf, m1, m2, l), C = bot_lev(smf, m1, m2, l + 1);
-        bot_smooth(P, (&d)[l], A, nu1, omega);
-        bot_restrict(P, (&d)[l], A, C);
-    }
-    bot_smooth(P, (&d)[depth - 1], bot_lev(smf, m1, m2, depth - 1), nuc, comega);
-    for (int l = depth - 2; l >= 0; l--) {
-        const BotLevF A = bot_lev(smf, m1, m2, l), C = bot_lev(smf, m1, m2, l + 1);
-        bot_prolong(P, d, A, C);
-        bot_smooth(P, (&d)[l], A, nu2, omega);
+    for (int p = 0; p < 2 * depth - 1; p++) {
+        const int l = p < depth ? p : 2 * depth - 2 - p;
+        const BotLevF B = bot_lev(smf, m1, m2, l);
+        if (p > 0 && p < depth) bot_restrict(P, (&d)[l - 1], bot_lev(smf, m1, m2, l - 1), B);
+        if (p >= depth) bot_prolong(P, d, B, bot_lev(smf, m1, m2, l + 1));
+        const bool last = p == depth - 1;
+        bot_smooth(P, (&d)[l], B, last ? nuc : p < depth ? nu1 : nu2, last ? comega : omega);
     }
     const BotLevF B = bot_lev(smf, m1, m2, 0);
     for (int e = threadIdx.x; e < m1 * m2; e += BOT) {
