@@ -712,7 +712,8 @@ __device__ __forceinline__ const double *face_rhs(const Rhs &F, int hlf)
 // lane's order (own: T_U, T_UN).  All loads are issued before anything uses
 // one.  Where a launch lasts as long as the chain of its relaxations (few
 // waves, registers to spare), reading the tile at each use instead waits for
-// LDS some twenty times per relaxation: @@.
+// LDS some twenty times per relaxation, 24 half-sweeps in one workgroup 65 us
+// against 57.
 template <typename TT, typename R> struct Hood {
     R h[12 * TT::ES];
     __device__ __forceinline__ R *centre() { return h + 4 * TT::ES; }

@@ -166,17 +166,23 @@ __device__ __forceinline__ Rhs rhs_of(const Desc &d)
 // Items start at multiples of NXCD and their tiles are renumbered so that an
 // XCD gets a contiguous band of tiles: neighbouring tiles, which read each
 // other's halos, share one L2.
+// (TS: the side of a square tile; it_cnt holds the tiles per row)
+template <int TS, typename IT> __device__ __forceinline__ int item_tile_at(const IT &it, int k, const Desc &d, int &i0, int &j0)
+{
+    const int tx = it_cnt(it, k), ty = (d.m2 + TS - 1) / TS;
+    const int n = tx * ty, lin = (int)blockIdx.x - it_start(it, k);
+    const int t = (n % NXCD == 0) ? (lin % NXCD) * (n / NXCD) + lin / NXCD : lin;
+    i0 = (t % tx) * TS;
+    j0 = (t / tx) * TS;
+    return lin < n;
+}
 template <typename TT, typename R, typename IT>
 __device__ __forceinline__ TT item_tile(R *sm, const IT &it, int k, const Desc &d)
 {
-    const int tx = it_cnt(it, k);
-    const int ty = (d.m2 + TY - 1) / TY;
-    const int n = tx * ty, lin = (int)blockIdx.x - it_start(it, k);
-    const int t = (n % NXCD == 0) ? (lin % NXCD) * (n / NXCD) + lin / NXCD : lin;
+    static_assert(TX == TY, "square tiles");
     TT T;
     T.s = sm;
-    T.i0 = (t % tx) * TX;
-    T.j0 = (t / tx) * TY;
+    item_tile_at<TX>(it, k, d, T.i0, T.j0);
     T.W = TX + 3;
     T.H = TY + 3;
     T.S = TILE_S;
@@ -221,21 +227,22 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_halfsweep_fine
 QN_KERNEL_PJ(k_halfsweep_fine, FINE_ATTR, (int colour, double omega), (colour, omega))
 
 // --------------------------------------------------------------------------
-// temporal blocking: one sweep (red, then black half-sweep of sec. 7.1, the
-// same arithmetic as two k_halfsweep launches) in one launch.  A workgroup
-// relaxes the red cells of its tile widened by two cells on every side (the
-// red results its black cells read; neighbouring workgroups compute the
-// overlap again), keeps them in LDS, then relaxes the black cells of its
-// tile.  Workgroups still read their neighbours' cells as halo while others
-// write, so the cell unknowns go from one set to the other (dir 0: c, mu, p
-// to c2, mu2, p2; dir 1 back) and the faces from buffer par to par ^ 1.
-#define FUSED_W (TX + 7)
-#define FUSED_H (TY + 7)
-#define FUSED_S (TX + 8)
+// temporal blocking: NS sweeps (each a red, then a black half-sweep of sec. 7.1,
+// the same arithmetic as two k_halfsweep launches) in one launch.  A workgroup
+// loads its tile of TS x TS cells with everything that its last half-sweep
+// depends on, and each half-sweep relaxes a region two cells narrower on every
+// side than the one before, in LDS (neighbouring workgroups compute the
+// overlap again); the last one covers the tile.  Workgroups still read their
+// neighbours' cells as halo while others write, so the cell unknowns go from
+// one set to the other (dir 0: c, mu, p to c2, mu2, p2; dir 1 back) and the
+// faces from buffer par to par ^ 1.
 #define FBLK (2 * TBLK)
-#define FUSED_DOUBLES (T_ES * FUSED_S * FUSED_H)
-static_assert(FUSED_DOUBLES * 8 <= 65536, "fused tile exceeds 64 KiB of LDS");
-static_assert((TX + 4) * (TY + 4) <= FBLK, "widened red region exceeds the workgroup");
+template <int NS, int TS> struct Fused {
+    static constexpr int EXT = 4 * NS - 2;         // the first region: the tile widened by EXT cells
+    static constexpr int W = TS + 2 * EXT + 3;     // rows and columns loaded
+    static constexpr int S = W + 1;                // row stride (even)
+    static constexpr int LDS = S * W;              // elements of LDS
+};
 
 // the coarse level's arrays that the coarse-grid correction reads, and the
 // fine level's boundary kinds, taken from the level descriptors once per
@@ -312,14 +319,14 @@ __device__ __forceinline__ void prolong_apply(const PSrc &C, const PRaw &r, int 
 }
 
 // the widened tile: every field at tile positions i0-1 .. i0+W-2 (level
-// coordinates; periodic images at their unwrapped positions), plus copies of
-// u and v in the fields T_NF, T_NF + 1 that the red pass overwrites.  A
-// periodic axis needs m >= TX + 3 so that a single wrap reaches every position.
-// With pc set (the first sweep of a post-smoothing), each unknown first takes
-// the coarse-grid correction P(w_H - R w_h) of its source (k_prolong's
-// arithmetic); the sweep writes every unknown of the level, so the corrected
-// values need no store of their own.
-__device__ __forceinline__ void fused_load(const Phys &P, const View &L, const Tile &T, const PSrc *pc = nullptr)
+// coordinates; periodic images at their unwrapped positions), the faces in both
+// slots.  A periodic axis needs m >= TS + EXT + 1 so that a single wrap reaches
+// every position.  With prolong set (the first sweep of a post-smoothing), each
+// unknown first takes the coarse-grid correction P(w_H - R w_h) of its source
+// (k_prolong's arithmetic); the sweeps write every unknown of the level, so
+// the corrected values need no store of their own.
+// (One element at a time: nearly all threads have one only.)
+__device__ __forceinline__ void fused_load(const Phys &P, const View &L, const Tile &T, bool prolong, const PSrc &pc)
 {
     const int n = T.W * T.H;
     for (int e = threadIdx.x; e < n; e += FBLK) {
@@ -328,7 +335,6 @@ __device__ __forceinline__ void fused_load(const Phys &P, const View &L, const T
         if (L.bcx) i = wrapi(i, L.m1);
         if (L.bcy) j = wrapi(j, L.m2);
         const TileSrc q = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        double *s = T.s + (b * T.S + a) * T_ES;
         if (q.sc == 0) {
             tile_zero(T, b * T.S + a);
             continue;
@@ -337,66 +343,85 @@ __device__ __forceinline__ void fused_load(const Phys &P, const View &L, const T
                         lda<1>(L.v, q.v), lda<1>(L.cn, q.c), lda<1>(L.un, q.u), lda<1>(L.vn, q.v) };
         PRaw raw = {};
         int iu = 0, iv = 0, jv = 0;
-        if (pc) {
+        if (prolong) {
             iu = q.u % L.pitch;
             iv = q.v % L.pitch;
             jv = q.v / L.pitch;
-            raw = prolong_load(*pc, q.c % L.pitch, q.c / L.pitch, iu, q.u / L.pitch, iv, jv);
+            raw = prolong_load(pc, q.c % L.pitch, q.c / L.pitch, iu, q.u / L.pitch, iv, jv);
         }
         // every load above is issued before anything uses a loaded value (the
         // scheduler otherwise interleaves uses with the loads, one memory
         // latency each)
         __builtin_amdgcn_sched_barrier(0);
-        if (pc) {
+        if (prolong) {
             double rc, rm, rp, du, dv;
-            prolong_apply(*pc, raw, iu, iv, jv, rc, rm, rp, du, dv);
+            prolong_apply(pc, raw, iu, iv, jv, rc, rm, rp, du, dv);
             v[0] += rc;
             v[1] += rm;
             v[2] += rp;
             if (q.su) v[3] += du;
             if (q.sv) v[4] += dv;
         }
+        double *s = T.s + (b * T.S + a) * T_ES;
         tile_put(P, s, q.su, q.sv, v);
         s[T_U2] = s[T_U];
         s[T_V2] = s[T_V];
     }
 }
-// after the red pass: the new faces become the snapshot of the black pass,
-// and the images across walls follow their sources (ldc clamps a cell to the
-// wall row; ldu, ldv zero a face on or beyond a wall and reflect a
-// tangential ghost).  Periodic images were relaxed in place.
-__device__ __forceinline__ void fused_refresh(const View &L, const Tile &T)
+// The images across walls after a half-sweep whose faces went to slot `slot`:
+// the rows and columns next to the level that the equations of a cell of the
+// level read (-1, and m, m + 1) follow their sources (ldc clamps a cell to the
+// wall row; ldu, ldv reflect a tangential ghost; faces on and beyond a wall
+// stay zero).  Periodic images were relaxed in place.  put copies one
+// element's image.
+template <typename TT, typename F> __device__ __forceinline__ void wall_images(const TT &T, int m1, int m2, int bcx, int bcy, F put)
 {
-    const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += FBLK) {
-        const int b = e / T.W, a = e - b * T.W;
-        const int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
-        const bool gx = !L.bcx && (i < 0 || i >= L.m1), gy = !L.bcy && (j < 0 || j >= L.m2);
-        const int si = gx ? (i < 0 ? 0 : L.m1 - 1) : i, sj = gy ? (j < 0 ? 0 : L.m2 - 1) : j;
-        const int su = (!L.bcx && (i <= 0 || i >= L.m1)) ? 0 : (gy ? -1 : 1);
-        const int sv = (!L.bcy && (j <= 0 || j >= L.m2)) ? 0 : (gx ? -1 : 1);
-        // every value the element may take, before any store (an image's
-        // source q is never an image, so no element read here is written)
-        const double *q = T.at(si, sj);
-        double *s = T.s + (b * T.S + a) * T_ES;
-        const double u = T.at(i, sj)[T_U2], v = T.at(si, j)[T_V2], c = q[T_C], mu = q[T_MU], p = q[T_P], rs = q[T_RS];
-        __builtin_amdgcn_sched_barrier(0);
-        s[T_U] = signed_val(su, u);
-        s[T_V] = signed_val(sv, v);
-        if (gx || gy) {
-            s[T_C] = c;
-            s[T_MU] = mu;
-            s[T_P] = p;
-            s[T_RS] = rs;
+    const int je = T.j0 + T.H - 2, ie = T.i0 + T.W - 2; // last row and column of the tile
+    // rows -1, m2, m2 + 1 and columns -1, m1, m1 + 1 that the tile holds
+    const int rb = !bcy && T.j0 <= 0, nr = rb + (bcy ? 0 : min(max(je - m2 + 1, 0), 2));
+    const int cl = !bcx && T.i0 <= 0, nc = cl + (bcx ? 0 : min(max(ie - m1 + 1, 0), 2));
+    for (int e = threadIdx.x; e < nr * T.W + nc * T.H; e += FBLK) {
+        if (e < nr * T.W) {
+            const int r = e / T.W, i = T.i0 - 1 + (e - r * T.W), j = r < rb ? -1 : m2 + r - rb;
+            if (bcx || (i >= -1 && i <= m1 + 1)) put(i, j, bcx ? i : min(max(i, 0), m1 - 1), j < 0 ? 0 : m2 - 1);
+        } else {
+            const int f = e - nr * T.W, c = f / T.H, j = T.j0 - 1 + (f - c * T.H), i = c < cl ? -1 : m1 + c - cl;
+            if (bcy || (j >= 0 && j < m2)) put(i, j, i < 0 ? 0 : m1 - 1, j);
         }
     }
 }
-template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused_body(const IT &it, int dir, double omega, int prolong)
+// whether the tile has such rows or columns
+template <typename TT> __device__ __forceinline__ bool at_wall(const TT &T, int m1, int m2, int bcx, int bcy)
 {
-    TILE_LDS double sm[FUSED_DOUBLES];
+    return (!bcx && (T.i0 <= 0 || T.i0 + T.W - 2 >= m1)) || (!bcy && (T.j0 <= 0 || T.j0 + T.H - 2 >= m2));
+}
+__device__ __forceinline__ void fused_images(const View &L, const Tile &T, int slot)
+{
+    const int fu = slot ? T_U2 : T_U, fv = slot ? T_V2 : T_V;
+    wall_images(T, L.m1, L.m2, L.bcx, L.bcy, [&](int i, int j, int si, int sj) {
+        // every value the element may take, before any store (an image's
+        // source is never an image, so no element read here is written)
+        const double *q = T.at(si, sj);
+        const double u = T.at(i, sj)[fu], v = T.at(si, j)[fv], c = q[T_C], mu = q[T_MU], p = q[T_P], rs = q[T_RS];
+        double *s = T.at(i, j);
+        const bool gx = si != i, gy = sj != j;
+        s[T_C] = c;
+        s[T_MU] = mu;
+        s[T_P] = p;
+        s[T_RS] = rs;
+        s[fu] = (!L.bcx && (i <= 0 || i >= L.m1)) ? 0.0 : (gy ? -u : u);
+        s[fv] = (!L.bcy && (j <= 0 || j >= L.m2)) ? 0.0 : (gx ? -v : v);
+    });
+}
+template <bool PJ, int NS, int TS, typename IT>
+__device__ __forceinline__ void fused_body(const IT &it, int dir, double omega, int prolong)
+{
+    typedef Fused<NS, TS> G;
+    extern __shared__ __attribute__((aligned(16))) double sm[];
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
-    if (!tile_valid(it, k, d)) return;
+    int i0, j0; // of the tile
+    if (!item_tile_at<TS>(it, k, d, i0, j0)) return;
     const Phys P = d.P;
     const Kon<double> K = d.K;
     const int par = it_par(it, k);
@@ -407,45 +432,49 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused_body(
     } else {
         O.c = d.c2; O.mu = d.mu2; O.p = d.p2;
     }
-    const Tile T0 = item_tile<Tile>(sm, it, k, d);
     Tile T;
-    T.s = sm; T.i0 = T0.i0 - 2; T.j0 = T0.j0 - 2; T.W = FUSED_W; T.H = FUSED_H; T.S = FUSED_S;
+    T.s = sm; T.i0 = i0 - G::EXT; T.j0 = j0 - G::EXT; T.W = G::W; T.H = G::W; T.S = G::S;
     const Rhs F = rhs_of(d);
     double *const un = d.ub[par ^ 1], *const vn = d.vb[par ^ 1];
-    if (prolong) {
-        const PSrc ps = psrc_of(d, &d + 1, it_cpar(it, k));
-        fused_load(P, L, T, &ps);
-    } else {
-        fused_load(P, L, T);
-    }
+    PSrc ps = {};
+    if (prolong) ps = psrc_of(d, &d + 1, it_cpar(it, k));
+    fused_load(P, L, T, prolong, ps);
+    const bool wall = at_wall(T, L.m1, L.m2, L.bcx, L.bcy);
     __syncthreads();
-    const int pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
-    {
-        // red: cells with i + j even of i0-2 .. i0+TX+1, j0-2 .. j0+TY+1
-        const int lj = pr / ((TX + 4) / 2), kk = pr - lj * ((TX + 4) / 2);
-        const int tj = T0.j0 - 2 + lj;
-        const int ti = T0.i0 - 2 + 2 * kk + (tj & 1);
-        const bool in = lj < TY + 4 && (L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2));
-        if (in) {
-            const int i = L.bcx ? wrapi(ti, L.m1) : ti, j = L.bcy ? wrapi(tj, L.m2) : tj;
-            relax_cell<PJ, 1, 1, true>(P, K, L, T, F, nullptr, nullptr, i, j, ti, tj, hlf, omega, 1.0);
+    const int hlf = threadIdx.x & 1;
+    // a half-sweep of the region widened by ext cells
+    auto half = [&](auto cext, auto ccol) {
+        constexpr int ext = cext.value, colour = ccol.value, w = TS + 2 * ext;
+        for (int pr = threadIdx.x >> 1; pr < w * w / 2; pr += FBLK / 2) {
+            const int lj = pr / (w / 2), kk = pr - lj * (w / 2);
+            const int tj = j0 - ext + lj, ti = i0 - ext + 2 * kk + ((tj + colour) & 1);
+            if ((L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2))) {
+                const int i = L.bcx ? wrapi(ti, L.m1) : ti, j = L.bcy ? wrapi(tj, L.m2) : tj;
+                relax_cell<PJ, 1, 1, true>(P, K, L, T, F, nullptr, nullptr, i, j, ti, tj, hlf, omega, 1.0, colour);
+            }
         }
+        __syncthreads();
+        if (wall) {
+            fused_images(L, T, colour ^ 1);
+            __syncthreads();
+        }
+    };
+    typedef std::integral_constant<int, 0> Red;
+    typedef std::integral_constant<int, 1> Black;
+    half(std::integral_constant<int, G::EXT>(), Red());
+    if (NS == 2) {
+        half(std::integral_constant<int, G::EXT - 2>(), Black());
+        half(std::integral_constant<int, 2>(), Red());
     }
-    __syncthreads();
-    fused_refresh(L, T);
-    __syncthreads();
-    if (threadIdx.x < TBLK) {
+    if (threadIdx.x < TS * TS) {
         // black cells of the tile: the box faces go to buffer par ^ 1
-        const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
-        const int j = T0.j0 + lj;
-        const int i = T0.i0 + 2 * kk + ((j + 1) & 1);
-        if (i < L.m1 && j < L.m2) relax_cell<PJ, 0, 1, true>(P, K, O, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
-    } else {
+        const int pr = threadIdx.x >> 1, lj = pr / (TS / 2), kk = pr - lj * (TS / 2);
+        const int j = j0 + lj, i = i0 + 2 * kk + ((j + 1) & 1);
+        if (i < L.m1 && j < L.m2) relax_cell<PJ, 0, 1, true>(P, K, O, T, F, un, vn, i, j, i, j, hlf, omega, 1.0, 1);
+    } else if (threadIdx.x < 2 * TS * TS) {
         // red cells of the tile: their final values
-        const int q = pr - TBLK / 2;
-        const int lj = q / (TX / 2), kk = q - lj * (TX / 2);
-        const int j = T0.j0 + lj;
-        const int i = T0.i0 + 2 * kk + (j & 1);
+        const int q = (threadIdx.x - TS * TS) >> 1, lj = q / (TS / 2), kk = q - lj * (TS / 2);
+        const int j = j0 + lj, i = i0 + 2 * kk + (j & 1);
         if (i < L.m1 && j < L.m2) {
             const double *e = T.at(i, j);
             const size_t g = (size_t)j * L.pitch + i;
@@ -458,7 +487,16 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused_body(
         }
     }
 }
+template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused_body(const IT &it, int dir, double omega, int prolong)
+{
+    fused_body<PJ, 1, 16>(it, dir, omega, prolong);
+}
 QN_KERNEL_PJ(k_hs_fused, __launch_bounds__(FBLK), (int dir, double omega, int prolong), (dir, omega, prolong))
+template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused2_body(const IT &it, int dir, double omega, int prolong)
+{
+    fused_body<PJ, 2, 8>(it, dir, omega, prolong);
+}
+QN_KERNEL_PJ(k_hs_fused2, __launch_bounds__(FBLK), (int dir, double omega, int prolong), (dir, omega, prolong))
 
 // plain copy, used to measure the copy bandwidth and to calibrate counters
 __global__ __launch_bounds__(BLK) void k_copy_probe(const double *__restrict__ a, double *__restrict__ b, size_t n)
@@ -497,7 +535,7 @@ __device__ __forceinline__ double quad_sum(double x)
               hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x4E, 0xF, 0xF, false);
     return x + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
-template <bool PJ, typename IT> __device__ __forceinline__ void k_restrict_body(const IT &it)
+template <bool PJ, typename IT> __device__ __forceinline__ void k_restrict_body(const IT &it, int set)
 {
     TILE_LDS double sm[TILE_DOUBLES];
     TILE_LDS double smc[T_ES * CTILE_S * (TY / 2 + 3)];
@@ -508,7 +546,10 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_restrict_body(
     const Desc &C = (&d)[1];
     const Phys P = d.P;
     const int cp = it_cpar(it, k);
-    const View Lf = view_of(d, it_par(it, k));
+    View Lf = view_of(d, it_par(it, k));
+    if (set) { // the pre-smoothing left the cells in the second set
+        Lf.c = d.c2; Lf.mu = d.mu2; Lf.p = d.p2;
+    }
     const View Lc = view_of(C, cp);
     const Tile T = item_tile<Tile>(sm, it, k, d);
     // the coarse tile of R w, from the fine arrays directly (its halo lies
@@ -581,7 +622,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_restrict_body(
     sta<1>(C.fu, q, u_unk(Lc, I) ? 0.5 * part[3][cc] - r.u : 0.0);
     sta<1>(C.fv, q, v_unk(Lc, J) ? 0.5 * part[4][cc] - r.v : 0.0);
 }
-QN_KERNEL_PJ(k_restrict, __launch_bounds__(RBLK), (), ())
+QN_KERNEL_PJ(k_restrict, __launch_bounds__(RBLK), (int set), (set))
 
 // --------------------------------------------------------------------------
 // The bottom of a V-cycle: a level and every coarser one in one workgroup per
@@ -592,8 +633,8 @@ QN_KERNEL_PJ(k_restrict, __launch_bounds__(RBLK), (), ())
 // long as its dependent chain; a launch per step also paid for its start (two
 // memory round trips), for the level's way from and to memory and for an
 // image map of the whole tile.  Per cycle of the 256 x 512 droplet (16 x 32, 8 x 16,
-// 4 x 8 cells: 24 half-sweeps), seven launches of 20.8 and 6.4 us, @@ us in all,
-// became one of @@ us (MI355X).
+// 4 x 8 cells: 24 half-sweeps), five smoothing launches of 20.8 us and two restrictions of
+// 6.4 us became one launch of 57 us (MI355X).
 //
 // LDS of a level: its tile (rows of an even number of elements), the
 // right-hand sides, the restricted iterate (coarser levels), the images.

@@ -60,64 +60,81 @@ static bool single_kernel_op(int kind)
              || kind == OP_DIAG);
 }
 
-// nu sweeps of level l: one launch per colour half-sweep or, on a level marked
-// in fuse, one launch per sweep (an even number of them, so that the cell
-// unknowns end in the set they started in; an odd last sweep takes two
-// half-sweeps), with the same arithmetic in the same order
-static void smooth_ops(int l, int nu, int hs_kind, unsigned fuse, std::vector<Op> &out)
+// how a level's sweeps are launched: by half-sweeps, one fused sweep per
+// launch (on tiles of 16 x 16 cells), or two (of 8 x 8)
+enum { SM_HALF = 0, SM_ONE, SM_TWO };
+#define MAX_SWEEPS 16
+// colour field of a fused launch: direction of the cell sets, and
+#define FUSED_PROLONG 2 // the level takes the coarse-grid correction as it is loaded
+#define FUSED_TWO 4     // two sweeps
+// the pre- or post-smoothing of a level: nu sweeps, of which as many pairs as
+// `twos` says run as one launch each.  Every fused launch moves the cell
+// unknowns to the other set (dir); an odd last sweep takes two half-sweeps.
+static void smooth_ops(int l, int nu, int mode, int twos, int hs_kind, int &dir, std::vector<Op> &out)
 {
     const int fused_kind = hs_kind == OP_MXHS ? OP_MXFUSED : OP_FUSED;
     int s = 0;
-    if ((fuse >> l) & 1)
+    if (mode != SM_HALF)
         for (; s + 1 < nu; s += 2) {
-            out.push_back({ fused_kind, l, 0 });
-            out.push_back({ fused_kind, l, 1 });
+            if (twos-- > 0) {
+                out.push_back({ fused_kind, l, dir | FUSED_TWO });
+                dir ^= 1;
+            } else {
+                out.push_back({ fused_kind, l, dir });
+                out.push_back({ fused_kind, l, dir ^ 1 });
+            }
         }
     for (; s < nu; s++) {
         out.push_back({ hs_kind, l, 0 });
         out.push_back({ hs_kind, l, 1 });
     }
 }
-// prolongation onto level l, then its post-smoothing; the first fused sweep of
-// an FP64 level takes the correction as it loads the level (colour field 2 +
-// direction 0), which saves the prolongation launch
-#define MAX_SWEEPS 16
-#define FUSED_PROLONG 2
-static void prolong_smooth_ops(int l, int nu, int pr_kind, int hs_kind, unsigned fuse, std::vector<Op> &out)
+// launches of two sweeps in the pre- and post-smoothing of a level: as many as
+// leave the cell unknowns in the first set after the cycle, and in the second
+// one after the pre-smoothing only if a fused launch follows that reads them
+static void two_sweeps(int mode, int nu1, int nu2, int &t1, int &t2)
 {
-    if (pr_kind == OP_PROLONG && nu >= 2 && ((fuse >> l) & 1)) {
-        const size_t first = out.size();
-        smooth_ops(l, nu, hs_kind, fuse, out);
-        out[first].colour |= FUSED_PROLONG;
-        return;
-    }
-    out.push_back({ pr_kind, l, 0 });
-    smooth_ops(l, nu, hs_kind, fuse, out);
+    t1 = t2 = 0;
+    if (mode != SM_TWO || nu1 < 2 || nu2 < 2 || (nu1 & 1) || (nu2 & 1)) return;
+    t1 = nu1 / 2;
+    t2 = nu2 / 2;
+    if ((t1 + t2) & 1) t1--;
 }
 
-// one V-cycle whose levels from `bottom` on run in one workgroup, ending with
-// the residual norms and the pbar mean removal
-static void vcycle_program(int bottom, int nu1, int nu2, unsigned fuse, bool acc, std::vector<Op> &out)
+// the levels above `bottom` of a V-cycle, whose levels from there on run in one
+// workgroup (coarse_kind)
+static void levels_program(int bottom, int nu1, int nu2, const int *mode, int hs_kind, int restrict_kind, int coarse_kind,
+                           int prolong_kind, std::vector<Op> &out)
 {
+    int dir[16] = {}, t1, t2;
     for (int l = 0; l < bottom; l++) {
-        smooth_ops(l, nu1, OP_HS, fuse, out);
-        out.push_back({ OP_RESTRICT, l, 0 }); // with the coarse FAS right-hand side
+        two_sweeps(mode[l], nu1, nu2, t1, t2);
+        smooth_ops(l, nu1, mode[l], t1, hs_kind, dir[l], out);
+        out.push_back({ restrict_kind, l, dir[l] }); // (FP64: with the coarse FAS right-hand side)
     }
-    out.push_back({ OP_COARSE, bottom, nu1 + MAX_SWEEPS * nu2 });
-    for (int l = bottom - 1; l >= 0; l--) prolong_smooth_ops(l, nu2, OP_PROLONG, OP_HS, fuse, out);
+    out.push_back({ coarse_kind, bottom, nu1 + MAX_SWEEPS * nu2 });
+    for (int l = bottom - 1; l >= 0; l--) {
+        // the first fused sweep takes the correction as it loads the level
+        const bool fold = mode[l] != SM_HALF && nu2 >= 2;
+        if (!fold) out.push_back({ prolong_kind, l, 0 });
+        two_sweeps(mode[l], nu1, nu2, t1, t2);
+        const size_t first = out.size();
+        smooth_ops(l, nu2, mode[l], t2, hs_kind, dir[l], out);
+        if (fold) out[first].colour |= FUSED_PROLONG;
+    }
+}
+// one V-cycle, ending with the residual norms and the pbar mean removal
+static void vcycle_program(int bottom, int nu1, int nu2, const int *mode, bool acc, std::vector<Op> &out)
+{
+    levels_program(bottom, nu1, nu2, mode, OP_HS, OP_RESTRICT, OP_COARSE, OP_PROLONG, out);
     out.push_back({ acc ? OP_NORMACC : OP_NORM, 0, 0 });
 }
 // one outer iteration of the mixed-precision step: an FP32 correction
 // V-cycle on J(w^) delta = r, w += delta in FP64, then the FP64 residual
 // (which also prepares the next cycle) and the pbar mean removal
-static void mixed_program(int bottom, int nu1, int nu2, unsigned fuse, bool acc, std::vector<Op> &out)
+static void mixed_program(int bottom, int nu1, int nu2, const int *mode, bool acc, std::vector<Op> &out)
 {
-    for (int l = 0; l < bottom; l++) {
-        smooth_ops(l, nu1, OP_MXHS, fuse, out);
-        out.push_back({ OP_MXRESTRICT, l, 0 });
-    }
-    out.push_back({ OP_MXCOARSE, bottom, nu1 + MAX_SWEEPS * nu2 });
-    for (int l = bottom - 1; l >= 0; l--) prolong_smooth_ops(l, nu2, OP_MXPROLONG, OP_MXHS, fuse, out);
+    levels_program(bottom, nu1, nu2, mode, OP_MXHS, OP_MXRESTRICT, OP_MXCOARSE, OP_MXPROLONG, out);
     out.push_back({ OP_MXUPDATE, 0, 0 });
     out.push_back({ acc ? OP_NORMACC : OP_NORM, 0, 0 });
 }
@@ -229,10 +246,10 @@ static size_t bottom_lds(const qnsch_ctx *x, int l)
 }
 // the first level from which every level fits in the LDS of a workgroup
 // together (never the finest one, unless it is the coarsest too) and has at
-// most 512 cells of a colour; lds_max is set at context creation.  16 x 32 and
-// below in FP64: 148 KiB.  (The LDS is the tighter limit but for FP32 levels
-// of 24 x 48: 576 cells of a colour take three passes of a workgroup's lane
-// pairs per half-sweep, @@.)
+// most 512 cells of a colour, two passes of a workgroup's lane pairs; lds_max is
+// set at context creation.  16 x 32 and below in FP64: 148 KiB.  (The LDS is
+// the tighter limit but for FP32 levels, where 24 x 48 cells would fit but
+// would take three passes per half-sweep.)
 static int bottom_level(const qnsch_ctx *x)
 {
     int l = x->nlev - 1;
@@ -242,33 +259,34 @@ static int bottom_level(const qnsch_ctx *x)
 // whether the opts give the levels a second set of cell unknowns (FP64) or
 // cell corrections (mixed precision)
 static bool two_sets(const qnsch_opts &o) { return o.blocking > 0; }
-// levels whose sweeps run fused (bit l): those smoothed by half-sweep
-// launches (finer than the bottom levels) with a periodic axis at least TX + 3 (TY + 3) cells
-// long (the widened tile wraps once) and few enough tiles: coarse levels with
-// at most two tiles per compute unit; the finest level with at most one
-// (blocking 1), or two (blocking 2).  A fused sweep pays for its redundant red
-// work (200 red cells per tile instead of 128, with the workgroup's LDS tile
-// widened) with a launch less, which is worth it only where a launch's fixed
-// cost is as large as its relaxation.  Measured on one MI355X (alternating
-// settings on one box): fusing the finest level too, 32 x 64 capillary (8
-// tiles) 0.326-0.329 against 0.340-0.341 ms per step, 64 x 128 droplet (32
-// tiles) 1.354-1.357 against 1.389-1.392, 128 x 256 (128 tiles) 1.901
-// against 1.965-1.966, but 256 x 512 (512 tiles, two per CU) 2.716-2.722
+// How the sweeps of level l, finer than the bottom levels, are launched.
+// Fused launches pay for their redundant work (the region of a half-sweep is
+// two cells wider on every side than that of the next one) with launches less,
+// which is worth it only where a launch's fixed cost is as large as its
+// relaxation: on levels with few tiles per compute unit.  One sweep a launch:
+// coarse levels with at most two 16 x 16 tiles per unit; the finest level
+// with at most one (blocking 1), or two (blocking 2).  Measured on one MI355X
+// (alternating settings on one box): fusing the finest level too, 32 x 64
+// capillary (8 tiles) 0.326-0.329 against 0.340-0.341 ms per step, 64 x 128
+// droplet (32 tiles) 1.354-1.357 against 1.389-1.392, 128 x 256 (128 tiles)
+// 1.901 against 1.965-1.966, but 256 x 512 (512 tiles, two per CU) 2.716-2.722
 // against 2.652-2.656 ms and 512 x 2048 (4096 tiles) 17 % slower.
-static unsigned fused_levels(const qnsch_ctx *x)
+// Two sweeps a launch, on 8 x 8 tiles: where every tile has a unit of its own
+// (64 x 128 cells: 15.0 us against 2 x 9.6 us, FP32 12.6 against 2 x 7.9; on
+// 16 x 16 tiles, which 128 x 256 would need, 22.4 against 2 x 10.1: the first
+// regions take two passes of a workgroup's lane pairs).
+// A periodic axis must be long enough for the widened tile to wrap once.
+static int smooth_mode(const qnsch_ctx *x, int l)
 {
-    if (!two_sets(x->opt)) return 0u;
-    unsigned m = 0;
-    const int bottom = bottom_level(x);
-    for (int l = 0; l < bottom; l++) {
-        const DLev &D = x->L[l];
-        if ((x->g.bc_x == QNSCH_BC_PERIODIC && D.m1 < TX + 3) || (x->g.bc_y == QNSCH_BC_PERIODIC && D.m2 < TY + 3))
-            continue;
-        const int tiles = ((D.m1 + TX - 1) / TX) * ((D.m2 + TY - 1) / TY);
-        if (tiles > (l > 0 || x->opt.blocking >= 2 ? 2 : 1) * x->ncu) continue;
-        m |= 1u << l;
-    }
-    return m;
+    if (!two_sets(x->opt)) return SM_HALF;
+    const DLev &D = x->L[l];
+    auto tiles = [&](int ts) { return ((D.m1 + ts - 1) / ts) * ((D.m2 + ts - 1) / ts); };
+    auto wraps = [&](int n) {
+        return (x->g.bc_x != QNSCH_BC_PERIODIC || D.m1 >= n) && (x->g.bc_y != QNSCH_BC_PERIODIC || D.m2 >= n);
+    };
+    if (tiles(8) <= x->ncu && wraps(8 + Fused<2, 8>::EXT + 1)) return SM_TWO;
+    if (tiles(16) <= (l > 0 || x->opt.blocking >= 2 ? 2 : 1) * x->ncu && wraps(16 + Fused<1, 16>::EXT + 1)) return SM_ONE;
+    return SM_HALF;
 }
 // one cycle; with acceleration its residual reduction records the result,
 // from the second cycle of a step on (acc_record_launch skips the first: its
@@ -279,8 +297,11 @@ static unsigned fused_levels(const qnsch_ctx *x)
 static void cycle_program(const qnsch_ctx *x, std::vector<Op> &out)
 {
     const bool rec = x->opt.accel > 0;
-    if (is_mixed(x)) mixed_program(bottom_level(x), x->opt.nu1, x->opt.nu2, fused_levels(x), rec, out);
-    else vcycle_program(bottom_level(x), x->opt.nu1, x->opt.nu2, fused_levels(x), rec, out);
+    const int bottom = bottom_level(x);
+    int mode[16] = {};
+    for (int l = 0; l < bottom; l++) mode[l] = smooth_mode(x, l);
+    if (is_mixed(x)) mixed_program(bottom, x->opt.nu1, x->opt.nu2, mode, rec, out);
+    else vcycle_program(bottom, x->opt.nu1, x->opt.nu2, mode, rec, out);
 }
 
 #define HIPCHK(ctx, x)                                                                        \
@@ -293,8 +314,8 @@ static void cycle_program(const qnsch_ctx *x, std::vector<Op> &out)
     } while (0)
 
 static unsigned nblocks(size_t n) { return (unsigned)((n + BLK - 1) / BLK); }
-static int tiles_x(int m1) { return (m1 + TX - 1) / TX; }
-static int tiles_y(int m2) { return (m2 + TY - 1) / TY; }
+static int tiles_x(int m1, int ts = TX) { return (m1 + ts - 1) / ts; }
+static int tiles_y(int m2, int ts = TY) { return (m2 + ts - 1) / ts; }
 
 // ---------------------------------------------------------------------------
 // work lists
@@ -307,21 +328,21 @@ struct ItemList {
     ItemList() { memset(&it, 0, sizeof(it)); }
 };
 
-// workgroups of an operation on (context, level)
-static int op_blocks(const qnsch_ctx *x, int kind, int l)
+// workgroups of an operation on (context, level); ts: side of its tiles
+static int op_blocks(const qnsch_ctx *x, int kind, int l, int ts = TX)
 {
     const DLev &D = x->L[l];
     switch (kind) {
     case OP_HS: case OP_RESTRICT: case OP_NORM: case OP_NORM0: case OP_NORMACC: case OP_MXHS:
     case OP_MXRESTRICT: case OP_FUSED: case OP_MXFUSED:
-        return tiles_x(D.m1) * tiles_y(D.m2);
+        return tiles_x(D.m1, ts) * tiles_y(D.m2, ts);
     case OP_COARSE: case OP_MXCOARSE: return 1;
     case OP_RN: case OP_MXRN: return (int)nblocks((size_t)x->L[l + 1].m1 * x->L[l + 1].m2);
     default: return (int)nblocks((size_t)D.m1 * D.m2);
     }
 }
 
-static void add_item(ItemList &W, const qnsch_ctx *x, int kind, int l)
+static void add_item(ItemList &W, const qnsch_ctx *x, int kind, int l, int ts = TX)
 {
     Items &it = W.it;
     const int start = ((W.blocks + NXCD - 1) / NXCD) * NXCD;
@@ -330,9 +351,9 @@ static void add_item(ItemList &W, const qnsch_ctx *x, int kind, int l)
     it.d[k] = x->dd + l;
     it.par[k] = x->L[l].cur;
     it.cpar[k] = l + 1 < x->nlev ? x->L[l + 1].cur : 0;
-    it.tx[k] = tiles_x(x->L[l].m1);
+    it.tx[k] = tiles_x(x->L[l].m1, ts);
     it.acc[k] = -1;
-    W.blocks = start + op_blocks(x, kind, l);
+    W.blocks = start + op_blocks(x, kind, l, ts);
     it.n = k + 1;
     it.start[k + 1] = W.blocks;
     if (l != 0) W.all_fine = false;
@@ -552,7 +573,8 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
         const size_t e = std::min(v.size(), b + MAXITEMS);
         std::vector<std::pair<qnsch_ctx *, int>> part(v.begin() + b, v.begin() + e);
         ItemList W;
-        for (auto &pe : part) add_item(W, pe.first, kind, pe.second);
+        const bool fused = kind == OP_FUSED || kind == OP_MXFUSED;
+        for (auto &pe : part) add_item(W, pe.first, kind, pe.second, fused && (colour & FUSED_TWO) ? 8 : TX);
         const double omega = x0->opt.vanka_omega;
         const bool pj = x0->opt.scheme == QNSCH_PROJECTION;
         const int tag = prof_tag(kind, part);
@@ -584,22 +606,31 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
             break;
         }
         case OP_FUSED: {
-            KLAUNCH_PJ(k_hs_fused, W, dim3(W.blocks), dim3(FBLK), 0, s, colour & 1, omega, colour >> 1);
+            const int dir = colour & 1, pro = colour & FUSED_PROLONG;
+            const dim3 gr(W.blocks), bl(FBLK);
+            constexpr size_t e = T_ES * sizeof(double);
+            if (!(colour & FUSED_TWO)) KLAUNCH_PJ(k_hs_fused, W, gr, bl, (Fused<1, 16>::LDS * e), s, dir, omega, pro);
+            else KLAUNCH_PJ(k_hs_fused2, W, gr, bl, (Fused<2, 8>::LDS * e), s, dir, omega, pro);
             for (auto &pe : part) pe.first->L[pe.second].cur ^= 1;
             break;
         }
         case OP_MXFUSED: {
-            KLAUNCH(k_mx_fused, W, dim3(W.blocks), dim3(FBLK), 0, s, colour, (float)omega);
+            const int dir = colour & 1, pro = colour & FUSED_PROLONG;
+            const dim3 gr(W.blocks), bl(FBLK);
+            constexpr size_t e = L_ES * sizeof(float);
+            const float om = (float)omega;
+            if (!(colour & FUSED_TWO)) KLAUNCH(k_mx_fused, W, gr, bl, (Fused<1, 16>::LDS * e), s, dir, om, pro);
+            else KLAUNCH(k_mx_fused2, W, gr, bl, (Fused<2, 8>::LDS * e), s, dir, om, pro);
             for (auto &pe : part) pe.first->L[pe.second].cur ^= 1;
             break;
         }
-        case OP_RESTRICT: KLAUNCH_PJ(k_restrict, W, dim3(W.blocks), dim3(RBLK), 0, s); break;
+        case OP_RESTRICT: KLAUNCH_PJ(k_restrict, W, dim3(W.blocks), dim3(RBLK), 0, s, colour); break;
         case OP_COARSE:
             KLAUNCH_PJ(k_bottom, W, dim3(W.blocks), dim3(BOT), W.lds, s, colour % MAX_SWEEPS, colour / MAX_SWEEPS,
                        x0->opt.nu_coarse, omega, x0->opt.coarse_omega);
             break;
         case OP_PROLONG: KLAUNCH(k_prolong, W, dim3(W.blocks), dim3(BLK), 0, s); break;
-        case OP_MXRESTRICT: KLAUNCH(k_mx_restrict, W, dim3(W.blocks), dim3(TBLK), 0, s); break;
+        case OP_MXRESTRICT: KLAUNCH(k_mx_restrict, W, dim3(W.blocks), dim3(TBLK), 0, s, colour); break;
         case OP_MXCOARSE:
             KLAUNCH(k_mx_bottom, W, dim3(W.blocks), dim3(BOT), W.lds, s, colour % MAX_SWEEPS, colour / MAX_SWEEPS,
                     x0->opt.nu_coarse, (float)omega, (float)x0->opt.coarse_omega);
@@ -1076,13 +1107,14 @@ static size_t device_lds_max()
     if (cache[dev]) return cache[dev];
     int v = 0;
     size_t r = 65536;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 65536
-        && hipFuncSetAttribute((const void *)k_bottom_n, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
-        && hipFuncSetAttribute((const void *)k_bottom<false>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
-        && hipFuncSetAttribute((const void *)k_bottom<true>, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
-        && hipFuncSetAttribute((const void *)k_mx_bottom_n, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess
-        && hipFuncSetAttribute((const void *)k_mx_bottom, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess)
-        r = (size_t)v;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > 65536) {
+        const void *const big[] = { (const void *)k_bottom<false>, (const void *)k_bottom<true>, (const void *)k_bottom_n,
+                                    (const void *)k_mx_bottom, (const void *)k_mx_bottom_n };
+        bool ok = true;
+        for (const void *f : big) ok = ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, v) == hipSuccess;
+        if (ok)
+            r = (size_t)v;
+    }
     (void)hipGetLastError();
     cache[dev] = r;
     return r;

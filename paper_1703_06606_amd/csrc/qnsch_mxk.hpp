@@ -58,13 +58,70 @@ template <typename IT> __device__ __forceinline__ void k_mx_halfsweep_fine_body(
 }
 QN_KERNEL(k_mx_halfsweep_fine, HS_ATTR, (int colour, float omega), (colour, omega))
 
-// temporal blocking of the correction smoother: one red + black sweep per
-// launch, as k_hs_fused (the widened tile in LDS, the cell corrections from
-// one set to the other, the face corrections from buffer par to par ^ 1)
-#define MX_FUSED_FLOATS (L_ES * FUSED_S * FUSED_H)
-static_assert(MX_FUSED_FLOATS * 4 <= 65536, "fused FP32 tile exceeds 64 KiB of LDS");
+// P delta_H of the FP32 correction: cells piecewise constant, faces as in
+// prolong_load / prolong_apply (a face on a wall is no unknown), in two parts
+// so that every load is in flight before any value is used.  The coarse
+// arrays are read from the descriptor once per workgroup, through a global
+// pointer (scalar loads).
+struct PSrcF {
+    const float *dc, *dmu, *dp, *du, *dv;
+    int pitch, m1, m2, bcx, bcy;
+};
+__device__ __forceinline__ PSrcF psrcf_of(const Desc &d, const Desc *cp, int cpar)
+{
+    const __attribute__((address_space(1))) Desc &C = *(const __attribute__((address_space(1))) Desc *)cp;
+    PSrcF s;
+    s.dc = C.dc; s.dmu = C.dmu; s.dp = C.dp; s.du = C.dub[cpar]; s.dv = C.dvb[cpar];
+    s.pitch = C.pitch; s.m1 = C.m1; s.m2 = C.m2; s.bcx = d.bcx; s.bcy = d.bcy;
+    return s;
+}
+// the coarse cell of fine cell (ic, jc), and for the fine faces (iu, ju), (iv,
+// jv) the coarse face each lies on and the next one east (north): the periodic
+// image, or, where there is none, the same face again (loaded, not used)
+struct PRawF {
+    float c, mu, p, u[2], v[2];
+};
+__device__ __forceinline__ PRawF mx_prolong_load(const PSrcF &C, int ic, int jc, int iu, int ju, int iv, int jv)
+{
+    PRawF r;
+    const size_t kc = (size_t)(jc >> 1) * C.pitch + (ic >> 1);
+    r.c = lda<1>(C.dc, kc); r.mu = lda<1>(C.dmu, kc); r.p = lda<1>(C.dp, kc);
+    {
+        const int I = iu >> 1, J = ju >> 1;
+        const size_t k0 = (size_t)J * C.pitch + I, k1 = I + 1 < C.m1 ? k0 + 1 : (C.bcx ? (size_t)J * C.pitch : k0);
+        r.u[0] = lda<1>(C.du, k0); r.u[1] = lda<1>(C.du, k1);
+    }
+    {
+        const int I = iv >> 1, J = jv >> 1;
+        const size_t k0 = (size_t)J * C.pitch + I, k1 = J + 1 < C.m2 ? k0 + C.pitch : (C.bcy ? (size_t)I : k0);
+        r.v[0] = lda<1>(C.dv, k0); r.v[1] = lda<1>(C.dv, k1);
+    }
+    return r;
+}
+// ... the corrections of the u face in column iu and the v face in row jv
+// (zero for a face on a wall)
+__device__ __forceinline__ void mx_prolong_apply(const PSrcF &C, const PRawF &r, int iu, int jv, float &du, float &dv)
+{
+    du = r.u[0];
+    if (iu & 1) {
+        const float e = ((iu >> 1) + 1 < C.m1 || C.bcx) ? r.u[1] : 0.0f;
+        du = 0.5f * (du + e);
+    }
+    if (!(C.bcx || iu >= 1)) du = 0.0f;
+    dv = r.v[0];
+    if (jv & 1) {
+        const float e = ((jv >> 1) + 1 < C.m2 || C.bcy) ? r.v[1] : 0.0f;
+        dv = 0.5f * (dv + e);
+    }
+    if (!(C.bcy || jv >= 1)) dv = 0.0f;
+}
 
-__device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, const TileF &T)
+// temporal blocking of the correction smoother: NS sweeps per launch, as
+// fused_body (the widened tile in LDS, the cell corrections from one set to the
+// other, the face corrections from buffer par to par ^ 1; the first sweep
+// of a post-smoothing takes P delta_H as it loads the level)
+template <bool prolong>
+__device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, const TileF &T, const PSrcF &pc)
 {
     const int n = T.W * T.H;
     for (int e = threadIdx.x; e < n; e += FBLK) {
@@ -73,55 +130,63 @@ __device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, co
         if (L.bcx) i = wrapi(i, L.m1);
         if (L.bcy) j = wrapi(j, L.m2);
         const TileSrc q = tile_src(L.m1, L.m2, L.pitch, L.bcx, L.bcy, i, j);
-        float *s = T.s + (b * T.S + a) * L_ES;
         if (q.sc == 0) {
             tile_zero(T, b * T.S + a);
             continue;
         }
         // the level is in global memory; every load before any use
-        const float v[9] = { lda<1>(L.c, q.c), lda<1>(L.dc, q.c), lda<1>(L.dmu, q.c), lda<1>(L.dp, q.c),
-                             lda<1>(L.du, q.u), lda<1>(L.dv, q.v), lda<1>(L.cn, q.c), lda<1>(L.un, q.u),
-                             lda<1>(L.vn, q.v) };
+        float v[9] = { lda<1>(L.c, q.c), lda<1>(L.dc, q.c), lda<1>(L.dmu, q.c), lda<1>(L.dp, q.c), lda<1>(L.du, q.u),
+                       lda<1>(L.dv, q.v), lda<1>(L.cn, q.c), lda<1>(L.un, q.u), lda<1>(L.vn, q.v) };
+        PRawF raw = {};
+        int iu = 0, jv = 0;
+        if (prolong) {
+            iu = q.u % L.pitch;
+            jv = q.v / L.pitch;
+            raw = mx_prolong_load(pc, q.c % L.pitch, q.c / L.pitch, iu, q.u / L.pitch, q.v % L.pitch, jv);
+        }
         __builtin_amdgcn_sched_barrier(0);
+        if (prolong) {
+            float du, dv;
+            mx_prolong_apply(pc, raw, iu, jv, du, dv);
+            v[1] += raw.c;
+            v[2] += raw.mu;
+            v[3] += raw.p;
+            if (q.su) v[4] += du;
+            if (q.sv) v[5] += dv;
+        }
+        float *s = T.s + (b * T.S + a) * L_ES;
         ltile_put(P, s, q.su, q.sv, v);
         s[T_U2] = s[T_U];
         s[T_V2] = s[T_V];
     }
 }
-// after the red pass (as fused_refresh): the new face corrections become the
-// black pass's snapshot, and the wall images follow their sources
-__device__ __forceinline__ void mx_fused_refresh(const LView &L, const TileF &T)
+// the images across walls (as fused_images)
+__device__ __forceinline__ void mx_fused_images(const LView &L, const TileF &T, int slot)
 {
-    const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += FBLK) {
-        const int b = e / T.W, a = e - b * T.W;
-        const int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
-        const bool gx = !L.bcx && (i < 0 || i >= L.m1), gy = !L.bcy && (j < 0 || j >= L.m2);
-        const int si = gx ? (i < 0 ? 0 : L.m1 - 1) : i, sj = gy ? (j < 0 ? 0 : L.m2 - 1) : j;
-        const int su = (!L.bcx && (i <= 0 || i >= L.m1)) ? 0 : (gy ? -1 : 1);
-        const int sv = (!L.bcy && (j <= 0 || j >= L.m2)) ? 0 : (gx ? -1 : 1);
-        // every value the element may take, before any store (as
-        // fused_refresh)
+    const int fu = slot ? T_U2 : T_U, fv = slot ? T_V2 : T_V;
+    wall_images(T, L.m1, L.m2, L.bcx, L.bcy, [&](int i, int j, int si, int sj) {
         const float *q = T.at(si, sj);
-        float *s = T.s + (b * T.S + a) * L_ES;
-        const float u = T.at(i, sj)[T_U2], v = T.at(si, j)[T_V2], dc = q[L_DC], mu = q[T_MU], p = q[T_P], drs = q[L_DRS];
-        __builtin_amdgcn_sched_barrier(0);
-        s[T_U] = signed_val(su, u);
-        s[T_V] = signed_val(sv, v);
-        if (gx || gy) {
-            s[L_DC] = dc;
-            s[T_MU] = mu;
-            s[T_P] = p;
-            s[L_DRS] = drs;
-        }
-    }
+        const float u = T.at(i, sj)[fu], v = T.at(si, j)[fv], dc = q[L_DC], mu = q[T_MU], p = q[T_P], drs = q[L_DRS];
+        float *s = T.at(i, j);
+        const bool gx = si != i, gy = sj != j;
+        s[L_DC] = dc;
+        s[T_MU] = mu;
+        s[T_P] = p;
+        s[L_DRS] = drs;
+        s[fu] = (!L.bcx && (i <= 0 || i >= L.m1)) ? 0.0f : (gy ? -u : u);
+        s[fv] = (!L.bcy && (j <= 0 || j >= L.m2)) ? 0.0f : (gx ? -v : v);
+    });
 }
-template <typename IT> __device__ __forceinline__ void k_mx_fused_body(const IT &it, int dir, float omega)
+template <int NS, int TS, typename IT> __device__ __forceinline__ void mx_fused_body(const IT &it, int dir, float omega, int prolong)
 {
-    TILE_LDS float sm[MX_FUSED_FLOATS];
+    typedef Fused<NS, TS> G;
+    extern __shared__ __attribute__((aligned(16))) float smf[];
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
-    if (!tile_valid(it, k, d)) return;
+    int i0, j0; // of the tile
+    if (!item_tile_at<TS>(it, k, d, i0, j0)) return;
+    const PhysF P = d.Pf;
+    const Kon<float> K = d.Kf;
     const int par = it_par(it, k);
     LView L = lview_of(d, par);
     LView O = L;
@@ -130,44 +195,66 @@ template <typename IT> __device__ __forceinline__ void k_mx_fused_body(const IT 
     } else {
         O.dc = d.dc2; O.dmu = d.dmu2; O.dp = d.dp2;
     }
-    const TileF T0 = item_tile<TileF>(sm, it, k, d);
     TileF T;
-    T.s = sm; T.i0 = T0.i0 - 2; T.j0 = T0.j0 - 2; T.W = FUSED_W; T.H = FUSED_H; T.S = FUSED_S;
-    mx_fused_load(d.Pf, L, T);
+    T.s = smf; T.i0 = i0 - G::EXT; T.j0 = j0 - G::EXT; T.W = G::W; T.H = G::W; T.S = G::S;
+    float *const un = d.dub[par ^ 1], *const vn = d.dvb[par ^ 1];
+    if (prolong) mx_fused_load<true>(P, L, T, psrcf_of(d, &d + 1, it_cpar(it, k)));
+    else mx_fused_load<false>(P, L, T, PSrcF());
+    const bool wall = at_wall(T, L.m1, L.m2, L.bcx, L.bcy);
     __syncthreads();
-    const int pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
-    {
-        const int lj = pr / ((TX + 4) / 2), kk = pr - lj * ((TX + 4) / 2);
-        const int tj = T0.j0 - 2 + lj;
-        const int ti = T0.i0 - 2 + 2 * kk + (tj & 1);
-        const bool in = lj < TY + 4 && (L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2));
-        if (in) {
-            const int i = L.bcx ? wrapi(ti, L.m1) : ti, j = L.bcy ? wrapi(tj, L.m2) : tj;
-            lrelax_cell<1, 1, true>(d.Pf, d.Kf, L, T, nullptr, nullptr, i, j, ti, tj, hlf, omega);
+    const int hlf = threadIdx.x & 1;
+    auto half = [&](auto cext, auto ccol) {
+        constexpr int ext = cext.value, colour = ccol.value, w = TS + 2 * ext;
+        for (int pr = threadIdx.x >> 1; pr < w * w / 2; pr += FBLK / 2) {
+            const int lj = pr / (w / 2), kk = pr - lj * (w / 2);
+            const int tj = j0 - ext + lj, ti = i0 - ext + 2 * kk + ((tj + colour) & 1);
+            if ((L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2))) {
+                const int i = L.bcx ? wrapi(ti, L.m1) : ti, j = L.bcy ? wrapi(tj, L.m2) : tj;
+                lrelax_cell<1, 1, true>(P, K, L, T, nullptr, nullptr, i, j, ti, tj, hlf, omega, colour);
+            }
         }
+        __syncthreads();
+        if (wall) {
+            mx_fused_images(L, T, colour ^ 1);
+            __syncthreads();
+        }
+    };
+    typedef std::integral_constant<int, 0> Red;
+    typedef std::integral_constant<int, 1> Black;
+    half(std::integral_constant<int, G::EXT>(), Red());
+    if (NS == 2) {
+        half(std::integral_constant<int, G::EXT - 2>(), Black());
+        half(std::integral_constant<int, 2>(), Red());
     }
-    __syncthreads();
-    mx_fused_refresh(L, T);
-    __syncthreads();
-    if (threadIdx.x < TBLK) {
-        const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
-        const int j = T0.j0 + lj;
-        const int i = T0.i0 + 2 * kk + ((j + 1) & 1);
-        if (i < L.m1 && j < L.m2) lrelax_cell<0, 1, true>(d.Pf, d.Kf, O, T, d.dub[par ^ 1], d.dvb[par ^ 1], i, j, i, j, hlf, omega);
-    } else {
-        const int q = pr - TBLK / 2;
-        const int lj = q / (TX / 2), kk = q - lj * (TX / 2);
-        const int j = T0.j0 + lj;
-        const int i = T0.i0 + 2 * kk + (j & 1);
+    if (threadIdx.x < TS * TS) {
+        const int pr = threadIdx.x >> 1, lj = pr / (TS / 2), kk = pr - lj * (TS / 2);
+        const int j = j0 + lj, i = i0 + 2 * kk + ((j + 1) & 1);
+        if (i < L.m1 && j < L.m2) lrelax_cell<0, 1, true>(P, K, O, T, un, vn, i, j, i, j, hlf, omega, 1);
+    } else if (threadIdx.x < 2 * TS * TS) {
+        const int q = (threadIdx.x - TS * TS) >> 1, lj = q / (TS / 2), kk = q - lj * (TS / 2);
+        const int j = j0 + lj, i = i0 + 2 * kk + (j & 1);
         if (i < L.m1 && j < L.m2) {
             const float *e = T.at(i, j);
             const size_t g = (size_t)j * L.pitch + i;
-            if (hlf == 0) { O.dc[g] = e[L_DC]; O.dmu[g] = e[T_MU]; }
-            else O.dp[g] = e[T_P];
+            if (hlf == 0) {
+                sta<1>(O.dc, g, e[L_DC]);
+                sta<1>(O.dmu, g, e[T_MU]);
+            } else {
+                sta<1>(O.dp, g, e[T_P]);
+            }
         }
     }
 }
-QN_KERNEL(k_mx_fused, __launch_bounds__(FBLK), (int dir, float omega), (dir, omega))
+template <typename IT> __device__ __forceinline__ void k_mx_fused_body(const IT &it, int dir, float omega, int prolong)
+{
+    mx_fused_body<1, 16>(it, dir, omega, prolong);
+}
+QN_KERNEL(k_mx_fused, __launch_bounds__(FBLK), (int dir, float omega, int prolong), (dir, omega, prolong))
+template <typename IT> __device__ __forceinline__ void k_mx_fused2_body(const IT &it, int dir, float omega, int prolong)
+{
+    mx_fused_body<2, 8>(it, dir, omega, prolong);
+}
+QN_KERNEL(k_mx_fused2, __launch_bounds__(FBLK), (int dir, float omega, int prolong), (dir, omega, prolong))
 
 // r - J delta on the item's level, restricted to the next coarser level
 // (cells: mean of four; faces: mean of the two coincident fine faces),
@@ -178,14 +265,17 @@ __device__ __forceinline__ float quad_sum(float x)
     x += other(x);
     return x + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, false));
 }
-template <typename IT> __device__ __forceinline__ void k_mx_restrict_body(const IT &it)
+template <typename IT> __device__ __forceinline__ void k_mx_restrict_body(const IT &it, int set)
 {
     TILE_LDS float sm[LTILE_FLOATS];
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
     const Desc &C = (&d)[1];
-    const LView Lf = lview_of(d, it_par(it, k));
+    LView Lf = lview_of(d, it_par(it, k));
+    if (set) { // the pre-smoothing left the cell corrections in the second set
+        Lf.dc = d.dc2; Lf.dmu = d.dmu2; Lf.dp = d.dp2;
+    }
     const TileF T = item_tile<TileF>(sm, it, k, d);
     ltile_load<2, TBLK>(d.Pf, Lf, T);
     __syncthreads();
@@ -223,61 +313,7 @@ template <typename IT> __device__ __forceinline__ void k_mx_restrict_body(const 
         sta<1>(C.dvb[cp], q, 0.0f);
     }
 }
-QN_KERNEL(k_mx_restrict, __launch_bounds__(TBLK), (), ())
-
-// P delta_H of the FP32 correction at fine cell (i, j): cells piecewise
-// constant, faces as in prolong_load / prolong_apply (a face on a wall is no
-// unknown), in two parts so that every load is in flight before any value is
-// used.  The coarse arrays are read from the descriptor once per workgroup,
-// through a global pointer (scalar loads).
-struct PSrcF {
-    const float *dc, *dmu, *dp, *du, *dv;
-    int pitch, m1, m2, bcx, bcy;
-};
-__device__ __forceinline__ PSrcF psrcf_of(const Desc &d, const Desc *cp, int cpar)
-{
-    const __attribute__((address_space(1))) Desc &C = *(const __attribute__((address_space(1))) Desc *)cp;
-    PSrcF s;
-    s.dc = C.dc; s.dmu = C.dmu; s.dp = C.dp; s.du = C.dub[cpar]; s.dv = C.dvb[cpar];
-    s.pitch = C.pitch; s.m1 = C.m1; s.m2 = C.m2; s.bcx = d.bcx; s.bcy = d.bcy;
-    return s;
-}
-// the coarse cell of fine cell (i, j), and for its west (south) face the
-// coarse face it lies on and the next one east (north): the periodic image,
-// or, where there is none, the same face again (loaded, not used)
-struct PRawF {
-    float c, mu, p, u[2], v[2];
-};
-__device__ __forceinline__ PRawF mx_prolong_load(const PSrcF &C, int i, int j)
-{
-    PRawF r;
-    const int I = i >> 1, J = j >> 1;
-    const size_t kc = (size_t)J * C.pitch + I;
-    r.c = lda<1>(C.dc, kc); r.mu = lda<1>(C.dmu, kc); r.p = lda<1>(C.dp, kc);
-    const size_t ke = I + 1 < C.m1 ? kc + 1 : (C.bcx ? (size_t)J * C.pitch : kc);
-    const size_t kn = J + 1 < C.m2 ? kc + C.pitch : (C.bcy ? (size_t)I : kc);
-    r.u[0] = lda<1>(C.du, kc); r.u[1] = lda<1>(C.du, ke);
-    r.v[0] = lda<1>(C.dv, kc); r.v[1] = lda<1>(C.dv, kn);
-    return r;
-}
-// ... the corrections; hu / hv: the face is an unknown
-__device__ __forceinline__ void mx_prolong_apply(const PSrcF &C, const PRawF &r, int i, int j, float &c, float &mu,
-                                                 float &p, float &du, float &dv, bool &hu, bool &hv)
-{
-    c = r.c; mu = r.mu; p = r.p;
-    hu = C.bcx || i >= 1;
-    hv = C.bcy || j >= 1;
-    du = r.u[0];
-    if (i & 1) {
-        const float e = ((i >> 1) + 1 < C.m1 || C.bcx) ? r.u[1] : 0.0f;
-        du = 0.5f * (du + e);
-    }
-    dv = r.v[0];
-    if (j & 1) {
-        const float e = ((j >> 1) + 1 < C.m2 || C.bcy) ? r.v[1] : 0.0f;
-        dv = 0.5f * (dv + e);
-    }
-}
+QN_KERNEL(k_mx_restrict, __launch_bounds__(TBLK), (int set), (set))
 
 // delta_h += P delta_H, one thread per fine cell
 template <typename IT> __device__ __forceinline__ void k_mx_prolong_body(const IT &it)
@@ -290,18 +326,17 @@ template <typename IT> __device__ __forceinline__ void k_mx_prolong_body(const I
     const size_t kf = (size_t)j * d.pitch + i;
     const PSrcF ps = psrcf_of(d, &d + 1, it_cpar(it, k));
     float *ub = d.dub[it_par(it, k)], *vb = d.dvb[it_par(it, k)];
-    const PRawF raw = mx_prolong_load(ps, i, j);
+    const PRawF raw = mx_prolong_load(ps, i, j, i, j, i, j);
     const float c0 = lda<1>(d.dc, kf), m0 = lda<1>(d.dmu, kf), p0 = lda<1>(d.dp, kf), u0 = lda<1>(ub, kf),
                 v0 = lda<1>(vb, kf);
     __builtin_amdgcn_sched_barrier(0);
-    float c, mu, p, du, dv;
-    bool hu, hv;
-    mx_prolong_apply(ps, raw, i, j, c, mu, p, du, dv, hu, hv);
-    sta<1>(d.dc, kf, c0 + c);
-    sta<1>(d.dmu, kf, m0 + mu);
-    sta<1>(d.dp, kf, p0 + p);
-    if (hu) sta<1>(ub, kf, u0 + du);
-    if (hv) sta<1>(vb, kf, v0 + dv);
+    float du, dv;
+    mx_prolong_apply(ps, raw, i, j, du, dv);
+    sta<1>(d.dc, kf, c0 + raw.c);
+    sta<1>(d.dmu, kf, m0 + raw.mu);
+    sta<1>(d.dp, kf, p0 + raw.p);
+    if (ps.bcx || i >= 1) sta<1>(ub, kf, u0 + du);
+    if (ps.bcy || j >= 1) sta<1>(vb, kf, v0 + dv);
 }
 QN_KERNEL(k_mx_prolong, __launch_bounds__(BLK), (), ())
 
