@@ -93,8 +93,9 @@ OP_KERNEL = {
 
 
 # kernels one operation launches (the residual reductions: the residual with
-# partial sums, their finalisation and, after a cycle, the pbar shift)
-KERNELS_PER_OP = {"residual": 3, "residual_acc": 3, "residual0": 2, "step_end": 2, "dissipation": 2,
+# partial sums and their finalisation, which after a cycle shifts pbar too;
+# more than 512 partials are folded first, a kernel more)
+KERNELS_PER_OP = {"residual": 2, "residual_acc": 2, "residual0": 2, "step_end": 2, "dissipation": 2,
                   "diagnostics": 2}
 
 

@@ -280,18 +280,16 @@ template <typename R, int ES_> struct TileT {
     __device__ __forceinline__ R q(int f, int i, int j) const { return at(i, j)[f]; }
 };
 typedef TileT<double, T_ES> Tile;
+// without the second face slot: the residual kernels (a half-sweep's lanes, on
+// every second element, meet fewer banks at 12 values: 41.1 us against 37.9 at 14)
+typedef TileT<double, T_NF> Tile1;
 
-// values per element of a tile
-template <typename R> struct Elem;
-template <> struct Elem<double> { static constexpr int N = T_ES; };
-template <> struct Elem<float> { static constexpr int N = L_ES; };
 // the element n elements from s (a row is S of them).  The offset is a
 // multiple of the element's size in the code, too: the compiler then knows the
 // element to be aligned to 16 bytes and loads a pair of fields as one
 // ds_read_b128; otherwise it makes a ds_read2_b64 of it, which takes the LDS
 // 15.5 cycles per wave instead of 4.5 (MI355X).
-template <typename R> __device__ __forceinline__ R *el(R *s, int n) { return s + n * Elem<R>::N; }
-template <typename R> __device__ __forceinline__ const R *el(const R *s, int n) { return s + n * Elem<R>::N; }
+template <int ES, typename R> __device__ __forceinline__ R *el(R *s, int n) { return s + n * ES; }
 
 // an element's fields from its eight loaded values (c, mubar, pbar, u, v, c^n,
 // u^n, v^n) and the signs of its faces
@@ -329,7 +327,7 @@ __device__ __forceinline__ bool tile_inner(int m1, int m2, int i0, int j0, int W
 // thread are loaded together: their sources first, then every load, then the
 // signs and cell functions (an element past the end is clamped to a valid
 // one and not stored).
-template <int NE, int NT> __device__ __forceinline__ void tile_load(const Phys &P, const View &L, const Tile &T)
+template <int NE, int NT, typename TT> __device__ __forceinline__ void tile_load(const Phys &P, const View &L, const TT &T)
 {
     const int n = T.W * T.H;
     double v[NE][8];
@@ -346,7 +344,7 @@ template <int NE, int NT> __device__ __forceinline__ void tile_load(const Phys &
 #pragma unroll
         for (int k = 0; k < NE; k++) {
             const int e = threadIdx.x + k * NT, b = e / T.W, a = e - b * T.W;
-            if (e < n) tile_put(P, T.s + (b * T.S + a) * T_ES, 1, 1, v[k]);
+            if (e < n) tile_put(P, T.s + (b * T.S + a) * TT::ES, 1, 1, v[k]);
         }
         return;
     }
@@ -366,7 +364,7 @@ template <int NE, int NT> __device__ __forceinline__ void tile_load(const Phys &
         const int e = threadIdx.x + k * NT, b = e / T.W, a = e - b * T.W;
         if (e >= n) continue;
         if (s[k].sc == 0) tile_zero(T, b * T.S + a);
-        else tile_put(P, T.s + (b * T.S + a) * T_ES, s[k].su, s[k].sv, v[k]);
+        else tile_put(P, T.s + (b * T.S + a) * TT::ES, s[k].su, s[k].sv, v[k]);
     }
 }
 
@@ -415,7 +413,8 @@ __device__ __forceinline__ void ring_build(const TT &T, int m1, int m2, int bcx,
 // (-ffp-contract=on), so every kernel that shares these functions computes
 // the same values.
 
-struct Ax {
+// (ES: values per element)
+template <int ES> struct Ax {
     int dn, dt;          // elements to the next one along the normal / tangential axis
     int fn, ft, fo;      // own velocity (T_U or T_V, or T_U2, T_V2), other velocity, new own velocity
     int fnn, ftn;        // own and other velocity of time n
@@ -427,9 +426,9 @@ struct Ax {
 // slot: the faces are in T_U, T_V and a sweep that stays in the tile puts the
 // new ones into T_U2, T_V2 (0), or the other way round (1)
 template <typename V, typename TT>
-__device__ __forceinline__ Ax make_ax(const V &L, const TT &T, int i, int j, int hlf, int slot = 0)
+__device__ __forceinline__ Ax<TT::ES> make_ax(const V &L, const TT &T, int i, int j, int hlf, int slot = 0)
 {
-    Ax a;
+    Ax<TT::ES> a;
     a.hlf = hlf;
     a.dn = hlf ? T.S : 1;
     a.dt = hlf ? 1 : T.S;
@@ -475,12 +474,12 @@ template <typename R> struct CellSum {
 };
 // u0, uP: the velocity on the cell's low and high face along the axis.  PJ:
 // the projection scheme, whose advection takes c and rho of time n+1.
-template <bool PJ>
-__device__ __forceinline__ CellSum<double> axis_cell(const Kon<double> &K, const double *s, const Ax &a, double r,
+template <bool PJ, int ES>
+__device__ __forceinline__ CellSum<double> axis_cell(const Kon<double> &K, const double *s, const Ax<ES> &a, double r,
                                                      double drs, double u0, double uP)
 {
     const bool wP = a.per || a.ia < a.ma - 1, wM = a.per || a.ia > 0;
-    const double *sP = el(s, a.dn), *sM = el(s, -a.dn);
+    const double *sP = el<ES>(s, a.dn), *sM = el<ES>(s, -a.dn);
     const double mP = sP[T_MOB] + s[T_MOB], mM = sM[T_MOB] + s[T_MOB];
     const double S = s[T_MU] + K.alpha * s[T_P];
     const double fP = (sP[T_MU] + K.alpha * sP[T_P]) - S, fM = S - (sM[T_MU] + K.alpha * sM[T_P]);
@@ -569,11 +568,11 @@ template <typename R> struct FaceEq {
 // LIN: the equation's linearisation at w^ applied to a correction (the
 // correction smoother): uh is the face's velocity at w^, which multiplies the
 // change of the density average (field L_DRS); gravity and u^n drop out.
-template <typename R, bool PJ, bool LIN>
-__device__ __forceinline__ FaceEq<R> face_eq(const Kon<R> &K, const R *s, const Ax &a, R uh = R(0))
+template <typename R, bool PJ, bool LIN, int ES>
+__device__ __forceinline__ FaceEq<R> face_eq(const Kon<R> &K, const R *s, const Ax<ES> &a, R uh = R(0))
 {
     const int dn = a.dn, dt = a.dt, fn = a.fn, ft = a.ft, fnn = a.fnn, ftn = a.ftn;
-    const R *L = el(s, -dn), *Rn = el(s, dn), *Lt = el(L, dt), *Lb = el(L, -dt), *St = el(s, dt), *Sb = el(s, -dt);
+    const R *L = el<ES>(s, -dn), *Rn = el<ES>(s, dn), *Lt = el<ES>(L, dt), *Lb = el<ES>(L, -dt), *St = el<ES>(s, dt), *Sb = el<ES>(s, -dt);
     const R rL = L[T_RN], rR = s[T_RN], mL = L[T_MV], mR = s[T_MV];
     const R a1 = rL + rR, b1 = mL + mR;
     const R At = (Lt[T_RN] + St[T_RN]) + a1, Ab = (Lb[T_RN] + Sb[T_RN]) + a1;
@@ -717,10 +716,10 @@ __device__ __forceinline__ const double *face_rhs(const Rhs &F, int hlf)
 template <typename TT, typename R> struct Hood {
     R h[12 * TT::ES];
     __device__ __forceinline__ R *centre() { return h + 4 * TT::ES; }
-    template <bool LIN> __device__ __forceinline__ Ax load(const R *e, const Ax &a)
+    template <bool LIN> __device__ __forceinline__ Ax<TT::ES> load(const R *e, const Ax<TT::ES> &a)
     {
         auto get = [&](int n, int t, int f, int g) {
-            h[((n + 1) * 3 + t + 1) * TT::ES + f] = el(e, n * a.dn + t * a.dt)[g];
+            h[((n + 1) * 3 + t + 1) * TT::ES + f] = el<TT::ES>(e, n * a.dn + t * a.dt)[g];
         };
 #pragma unroll
         for (int n = -1; n <= 1; n++) {
@@ -756,7 +755,7 @@ template <typename TT, typename R> struct Hood {
                 get(n, t, T_VN, a.ftn);
             }
         __builtin_amdgcn_sched_barrier(0);
-        Ax b = a;
+        Ax<TT::ES> b = a;
         b.dn = 3;
         b.dt = 1;
         b.fn = T_U;
@@ -805,8 +804,8 @@ template <typename TT, typename R> struct Hood {
 // waves per SIMD instead of two): 50.4 -> 38.0 us on 512 x 2048 (MI355X).
 
 // what a sweep of one cell starts from
-struct CellPos {
-    Ax a;
+template <int ES> struct CellPos {
+    Ax<ES> a;
     bool hlo, hhi;    // the lane's faces are unknowns
     size_t k, khi;    // level index of the cell (and its low faces), of the lane's high face
     // where the new high face goes in the tile, from the cell's element
@@ -816,9 +815,9 @@ struct CellPos {
     }
 };
 template <typename V, typename TT>
-__device__ __forceinline__ CellPos cell_pos(const V &L, const TT &T, int i, int j, int ti, int tj, int hlf, int slot)
+__device__ __forceinline__ CellPos<TT::ES> cell_pos(const V &L, const TT &T, int i, int j, int ti, int tj, int hlf, int slot)
 {
-    CellPos c;
+    CellPos<TT::ES> c;
     c.a = make_ax(L, T, i, j, hlf, slot);
     c.hlo = c.a.per || c.a.ia >= 1;
     c.hhi = c.a.per || c.a.ia + 1 < c.a.ma;
@@ -831,29 +830,29 @@ __device__ __forceinline__ CellPos cell_pos(const V &L, const TT &T, int i, int 
 // the next face beyond each box face is the box's other face, which so
 // enters each face row a second time, through the other cell's advection
 // weight and viscosity)
-template <typename R>
-__device__ __forceinline__ void box_offdiag(const Kon<R> &K, const R *s, const Ax &a, bool hlo, bool hhi, R &alh, R &ahl)
+template <typename R, int ES>
+__device__ __forceinline__ void box_offdiag(const Kon<R> &K, const R *s, const Ax<ES> &a, bool hlo, bool hhi, R &alh, R &ahl)
 {
     const int fnn = a.fnn;
-    const R un = s[fnn] + el(s, a.dn)[fnn];
+    const R un = s[fnn] + el<ES>(s, a.dn)[fnn];
     const R w = R(4) * (K.ka * (s[T_RN] * un)), vis = R(4) * (K.kv * s[T_MV]);
     alh = hlo ? w - vis : R(0);
     ahl = hhi ? -w - vis : R(0);
     if (a.per && a.ma == 2) {
-        const R *o = el(s, -a.dn);
+        const R *o = el<ES>(s, -a.dn);
         const R wo = R(4) * (K.ka * (o[T_RN] * un)), vo = R(4) * (K.kv * o[T_MV]);
         alh = alh - (wo + vo);
         ahl = ahl + (wo - vo);
     }
 }
 
-template <int TO, int AS, bool HOOD>
-__device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, const View &L, const Tile &T, const Rhs &F,
+template <int TO, int AS, bool HOOD, typename TT>
+__device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, const View &L, const TT &T, const Rhs &F,
                                          double *unew, double *vnew, int i, int j, int ti, int tj, int hlf,
                                          double omega, double pomega, int slot);
 
-template <bool PJ, int TO, int AS, bool HOOD>
-__device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, const View &L, const Tile &T,
+template <bool PJ, int TO, int AS, bool HOOD, typename TT>
+__device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, const View &L, const TT &T,
                                            const Rhs &F, double *unew, double *vnew, int i, int j, int ti, int tj,
                                            int hlf, double omega, double pomega, int slot = 0)
 {
@@ -861,11 +860,12 @@ __device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, 
         relax_pj<TO, AS, HOOD>(P, K, L, T, F, unew, vnew, i, j, ti, tj, hlf, omega, pomega, slot);
         return;
     }
-    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
+    constexpr int ES = TT::ES;
+    const CellPos<ES> b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
     double *const e = T.at(ti, tj); // results go here, everything is read at s
-    Hood<Tile, double> H;
+    Hood<TT, double> H;
     const double *s = e;
-    Ax a = b.a;
+    Ax<ES> a = b.a;
     const bool cpl = P.coupled;
     // the right-hand sides first: their loads are then in flight during the
     // cell equations
@@ -885,7 +885,7 @@ __device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, 
     }
     double r, drs;
     cell_r(K, s, r, drs);
-    const double ulo = s[a.fn], uhi = el(s, a.dn)[a.fn];
+    const double ulo = s[a.fn], uhi = el<ES>(s, a.dn)[a.fn];
     const CellSum<double> xo = axis_cell<false>(K, s, a, r, drs, ulo, uhi), x = xo + other(xo);
     const CellEq q = cell_eq(K, s, x, r, drs);
     const double r1 = f_c - q.Nc, r2 = f_mu - q.Nmu;
@@ -926,8 +926,8 @@ __device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, 
         bp -= Jcp * dm;
     }
     // ---- the box: this lane's two faces along its axis
-    const FaceEq<double> flo = face_eq<double, false, false>(K, s, a), fhi = face_eq<double, false, false>(K, el(s, a.dn), a);
-    const double *P1 = el(s, a.dn), *M1 = el(s, -a.dn);
+    const FaceEq<double> flo = face_eq<double, false, false>(K, s, a), fhi = face_eq<double, false, false>(K, el<ES>(s, a.dn), a);
+    const double *P1 = el<ES>(s, a.dn), *M1 = el<ES>(s, -a.dn);
     const double alo = b.hlo ? K.hih * (M1[T_RN] * (s[T_CN] - M1[T_CN])) : 0.0;
     const double ahi = b.hhi ? K.hih * (P1[T_RN] * (P1[T_CN] - s[T_CN])) : 0.0;
     double alh, ahl;
@@ -944,7 +944,7 @@ __device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, 
     const double np = p0 + omega * dp;
     if (TO) {
         if (b.hlo) e[b.a.fo] = nlo;
-        if (b.hhi) el(e, b.hi<TO>())[b.a.fo] = nhi;
+        if (b.hhi) el<ES>(e, b.template hi<TO>())[b.a.fo] = nhi;
         if (hlf == 0) {
             e[T_P] = np;
             if (cpl) {
@@ -993,10 +993,11 @@ struct Resid {
 // on north-south faces (gravity acts in the projection equation, as in the
 // time-discrete scheme (pj-pj)); zero on a wall face.  ut is u~ on the face;
 // w receives 2 dt / (2 A rho).
-__device__ __forceinline__ double face_final(const Kon<double> &K, const double *s, const Ax &a, bool unk, double ut,
+template <int ES>
+__device__ __forceinline__ double face_final(const Kon<double> &K, const double *s, const Ax<ES> &a, bool unk, double ut,
                                              double &w)
 {
-    const double *L = el(s, -a.dn);
+    const double *L = el<ES>(s, -a.dn);
     const double rL = L[T_RS], rR = s[T_RS], A2 = rL + rR;
     const double st = 0.5 * (rR * L[T_MU] + rL * s[T_MU]) * (s[T_C] - L[T_C]);
     double f = K.kp * (st - (s[T_P] - L[T_P]));
@@ -1005,23 +1006,24 @@ __device__ __forceinline__ double face_final(const Kon<double> &K, const double 
     return unk ? ut + w * f : 0.0;
 }
 
-template <bool PJ, int AS = 1>
-__device__ __forceinline__ Resid resid_cell(const Kon<double> &K, const View &L, const Tile &T, const Rhs &F, int i,
+template <bool PJ, int AS = 1, typename TT>
+__device__ __forceinline__ Resid resid_cell(const Kon<double> &K, const View &L, const TT &T, const Rhs &F, int i,
                                             int j)
 {
+    constexpr int ES = TT::ES;
     const double *e = T.at(i, j);
-    const Ax ax = make_ax(L, T, i, j, 0), ay = make_ax(L, T, i, j, 1);
+    const Ax<ES> ax = make_ax(L, T, i, j, 0), ay = make_ax(L, T, i, j, 1);
     const size_t k = (size_t)j * L.pitch + i;
     Resid f = {};
     if (F.fc) f = { lda<AS>(F.fc, k), lda<AS>(F.fmu, k), lda<AS>(F.fp, k), lda<AS>(F.fu, k), lda<AS>(F.fv, k) };
     const bool hu = ax.per || i >= 1, hv = ay.per || j >= 1;
-    double ulo = e[T_U], uhi = el(e, ax.dn)[T_U], vlo = e[T_V], vhi = el(e, ay.dn)[T_V];
+    double ulo = e[T_U], uhi = el<ES>(e, ax.dn)[T_U], vlo = e[T_V], vhi = el<ES>(e, ay.dn)[T_V];
     if (PJ) {
         double w;
         ulo = face_final(K, e, ax, hu, ulo, w);
-        uhi = face_final(K, el(e, ax.dn), ax, ax.per || i + 1 < L.m1, uhi, w);
+        uhi = face_final(K, el<ES>(e, ax.dn), ax, ax.per || i + 1 < L.m1, uhi, w);
         vlo = face_final(K, e, ay, hv, vlo, w);
-        vhi = face_final(K, el(e, ay.dn), ay, ay.per || j + 1 < L.m2, vhi, w);
+        vhi = face_final(K, el<ES>(e, ay.dn), ay, ay.per || j + 1 < L.m2, vhi, w);
     }
     double r, drs;
     cell_r(K, e, r, drs);
@@ -1051,16 +1053,17 @@ __device__ __forceinline__ Resid resid_cell(const Kon<double> &K, const View &L,
 //  4. the velocity of time n+1 is never stored, so nothing is left to update.
 // The tile entries of the cell (c, mubar, rho(c)) are updated after step 1; no
 // other pair of this colour reads them.
-template <int TO, int AS, bool HOOD>
-__device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, const View &L, const Tile &T, const Rhs &F,
+template <int TO, int AS, bool HOOD, typename TT>
+__device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, const View &L, const TT &T, const Rhs &F,
                                          double *unew, double *vnew, int i, int j, int ti, int tj, int hlf,
                                          double omega, double pomega, int slot)
 {
-    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
+    constexpr int ES = TT::ES;
+    const CellPos<ES> b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
     double *const e = T.at(ti, tj); // results go here, everything is read at s
-    Hood<Tile, double> H;
+    Hood<TT, double> H;
     double *s = e;
-    Ax a = b.a;
+    Ax<ES> a = b.a;
     const double *fN = face_rhs(F, hlf);
     // (a level in LDS has them; the high face of a wall: loaded, not used)
     double f_c = 0.0, f_mu = 0.0, f_p = 0.0, f_lo = 0.0, f_hi = 0.0;
@@ -1075,7 +1078,7 @@ __device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, co
         a = H.template load<false>(e, b.a);
         s = H.centre();
     }
-    const double *P1 = el(s, a.dn), *M1 = el(s, -a.dn);
+    const double *P1 = el<ES>(s, a.dn), *M1 = el<ES>(s, -a.dn);
     // ---- step 1
     double wlo, whi;
     const double ulo0 = face_final(K, s, a, b.hlo, s[a.fn], wlo);
@@ -1145,7 +1148,7 @@ __device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, co
     const double ulo = ut0 + omega * (X.xb[0] + t * X.xs[0]), uhi = ut1 + omega * (X.xb[1] + t * X.xs[1]);
     if (TO) {
         if (b.hlo) e[b.a.fo] = ulo;
-        if (b.hhi) el(e, b.hi<TO>())[b.a.fo] = uhi;
+        if (b.hhi) el<ES>(e, b.template hi<TO>())[b.a.fo] = uhi;
     } else {
         double *fo = hlf ? vnew : unew;
         if (b.hlo) sta<AS>(fo, b.k, ulo);

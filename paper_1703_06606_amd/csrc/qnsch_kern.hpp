@@ -29,17 +29,7 @@ namespace qn {
 #define TX QN_TX
 #define TY QN_TY
 #define TBLK (TX * TY)
-// The FP64 finest-level half-sweep is register-limited to 2 waves per SIMD.
-// With the segregated smoother alone, asking for 3 cost a few spilled
-// registers and bought a third resident workgroup per CU (18 % faster on
-// 512 x 2048); the coupled box needs some 25 more registers, whose spills at 3
-// waves cost more than the third workgroup gains, so the finest level keeps 2.
-// The attribute stays separate so that the trade can be re-measured.
-#ifndef QN_FINE_WAVES
-#define QN_FINE_WAVES 2
-#endif
 #define HS_ATTR __launch_bounds__(TBLK)
-#define FINE_ATTR __launch_bounds__(TBLK) __attribute__((amdgpu_waves_per_eu(QN_FINE_WAVES)))
 #define TILE_S (TX + 4)
 #define TILE_DOUBLES (T_ES * TILE_S * (TY + 3))
 #define TILE_LDS __shared__ __attribute__((aligned(16)))
@@ -176,16 +166,22 @@ template <int TS, typename IT> __device__ __forceinline__ int item_tile_at(const
     j0 = (t / tx) * TS;
     return lin < n;
 }
-template <typename TT, typename R, typename IT>
+// (W: the elements that the tile's cells read, -1 .. TX+1 along an axis for a
+// box, whose high face is an unknown, -1 .. TX for a residual)
+// places per slot of a simulation's partials: as many as its finest level has
+// tiles (no fewer than blocks of BLK cells)
+__device__ __forceinline__ int part_stride(const Desc &d) { return ((d.m1 + TX - 1) / TX) * ((d.m2 + TY - 1) / TY); }
+
+template <typename TT, int W = TX + 3, int S = TILE_S, typename R, typename IT>
 __device__ __forceinline__ TT item_tile(R *sm, const IT &it, int k, const Desc &d)
 {
     static_assert(TX == TY, "square tiles");
     TT T;
     T.s = sm;
     item_tile_at<TX>(it, k, d, T.i0, T.j0);
-    T.W = TX + 3;
-    T.H = TY + 3;
-    T.S = TILE_S;
+    T.W = W;
+    T.H = W;
+    T.S = S;
     return T;
 }
 template <typename IT> __device__ __forceinline__ bool tile_valid(const IT &it, int k, const Desc &d)
@@ -224,7 +220,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_halfsweep_fine
 {
     k_halfsweep_body<PJ>(it, colour, omega);
 }
-QN_KERNEL_PJ(k_halfsweep_fine, FINE_ATTR, (int colour, double omega), (colour, omega))
+QN_KERNEL_PJ(k_halfsweep_fine, HS_ATTR, (int colour, double omega), (colour, omega))
 
 // --------------------------------------------------------------------------
 // temporal blocking: NS sweeps (each a red, then a black half-sweep of sec. 7.1,
@@ -520,11 +516,14 @@ __device__ __forceinline__ double rw_mean(double a, double b, double c, double d
 // fine arrays directly (the neighbouring workgroups write the coarse iterate
 // meanwhile).
 //
+// Single-slot elements of 12 values and tiles of only what a residual reads, 18 x
+// 18, fit three workgroups in a CU's LDS instead of two: 512 x 2048 cells 52
+// instead of 71 us.  (Rows of 20 elements keep a quad's cells on different banks.)
 // One lane per fine cell (waves 0-3, a coarse cell's children in a quad of
 // lanes, summed by DPP), a fifth wave for the residuals of the tile's 64 coarse
 // cells meanwhile.
 #define RBLK (TBLK + 64)
-#define CTILE_S (TX / 2 + 4)
+#define CTILE_S (TX / 2 + 2)
 static_assert((TX / 2) * (TY / 2) == 64, "k_restrict: one wave of coarse cells");
 // sum over a quad of lanes as (0 + 1) + (2 + 3), the order of rw_mean
 __device__ __forceinline__ double quad_sum(double x)
@@ -537,8 +536,8 @@ __device__ __forceinline__ double quad_sum(double x)
 }
 template <bool PJ, typename IT> __device__ __forceinline__ void k_restrict_body(const IT &it, int set)
 {
-    TILE_LDS double sm[TILE_DOUBLES];
-    TILE_LDS double smc[T_ES * CTILE_S * (TY / 2 + 3)];
+    TILE_LDS double sm[T_NF * TILE_S * (TY + 2)];
+    TILE_LDS double smc[T_NF * CTILE_S * (TY / 2 + 2)];
     __shared__ double part[5][(TX / 2) * (TY / 2)]; // sums of the fine residuals
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
@@ -551,13 +550,13 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_restrict_body(
         Lf.c = d.c2; Lf.mu = d.mu2; Lf.p = d.p2;
     }
     const View Lc = view_of(C, cp);
-    const Tile T = item_tile<Tile>(sm, it, k, d);
+    const Tile1 T = item_tile<Tile1, TX + 2>(sm, it, k, d);
     // the coarse tile of R w, from the fine arrays directly (its halo lies
     // in the neighbouring workgroups' tiles), loaded together with the fine
     // tile: cells the mean of the four children, faces the mean of the two
     // coincident fine faces
-    Tile Tc;
-    Tc.s = smc; Tc.i0 = T.i0 / 2; Tc.j0 = T.j0 / 2; Tc.W = TX / 2 + 3; Tc.H = TY / 2 + 3; Tc.S = CTILE_S;
+    Tile1 Tc;
+    Tc.s = smc; Tc.i0 = T.i0 / 2; Tc.j0 = T.j0 / 2; Tc.W = TX / 2 + 2; Tc.H = TY / 2 + 2; Tc.S = CTILE_S;
     {
         const int n = Tc.W * Tc.H, e = RBLK - 1 - threadIdx.x;
         const Phys PC = C.P;
@@ -582,7 +581,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_restrict_body(
             } else {
                 const double w[8] = { rw_mean(c4[0], c4[1], c4[2], c4[3]), rw_mean(m4[0], m4[1], m4[2], m4[3]),
                                       rw_mean(p4[0], p4[1], p4[2], p4[3]), 0.5 * (u0 + u1), 0.5 * (w0 + w1), cn, un, vn };
-                tile_put(PC, Tc.s + (bb * CTILE_S + aa) * T_ES, s.su, s.sv, w);
+                tile_put(PC, Tc.s + (bb * CTILE_S + aa) * T_NF, s.su, s.sv, w);
             }
         }
     }
@@ -935,7 +934,32 @@ QN_KERNEL(k_prolong, __launch_bounds__(BLK), (), ())
 // wave64 + LDS block sum of NRED values (blocks of NT threads).  Within a
 // wave each exchange halves the number of slots a lane is responsible for
 // (lane l ends with the sum of slot l / 4): 17 exchanges instead of 6 per slot.
-template <int NT> __device__ __forceinline__ void block_sum_store(double (&v)[NRED], double *out)
+// Sums over the block of its threads' first N values (a power of two), through
+// N * NT doubles of LDS that nothing else holds any more: a value's NT terms
+// are added by NT / N threads each, in a fixed order.  Against a reduction in
+// registers (shuffles and selects of all NRED values: 380 of the residual
+// norms' 970 vector instructions per wave) the norms of 2048 x 2048 cells took 103
+// instead of 146 us.
+template <int NT, int N> __device__ __forceinline__ void block_sum_lds(const double (&v)[NRED], double *sm, double *out, int st)
+{
+    constexpr int G = NT / N; // threads per value
+    static_assert(G <= 64 && G >= 16 && NT % (2 * G) == 0, "block_sum_lds");
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < N; q++) sm[q * NT + threadIdx.x] = v[q];
+    __syncthreads();
+    const int q = threadIdx.x / G, g = threadIdx.x % G;
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < NT; k += 2 * G) {
+        const double *p = sm + q * NT + k + 2 * g;
+        s += p[0] + p[1];
+    }
+    for (int m = 1; m < G; m <<= 1) s += __shfl_xor(s, m, 64);
+    if (g == 0) out[(size_t)q * st] = s;
+    if (N < NRED && threadIdx.x >= N && threadIdx.x < NRED) out[(size_t)threadIdx.x * st] = 0.0;
+}
+template <int NT> __device__ __forceinline__ void block_sum_store(double (&v)[NRED], double *out, int st)
 {
     static_assert(NRED == 16, "block_sum_store");
     __shared__ double sh[NT / 64][NRED];
@@ -959,7 +983,7 @@ template <int NT> __device__ __forceinline__ void block_sum_store(double (&v)[NR
     if (threadIdx.x < NRED) {
         double s = 0.0;
         for (int ww = 0; ww < NT / 64; ww++) s += sh[ww][threadIdx.x];
-        out[threadIdx.x] = s;
+        out[(size_t)threadIdx.x * st] = s;
     }
 }
 
@@ -1008,7 +1032,8 @@ __device__ __forceinline__ void acc_record(const Desc &d, int ac, size_t w, cons
 // order); optionally the residual fields themselves.  One lane per cell.
 template <bool PJ, typename IT> __device__ __forceinline__ void k_resid_norm_body(const IT &it)
 {
-    TILE_LDS double sm[TILE_DOUBLES];
+    TILE_LDS double sm[NRED * TBLK]; // the tile, then the sums
+    static_assert(T_NF * (TX + 2) * (TY + 2) <= NRED * TBLK, "k_resid_norm");
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
@@ -1016,7 +1041,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_resid_norm_bod
     const Kon<double> K = d.K;
     const int par = it_par(it, k);
     const View L = view_of(d, par);
-    const Tile T = item_tile<Tile>(sm, it, k, d);
+    const Tile1 T = item_tile<Tile1, TX + 2, TX + 2>(sm, it, k, d);
     tile_load<2, TBLK>(P, L, T);
     __syncthreads();
     double v[NRED] = {};
@@ -1054,7 +1079,10 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_resid_norm_bod
         if (ac >= 0 && d.ar) acc_record(d, ac, w, r, t, v);
     }
     const int tl = (T.j0 / TY) * it_cnt(it, k) + T.i0 / TX;
-    block_sum_store<BLK>(v, d.partials + (size_t)tl * NRED);
+    double *const out = d.partials + tl;
+    const int st = part_stride(d);
+    if (it_acc(it, k) >= 0 && d.ar) block_sum_lds<TBLK, NRED>(v, sm, out, st);
+    else block_sum_lds<TBLK, 8>(v, sm, out, st);
 }
 QN_KERNEL_PJ(k_resid_norm, __launch_bounds__(TBLK), (), ())
 
@@ -1066,6 +1094,7 @@ template <typename IT> __device__ __forceinline__ void k_mass_energy_body(const 
     const View L = view_of(d, it_par(it, k));
     const Phys &P = d.P;
     const int b = (int)blockIdx.x - it_start(it, k);
+    if (b * BLK >= d.m1 * d.m2) return; // pads the list: no partials of its own
     const int t = b * BLK + threadIdx.x;
     double v[NRED] = {};
     if (t < L.m1 * L.m2) {
@@ -1086,7 +1115,7 @@ template <typename IT> __device__ __forceinline__ void k_mass_energy_body(const 
         v[4] = r * dwell(c);
         v[5] = (r - P.rho_ref) * (j + 0.5) * d.h;
     }
-    block_sum_store<BLK>(v, d.partials + (size_t)b * NRED);
+    block_sum_store<BLK>(v, d.partials + b, part_stride(d));
 }
 QN_KERNEL(k_mass_energy, __launch_bounds__(BLK), (), ())
 
@@ -1111,6 +1140,7 @@ template <typename IT> __device__ __forceinline__ void k_dissipation_body(const 
     const double *uf = d.ub[it_par(it, k)], *vf = d.vb[it_par(it, k)];
     const Phys &P = d.P;
     const int b = (int)blockIdx.x - it_start(it, k);
+    if (b * BLK >= d.m1 * d.m2) return; // pads the list: no partials of its own
     const int t = b * BLK + threadIdx.x;
     double v[NRED] = {};
     if (t < L.m1 * L.m2) {
@@ -1161,7 +1191,7 @@ template <typename IT> __device__ __forceinline__ void k_dissipation_body(const 
             }
         }
     }
-    block_sum_store<BLK>(v, d.partials + (size_t)b * NRED);
+    block_sum_store<BLK>(v, d.partials + b, part_stride(d));
 }
 QN_KERNEL(k_dissipation, __launch_bounds__(BLK), (), ())
 
@@ -1217,6 +1247,7 @@ template <typename IT> __device__ __forceinline__ void k_diagnostics_body(const 
     const Desc &d = it_desc(it, k);
     const View L = view_of(d, it_par(it, k));
     const int b = (int)blockIdx.x - it_start(it, k);
+    if (b * BLK >= d.m1 * d.m2) return; // pads the list: no partials of its own
     const int t = b * BLK + threadIdx.x;
     double v[NRED] = { 0, 0, 0, 0, 0, -DIAG_NONE, DIAG_NONE, -DIAG_NONE };
     if (t < L.m1 * L.m2) {
@@ -1263,63 +1294,100 @@ template <typename IT> __device__ __forceinline__ void k_diagnostics_body(const 
             const double w = sh[ww][r];
             acc = (r == 2 || r == 5 || r == 7) ? fmax(acc, w) : (r == 6 ? fmin(acc, w) : acc + w);
         }
-        d.partials[(size_t)b * NRED + r] = acc;
+        d.partials[(size_t)r * part_stride(d) + b] = acc;
     }
 }
 QN_KERNEL(k_diagnostics, __launch_bounds__(BLK), (), ())
 
-// fixed-order sum of a simulation's partials (one workgroup per item); the
-// norms become sqrt(h^2 sum r^2); written to device and pinned host memory.
+// The reduction of a simulation's partials, in a fixed order: the norms become
+// sqrt(h^2 sum r^2), everything goes to device and pinned host memory.
 // mode 0: residual reduction (5 norms, sum p, bad count); 1: plain sums;
 // 2: the diagnostics slots (sum, max or min per slot as in k_diagnostics).
-template <typename IT> __device__ __forceinline__ void k_finalize_body(const IT &it, int mode)
+// Slot q combines by sum (op 0), max (1) or min (2).
+__device__ __forceinline__ int red_op(int mode, int q)
 {
-    __shared__ double sh[BLK][NRED];
-    const int k = blockIdx.x;
-    if (k >= it_count(it)) return;
-    const Desc &d = it_desc(it, k);
-    const int nblk = it_cnt(it, k);
-    // slot q combines by sum, or (diagnostics) by max (op 1) or min (op 2)
-    auto op = [&](int q) { return mode != 2 ? 0 : (q == 2 || q == 5 || q == 7) ? 1 : (q == 6 ? 2 : 0); };
-    auto comb = [&](int q, double a, double b) { const int o = op(q); return o == 0 ? a + b : (o == 1 ? fmax(a, b) : fmin(a, b)); };
-    double s[NRED];
-#pragma unroll
-    for (int q = 0; q < NRED; q++) s[q] = op(q) == 0 ? 0.0 : (op(q) == 1 ? -DIAG_NONE : DIAG_NONE);
-    for (int b = threadIdx.x; b < nblk; b += BLK)
-#pragma unroll
-        for (int q = 0; q < NRED; q++) s[q] = comb(q, s[q], d.partials[(size_t)b * NRED + q]);
-#pragma unroll
-    for (int q = 0; q < NRED; q++) sh[threadIdx.x][q] = s[q];
-    __syncthreads();
-    for (int o = BLK / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o)
-#pragma unroll
-            for (int q = 0; q < NRED; q++) sh[threadIdx.x][q] = comb(q, sh[threadIdx.x][q], sh[threadIdx.x + o][q]);
-        __syncthreads();
-    }
-    if (threadIdx.x < NRED) {
-        double x = sh[0][threadIdx.x];
-        if (mode == 0 && threadIdx.x < 5) x = sqrt(d.h * d.h * x);
-        d.red[threadIdx.x] = x;
-        d.red_host[threadIdx.x] = x;
-        // a recorded cycle result: the pbar mean k_shift_p removes from it
-        if (mode == 0 && threadIdx.x == 5 && it_acc(it, k) >= 0 && d.amean)
-            d.amean[it_acc(it, k) & 15] = x / (double)(d.m1 * d.m2);
-    }
+    return mode != 2 ? 0 : (q == 2 || q == 5 || q == 7) ? 1 : (q == 6 ? 2 : 0);
 }
-QN_KERNEL(k_finalize, __launch_bounds__(BLK), (int mode), (mode))
-
-// pbar -= mean(pbar), the mean from the reduced sums
-template <typename IT> __device__ __forceinline__ void k_shift_p_body(const IT &it)
+__device__ __forceinline__ double red_comb(int op, double a, double b)
 {
+    return op == 0 ? a + b : (op == 1 ? fmax(a, b) : fmin(a, b));
+}
+// slot q of the partials lo, lo + step, .. < hi, by the 16 threads g of the slot
+__device__ __forceinline__ double red_slot(const double *p, int mode, int q, int g, int lo, int hi, int step)
+{
+    const int op = red_op(mode, q);
+    double s = op == 0 ? 0.0 : (op == 1 ? -DIAG_NONE : DIAG_NONE);
+    for (int b0 = lo + g * step; b0 < hi; b0 += 16 * 16 * step) {
+        double v[16]; // loaded before any use
+#pragma unroll
+        for (int u = 0; u < 16; u++) v[u] = p[min(b0 + u * 16 * step, hi - 1)];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 16; u++)
+            if (b0 + u * 16 * step < hi) s = red_comb(op, s, v[u]);
+    }
+    for (int m = 8; m > 0; m >>= 1) s = red_comb(op, s, __shfl_xor(s, m, 64));
+    return s;
+}
+// Many partials are first folded in at most 64 chunks, a workgroup each, the
+// chunk's result in its first place: one workgroup reads them at about 35 GB/s
+// (16384 partials of 16 slots: 61 us, folded 6.4 + 5.7; 4096: 20 us, folded 5.0 +
+// 4.2; 512 with the shift of pbar below: 6.4 us, folded 5.0 + 4.6).
+#define FOLD_MIN 512
+static __host__ __device__ __forceinline__ int fold_chunk(int n) { return n > FOLD_MIN ? (n + 63) / 64 : 1; }
+template <typename IT> __device__ __forceinline__ void k_fold_body(const IT &it, int mode)
+{
+    static_assert(BLK == 16 * NRED, "16 threads per slot");
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
-    const int t = ((int)blockIdx.x - it_start(it, k)) * BLK + threadIdx.x;
-    if (t >= d.m1 * d.m2) return;
-    const int j = t / d.m1, i = t - j * d.m1;
-    d.p[(size_t)j * d.pitch + i] -= d.red[5] / (double)(d.m1 * d.m2);
+    const int n = it_cnt(it, k), ch = fold_chunk(n), lo = ((int)blockIdx.x - it_start(it, k)) * ch;
+    if (lo >= n) return;
+    const int q = threadIdx.x >> 4, g = threadIdx.x & 15;
+    double *p = d.partials + (size_t)q * part_stride(d);
+    const double s = red_slot(p, mode, q, g, lo, min(lo + ch, n), 1);
+    if (g == 0) p[lo] = s; // (the slot's threads, all of this wave, have read the chunk)
 }
-QN_KERNEL(k_shift_p, __launch_bounds__(BLK), (), ())
+QN_KERNEL(k_fold, __launch_bounds__(BLK), (int mode), (mode))
+
+// shift (mode 0): also pbar -= mean(pbar), a thread per cell; every workgroup
+// sums the pbar partials itself (at most 512, contiguous), which saves the
+// launch of a kernel that waits for the sum: 5.4 + 4.1 us became 4.2 on 40 x 40,
+// 7.6 + 4.3 became 6.4 on 256 x 512.
+template <typename IT> __device__ __forceinline__ void k_finalize_body(const IT &it, int mode, int shift)
+{
+    __shared__ double sh[BLK / 64];
+    const int k = find_item(it);
+    const Desc &d = it_desc(it, k);
+    const int n = it_cnt(it, k), ch = fold_chunk(n), blk = (int)blockIdx.x - it_start(it, k);
+    const int st = part_stride(d);
+    double psum = 0.0;
+    if (shift) {
+        const int t = blk * BLK + threadIdx.x, nc = d.m1 * d.m2;
+        if (blk * BLK >= nc) return;
+        const int j = min(t, nc - 1) / d.m1, i = min(t, nc - 1) - j * d.m1;
+        double *const p = d.p + (size_t)j * d.pitch + i;
+        const double p0 = *p;
+        for (int b = threadIdx.x * ch; b < n; b += BLK * ch) psum += d.partials[(size_t)5 * st + b];
+        for (int m = 32; m > 0; m >>= 1) psum += __shfl_xor(psum, m, 64);
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = psum;
+        __syncthreads();
+        psum = sh[0];
+#pragma unroll
+        for (int w = 1; w < BLK / 64; w++) psum += sh[w];
+        if (t < nc) *p = p0 - psum / (double)nc;
+    }
+    if (blk) return;
+    const int q = threadIdx.x >> 4, g = threadIdx.x & 15;
+    double x = red_slot(d.partials + (size_t)q * st, mode, q, g, 0, n, ch);
+    if (g) return;
+    if (mode == 0 && q < 5) x = sqrt(d.h * d.h * x);
+    if (shift && q == 5) x = psum;
+    d.red[q] = x;
+    d.red_host[q] = x;
+    // a recorded cycle result: the pbar mean removed from it
+    if (mode == 0 && q == 5 && it_acc(it, k) >= 0 && d.amean) d.amean[it_acc(it, k) & 15] = x / (double)(d.m1 * d.m2);
+}
+QN_KERNEL(k_finalize, __launch_bounds__(BLK), (int mode, int shift), (mode, shift))
 
 // coefficients of the accelerated combination, per item
 template <int N> struct AccCoef {

@@ -360,22 +360,37 @@ static void add_item(ItemList &W, const qnsch_ctx *x, int kind, int l, int ts = 
     if (kind == OP_COARSE || kind == OP_MXCOARSE) W.lds = std::max(W.lds, bottom_lds(x, l));
 }
 
-// finalize list: one workgroup per simulation, tx = number of partials
-static ItemList finalize_list(const std::vector<std::pair<qnsch_ctx *, int>> &v, int partial_kind)
+// Lists over the n partials of a simulation's reduction, n in tx: the folding of
+// many partials (an item per simulation that has many: blocks 0 if none), and
+// the reduction itself: a workgroup per simulation, or as many as shift pbar.
+static void add_reduction(ItemList &W, const qnsch_ctx *x, int n, int blocks)
+{
+    Items &it = W.it;
+    const int k = it.n;
+    it.start[k] = W.blocks;
+    it.d[k] = x->dd;
+    it.par[k] = x->L[0].cur;
+    it.cpar[k] = 0;
+    it.tx[k] = n;
+    it.acc[k] = -1;
+    W.blocks += blocks;
+    it.n = k + 1;
+    it.start[k + 1] = W.blocks;
+}
+static ItemList fold_list(const std::vector<std::pair<qnsch_ctx *, int>> &v, int partial_kind)
 {
     ItemList F;
     for (auto &e : v) {
-        qnsch_ctx *x = e.first;
-        const int k = F.it.n;
-        F.it.d[k] = x->dd;
-        F.it.par[k] = x->L[0].cur;
-        F.it.tx[k] = op_blocks(x, partial_kind, 0);
-        F.it.acc[k] = -1;
-        F.it.start[k] = k;
-        F.it.n = k + 1;
-        F.it.start[k + 1] = k + 1;
+        const int n = op_blocks(e.first, partial_kind, 0), ch = fold_chunk(n);
+        if (ch > 1) add_reduction(F, e.first, n, (n + ch - 1) / ch);
     }
-    F.blocks = F.it.n;
+    return F;
+}
+static ItemList finalize_list(const std::vector<std::pair<qnsch_ctx *, int>> &v, int partial_kind, bool shift)
+{
+    ItemList F;
+    for (auto &e : v)
+        add_reduction(F, e.first, op_blocks(e.first, partial_kind, 0), shift ? op_blocks(e.first, OP_BEGIN, 0) : 1);
     return F;
 }
 
@@ -562,6 +577,14 @@ static int one_w(const Items &a) { return (a.par[0] & 1) | (a.cpar[0] & 1) << 1 
         else KLAUNCHN(K##_n, L, GRID, BLOCK, LDS, ST, ##__VA_ARGS__);                                \
     } while (0)
 
+// the reduction of the partials of an operation without a pbar shift
+#define REDUCE(KIND, MODE)                                                                         \
+    do {                                                                                           \
+        ItemList F = finalize_list(part, KIND, false), C = fold_list(part, KIND);                      \
+        if (C.blocks) KLAUNCH(k_fold, C, dim3(C.blocks), dim3(BLK), 0, s, MODE);                       \
+        KLAUNCH(k_finalize, F, dim3(F.blocks), dim3(BLK), 0, s, MODE, 0);                              \
+    } while (0)
+
 // Launch one operation for a set of (context, level) entries, in lists of at
 // most MAXITEMS; all entries share the kind and colour.  Errors are reported
 // on the first context.
@@ -647,26 +670,21 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
             if (kind == OP_NORMACC)
                 for (size_t q = 0; q < part.size(); q++) acc_record_launch(part[q].first, W.it.acc[q]);
             KLAUNCH_PJ(k_resid_norm, W, dim3(W.blocks), dim3(TBLK), 0, s);
-            ItemList F = finalize_list(part, OP_NORM);
+            const int shift = kind != OP_NORM0;
+            ItemList F = finalize_list(part, OP_NORM, shift), C = fold_list(part, OP_NORM);
             for (size_t q = 0; q < part.size(); q++) F.it.acc[q] = W.it.acc[q];
-            KLAUNCH(k_finalize, F, dim3(F.blocks), dim3(BLK), 0, s, 0);
-            if (kind != OP_NORM0) {
-                ItemList S;
-                for (auto &pe : part) add_item(S, pe.first, OP_BEGIN, 0);
-                KLAUNCH(k_shift_p, S, dim3(S.blocks), dim3(BLK), 0, s);
-            }
+            if (C.blocks) KLAUNCH(k_fold, C, dim3(C.blocks), dim3(BLK), 0, s, 0);
+            KLAUNCH(k_finalize, F, dim3(F.blocks), dim3(BLK), 0, s, 0, shift);
             break;
         }
         case OP_STEPEND: {
             KLAUNCH(k_mass_energy, W, dim3(W.blocks), dim3(BLK), 0, s);
-            ItemList F = finalize_list(part, OP_STEPEND);
-            KLAUNCH(k_finalize, F, dim3(F.blocks), dim3(BLK), 0, s, 1);
+            REDUCE(OP_STEPEND, 1);
             break;
         }
         case OP_DISSIP: {
             KLAUNCH(k_dissipation, W, dim3(W.blocks), dim3(BLK), 0, s);
-            ItemList F = finalize_list(part, OP_DISSIP);
-            KLAUNCH(k_finalize, F, dim3(F.blocks), dim3(BLK), 0, s, 1);
+            REDUCE(OP_DISSIP, 1);
             break;
         }
         case OP_ACCEL: {
@@ -694,8 +712,7 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
         }
         case OP_DIAG: {
             KLAUNCH(k_diagnostics, W, dim3(W.blocks), dim3(BLK), 0, s);
-            ItemList F = finalize_list(part, OP_DIAG);
-            KLAUNCH(k_finalize, F, dim3(F.blocks), dim3(BLK), 0, s, 2);
+            REDUCE(OP_DIAG, 2);
             break;
         }
         default: break;
@@ -1792,7 +1809,9 @@ int qnsch_residual_noalloc(const qnsch_grid *g, const qnsch_params *prm, double 
     hipError_t e = hipMemcpyAsync(base, &d, sizeof(d), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_resid_norm<false>, dim3(tx * ty), dim3(TBLK), 0, s, (const Desc *)base, 0, tx);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(BLK), 0, s, (const Desc *)base, 0, tx * ty, 0);
+        const int n = tx * ty, ch = fold_chunk(n);
+        if (ch > 1) hipLaunchKernelGGL(k_fold, dim3((n + ch - 1) / ch), dim3(BLK), 0, s, (const Desc *)base, 0, n, 0);
+        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(BLK), 0, s, (const Desc *)base, 0, n, 0, 0);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(norms, d.red, 5 * sizeof(double), hipMemcpyDeviceToHost, s);

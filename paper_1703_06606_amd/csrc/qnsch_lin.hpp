@@ -125,11 +125,12 @@ template <int NE, int NT> __device__ __forceinline__ void ltile_load(const PhysF
 // corrections, with lr the linearised gradient-energy and capillary terms of
 // the chemical row beside the pointwise ones (across a wall the mirrored
 // ghost makes both the difference of c^ and that of dc vanish)
-__device__ __forceinline__ CellSum<float> laxis_cell(const Kon<float> &K, const float *s, const Ax &a, float r,
+template <int ES>
+__device__ __forceinline__ CellSum<float> laxis_cell(const Kon<float> &K, const float *s, const Ax<ES> &a, float r,
                                                      float drs)
 {
     const bool wP = a.per || a.ia < a.ma - 1, wM = a.per || a.ia > 0;
-    const float *sP = el(s, a.dn), *sM = el(s, -a.dn);
+    const float *sP = el<ES>(s, a.dn), *sM = el<ES>(s, -a.dn);
     const float mP = sP[T_MOB] + s[T_MOB], mM = sM[T_MOB] + s[T_MOB];
     const float S = s[T_MU] + K.alpha * s[T_P];
     const float fP = (sP[T_MU] + K.alpha * sP[T_P]) - S, fM = S - (sM[T_MU] + K.alpha * sM[T_P]);
@@ -205,11 +206,12 @@ __device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K,
                                             float *dunew, float *dvnew, int i, int j, int ti, int tj, int hlf,
                                             float omega, int slot = 0)
 {
-    const CellPos b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
+    constexpr int ES = TileF::ES;
+    const CellPos<ES> b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
     float *const e = T.at(ti, tj); // results go here, everything is read at s
     Hood<TileF, float> H;
     const float *s = e;
-    Ax a = b.a;
+    Ax<ES> a = b.a;
     const bool cpl = P.coupled;
     const float muh = lda<AS>(L.mu, b.k), f_c = lda<AS>(L.rc, b.k), f_mu = lda<AS>(L.rmu, b.k),
                 f_p = lda<AS>(L.rp, b.k);
@@ -262,8 +264,8 @@ __device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K,
         bp -= Jcp * dm;
     }
     // ---- the box
-    const FaceEq<float> flo = face_eq<float, false, true>(K, s, a, uhlo), fhi = face_eq<float, false, true>(K, el(s, a.dn), a, uhhi);
-    const float *P1 = el(s, a.dn), *M1 = el(s, -a.dn);
+    const FaceEq<float> flo = face_eq<float, false, true>(K, s, a, uhlo), fhi = face_eq<float, false, true>(K, el<ES>(s, a.dn), a, uhhi);
+    const float *P1 = el<ES>(s, a.dn), *M1 = el<ES>(s, -a.dn);
     const float alo = b.hlo ? K.hih * (M1[T_RN] * (s[T_CN] - M1[T_CN])) : 0.0f;
     const float ahi = b.hhi ? K.hih * (P1[T_RN] * (P1[T_CN] - s[T_CN])) : 0.0f;
     float alh, ahl;
@@ -280,7 +282,7 @@ __device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K,
     const float np = p0 + omega * dp;
     if (TO) {
         if (b.hlo) e[b.a.fo] = nlo;
-        if (b.hhi) el(e, b.hi<TO>())[b.a.fo] = nhi;
+        if (b.hhi) el<ES>(e, b.hi<TO>())[b.a.fo] = nhi;
         if (hlf == 0) {
             e[T_P] = np;
             if (cpl) {
@@ -314,7 +316,8 @@ __device__ __forceinline__ ResidF lresid_cell(const Kon<float> &K, const LView &
 {
     const size_t k = (size_t)j * L.pitch + i;
     const float *e = T.at(i, j);
-    const Ax ax = make_ax(L, T, i, j, 0), ay = make_ax(L, T, i, j, 1);
+    constexpr int ES = TileF::ES;
+    const Ax<ES> ax = make_ax(L, T, i, j, 0), ay = make_ax(L, T, i, j, 1);
     const ResidF f = { lda<AS>(L.rc, k), lda<AS>(L.rmu, k), lda<AS>(L.rp, k), lda<AS>(L.ru, k), lda<AS>(L.rv, k) };
     const float muh = lda<AS>(L.mu, k), uh = lda<AS>(L.u, k), vh = lda<AS>(L.v, k);
     float r, drs;

@@ -267,7 +267,7 @@ __device__ __forceinline__ float quad_sum(float x)
 }
 template <typename IT> __device__ __forceinline__ void k_mx_restrict_body(const IT &it, int set)
 {
-    TILE_LDS float sm[LTILE_FLOATS];
+    TILE_LDS float sm[L_ES * TILE_S * (TY + 2)];
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
@@ -276,7 +276,7 @@ template <typename IT> __device__ __forceinline__ void k_mx_restrict_body(const 
     if (set) { // the pre-smoothing left the cell corrections in the second set
         Lf.dc = d.dc2; Lf.dmu = d.dmu2; Lf.dp = d.dp2;
     }
-    const TileF T = item_tile<TileF>(sm, it, k, d);
+    const TileF T = item_tile<TileF, TX + 2>(sm, it, k, d);
     ltile_load<2, TBLK>(d.Pf, Lf, T);
     __syncthreads();
     const int cc = threadIdx.x >> 2, ch = threadIdx.x & 3;
@@ -614,12 +614,12 @@ QN_KERNEL(k_mx_restrict_n, __launch_bounds__(BLK), (), ())
 // field, packed), for checking the linearisation
 template <typename IT> __device__ __forceinline__ void k_mx_linresid_body(const IT &it)
 {
-    TILE_LDS float sm[LTILE_FLOATS];
+    TILE_LDS float sm[L_ES * TILE_S * (TY + 2)];
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
     const LView L = lview_of(d, it_par(it, k));
-    const TileF T = item_tile<TileF>(sm, it, k, d);
+    const TileF T = item_tile<TileF, TX + 2>(sm, it, k, d);
     ltile_load<2, TBLK>(d.Pf, L, T);
     __syncthreads();
     const size_t n = (size_t)L.m1 * L.m2;
