@@ -364,51 +364,6 @@ __device__ __forceinline__ void fused_load(const Phys &P, const View &L, const T
         s[T_V2] = s[T_V];
     }
 }
-// The images across walls after a half-sweep whose faces went to slot `slot`:
-// the rows and columns next to the level that the equations of a cell of the
-// level read (-1, and m, m + 1) follow their sources (ldc clamps a cell to the
-// wall row; ldu, ldv reflect a tangential ghost; faces on and beyond a wall
-// stay zero).  Periodic images were relaxed in place.  put copies one
-// element's image.
-template <typename TT, typename F> __device__ __forceinline__ void wall_images(const TT &T, int m1, int m2, int bcx, int bcy, F put)
-{
-    const int je = T.j0 + T.H - 2, ie = T.i0 + T.W - 2; // last row and column of the tile
-    // rows -1, m2, m2 + 1 and columns -1, m1, m1 + 1 that the tile holds
-    const int rb = !bcy && T.j0 <= 0, nr = rb + (bcy ? 0 : min(max(je - m2 + 1, 0), 2));
-    const int cl = !bcx && T.i0 <= 0, nc = cl + (bcx ? 0 : min(max(ie - m1 + 1, 0), 2));
-    for (int e = threadIdx.x; e < nr * T.W + nc * T.H; e += FBLK) {
-        if (e < nr * T.W) {
-            const int r = e / T.W, i = T.i0 - 1 + (e - r * T.W), j = r < rb ? -1 : m2 + r - rb;
-            if (bcx || (i >= -1 && i <= m1 + 1)) put(i, j, bcx ? i : min(max(i, 0), m1 - 1), j < 0 ? 0 : m2 - 1);
-        } else {
-            const int f = e - nr * T.W, c = f / T.H, j = T.j0 - 1 + (f - c * T.H), i = c < cl ? -1 : m1 + c - cl;
-            if (bcy || (j >= 0 && j < m2)) put(i, j, i < 0 ? 0 : m1 - 1, j);
-        }
-    }
-}
-// whether the tile has such rows or columns
-template <typename TT> __device__ __forceinline__ bool at_wall(const TT &T, int m1, int m2, int bcx, int bcy)
-{
-    return (!bcx && (T.i0 <= 0 || T.i0 + T.W - 2 >= m1)) || (!bcy && (T.j0 <= 0 || T.j0 + T.H - 2 >= m2));
-}
-__device__ __forceinline__ void fused_images(const View &L, const Tile &T, int slot)
-{
-    const int fu = slot ? T_U2 : T_U, fv = slot ? T_V2 : T_V;
-    wall_images(T, L.m1, L.m2, L.bcx, L.bcy, [&](int i, int j, int si, int sj) {
-        // every value the element may take, before any store (an image's
-        // source is never an image, so no element read here is written)
-        const double *q = T.at(si, sj);
-        const double u = T.at(i, sj)[fu], v = T.at(si, j)[fv], c = q[T_C], mu = q[T_MU], p = q[T_P], rs = q[T_RS];
-        double *s = T.at(i, j);
-        const bool gx = si != i, gy = sj != j;
-        s[T_C] = c;
-        s[T_MU] = mu;
-        s[T_P] = p;
-        s[T_RS] = rs;
-        s[fu] = (!L.bcx && (i <= 0 || i >= L.m1)) ? 0.0 : (gy ? -u : u);
-        s[fv] = (!L.bcy && (j <= 0 || j >= L.m2)) ? 0.0 : (gx ? -v : v);
-    });
-}
 template <bool PJ, int NS, int TS, typename IT>
 __device__ __forceinline__ void fused_body(const IT &it, int dir, double omega, int prolong)
 {
@@ -435,7 +390,6 @@ __device__ __forceinline__ void fused_body(const IT &it, int dir, double omega, 
     PSrc ps = {};
     if (prolong) ps = psrc_of(d, &d + 1, it_cpar(it, k));
     fused_load(P, L, T, prolong, ps);
-    const bool wall = at_wall(T, L.m1, L.m2, L.bcx, L.bcy);
     __syncthreads();
     const int hlf = threadIdx.x & 1;
     // a half-sweep of the region widened by ext cells
@@ -450,10 +404,6 @@ __device__ __forceinline__ void fused_body(const IT &it, int dir, double omega, 
             }
         }
         __syncthreads();
-        if (wall) {
-            fused_images(L, T, colour ^ 1);
-            __syncthreads();
-        }
     };
     typedef std::integral_constant<int, 0> Red;
     typedef std::integral_constant<int, 1> Black;
@@ -685,22 +635,22 @@ __device__ __forceinline__ Rhs bot_rhs(const BotLev &B)
     const Rhs F = { B.f, B.f + n, B.f + 2 * n, B.f + 3 * n, B.f + 4 * n };
     return F;
 }
-// the images follow their sources; the faces are in slot `slot`
-__device__ __forceinline__ void bot_images(const BotLev &B, int slot)
+// the images follow their sources, for a residual (relaxations read the sources)
+__device__ __forceinline__ void bot_images(const BotLev &B)
 {
-    const int n = ring_size(B.m1, B.m2), fu = slot ? T_U2 : T_U, fv = slot ? T_V2 : T_V;
+    const int n = ring_size(B.m1, B.m2);
     for (int k = threadIdx.x; k < n; k += BOT) {
         const Image g = B.ring[k];
         const double *s = B.T.s + g.c * T_ES;
         const double c = s[T_C], mu = s[T_MU], p = s[T_P], rs = s[T_RS];
-        const double u = B.T.s[(g.u >> 2) * T_ES + fu], v = B.T.s[(g.v >> 2) * T_ES + fv];
+        const double u = B.T.s[(g.u >> 2) * T_ES + T_U], v = B.T.s[(g.v >> 2) * T_ES + T_V];
         double *t = B.T.s + g.e * T_ES;
         t[T_C] = c;
         t[T_MU] = mu;
         t[T_P] = p;
         t[T_RS] = rs;
-        t[fu] = signed_val((g.u & 3) - 1, u);
-        t[fv] = signed_val((g.v & 3) - 1, v);
+        t[T_U] = signed_val((g.u & 3) - 1, u);
+        t[T_V] = signed_val((g.v & 3) - 1, v);
     }
 }
 // sweeps of a level (an even number of half-sweeps: the faces end in slot 0)
@@ -724,8 +674,6 @@ __device__ __forceinline__ void bot_smooth(const Phys &P, const Desc &d, const B
             if (i >= B.m1) { i -= B.m1; j++; }
         }
         __syncthreads();
-        bot_images(B, colour.value ^ 1);
-        __syncthreads();
     };
     for (int s = 0; s < sweeps; s++) {
         sweep(std::integral_constant<int, 0>());
@@ -738,6 +686,8 @@ template <bool PJ>
 __device__ __forceinline__ void bot_restrict(const Phys &P, const Desc &d, const BotLev &A, const BotLev &C)
 {
     const int nc = C.m1 * C.m2;
+    bot_images(A);
+    __syncthreads();
     {
         const Kon<double> K = d.K;
         const View L = bot_view(A, d);
@@ -770,7 +720,7 @@ __device__ __forceinline__ void bot_restrict(const Phys &P, const Desc &d, const
         }
     }
     __syncthreads();
-    bot_images(C, 0);
+    bot_images(C);
     __syncthreads();
     {
         const Desc &dc = (&d)[1];
@@ -817,8 +767,6 @@ __device__ __forceinline__ void bot_prolong(const Phys &P, const Desc &d, const 
         if (bx || i >= 1) o[T_U] += du;
         if (by || j >= 1) o[T_V] += dv;
     }
-    __syncthreads();
-    bot_images(A, 0);
     __syncthreads();
 }
 template <bool PJ, typename IT>
@@ -874,6 +822,7 @@ __device__ __forceinline__ void k_bottom_body(const IT &it, int nu1, int nu2, in
             t[T_MOB] = mob_of(P, n);
             t[T_UN] = signed_val(q.su, u);
             t[T_VN] = signed_val(q.sv, v);
+            t[T_U2] = t[T_V2] = 0.0; // on the faces of a high wall
         }
         ring_build(B.T, B.m1, B.m2, L.bcx, L.bcy, B.ring, threadIdx.x, BOT);
     }

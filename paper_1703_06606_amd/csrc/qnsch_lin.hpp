@@ -221,7 +221,7 @@ __device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K,
     const float uhlo = lda<AS>(fw, b.k), uhhi = lda<AS>(fw, b.khi);
     const float f_lo = lda<AS>(fN, b.k), f_hi = lda<AS>(fN, b.khi);
     if (HOOD) {
-        a = H.template load<true>(e, b.a);
+        a = H.template load<true, TO == 2>(e, b.a);
         s = H.centre();
     }
     float r, drs;

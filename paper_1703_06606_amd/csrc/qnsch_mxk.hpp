@@ -160,23 +160,6 @@ __device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, co
         s[T_V2] = s[T_V];
     }
 }
-// the images across walls (as fused_images)
-__device__ __forceinline__ void mx_fused_images(const LView &L, const TileF &T, int slot)
-{
-    const int fu = slot ? T_U2 : T_U, fv = slot ? T_V2 : T_V;
-    wall_images(T, L.m1, L.m2, L.bcx, L.bcy, [&](int i, int j, int si, int sj) {
-        const float *q = T.at(si, sj);
-        const float u = T.at(i, sj)[fu], v = T.at(si, j)[fv], dc = q[L_DC], mu = q[T_MU], p = q[T_P], drs = q[L_DRS];
-        float *s = T.at(i, j);
-        const bool gx = si != i, gy = sj != j;
-        s[L_DC] = dc;
-        s[T_MU] = mu;
-        s[T_P] = p;
-        s[L_DRS] = drs;
-        s[fu] = (!L.bcx && (i <= 0 || i >= L.m1)) ? 0.0f : (gy ? -u : u);
-        s[fv] = (!L.bcy && (j <= 0 || j >= L.m2)) ? 0.0f : (gx ? -v : v);
-    });
-}
 template <int NS, int TS, typename IT> __device__ __forceinline__ void mx_fused_body(const IT &it, int dir, float omega, int prolong)
 {
     typedef Fused<NS, TS> G;
@@ -200,7 +183,6 @@ template <int NS, int TS, typename IT> __device__ __forceinline__ void mx_fused_
     float *const un = d.dub[par ^ 1], *const vn = d.dvb[par ^ 1];
     if (prolong) mx_fused_load<true>(P, L, T, psrcf_of(d, &d + 1, it_cpar(it, k)));
     else mx_fused_load<false>(P, L, T, PSrcF());
-    const bool wall = at_wall(T, L.m1, L.m2, L.bcx, L.bcy);
     __syncthreads();
     const int hlf = threadIdx.x & 1;
     auto half = [&](auto cext, auto ccol) {
@@ -214,10 +196,6 @@ template <int NS, int TS, typename IT> __device__ __forceinline__ void mx_fused_
             }
         }
         __syncthreads();
-        if (wall) {
-            mx_fused_images(L, T, colour ^ 1);
-            __syncthreads();
-        }
     };
     typedef std::integral_constant<int, 0> Red;
     typedef std::integral_constant<int, 1> Black;
@@ -382,21 +360,21 @@ __device__ __forceinline__ LView bot_view(const BotLevF &B, const Desc &d)
     L.rc = B.r; L.rmu = B.r + n; L.rp = B.r + 2 * n; L.ru = B.r + 3 * n; L.rv = B.r + 4 * n;
     return L;
 }
-__device__ __forceinline__ void bot_images(const BotLevF &B, int slot)
+__device__ __forceinline__ void bot_images(const BotLevF &B)
 {
-    const int n = ring_size(B.m1, B.m2), fu = slot ? T_U2 : T_U, fv = slot ? T_V2 : T_V;
+    const int n = ring_size(B.m1, B.m2);
     for (int k = threadIdx.x; k < n; k += BOT) {
         const Image g = B.ring[k];
         const float *s = B.T.s + g.c * L_ES;
         const float dc = s[L_DC], mu = s[T_MU], p = s[T_P], drs = s[L_DRS];
-        const float u = B.T.s[(g.u >> 2) * L_ES + fu], v = B.T.s[(g.v >> 2) * L_ES + fv];
+        const float u = B.T.s[(g.u >> 2) * L_ES + T_U], v = B.T.s[(g.v >> 2) * L_ES + T_V];
         float *t = B.T.s + g.e * L_ES;
         t[L_DC] = dc;
         t[T_MU] = mu;
         t[T_P] = p;
         t[L_DRS] = drs;
-        t[fu] = signed_val((g.u & 3) - 1, u);
-        t[fv] = signed_val((g.v & 3) - 1, v);
+        t[T_U] = signed_val((g.u & 3) - 1, u);
+        t[T_V] = signed_val((g.v & 3) - 1, v);
     }
 }
 __device__ __forceinline__ void bot_smooth(const PhysF &P, const Desc &d, const BotLevF &B, int sweeps, float omega)
@@ -415,8 +393,6 @@ __device__ __forceinline__ void bot_smooth(const PhysF &P, const Desc &d, const 
             if (i >= B.m1) { i -= B.m1; j++; }
         }
         __syncthreads();
-        bot_images(B, colour.value ^ 1);
-        __syncthreads();
     };
     for (int s = 0; s < sweeps; s++) {
         sweep(std::integral_constant<int, 0>());
@@ -430,6 +406,8 @@ __device__ __forceinline__ void bot_restrict(const PhysF &P, const Desc &d, cons
     const int nc = C.m1 * C.m2, na = A.m1 * A.m2;
     const Kon<float> K = d.Kf;
     const LView L = bot_view(A, d);
+    bot_images(A);
+    __syncthreads();
     for (int t = threadIdx.x; t < 4 * nc; t += BOT) {
         const int cc = t >> 2, ch = t & 3;
         const int J = cc / C.m1, I = cc - J * C.m1, i = 2 * I + (ch & 1), j = 2 * J + (ch >> 1), w = j * A.m1 + i;
@@ -461,8 +439,8 @@ __device__ __forceinline__ void bot_restrict(const PhysF &P, const Desc &d, cons
         float *t = C.T.s + g.e * L_ES;
         t[T_C] = s[T_C];
         t[T_RS] = s[T_RS];
+        t[T_U] = t[T_U2] = t[T_V] = t[T_V2] = 0.0f; // on the faces of a high wall
     }
-    bot_images(C, 0);
     __syncthreads();
 }
 // delta_A += P delta_C (k_mx_prolong's arithmetic)
@@ -493,8 +471,6 @@ __device__ __forceinline__ void bot_prolong(const PhysF &P, const Desc &d, const
         if (bx || i >= 1) o[T_U] += du;
         if (by || j >= 1) o[T_V] += dv;
     }
-    __syncthreads();
-    bot_images(A, 0);
     __syncthreads();
 }
 template <typename IT>
