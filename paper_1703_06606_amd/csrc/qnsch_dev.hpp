@@ -376,31 +376,27 @@ struct alignas(16) Image {
     int e, c, u, v; // element; elements of the sources, faces' signs + 1 in the low two bits
 };
 __host__ __device__ __forceinline__ int ring_size(int m1, int m2) { return (m1 + 3) * (m2 + 3) - m1 * m2; }
-// build the ring's entries (thread t of NT)
-template <typename TT>
-__device__ __forceinline__ void ring_build(const TT &T, int m1, int m2, int bcx, int bcy, Image *ring, int t, int NT)
+// entry k of the ring
+template <typename TT> __device__ __forceinline__ Image ring_entry(const TT &T, int m1, int m2, int bcx, int bcy, int k)
 {
-    const int n = ring_size(m1, m2);
-    for (int k = t; k < n; k += NT) {
-        int i, j;
-        // rows -1, m2, m2 + 1, then columns -1, m1, m1 + 1 of the other rows
-        if (k < 3 * (m1 + 3)) {
-            const int r = k / (m1 + 3);
-            i = k - r * (m1 + 3) - 1;
-            j = r == 0 ? -1 : m2 + r - 1;
-        } else {
-            const int q = k - 3 * (m1 + 3), r = q / 3, s = q - 3 * r;
-            j = r;
-            i = s == 0 ? -1 : m1 + s - 1;
-        }
-        const TileSrcIJ q = tile_src_ij(m1, m2, bcx, bcy, i, j);
-        Image g;
-        g.e = T.idx(i, j);
-        g.c = T.idx(q.ic, q.jc);
-        g.u = T.idx(q.iu, q.ju) * 4 + q.su + 1;
-        g.v = T.idx(q.iv, q.jv) * 4 + q.sv + 1;
-        ring[k] = g;
+    int i, j;
+    // rows -1, m2, m2 + 1, then columns -1, m1, m1 + 1 of the other rows
+    if (k < 3 * (m1 + 3)) {
+        const int r = k / (m1 + 3);
+        i = k - r * (m1 + 3) - 1;
+        j = r == 0 ? -1 : m2 + r - 1;
+    } else {
+        const int q = k - 3 * (m1 + 3), r = q / 3, s = q - 3 * r;
+        j = r;
+        i = s == 0 ? -1 : m1 + s - 1;
     }
+    const TileSrcIJ q = tile_src_ij(m1, m2, bcx, bcy, i, j);
+    Image g;
+    g.e = T.idx(i, j);
+    g.c = T.idx(q.ic, q.jc);
+    g.u = T.idx(q.iu, q.ju) * 4 + q.su + 1;
+    g.v = T.idx(q.iv, q.jv) * 4 + q.sv + 1;
+    return g;
 }
 
 // --------------------------------------------------------------------------

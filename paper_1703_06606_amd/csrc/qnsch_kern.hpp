@@ -622,6 +622,26 @@ __device__ __forceinline__ BotLev bot_lev(double *sm, int m1, int m2, int l)
     B.ring = (Image *)(top ? B.w0 : B.w0 + 5 * m1 * m2);
     return B;
 }
+// item e of the items of levels l, l + 1, .. of `depth`, size(m1, m2) on each:
+// its level and its place there; whether there is one
+template <typename F> __device__ __forceinline__ bool bot_find(int &l, int &e, int depth, int m1, int m2, F size)
+{
+    for (; l < depth; l++) {
+        const int n = size(m1 >> l, m2 >> l);
+        if (e < n) return true;
+        e -= n;
+    }
+    return false;
+}
+// f(lev(l), k) for the ring entries k of every level l
+template <typename L, typename F> __device__ __forceinline__ void bot_rings(int depth, int m1, int m2, L lev, F f)
+{
+    for (int e = threadIdx.x;; e += BOT) {
+        int l = 0, k = e;
+        if (!bot_find(l, k, depth, m1, m2, ring_size)) break;
+        f(lev(l), k);
+    }
+}
 __device__ __forceinline__ View bot_view(const BotLev &B, const Desc &d)
 {
     View L = {};
@@ -636,10 +656,11 @@ __device__ __forceinline__ Rhs bot_rhs(const BotLev &B)
     return F;
 }
 // the images follow their sources, for a residual (relaxations read the sources)
-__device__ __forceinline__ void bot_images(const BotLev &B)
+// (thread t of BOT)
+__device__ __forceinline__ void bot_images(const BotLev &B, int t)
 {
     const int n = ring_size(B.m1, B.m2);
-    for (int k = threadIdx.x; k < n; k += BOT) {
+    for (int k = t; k < n; k += BOT) {
         const Image g = B.ring[k];
         const double *s = B.T.s + g.c * T_ES;
         const double c = s[T_C], mu = s[T_MU], p = s[T_P], rs = s[T_RS];
@@ -685,42 +706,44 @@ __device__ __forceinline__ void bot_smooth(const Phys &P, const Desc &d, const B
 template <bool PJ>
 __device__ __forceinline__ void bot_restrict(const Phys &P, const Desc &d, const BotLev &A, const BotLev &C)
 {
-    const int nc = C.m1 * C.m2;
-    bot_images(A);
+    const int nc = C.m1 * C.m2, rt = BOT - 1 - threadIdx.x;
+    // R w, by the last threads, while the first ones update the images of A
+    for (int t = rt; t < nc; t += BOT) {
+        const int J = t / C.m1, I = t - J * C.m1;
+        const double *a = A.T.at(2 * I, 2 * J), *b = a + T_ES, *s = el<T_ES>(a, A.T.S), *e = s + T_ES;
+        const double w[5] = { 0.25 * ((a[T_C] + b[T_C]) + (s[T_C] + e[T_C])), 0.25 * ((a[T_MU] + b[T_MU]) + (s[T_MU] + e[T_MU])),
+                              0.25 * ((a[T_P] + b[T_P]) + (s[T_P] + e[T_P])), 0.5 * (a[T_U] + s[T_U]),
+                              0.5 * (a[T_V] + b[T_V]) };
+        double *o = C.T.at(I, J);
+        o[T_C] = w[0];
+        o[T_MU] = w[1];
+        o[T_P] = w[2];
+        o[T_RS] = rho_of(P, w[0]);
+        o[T_U] = o[T_U2] = w[3];
+        o[T_V] = o[T_V2] = w[4];
+#pragma unroll
+        for (int q = 0; q < 5; q++) C.w0[q * nc + t] = w[q];
+    }
+    bot_images(A, threadIdx.x);
     __syncthreads();
+    // R r; the images of C meanwhile
     {
         const Kon<double> K = d.K;
         const View L = bot_view(A, d);
         const Rhs F = bot_rhs(A);
+        bot_images(C, rt);
         for (int t = threadIdx.x; t < 4 * nc; t += BOT) {
             const int cc = t >> 2, ch = t & 3;
             const int J = cc / C.m1, I = cc - J * C.m1, i = 2 * I + (ch & 1), j = 2 * J + (ch >> 1);
             const Resid r = resid_cell<PJ, 3>(K, L, A.T, F, i, j);
-            const double *e = A.T.at(i, j);
             const bool wu = (ch & 1) == 0, wv = (ch >> 1) == 0; // faces of the coarse cell
-            const double c = 0.25 * quad_sum(e[T_C]), mu = 0.25 * quad_sum(e[T_MU]), p = 0.25 * quad_sum(e[T_P]),
-                         u = 0.5 * quad_sum(wu ? e[T_U] : 0.0), v = 0.5 * quad_sum(wv ? e[T_V] : 0.0);
             const double f[5] = { 0.25 * quad_sum(r.c), 0.25 * quad_sum(r.mu), 0.25 * quad_sum(r.p),
                                   0.5 * quad_sum(wu ? r.u : 0.0), 0.5 * quad_sum(wv ? r.v : 0.0) };
-            if (ch == 0) {
-                double *o = C.T.at(I, J);
-                const double w[5] = { c, mu, p, u, v };
-                o[T_C] = c;
-                o[T_MU] = mu;
-                o[T_P] = p;
-                o[T_RS] = rho_of(P, c);
-                o[T_U] = o[T_U2] = u;
-                o[T_V] = o[T_V2] = v;
+            if (ch == 0)
 #pragma unroll
-                for (int q = 0; q < 5; q++) {
-                    C.w0[q * nc + cc] = w[q];
-                    C.f[q * nc + cc] = f[q];
-                }
-            }
+                for (int q = 0; q < 5; q++) C.f[q * nc + cc] = f[q];
         }
     }
-    __syncthreads();
-    bot_images(C);
     __syncthreads();
     {
         const Desc &dc = (&d)[1];
@@ -747,17 +770,11 @@ __device__ __forceinline__ void bot_prolong(const Phys &P, const Desc &d, const 
     for (int t = threadIdx.x; t < na; t += BOT) {
         const int j = t / A.m1, i = t - j * A.m1, I = i >> 1, J = j >> 1;
         auto corr = [&](int f, int a, int b) { return C.T.at(a, b)[f] - C.w0[(f == T_C ? 0 : f == T_MU ? 1 : f == T_P ? 2 : f == T_U ? 3 : 4) * nc + b * C.m1 + a]; };
-        double du = corr(T_U, I, J), dv = corr(T_V, I, J);
-        if (i & 1) {
-            const bool in = I + 1 < C.m1;
-            const double e = in || bx ? corr(T_U, in ? I + 1 : 0, J) : 0.0;
-            du = 0.5 * (du + e);
-        }
-        if (j & 1) {
-            const bool in = J + 1 < C.m2;
-            const double e = in || by ? corr(T_V, I, in ? J + 1 : 0) : 0.0;
-            dv = 0.5 * (dv + e);
-        }
+        // (no loads under a condition: they would wait for each other)
+        const bool ix = I + 1 < C.m1, jy = J + 1 < C.m2;
+        const double u0 = corr(T_U, I, J), u1 = corr(T_U, ix ? I + 1 : 0, J), v0 = corr(T_V, I, J),
+                     v1 = corr(T_V, I, jy ? J + 1 : 0);
+        const double du = i & 1 ? 0.5 * (u0 + (ix || bx ? u1 : 0.0)) : u0, dv = j & 1 ? 0.5 * (v0 + (jy || by ? v1 : 0.0)) : v0;
         double *o = A.T.at(i, j);
         const double c = o[T_C] + corr(T_C, I, J);
         o[T_C] = c;
@@ -779,53 +796,74 @@ __device__ __forceinline__ void k_bottom_body(const IT &it, int nu1, int nu2, in
     const int par = it_par(it, k), m1 = d.m1, m2 = d.m2, depth = d.depth;
     const View L = view_of(d, par);
     double *const ua = d.ub[par], *const va = d.vb[par];
-    // the top level with its images and right-hand sides, and the time-n data
-    // of the coarser ones; every load of an element before any use
+    // The cells of the top level with their right-hand sides, and the time-n data
+    // of the coarser levels' cells (no more than BOT in all), every load before
+    // any use; the images' sources meanwhile, and then the images' time-n data.
+    const int n = m1 * m2;
+    int lc = 1, ec = threadIdx.x;
+    const bool hc = bot_find(lc, ec, depth, m1, m2, [](int a, int b) { return a * b; });
+    auto lev = [&](int l) { return bot_lev(sm, m1, m2, l); };
+    const BotLev Bc = lev(hc ? lc : 0);
+    const int jc = ec / Bc.m1, ic = ec - jc * Bc.m1;
+    const Desc &dc = (&d)[hc ? lc : 0];
+    const double *const pc = dc.cn, *const pu = dc.un, *const pv = dc.vn;
     {
         const Rhs F = rhs_of(d);
         const BotLev B = bot_lev(sm, m1, m2, 0);
-        const int n = m1 * m2;
-        for (int e = threadIdx.x; e < B.T.W * B.T.H; e += BOT) {
-            const int b = e / B.T.W, a = e - b * B.T.W, i = a - 1, j = b - 1;
+        for (int t0 = threadIdx.x; t0 < n || t0 < BOT; t0 += BOT) {
+            const int e = min(t0, n - 1), j = e / m1, i = e - j * m1;
             const TileSrc q = tile_src(m1, m2, L.pitch, L.bcx, L.bcy, i, j);
-            const bool cell = i >= 0 && i < m1 && j >= 0 && j < m2;
             const double v[8] = { lda<1>(L.c, q.c), lda<1>(L.mu, q.c), lda<1>(L.p, q.c), lda<1>(L.u, q.u),
                                   lda<1>(L.v, q.v), lda<1>(L.cn, q.c), lda<1>(L.un, q.u), lda<1>(L.vn, q.v) };
             double f[5] = { 0.0, 0.0, 0.0, 0.0, 0.0 };
-            if (F.fc && cell) {
+            if (F.fc) {
                 f[0] = lda<1>(F.fc, q.c); f[1] = lda<1>(F.fmu, q.c); f[2] = lda<1>(F.fp, q.c);
                 f[3] = lda<1>(F.fu, q.c); f[4] = lda<1>(F.fv, q.c);
             }
+            const bool co = hc && t0 < BOT;
+            double w[3] = { 0.0, 0.0, 0.0 };
+            TileSrc qc = {};
+            if (co) {
+                qc = tile_src(Bc.m1, Bc.m2, Bc.m1, L.bcx, L.bcy, ic, jc);
+                w[0] = lda<1>(pc, qc.c); w[1] = lda<1>(pu, qc.u); w[2] = lda<1>(pv, qc.v);
+            }
+            if (t0 < BOT)
+                bot_rings(depth, m1, m2, lev, [&](const BotLev &R, int k) { R.ring[k] = ring_entry(R.T, R.m1, R.m2, L.bcx, L.bcy, k); });
             __builtin_amdgcn_sched_barrier(0);
-            double *t = B.T.s + (b * B.T.S + a) * T_ES;
-            tile_put(P, t, q.su, q.sv, v);
-            t[T_U2] = t[T_U];
-            t[T_V2] = t[T_V];
-            if (cell)
+            if (t0 < n) {
+                double *t = B.T.at(i, j);
+                tile_put(P, t, q.su, q.sv, v);
+                t[T_U2] = t[T_U];
+                t[T_V2] = t[T_V];
 #pragma unroll
-                for (int g = 0; g < 5; g++) B.f[g * n + j * m1 + i] = f[g];
+                for (int g = 0; g < 5; g++) B.f[g * n + e] = f[g];
+            }
+            if (co) {
+                double *o = Bc.T.at(ic, jc);
+                o[T_CN] = w[0];
+                o[T_RN] = rho_of(P, w[0]);
+                o[T_MV] = visc_of(P, w[0]);
+                o[T_MOB] = mob_of(P, w[0]);
+                o[T_UN] = signed_val(qc.su, w[1]);
+                o[T_VN] = signed_val(qc.sv, w[2]);
+            }
         }
-        ring_build(B.T, m1, m2, L.bcx, L.bcy, B.ring, threadIdx.x, BOT);
     }
-    for (int l = 1; l < depth; l++) {
-        const BotLev B = bot_lev(sm, m1, m2, l);
-        const Desc &c = (&d)[l];
-        const double *const cn = c.cn, *const un = c.un, *const vn = c.vn;
-        for (int e = threadIdx.x; e < B.T.W * B.T.H; e += BOT) {
-            const int b = e / B.T.W, a = e - b * B.T.W;
-            const TileSrc q = tile_src(B.m1, B.m2, B.m1, L.bcx, L.bcy, a - 1, b - 1);
-            const double n = lda<1>(cn, q.c), u = lda<1>(un, q.u), v = lda<1>(vn, q.v);
-            double *t = B.T.s + (b * B.T.S + a) * T_ES;
-            t[T_CN] = n;
-            t[T_RN] = rho_of(P, n);
-            t[T_MV] = visc_of(P, n);
-            t[T_MOB] = mob_of(P, n);
-            t[T_UN] = signed_val(q.su, u);
-            t[T_VN] = signed_val(q.sv, v);
-            t[T_U2] = t[T_V2] = 0.0; // on the faces of a high wall
-        }
-        ring_build(B.T, B.m1, B.m2, L.bcx, L.bcy, B.ring, threadIdx.x, BOT);
-    }
+    __syncthreads();
+    bot_rings(depth, m1, m2, lev, [&](const BotLev &R, int k) {
+        const Image g = R.ring[k];
+        const double *s = R.T.s + g.c * T_ES;
+        const double cn = s[T_CN], rn = s[T_RN], mv = s[T_MV], mb = s[T_MOB], un = R.T.s[(g.u >> 2) * T_ES + T_UN],
+                     vn = R.T.s[(g.v >> 2) * T_ES + T_VN];
+        double *t = R.T.s + g.e * T_ES;
+        t[T_CN] = cn;
+        t[T_RN] = rn;
+        t[T_MV] = mv;
+        t[T_MOB] = mb;
+        t[T_UN] = signed_val((g.u & 3) - 1, un);
+        t[T_VN] = signed_val((g.v & 3) - 1, vn);
+        t[T_U] = t[T_U2] = t[T_V] = t[T_V2] = 0.0; // on the faces of a high wall
+    });
     __syncthreads();
     // down to the coarsest level and back up (one copy of the code of each
     // phase: it is fetched once).  The coarsest level over-relaxes the velocity

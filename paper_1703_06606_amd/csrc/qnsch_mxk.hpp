@@ -360,10 +360,10 @@ __device__ __forceinline__ LView bot_view(const BotLevF &B, const Desc &d)
     L.rc = B.r; L.rmu = B.r + n; L.rp = B.r + 2 * n; L.ru = B.r + 3 * n; L.rv = B.r + 4 * n;
     return L;
 }
-__device__ __forceinline__ void bot_images(const BotLevF &B)
+__device__ __forceinline__ void bot_images(const BotLevF &B, int t)
 {
     const int n = ring_size(B.m1, B.m2);
-    for (int k = threadIdx.x; k < n; k += BOT) {
+    for (int k = t; k < n; k += BOT) {
         const Image g = B.ring[k];
         const float *s = B.T.s + g.c * L_ES;
         const float dc = s[L_DC], mu = s[T_MU], p = s[T_P], drs = s[L_DRS];
@@ -403,43 +403,45 @@ __device__ __forceinline__ void bot_smooth(const PhysF &P, const Desc &d, const 
 // C, whose correction starts at zero (its time-n fields are in the tile)
 __device__ __forceinline__ void bot_restrict(const PhysF &P, const Desc &d, const BotLevF &A, const BotLevF &C)
 {
-    const int nc = C.m1 * C.m2, na = A.m1 * A.m2;
-    const Kon<float> K = d.Kf;
-    const LView L = bot_view(A, d);
-    bot_images(A);
-    __syncthreads();
-    for (int t = threadIdx.x; t < 4 * nc; t += BOT) {
-        const int cc = t >> 2, ch = t & 3;
-        const int J = cc / C.m1, I = cc - J * C.m1, i = 2 * I + (ch & 1), j = 2 * J + (ch >> 1), w = j * A.m1 + i;
-        const ResidF r = lresid_cell<3>(K, L, A.T, i, j);
-        const bool wu = (ch & 1) == 0, wv = (ch >> 1) == 0; // faces of the coarse cell
-        const float f[5] = { 0.25f * quad_sum(r.c), 0.25f * quad_sum(r.mu), 0.25f * quad_sum(r.p),
-                             0.5f * quad_sum(wu ? r.u : 0.0f), 0.5f * quad_sum(wv ? r.v : 0.0f) };
-        const float x[3] = { 0.25f * quad_sum(A.x[w]), 0.5f * quad_sum(wu ? A.x[na + w] : 0.0f),
-                             0.5f * quad_sum(wv ? A.x[2 * na + w] : 0.0f) };
-        const float c = 0.25f * quad_sum(A.T.at(i, j)[T_C]);
-        if (ch == 0) {
-            float *o = C.T.at(I, J);
-            o[T_C] = c;
-            o[T_RS] = rhof(P, c);
-            o[T_MU] = o[T_P] = o[L_DC] = o[L_DRS] = 0.0f;
-            o[T_U] = o[T_U2] = o[T_V] = o[T_V2] = 0.0f;
-#pragma unroll
-            for (int q = 0; q < 5; q++) C.r[q * nc + cc] = f[q];
-#pragma unroll
-            for (int q = 0; q < 3; q++) C.x[q * nc + cc] = x[q];
-        }
+    const int nc = C.m1 * C.m2, na = A.m1 * A.m2, rt = BOT - 1 - threadIdx.x;
+    for (int t = rt; t < nc; t += BOT) {
+        const int J = t / C.m1, I = t - J * C.m1, w = 2 * J * A.m1 + 2 * I;
+        const float *a = A.T.at(2 * I, 2 * J), *b = a + L_ES, *s = el<L_ES>(a, A.T.S), *e = s + L_ES;
+        const float *x = A.x + w, *y = x + A.m1;
+        const float c = 0.25f * ((a[T_C] + b[T_C]) + (s[T_C] + e[T_C]));
+        const float xm = 0.25f * ((x[0] + x[1]) + (y[0] + y[1])), xu = 0.5f * (x[na] + y[na]), xv = 0.5f * (x[2 * na] + x[2 * na + 1]);
+        float *o = C.T.at(I, J);
+        o[T_C] = c;
+        o[T_RS] = rhof(P, c);
+        o[T_MU] = o[T_P] = o[L_DC] = o[L_DRS] = 0.0f;
+        o[T_U] = o[T_U2] = o[T_V] = o[T_V2] = 0.0f;
+        C.x[t] = xm;
+        C.x[nc + t] = xu;
+        C.x[2 * nc + t] = xv;
     }
+    bot_images(A, threadIdx.x);
     __syncthreads();
     // images: also of the linearisation point's c and rho, once
     const int n = ring_size(C.m1, C.m2);
-    for (int k = threadIdx.x; k < n; k += BOT) {
+    for (int k = rt; k < n; k += BOT) {
         const Image g = C.ring[k];
         const float *s = C.T.s + g.c * L_ES;
         float *t = C.T.s + g.e * L_ES;
         t[T_C] = s[T_C];
         t[T_RS] = s[T_RS];
-        t[T_U] = t[T_U2] = t[T_V] = t[T_V2] = 0.0f; // on the faces of a high wall
+    }
+    const Kon<float> K = d.Kf;
+    const LView L = bot_view(A, d);
+    for (int t = threadIdx.x; t < 4 * nc; t += BOT) {
+        const int cc = t >> 2, ch = t & 3;
+        const int J = cc / C.m1, I = cc - J * C.m1, i = 2 * I + (ch & 1), j = 2 * J + (ch >> 1);
+        const ResidF r = lresid_cell<3>(K, L, A.T, i, j);
+        const bool wu = (ch & 1) == 0, wv = (ch >> 1) == 0; // faces of the coarse cell
+        const float f[5] = { 0.25f * quad_sum(r.c), 0.25f * quad_sum(r.mu), 0.25f * quad_sum(r.p),
+                             0.5f * quad_sum(wu ? r.u : 0.0f), 0.5f * quad_sum(wv ? r.v : 0.0f) };
+        if (ch == 0)
+#pragma unroll
+            for (int q = 0; q < 5; q++) C.r[q * nc + cc] = f[q];
     }
     __syncthreads();
 }
@@ -451,17 +453,9 @@ __device__ __forceinline__ void bot_prolong(const PhysF &P, const Desc &d, const
     for (int t = threadIdx.x; t < na; t += BOT) {
         const int j = t / A.m1, i = t - j * A.m1, I = i >> 1, J = j >> 1;
         const float *s = C.T.at(I, J);
-        float du = s[T_U], dv = s[T_V];
-        if (i & 1) {
-            const bool in = I + 1 < C.m1;
-            const float e = in || bx ? C.T.at(in ? I + 1 : 0, J)[T_U] : 0.0f;
-            du = 0.5f * (du + e);
-        }
-        if (j & 1) {
-            const bool in = J + 1 < C.m2;
-            const float e = in || by ? C.T.at(I, in ? J + 1 : 0)[T_V] : 0.0f;
-            dv = 0.5f * (dv + e);
-        }
+        const bool ix = I + 1 < C.m1, jy = J + 1 < C.m2;
+        const float u0 = s[T_U], u1 = C.T.at(ix ? I + 1 : 0, J)[T_U], v0 = s[T_V], v1 = C.T.at(I, jy ? J + 1 : 0)[T_V];
+        const float du = i & 1 ? 0.5f * (u0 + (ix || bx ? u1 : 0.0f)) : u0, dv = j & 1 ? 0.5f * (v0 + (jy || by ? v1 : 0.0f)) : v0;
         float *o = A.T.at(i, j);
         const float dc = o[L_DC] + s[L_DC], rs = o[T_RS];
         o[L_DC] = dc;
@@ -483,51 +477,70 @@ __device__ __forceinline__ void k_mx_bottom_body(const IT &it, int nu1, int nu2,
     const int par = it_par(it, k), m1 = d.m1, m2 = d.m2, depth = d.depth;
     const LView L = lview_of(d, par);
     float *const ua = d.dub[par], *const va = d.dvb[par];
+    const int n = m1 * m2;
+    int lc = 1, ec = threadIdx.x;
+    const bool hc = bot_find(lc, ec, depth, m1, m2, [](int a, int b) { return a * b; });
+    auto lev = [&](int l) { return bot_lev(smf, m1, m2, l); };
+    const BotLevF Bc = lev(hc ? lc : 0);
+    const int jc = ec / Bc.m1, ic = ec - jc * Bc.m1;
+    const Desc &dc = (&d)[hc ? lc : 0];
+    const float *const pc = dc.cnf, *const pu = dc.unf, *const pv = dc.vnf;
     {
         const BotLevF B = bot_lev(smf, m1, m2, 0);
-        const int n = m1 * m2;
-        for (int e = threadIdx.x; e < B.T.W * B.T.H; e += BOT) {
-            const int b = e / B.T.W, a = e - b * B.T.W, i = a - 1, j = b - 1;
+        for (int t0 = threadIdx.x; t0 < n || t0 < BOT; t0 += BOT) {
+            const int e = min(t0, n - 1), j = e / m1, i = e - j * m1;
             const TileSrc q = tile_src(m1, m2, L.pitch, L.bcx, L.bcy, i, j);
-            const bool cell = i >= 0 && i < m1 && j >= 0 && j < m2;
             const float v[9] = { lda<1>(L.c, q.c), lda<1>(L.dc, q.c), lda<1>(L.dmu, q.c), lda<1>(L.dp, q.c),
                                  lda<1>(L.du, q.u), lda<1>(L.dv, q.v), lda<1>(L.cn, q.c), lda<1>(L.un, q.u),
                                  lda<1>(L.vn, q.v) };
-            float f[8] = {};
-            if (cell) {
-                f[0] = lda<1>(L.rc, q.c); f[1] = lda<1>(L.rmu, q.c); f[2] = lda<1>(L.rp, q.c);
-                f[3] = lda<1>(L.ru, q.c); f[4] = lda<1>(L.rv, q.c);
-                f[5] = lda<1>(L.mu, q.c); f[6] = lda<1>(L.u, q.c); f[7] = lda<1>(L.v, q.c);
+            const float f[8] = { lda<1>(L.rc, q.c), lda<1>(L.rmu, q.c), lda<1>(L.rp, q.c), lda<1>(L.ru, q.c),
+                                 lda<1>(L.rv, q.c), lda<1>(L.mu, q.c), lda<1>(L.u, q.c), lda<1>(L.v, q.c) };
+            const bool co = hc && t0 < BOT;
+            float w[3] = { 0.0f, 0.0f, 0.0f };
+            TileSrc qc = {};
+            if (co) {
+                qc = tile_src(Bc.m1, Bc.m2, Bc.m1, L.bcx, L.bcy, ic, jc);
+                w[0] = lda<1>(pc, qc.c); w[1] = lda<1>(pu, qc.u); w[2] = lda<1>(pv, qc.v);
             }
+            if (t0 < BOT)
+                bot_rings(depth, m1, m2, lev, [&](const BotLevF &R, int k) { R.ring[k] = ring_entry(R.T, R.m1, R.m2, L.bcx, L.bcy, k); });
             __builtin_amdgcn_sched_barrier(0);
-            float *t = B.T.s + (b * B.T.S + a) * L_ES;
-            ltile_put(P, t, q.su, q.sv, v);
-            t[T_U2] = t[T_U];
-            t[T_V2] = t[T_V];
-            if (cell)
+            if (t0 < n) {
+                float *t = B.T.at(i, j);
+                ltile_put(P, t, q.su, q.sv, v);
+                t[T_U2] = t[T_U];
+                t[T_V2] = t[T_V];
 #pragma unroll
-                for (int g = 0; g < 8; g++) B.r[g * n + j * m1 + i] = f[g]; // r, then x
+                for (int g = 0; g < 8; g++) B.r[g * n + e] = f[g]; // r, then x
+            }
+            if (co) {
+                float *o = Bc.T.at(ic, jc);
+                o[T_CN] = w[0];
+                o[T_RN] = rhof(P, w[0]);
+                o[T_MV] = viscf(P, w[0]);
+                o[T_MOB] = mobf(P, w[0]);
+                o[T_UN] = signed_val(qc.su, w[1]);
+                o[T_VN] = signed_val(qc.sv, w[2]);
+            }
         }
-        ring_build(B.T, m1, m2, L.bcx, L.bcy, B.ring, threadIdx.x, BOT);
     }
-    for (int l = 1; l < depth; l++) {
-        const BotLevF B = bot_lev(smf, m1, m2, l);
-        const Desc &c = (&d)[l];
-        const float *const cn = c.cnf, *const un = c.unf, *const vn = c.vnf;
-        for (int e = threadIdx.x; e < B.T.W * B.T.H; e += BOT) {
-            const int b = e / B.T.W, a = e - b * B.T.W;
-            const TileSrc q = tile_src(B.m1, B.m2, B.m1, L.bcx, L.bcy, a - 1, b - 1);
-            const float n = lda<1>(cn, q.c), u = lda<1>(un, q.u), v = lda<1>(vn, q.v);
-            float *t = B.T.s + (b * B.T.S + a) * L_ES;
-            t[T_CN] = n;
-            t[T_RN] = rhof(P, n);
-            t[T_MV] = viscf(P, n);
-            t[T_MOB] = mobf(P, n);
-            t[T_UN] = signed_val(q.su, u);
-            t[T_VN] = signed_val(q.sv, v);
-        }
-        ring_build(B.T, B.m1, B.m2, L.bcx, L.bcy, B.ring, threadIdx.x, BOT);
-    }
+    __syncthreads();
+    bot_rings(depth, m1, m2, lev, [&](const BotLevF &R, int k) {
+        const Image g = R.ring[k];
+        const float *s = R.T.s + g.c * L_ES;
+        const float c = s[T_C], rs = s[T_RS], cn = s[T_CN], rn = s[T_RN], mv = s[T_MV], mb = s[T_MOB],
+                    un = R.T.s[(g.u >> 2) * L_ES + T_UN], vn = R.T.s[(g.v >> 2) * L_ES + T_VN];
+        float *t = R.T.s + g.e * L_ES;
+        t[T_C] = c; // (of the top level: the others' come with the restriction)
+        t[T_RS] = rs;
+        t[T_CN] = cn;
+        t[T_RN] = rn;
+        t[T_MV] = mv;
+        t[T_MOB] = mb;
+        t[T_UN] = signed_val((g.u & 3) - 1, un);
+        t[T_VN] = signed_val((g.v & 3) - 1, vn);
+        t[T_U] = t[T_U2] = t[T_V] = t[T_V2] = 0.0f; // on the faces of a high wall
+    });
     __syncthreads();
     for (int p = 0; p < 2 * depth - 1; p++) {
         const int l = p < depth ? p : 2 * depth - 2 - p;
