@@ -192,7 +192,7 @@ template <typename IT> __device__ __forceinline__ bool tile_valid(const IT &it, 
 // --------------------------------------------------------------------------
 // one colour half-sweep (sec. 7.1) on a tile: a lane pair per cell of the
 // colour.  The u/v snapshot is buffer par, the new faces go to buffer par^1.
-template <bool PJ, typename IT> __device__ __forceinline__ void k_halfsweep_body(const IT &it, int colour, double omega)
+template <bool PJ, bool RHS = true, typename IT> __device__ __forceinline__ void k_halfsweep_body(const IT &it, int colour, double omega)
 {
     TILE_LDS double sm[TILE_DOUBLES];
     const int k = find_item(it);
@@ -202,7 +202,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_halfsweep_body
     const Kon<double> K = d.K;
     const int par = it_par(it, k);
     const View L = view_of(d, par);
-    const Rhs F = rhs_of(d);
+    const Rhs F = RHS ? rhs_of(d) : Rhs();
     double *const un = d.ub[par ^ 1], *const vn = d.vb[par ^ 1];
     const Tile T = item_tile<Tile>(sm, it, k, d);
     tile_load<2, TBLK>(P, L, T);
@@ -214,11 +214,17 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_halfsweep_body
     if (i < L.m1 && j < L.m2) relax_cell<PJ, 0, 1, false>(P, K, L, T, F, un, vn, i, j, i, j, hlf, omega, 1.0);
 }
 QN_KERNEL_PJ(k_halfsweep, HS_ATTR, (int colour, double omega), (colour, omega))
-// the same kernel under its own name for launches whose items are all finest
-// levels, so that profiles tell the finest level apart
+// the same for launches whose items are all finest levels, which have no
+// right-hand sides (512 x 2048: 37.5 us with them, 36.2 without), under its own
+// name, so that profiles tell the finest level apart.  What bounds it there:
+// neither memory (105 MB, 2.9 TB/s) nor the vector units (19 us of issue), but
+// three workgroups per CU, by registers and LDS, that load, relax and store in
+// turn.  A lane per cell on tiles of 32 x 16 (35 % fewer instructions, two
+// workgroups per CU) took 37.3 us, workgroups that stay and prefetch their next
+// tile 48, four waves per SIMD at the price of spills 48.
 template <bool PJ, typename IT> __device__ __forceinline__ void k_halfsweep_fine_body(const IT &it, int colour, double omega)
 {
-    k_halfsweep_body<PJ>(it, colour, omega);
+    k_halfsweep_body<PJ, false>(it, colour, omega);
 }
 QN_KERNEL_PJ(k_halfsweep_fine, HS_ATTR, (int colour, double omega), (colour, omega))
 
@@ -232,7 +238,12 @@ QN_KERNEL_PJ(k_halfsweep_fine, HS_ATTR, (int colour, double omega), (colour, ome
 // neighbours' cells as halo while others write, so the cell unknowns go from
 // one set to the other (dir 0: c, mu, p to c2, mu2, p2; dir 1 back) and the
 // faces from buffer par to par ^ 1.
-#define FBLK (2 * TBLK)
+// Threads: the tile's 23 x 23 elements load in one round (512 threads take a
+// second one for 17 elements: one sweep of 128 x 256 cells 10.3 us against 9.7,
+// two of 64 x 128 13.8 against 13.7, FP32 11.0 against 10.4).  The projection
+// scheme's registers do not fit nine waves (13.7 against 15.6 us).
+#define FUSED_BLK(PJ) ((PJ) ? 2 * TBLK : 2 * TBLK + 64)
+static constexpr bool PJ = false; // of the kernels over lists
 template <int NS, int TS> struct Fused {
     static constexpr int EXT = 4 * NS - 2;         // the first region: the tile widened by EXT cells
     static constexpr int W = TS + 2 * EXT + 3;     // rows and columns loaded
@@ -321,11 +332,10 @@ __device__ __forceinline__ void prolong_apply(const PSrc &C, const PRaw &r, int 
 // unknown first takes the coarse-grid correction P(w_H - R w_h) of its source
 // (k_prolong's arithmetic); the sweeps write every unknown of the level, so
 // the corrected values need no store of their own.
-// (One element at a time: nearly all threads have one only.)
-__device__ __forceinline__ void fused_load(const Phys &P, const View &L, const Tile &T, bool prolong, const PSrc &pc)
+template <int NT> __device__ __forceinline__ void fused_load(const Phys &P, const View &L, const Tile &T, bool prolong, const PSrc &pc)
 {
     const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += FBLK) {
+    for (int e = threadIdx.x; e < n; e += NT) {
         const int b = e / T.W, a = e - b * T.W;
         int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
         if (L.bcx) i = wrapi(i, L.m1);
@@ -368,6 +378,7 @@ template <bool PJ, int NS, int TS, typename IT>
 __device__ __forceinline__ void fused_body(const IT &it, int dir, double omega, int prolong)
 {
     typedef Fused<NS, TS> G;
+    constexpr int NT = FUSED_BLK(PJ);
     extern __shared__ __attribute__((aligned(16))) double sm[];
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
@@ -389,13 +400,13 @@ __device__ __forceinline__ void fused_body(const IT &it, int dir, double omega, 
     double *const un = d.ub[par ^ 1], *const vn = d.vb[par ^ 1];
     PSrc ps = {};
     if (prolong) ps = psrc_of(d, &d + 1, it_cpar(it, k));
-    fused_load(P, L, T, prolong, ps);
+    fused_load<NT>(P, L, T, prolong, ps);
     __syncthreads();
     const int hlf = threadIdx.x & 1;
     // a half-sweep of the region widened by ext cells
     auto half = [&](auto cext, auto ccol) {
         constexpr int ext = cext.value, colour = ccol.value, w = TS + 2 * ext;
-        for (int pr = threadIdx.x >> 1; pr < w * w / 2; pr += FBLK / 2) {
+        for (int pr = threadIdx.x >> 1; pr < w * w / 2; pr += NT / 2) {
             const int lj = pr / (w / 2), kk = pr - lj * (w / 2);
             const int tj = j0 - ext + lj, ti = i0 - ext + 2 * kk + ((tj + colour) & 1);
             if ((L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2))) {
@@ -437,12 +448,12 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused_body(
 {
     fused_body<PJ, 1, 16>(it, dir, omega, prolong);
 }
-QN_KERNEL_PJ(k_hs_fused, __launch_bounds__(FBLK), (int dir, double omega, int prolong), (dir, omega, prolong))
+QN_KERNEL_PJ(k_hs_fused, __launch_bounds__(FUSED_BLK(PJ)), (int dir, double omega, int prolong), (dir, omega, prolong))
 template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused2_body(const IT &it, int dir, double omega, int prolong)
 {
     fused_body<PJ, 2, 8>(it, dir, omega, prolong);
 }
-QN_KERNEL_PJ(k_hs_fused2, __launch_bounds__(FBLK), (int dir, double omega, int prolong), (dir, omega, prolong))
+QN_KERNEL_PJ(k_hs_fused2, __launch_bounds__(FUSED_BLK(PJ)), (int dir, double omega, int prolong), (dir, omega, prolong))
 
 // plain copy, used to measure the copy bandwidth and to calibrate counters
 __global__ __launch_bounds__(BLK) void k_copy_probe(const double *__restrict__ a, double *__restrict__ b, size_t n)

@@ -630,7 +630,7 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
         }
         case OP_FUSED: {
             const int dir = colour & 1, pro = colour & FUSED_PROLONG;
-            const dim3 gr(W.blocks), bl(FBLK);
+            const dim3 gr(W.blocks), bl(FUSED_BLK(pj));
             constexpr size_t e = T_ES * sizeof(double);
             if (!(colour & FUSED_TWO)) KLAUNCH_PJ(k_hs_fused, W, gr, bl, (Fused<1, 16>::LDS * e), s, dir, omega, pro);
             else KLAUNCH_PJ(k_hs_fused2, W, gr, bl, (Fused<2, 8>::LDS * e), s, dir, omega, pro);
@@ -639,7 +639,7 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
         }
         case OP_MXFUSED: {
             const int dir = colour & 1, pro = colour & FUSED_PROLONG;
-            const dim3 gr(W.blocks), bl(FBLK);
+            const dim3 gr(W.blocks), bl(FUSED_BLK(false));
             constexpr size_t e = L_ES * sizeof(float);
             const float om = (float)omega;
             if (!(colour & FUSED_TWO)) KLAUNCH(k_mx_fused, W, gr, bl, (Fused<1, 16>::LDS * e), s, dir, om, pro);

@@ -124,7 +124,7 @@ template <bool prolong>
 __device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, const TileF &T, const PSrcF &pc)
 {
     const int n = T.W * T.H;
-    for (int e = threadIdx.x; e < n; e += FBLK) {
+    for (int e = threadIdx.x; e < n; e += FUSED_BLK(false)) {
         const int b = e / T.W, a = e - b * T.W;
         int i = T.i0 - 1 + a, j = T.j0 - 1 + b;
         if (L.bcx) i = wrapi(i, L.m1);
@@ -187,7 +187,7 @@ template <int NS, int TS, typename IT> __device__ __forceinline__ void mx_fused_
     const int hlf = threadIdx.x & 1;
     auto half = [&](auto cext, auto ccol) {
         constexpr int ext = cext.value, colour = ccol.value, w = TS + 2 * ext;
-        for (int pr = threadIdx.x >> 1; pr < w * w / 2; pr += FBLK / 2) {
+        for (int pr = threadIdx.x >> 1; pr < w * w / 2; pr += FUSED_BLK(false) / 2) {
             const int lj = pr / (w / 2), kk = pr - lj * (w / 2);
             const int tj = j0 - ext + lj, ti = i0 - ext + 2 * kk + ((tj + colour) & 1);
             if ((L.bcx || (ti >= 0 && ti < L.m1)) && (L.bcy || (tj >= 0 && tj < L.m2))) {
@@ -227,12 +227,12 @@ template <typename IT> __device__ __forceinline__ void k_mx_fused_body(const IT 
 {
     mx_fused_body<1, 16>(it, dir, omega, prolong);
 }
-QN_KERNEL(k_mx_fused, __launch_bounds__(FBLK), (int dir, float omega, int prolong), (dir, omega, prolong))
+QN_KERNEL(k_mx_fused, __launch_bounds__(FUSED_BLK(false)), (int dir, float omega, int prolong), (dir, omega, prolong))
 template <typename IT> __device__ __forceinline__ void k_mx_fused2_body(const IT &it, int dir, float omega, int prolong)
 {
     mx_fused_body<2, 8>(it, dir, omega, prolong);
 }
-QN_KERNEL(k_mx_fused2, __launch_bounds__(FBLK), (int dir, float omega, int prolong), (dir, omega, prolong))
+QN_KERNEL(k_mx_fused2, __launch_bounds__(FUSED_BLK(false)), (int dir, float omega, int prolong), (dir, omega, prolong))
 
 // r - J delta on the item's level, restricted to the next coarser level
 // (cells: mean of four; faces: mean of the two coincident fine faces),
