@@ -81,6 +81,7 @@ FP64_PEAK_TFLOPS = 78.6
 # reduction's finalisation and, after a cycle, the pbar shift)
 OP_KERNEL = {
     "halfsweep": ("k_halfsweep_fine", "k_halfsweep"), "fused_sweep": ("k_hs_fused", "k_hs_fused"),
+    "smooth": ("k_hs_fused2",) * 2, "mx_smooth": ("k_mx_fused2",) * 2,
     "coarse_solve": ("k_bottom", "k_bottom"),
     "restrict": ("k_restrict", "k_restrict"),
     "prolong": ("k_prolong", "k_prolong"), "residual": ("k_resid_norm",) * 2, "residual0": ("k_resid_norm",) * 2,
@@ -114,15 +115,21 @@ def class_bytes(op, lev, launches, cells, opts):
     if op == "fused_sweep":
         return launches * SWEEP_B[fine] * n
     if op == "smooth":
-        # level-resident smoothing: pre- and post-smoothing launches alternate,
-        # nu1 and nu2 sweeps, the post-smoothing taking the prolongation too
+        # all sweeps of a smoothing in one launch (two): pre- and post-smoothing
+        # alternate, nu1 and nu2 sweeps, the latter taking the prolongation too
         half = launches / 2.0
         return (half * opts["nu1"] + half * opts["nu2"]) * SWEEP_B[False] * n + half * TRANSFER_B * n
     if op == "coarse_solve":
-        # the coarsest solve's sweeps (0 in the options: the library's
-        # automatic 4 for the primitive scheme on 6 levels or more, else 6)
+        # the cycle from this level on, in one workgroup: sweeps and transfers
+        # of the levels above the coarsest, and the coarsest solve's sweeps
+        # (0 in the options: the library's automatic 4 for the primitive
+        # scheme on 6 levels or more, else 6)
         nu_c = opts["nu_coarse"] or (4 if opts.get("scheme", 0) != Q.PROJECTION and len(cells) >= 6 else 6)
-        return launches * nu_c * SWEEP_B[False] * n
+        b = nu_c * SWEEP_B[False] * cells[-1]
+        for l in range(lev, len(cells) - 1):
+            b += (opts["nu1"] + opts["nu2"]) * SWEEP_B[False] * cells[l]
+            b += 2 * TRANSFER_B * cells[l] + RESID_B[False] * cells[l + 1]
+        return launches * b
     if op == "restrict":
         # the residual and the restriction (per fine cell), then the coarse
         # right-hand side, a residual of the coarse level

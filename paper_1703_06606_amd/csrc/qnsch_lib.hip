@@ -38,20 +38,24 @@ enum OpKind { OP_BEGIN, OP_RN, OP_NORM0, OP_NORM, OP_HS, OP_RESTRICT, OP_COARSE,
               OP_MXRN, OP_MXHS, OP_MXRESTRICT, OP_MXCOARSE, OP_MXPROLONG, OP_MXUPDATE,
               // diagnostics of the current state
               OP_DISSIP, OP_DIAG, OP_PJFINAL,
-              // (numbers of operations that are no longer issued)
+              // (timing tags of fused launches of two sweeps)
               OP_SMOOTH, OP_MXSMOOTH,
               // acceleration of the cycle iteration: residual norms that also
               // record the result, and the combination before the next cycle
               OP_NORMACC, OP_ACCEL,
-              // one red + black sweep of a level in one launch (temporal
-              // blocking); colour field = direction of the cell sets
+              // one red + black sweep of a level, or two, in one launch
+              // (temporal blocking); colour field = direction of the cell
+              // sets, FUSED_PROLONG, FUSED_TWO
               OP_FUSED, OP_MXFUSED, NOPS };
 struct Op {
     int kind, level, colour;
 };
 // timing tags: operation * PROF_LEVELS + level
 #define PROF_LEVELS 16
-static bool is_smoother_op(int kind) { return kind == OP_HS || kind == OP_MXHS || kind == OP_FUSED || kind == OP_MXFUSED; }
+static bool is_smoother_op(int kind)
+{
+    return kind == OP_HS || kind == OP_MXHS || kind == OP_FUSED || kind == OP_MXFUSED || kind == OP_SMOOTH || kind == OP_MXSMOOTH;
+}
 // operations that launch one kernel (timed by the kernel's own timestamps);
 // the reductions launch two or three
 static bool single_kernel_op(int kind)
@@ -266,15 +270,16 @@ static bool two_sets(const qnsch_opts &o) { return o.blocking > 0; }
 // relaxation: on levels with few tiles per compute unit.  One sweep a launch:
 // coarse levels with at most two 16 x 16 tiles per unit; the finest level
 // with at most one (blocking 1), or two (blocking 2).  Measured on one MI355X
-// (alternating settings on one box): fusing the finest level too, 32 x 64
-// capillary (8 tiles) 0.326-0.329 against 0.340-0.341 ms per step, 64 x 128
-// droplet (32 tiles) 1.354-1.357 against 1.389-1.392, 128 x 256 (128 tiles)
-// 1.901 against 1.965-1.966, but 256 x 512 (512 tiles, two per CU) 2.716-2.722
-// against 2.652-2.656 ms and 512 x 2048 (4096 tiles) 17 % slower.
+// (alternating settings on one box, ms per cycle), fusing the finest level too
+// against half-sweeps there: 32 x 64 (8 tiles) 0.158-0.160 against 0.169-0.177,
+// 64 x 128 (32 tiles) 0.167-0.170 against 0.185-0.190 (FP32 0.145 against 0.164),
+// 128 x 256 (128 tiles) 0.207 against 0.214-0.219 (FP32 0.175 against 0.186),
+// 160 x 320 (200 tiles) 0.199 against 0.210, but 192 x 384 (288 tiles) 0.271
+// against 0.263 and 256 x 512 (512 tiles, two per CU) 0.297 against 0.293.
 // Two sweeps a launch, on 8 x 8 tiles: where every tile has a unit of its own
-// (64 x 128 cells: 15.0 us against 2 x 9.6 us, FP32 12.6 against 2 x 7.9; on
-// 16 x 16 tiles, which 128 x 256 would need, 22.4 against 2 x 10.1: the first
-// regions take two passes of a workgroup's lane pairs).
+// (64 x 128 cells: 13.5 us against 2 x 9.7 us, FP32 10.4 against 2 x 7.6; 128 x 256,
+// two tiles a unit, 26.2 against 2 x 9.9; on 16 x 16 tiles, one a unit there, 22.4:
+// the first regions take two passes of a workgroup's lane pairs).
 // A periodic axis must be long enough for the widened tile to wrap once.
 static int smooth_mode(const qnsch_ctx *x, int l)
 {
@@ -596,11 +601,11 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
         const size_t e = std::min(v.size(), b + MAXITEMS);
         std::vector<std::pair<qnsch_ctx *, int>> part(v.begin() + b, v.begin() + e);
         ItemList W;
-        const bool fused = kind == OP_FUSED || kind == OP_MXFUSED;
-        for (auto &pe : part) add_item(W, pe.first, kind, pe.second, fused && (colour & FUSED_TWO) ? 8 : TX);
+        const bool two = (kind == OP_FUSED || kind == OP_MXFUSED) && (colour & FUSED_TWO);
+        for (auto &pe : part) add_item(W, pe.first, kind, pe.second, two ? 8 : TX);
         const double omega = x0->opt.vanka_omega;
         const bool pj = x0->opt.scheme == QNSCH_PROJECTION;
-        const int tag = prof_tag(kind, part);
+        const int tag = prof_tag(two ? (kind == OP_FUSED ? OP_SMOOTH : OP_MXSMOOTH) : kind, part);
         // launches timed in mode 1 take the kernel's own start and end
         // timestamps; other timed launches are bracketed by event records
         const bool stamp = tag >= 0 && single_kernel_op(kind) && part[0].first->prof == 1;
@@ -1618,7 +1623,8 @@ int qnsch_profile(qnsch_ctx *x, int enable)
 {
     if (!x) return QNSCH_EINVAL;
     const int mode = enable < 0 || enable > 2 ? 1 : enable;
-    const uint64_t smoothers = (1ull << OP_HS) | (1ull << OP_MXHS) | (1ull << OP_FUSED) | (1ull << OP_MXFUSED);
+    const uint64_t smoothers = (1ull << OP_HS) | (1ull << OP_MXHS) | (1ull << OP_FUSED) | (1ull << OP_MXFUSED)
+                             | (1ull << OP_SMOOTH) | (1ull << OP_MXSMOOTH);
     return profile_reset(x, mode, mode == 1 ? smoothers : 0, mode == 1);
 }
 
@@ -2146,7 +2152,8 @@ int qnsch_server_submit(qnsch_server *S, const qnsch_grid *g, const qnsch_params
     // no temporal blocking in a server: its launches merge the same sweep of
     // many requests and so fill the device, where a fused sweep's redundant
     // red work costs more than the launch it saves (measured on one MI355X,
-    // the served droplet stream: 5 % lower throughput with it)
+    // bursts of droplets: from 12 requests on up to 10 % lower throughput with
+    // it in FP64, up to 4 % in mixed precision)
     r->o.blocking = 0;
     r->c0.assign(c0, c0 + (size_t)g->m1 * g->m2);
     r->nsteps = nsteps;
