@@ -152,13 +152,14 @@ typedef struct {
  * cost is as large as its relaxation, a red and the following black
  * half-sweep run in one launch: each tile relaxes the red
  * cells of its tile widened by two cells on every side in LDS, then its own
- * black cells.  Sweeps go in pairs (an odd last sweep takes two half-sweep
- * launches).  Needs a second set of
+ * black cells.  Where every 8 x 8 tile has a compute unit of its own, two
+ * sweeps run in one launch the same way.  Sweeps go in pairs (an odd last
+ * sweep takes two half-sweep launches).  Needs a second set of
  * c, mubar, pbar per level (24 bytes per cell of every level), in mixed
  * precision of the FP32 corrections dc, dmu, dp (12 bytes), whose smoother is
  * fused the same way, as is the projection scheme's smoother of sec. 7.2; a
- * level with a periodic axis shorter than 19 cells keeps the half-sweep
- * launches. */
+ * level with a periodic axis shorter than 19 cells (15 for two sweeps in a
+ * launch) keeps the half-sweep launches. */
 
 /* Acceleration of the cycle iteration (not part of the paper, whose sec. 7.1
  * asks only for a standard FAS V-cycle; the discrete system, its root and the
