@@ -327,7 +327,8 @@ __device__ __forceinline__ bool tile_inner(int m1, int m2, int i0, int j0, int W
 // thread are loaded together: their sources first, then every load, then the
 // signs and cell functions (an element past the end is clamped to a valid
 // one and not stored).
-template <int NE, int NT, typename TT> __device__ __forceinline__ void tile_load(const Phys &P, const View &L, const TT &T)
+// (D: the level's descriptor, whose constants are read behind the loads)
+template <int NE, int NT, typename TT, typename D> __device__ __forceinline__ void tile_load(const D &d, const View &L, const TT &T)
 {
     const int n = T.W * T.H;
     double v[NE][8];
@@ -341,6 +342,7 @@ template <int NE, int NT, typename TT> __device__ __forceinline__ void tile_load
             for (int f = 0; f < 8; f++) v[k][f] = lda<1>(src[f], q);
         }
         __builtin_amdgcn_sched_barrier(0);
+        const Phys P = d.P;
 #pragma unroll
         for (int k = 0; k < NE; k++) {
             const int e = threadIdx.x + k * NT, b = e / T.W, a = e - b * T.W;
@@ -359,6 +361,7 @@ template <int NE, int NT, typename TT> __device__ __forceinline__ void tile_load
         for (int f = 0; f < 8; f++) v[k][f] = w[f];
     }
     __builtin_amdgcn_sched_barrier(0);
+    const Phys P = d.P;
 #pragma unroll
     for (int k = 0; k < NE; k++) {
         const int e = threadIdx.x + k * NT, b = e / T.W, a = e - b * T.W;

@@ -82,17 +82,28 @@ struct Items {
     int tx[MAXITEMS];         // tiles per row (tile kernels); partial count (k_finalize)
     int acc[MAXITEMS];        // acceleration ring slot s | (earlier results used) << 4; -1 none
 };
-// A list of one item (a simulation run on its own), as three kernel arguments
-// of 16 bytes in all.  They arrive in scalar registers with the wave (kernel
+// A list of one item (a simulation run on its own), as five kernel arguments of
+// 28 bytes in all.  They arrive in scalar registers with the wave (kernel
 // argument preloading), so that a kernel's first memory access is the level
 // descriptor's: read from memory, as the many-item list's 1.8 KB are, the
 // arguments cost every kernel a round trip of ~0.5 us before it, and a
 // dependent launch another 1.5 us for 1.4 KB of them.
 // w: u/v buffer of the level, of the next coarser one << 1, (acceleration
 // slot and earlier results, or -1) + 1 << 2; cnt: tiles per row, or partials.
+// base, geom: where the level's arrays are (Lay), for the smoothing and residual
+// kernels, whose first reads are its fields: these start with the wave then, and
+// the descriptor's constants come behind them, instead of behind some eight
+// scalar reads that wait for each other (one fused sweep of 256 tiles 10.2 us
+// against 9.3, two of 32 tiles 13.5 against 13.1, the half-sweep of 1024 tiles
+// 13.1 against 12.5).  NULL: the arrays are the descriptor's.  (The restriction
+// and the bottom levels, which read several descriptors in any case, and FP32
+// gained nothing: 5.7 against 6.0 us, 53.8 against 54.7, two sweeps 10.3 against
+// 10.4.)
 struct Item1 {
     const Desc *d;
     int w, cnt;
+    const char *base;
+    unsigned geom;
 };
 
 __device__ __forceinline__ int find_item(const Items &it)
@@ -123,15 +134,15 @@ __device__ __forceinline__ int it_count(const Item1 &) { return 1; }
 // parameter PJ (projection scheme; not served, so no NAME_n of it).
 #define QN_MORE(...) , ##__VA_ARGS__
 #define QN_KERNEL(NAME, ATTR, PARAMS, ARGS)                                                        \
-    __global__ ATTR void NAME(const Desc *__restrict__ d, int w, int cnt QN_MORE PARAMS)                       \
+    __global__ ATTR void NAME(const Desc *__restrict__ d, int w, int cnt, const char *base, unsigned geom QN_MORE PARAMS)                       \
     {                                                                                              \
-        NAME##_body(Item1{ d, w, cnt } QN_MORE ARGS);                                              \
+        NAME##_body(Item1{ d, w, cnt, base, geom } QN_MORE ARGS);                                              \
     }                                                                                              \
     __global__ ATTR void NAME##_n(Items it QN_MORE PARAMS) { NAME##_body(it QN_MORE ARGS); }
 #define QN_KERNEL_PJ(NAME, ATTR, PARAMS, ARGS)                                                     \
-    template <bool PJ> __global__ ATTR void NAME(const Desc *__restrict__ d, int w, int cnt QN_MORE PARAMS)    \
+    template <bool PJ> __global__ ATTR void NAME(const Desc *__restrict__ d, int w, int cnt, const char *base, unsigned geom QN_MORE PARAMS)    \
     {                                                                                              \
-        NAME##_body<PJ>(Item1{ d, w, cnt } QN_MORE ARGS);                                          \
+        NAME##_body<PJ>(Item1{ d, w, cnt, base, geom } QN_MORE ARGS);                                          \
     }                                                                                              \
     __global__ ATTR void NAME##_n(Items it QN_MORE PARAMS) { NAME##_body<false>(it QN_MORE ARGS); }
 
@@ -146,6 +157,86 @@ __device__ __forceinline__ View view_of(const Desc &d, int par)
     V.inv_h = d.inv_h;
     return V;
 }
+// The FP64 arrays of a level lie one after the other, ARR_* arrays of the same
+// size (rounded up to 256 bytes), and levels follow each other.  geom: cells,
+// boundary kinds, whether there is a second set of cell unknowns, whether the
+// level is the finest (which has no right-hand sides and restricted iterate).
+enum { ARR_C, ARR_MU, ARR_P, ARR_U0, ARR_V0, ARR_U1, ARR_V1, ARR_CN, ARR_UN, ARR_VN, ARR_C2, ARR_RHS = ARR_C2, ARR_W0 = ARR_RHS + 5,
+       ARR_END = ARR_W0 + 5 };
+#define GEOM_MAX 0x3fff
+static __host__ __device__ __forceinline__ size_t arr_bytes(int m1, int m2) { return ((size_t)m1 * m2 * sizeof(double) + 255) & ~(size_t)255; }
+struct Lay {
+    const char *base;
+    int m1, m2, bcx, bcy, two, fine;
+    __device__ __forceinline__ double *arr(int k) const { return (double *)(base + k * arr_bytes(m1, m2)); }
+    __device__ __forceinline__ double *set2(int k) const { return arr(ARR_C2 + k); }
+    __device__ __forceinline__ double *rhs(int k) const { return arr(ARR_RHS + 3 * two + k); }
+    __device__ __forceinline__ double *w0(int k) const { return arr(ARR_W0 + 3 * two + k); }
+    __device__ __forceinline__ double *u(int par) const { return arr(par ? ARR_U1 : ARR_U0); }
+    __device__ __forceinline__ double *v(int par) const { return arr(par ? ARR_V1 : ARR_V0); }
+    __device__ __forceinline__ Lay next() const
+    {
+        Lay n = *this;
+        n.base = (const char *)arr((fine ? (int)ARR_RHS : (int)ARR_END) + 3 * two);
+        n.m1 >>= 1;
+        n.m2 >>= 1;
+        n.fine = 0;
+        return n;
+    }
+};
+__device__ __forceinline__ Lay lay_of(const Item1 &it)
+{
+    const unsigned g = it.geom;
+    return { it.base, (int)(g & GEOM_MAX), (int)(g >> 14 & GEOM_MAX), (int)(g >> 28 & 1), (int)(g >> 29 & 1), (int)(g >> 30 & 1),
+             (int)(g >> 31) };
+}
+__device__ __forceinline__ View view_of(const Items &, const Desc &d, int par) { return view_of(d, par); }
+__device__ __forceinline__ View view_of(const Lay &L, int par)
+{
+    View V;
+    V.c = L.arr(ARR_C); V.mu = L.arr(ARR_MU); V.p = L.arr(ARR_P);
+    V.u = L.u(par); V.v = L.v(par);
+    V.cn = L.arr(ARR_CN); V.un = L.arr(ARR_UN); V.vn = L.arr(ARR_VN);
+    V.m1 = L.m1; V.m2 = L.m2; V.pitch = L.m1;
+    V.bcx = L.bcx; V.bcy = L.bcy;
+    V.inv_h = 0.0; // (not a tile kernel's)
+    return V;
+}
+__device__ __forceinline__ View view_of(const Item1 &it, const Desc &d, int par)
+{
+    return it.base ? view_of(lay_of(it), par) : view_of(d, par);
+}
+// the level's constants: of one item the descriptor, read where they are used,
+// behind the first loads; of a list a copy, read before a kernel's first store
+// (its descriptors are not known to be apart from the stores: read later, their
+// fields would be vector loads)
+struct Consts {
+    Phys P;
+    Kon<double> K;
+};
+__device__ __forceinline__ Consts consts_of(const Items &, const Desc &d) { return { d.P, d.K }; }
+__device__ __forceinline__ const Desc &consts_of(const Item1 &, const Desc &d) { return d; }
+// what a smoothing kernel reads and writes of a level: its right-hand sides
+// (none on a finest level), the other u/v buffer, the second set of cells
+struct LevOut {
+    Rhs F;
+    double *un, *vn, *c2, *mu2, *p2;
+};
+__device__ __forceinline__ LevOut out_of(const Desc &d, int par)
+{
+    return { { d.fc, d.fmu, d.fp, d.fu, d.fv }, d.ub[par ^ 1], d.vb[par ^ 1], d.c2, d.mu2, d.p2 };
+}
+__device__ __forceinline__ LevOut out_of(const Items &, const Desc &d, int par) { return out_of(d, par); }
+__device__ __forceinline__ LevOut out_of(const Item1 &it, const Desc &d, int par)
+{
+    if (!it.base) return out_of(d, par);
+    const Lay L = lay_of(it);
+    LevOut o = { {}, L.u(par ^ 1), L.v(par ^ 1), L.set2(0), L.set2(1), L.set2(2) };
+    if (!L.fine) o.F = { L.rhs(0), L.rhs(1), L.rhs(2), L.rhs(3), L.rhs(4) };
+    return o;
+}
+__device__ __forceinline__ int it_m2(const Items &, const Desc &d) { return d.m2; }
+__device__ __forceinline__ int it_m2(const Item1 &it, const Desc &d) { return it.base ? (int)(it.geom >> 14 & GEOM_MAX) : d.m2; }
 __device__ __forceinline__ Rhs rhs_of(const Desc &d)
 {
     const Rhs F = { d.fc, d.fmu, d.fp, d.fu, d.fv };
@@ -159,7 +250,7 @@ __device__ __forceinline__ Rhs rhs_of(const Desc &d)
 // (TS: the side of a square tile; it_cnt holds the tiles per row)
 template <int TS, typename IT> __device__ __forceinline__ int item_tile_at(const IT &it, int k, const Desc &d, int &i0, int &j0)
 {
-    const int tx = it_cnt(it, k), ty = (d.m2 + TS - 1) / TS;
+    const int tx = it_cnt(it, k), ty = (it_m2(it, d) + TS - 1) / TS;
     const int n = tx * ty, lin = (int)blockIdx.x - it_start(it, k);
     const int t = (n % NXCD == 0) ? (lin % NXCD) * (n / NXCD) + lin / NXCD : lin;
     i0 = (t % tx) * TS;
@@ -186,7 +277,7 @@ __device__ __forceinline__ TT item_tile(R *sm, const IT &it, int k, const Desc &
 }
 template <typename IT> __device__ __forceinline__ bool tile_valid(const IT &it, int k, const Desc &d)
 {
-    return (int)blockIdx.x - it_start(it, k) < it_cnt(it, k) * ((d.m2 + TY - 1) / TY);
+    return (int)blockIdx.x - it_start(it, k) < it_cnt(it, k) * ((it_m2(it, d) + TY - 1) / TY);
 }
 
 // --------------------------------------------------------------------------
@@ -198,14 +289,16 @@ template <bool PJ, bool RHS = true, typename IT> __device__ __forceinline__ void
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
-    const Phys P = d.P;
-    const Kon<double> K = d.K;
     const int par = it_par(it, k);
-    const View L = view_of(d, par);
-    const Rhs F = RHS ? rhs_of(d) : Rhs();
-    double *const un = d.ub[par ^ 1], *const vn = d.vb[par ^ 1];
+    const View L = view_of(it, d, par);
     const Tile T = item_tile<Tile>(sm, it, k, d);
-    tile_load<2, TBLK>(P, L, T);
+    const LevOut o = out_of(it, d, par);
+    const auto &dc = consts_of(it, d);
+    tile_load<2, TBLK>(dc, L, T);
+    const Phys P = dc.P;
+    const Kon<double> K = dc.K;
+    const Rhs F = RHS ? o.F : Rhs();
+    double *const un = o.un, *const vn = o.vn;
     __syncthreads();
     const int pr = threadIdx.x >> 1, hlf = threadIdx.x & 1;
     const int lj = pr / (TX / 2), kk = pr - lj * (TX / 2);
@@ -325,6 +418,15 @@ __device__ __forceinline__ void prolong_apply(const PSrc &C, const PRaw &r, int 
     if (!(C.bcy || jv >= 1)) dv = 0.0;
 }
 
+__device__ __forceinline__ PSrc psrc_of(const Items &, const Desc &d, int cpar) { return psrc_of(d, &d + 1, cpar); }
+__device__ __forceinline__ PSrc psrc_of(const Item1 &it, const Desc &d, int cpar)
+{
+    if (!it.base) return psrc_of(d, &d + 1, cpar);
+    const Lay C = lay_of(it).next();
+    return { C.arr(ARR_C), C.w0(0), C.arr(ARR_MU), C.w0(1), C.arr(ARR_P), C.w0(2), C.u(cpar), C.w0(3), C.v(cpar), C.w0(4),
+             C.m1, C.m1, C.m2, C.bcx, C.bcy };
+}
+
 // the widened tile: every field at tile positions i0-1 .. i0+W-2 (level
 // coordinates; periodic images at their unwrapped positions), the faces in both
 // slots.  A periodic axis needs m >= TS + EXT + 1 so that a single wrap reaches
@@ -332,7 +434,7 @@ __device__ __forceinline__ void prolong_apply(const PSrc &C, const PRaw &r, int 
 // unknown first takes the coarse-grid correction P(w_H - R w_h) of its source
 // (k_prolong's arithmetic); the sweeps write every unknown of the level, so
 // the corrected values need no store of their own.
-template <int NT> __device__ __forceinline__ void fused_load(const Phys &P, const View &L, const Tile &T, bool prolong, const PSrc &pc)
+template <int NT, typename D> __device__ __forceinline__ void fused_load(const D &d, const View &L, const Tile &T, bool prolong, const PSrc &pc)
 {
     const int n = T.W * T.H;
     for (int e = threadIdx.x; e < n; e += NT) {
@@ -359,6 +461,7 @@ template <int NT> __device__ __forceinline__ void fused_load(const Phys &P, cons
         // scheduler otherwise interleaves uses with the loads, one memory
         // latency each)
         __builtin_amdgcn_sched_barrier(0);
+        const Phys P = d.P;
         if (prolong) {
             double rc, rm, rp, du, dv;
             prolong_apply(pc, raw, iu, iv, jv, rc, rm, rp, du, dv);
@@ -384,23 +487,25 @@ __device__ __forceinline__ void fused_body(const IT &it, int dir, double omega, 
     const Desc &d = it_desc(it, k);
     int i0, j0; // of the tile
     if (!item_tile_at<TS>(it, k, d, i0, j0)) return;
-    const Phys P = d.P;
-    const Kon<double> K = d.K;
     const int par = it_par(it, k);
-    View L = view_of(d, par);
+    View L = view_of(it, d, par);
+    const LevOut o = out_of(it, d, par);
     View O = L; // where the sweep's cell results go
     if (dir) {
-        L.c = d.c2; L.mu = d.mu2; L.p = d.p2;
+        L.c = o.c2; L.mu = o.mu2; L.p = o.p2;
     } else {
-        O.c = d.c2; O.mu = d.mu2; O.p = d.p2;
+        O.c = o.c2; O.mu = o.mu2; O.p = o.p2;
     }
     Tile T;
     T.s = sm; T.i0 = i0 - G::EXT; T.j0 = j0 - G::EXT; T.W = G::W; T.H = G::W; T.S = G::S;
-    const Rhs F = rhs_of(d);
-    double *const un = d.ub[par ^ 1], *const vn = d.vb[par ^ 1];
     PSrc ps = {};
-    if (prolong) ps = psrc_of(d, &d + 1, it_cpar(it, k));
-    fused_load<NT>(P, L, T, prolong, ps);
+    if (prolong) ps = psrc_of(it, d, it_cpar(it, k));
+    const auto &dc = consts_of(it, d);
+    fused_load<NT>(dc, L, T, prolong, ps);
+    const Phys P = dc.P;
+    const Kon<double> K = dc.K;
+    const Rhs F = o.F;
+    double *const un = o.un, *const vn = o.vn;
     __syncthreads();
     const int hlf = threadIdx.x & 1;
     // a half-sweep of the region widened by ext cells
@@ -504,7 +609,9 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_restrict_body(
     const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
     const Desc &C = (&d)[1];
-    const Phys P = d.P;
+    const struct {
+        Phys P;
+    } dp = { d.P }; // (read at once with the pointers of both levels)
     const int cp = it_cpar(it, k);
     View Lf = view_of(d, it_par(it, k));
     if (set) { // the pre-smoothing left the cells in the second set
@@ -546,7 +653,7 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_restrict_body(
             }
         }
     }
-    tile_load<2, RBLK>(P, Lf, T);
+    tile_load<2, RBLK>(dp, Lf, T);
     __syncthreads();
     const bool fine = threadIdx.x < TBLK;
     const int cc = fine ? (int)threadIdx.x >> 2 : (int)threadIdx.x - TBLK, ch = threadIdx.x & 3;
@@ -1035,12 +1142,13 @@ template <bool PJ, typename IT> __device__ __forceinline__ void k_resid_norm_bod
     const int k = find_item(it);
     const Desc &d = it_desc(it, k);
     if (!tile_valid(it, k, d)) return;
-    const Phys P = d.P;
-    const Kon<double> K = d.K;
     const int par = it_par(it, k);
-    const View L = view_of(d, par);
+    const View L = view_of(it, d, par);
     const Tile1 T = item_tile<Tile1, TX + 2, TX + 2>(sm, it, k, d);
-    tile_load<2, TBLK>(P, L, T);
+    const auto &dc = consts_of(it, d);
+    tile_load<2, TBLK>(dc, L, T);
+    const Phys P = dc.P;
+    const Kon<double> K = dc.K;
     __syncthreads();
     double v[NRED] = {};
     const size_t n = (size_t)L.m1 * L.m2;
@@ -1459,9 +1567,9 @@ template <typename IT, int N> __device__ __forceinline__ void k_accel_body(const
         d.xc[q] = (float)y[0]; d.xmu[q] = (float)y[1]; d.xu[q] = (float)y[3]; d.xv[q] = (float)y[4];
     }
 }
-__global__ __launch_bounds__(BLK) void k_accel(const Desc *d, int w, int cnt, AccCoef<1> G)
+__global__ __launch_bounds__(BLK) void k_accel(const Desc *d, int w, int cnt, const char *base, unsigned geom, AccCoef<1> G)
 {
-    k_accel_body(Item1{ d, w, cnt }, G);
+    k_accel_body(Item1{ d, w, cnt, base, geom }, G);
 }
 __global__ __launch_bounds__(BLK) void k_accel_n(Items it, AccCoef<MAXITEMS> G) { k_accel_body(it, G); }
 

@@ -174,6 +174,7 @@ struct DLev {
 } // namespace
 
 struct qnsch_ctx {
+    bool lay = false; // the levels' arrays lie as Lay takes them to (FP64)
     qnsch_grid g;
     qnsch_params prm;
     qnsch_opts opt;
@@ -330,6 +331,8 @@ struct ItemList {
     int blocks = 0;
     size_t lds = 0;
     bool all_fine = true;
+    const char *base = nullptr; // of a list of one item (Item1)
+    unsigned geom = 0;
     ItemList() { memset(&it, 0, sizeof(it)); }
 };
 
@@ -347,6 +350,27 @@ static int op_blocks(const qnsch_ctx *x, int kind, int l, int ts = TX)
     }
 }
 
+// whether the arrays of an FP64 context's levels lie as Lay takes them to
+static bool lay_holds(const Desc *hd, int nl)
+{
+    for (int l = 0; l < nl; l++) {
+        const Desc &d = hd[l];
+        const size_t n = arr_bytes(d.m1, d.m2);
+        size_t k = 0;
+        bool ok = true;
+        auto next = [&](const void *p) { ok = ok && (const char *)p == (const char *)d.c + n * k++; };
+        next(d.c); next(d.mu); next(d.p); next(d.ub[0]); next(d.vb[0]); next(d.ub[1]); next(d.vb[1]);
+        next(d.cn); next(d.un); next(d.vn);
+        if (d.c2) { next(d.c2); next(d.mu2); next(d.p2); }
+        if (l > 0) {
+            next(d.fc); next(d.fmu); next(d.fp); next(d.fu); next(d.fv);
+            next(d.c0); next(d.mu0); next(d.p0); next(d.u0); next(d.v0);
+        }
+        if (l + 1 < nl) next(hd[l + 1].c);
+        if (!ok) return false;
+    }
+    return true;
+}
 static void add_item(ItemList &W, const qnsch_ctx *x, int kind, int l, int ts = TX)
 {
     Items &it = W.it;
@@ -362,6 +386,13 @@ static void add_item(ItemList &W, const qnsch_ctx *x, int kind, int l, int ts = 
     it.n = k + 1;
     it.start[k + 1] = W.blocks;
     if (l != 0) W.all_fine = false;
+    const DLev &D = x->L[l];
+    if (x->lay && D.m1 <= GEOM_MAX && D.m2 <= GEOM_MAX
+        && (kind == OP_HS || kind == OP_FUSED || kind == OP_NORM || kind == OP_NORM0 || kind == OP_NORMACC)) {
+        W.base = (const char *)x->hd[l].c;
+        W.geom = (unsigned)D.m1 | (unsigned)D.m2 << 14 | (unsigned)(x->g.bc_x == QNSCH_BC_PERIODIC) << 28
+               | (unsigned)(x->g.bc_y == QNSCH_BC_PERIODIC) << 29 | (unsigned)two_sets(x->opt) << 30 | (unsigned)(l == 0) << 31;
+    }
     if (kind == OP_COARSE || kind == OP_MXCOARSE) W.lds = std::max(W.lds, bottom_lds(x, l));
 }
 
@@ -558,10 +589,10 @@ static int one_w(const Items &a) { return (a.par[0] & 1) | (a.cpar[0] & 1) << 1 
     do {                                                                                           \
         if (e0)                                                                                    \
             hipExtLaunchKernelGGL(K, GRID, BLOCK, LDS, ST, e0, e1, 0, (L).it.d[0], one_w((L).it),     \
-                                  (L).it.tx[0], ##__VA_ARGS__);                                    \
+                                  (L).it.tx[0], (L).base, (L).geom, ##__VA_ARGS__);                \
         else                                                                                       \
             hipLaunchKernelGGL(K, GRID, BLOCK, LDS, ST, (L).it.d[0], one_w((L).it), (L).it.tx[0],      \
-                               ##__VA_ARGS__);                                                     \
+                               (L).base, (L).geom, ##__VA_ARGS__);                                                     \
     } while (0)
 #define KLAUNCHN(K, L, GRID, BLOCK, LDS, ST, ...)                                                    \
     do {                                                                                           \
@@ -1194,6 +1225,7 @@ static int ctx_init(qnsch_ctx *x, const qnsch_grid *g, const qnsch_params *p, co
         d.h = D.h; d.inv_h = 1.0 / D.h;
         d.depth = x->nlev - l;
     }
+    x->lay = !mixed && lay_holds(x->hd, x->nlev);
     set_params(x, p);
     x->hd[0].red_host = x->red_host;
     x->hd[0].rout = nullptr;
@@ -1814,10 +1846,10 @@ int qnsch_residual_noalloc(const qnsch_grid *g, const qnsch_params *prm, double 
     d.red_host = d.red + NRED;  // the reduced values stay on the device
     hipError_t e = hipMemcpyAsync(base, &d, sizeof(d), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_resid_norm<false>, dim3(tx * ty), dim3(TBLK), 0, s, (const Desc *)base, 0, tx);
+        hipLaunchKernelGGL(k_resid_norm<false>, dim3(tx * ty), dim3(TBLK), 0, s, (const Desc *)base, 0, tx, (const char *)nullptr, 0u);
         const int n = tx * ty, ch = fold_chunk(n);
-        if (ch > 1) hipLaunchKernelGGL(k_fold, dim3((n + ch - 1) / ch), dim3(BLK), 0, s, (const Desc *)base, 0, n, 0);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(BLK), 0, s, (const Desc *)base, 0, n, 0, 0);
+        if (ch > 1) hipLaunchKernelGGL(k_fold, dim3((n + ch - 1) / ch), dim3(BLK), 0, s, (const Desc *)base, 0, n, (const char *)nullptr, 0u, 0);
+        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(BLK), 0, s, (const Desc *)base, 0, n, (const char *)nullptr, 0u, 0, 0);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipMemcpyAsync(norms, d.red, 5 * sizeof(double), hipMemcpyDeviceToHost, s);
