@@ -244,7 +244,7 @@ __device__ __forceinline__ Rhs rhs_of(const Desc &d)
 }
 
 // Workgroups are dispatched round-robin over the XCDs, each with its own L2.
-// Items start at multiples of NXCD and their tiles are renumbered so that an
+// Items of many tiles start at multiples of NXCD and their tiles are renumbered so that an
 // XCD gets a contiguous band of tiles: neighbouring tiles, which read each
 // other's halos, share one L2.
 // (TS: the side of a square tile; it_cnt holds the tiles per row)
@@ -909,6 +909,7 @@ __device__ __forceinline__ void k_bottom_body(const IT &it, int nu1, int nu2, in
 {
     extern __shared__ __attribute__((aligned(16))) double sm[];
     const int k = find_item(it);
+    if ((int)blockIdx.x != it_start(it, k)) return; // pads the list: the levels are one workgroup's, in place
     const Desc &d = it_desc(it, k);
     const Phys P = d.P;
     const int par = it_par(it, k), m1 = d.m1, m2 = d.m2, depth = d.depth;

@@ -374,7 +374,10 @@ static bool lay_holds(const Desc *hd, int nl)
 static void add_item(ItemList &W, const qnsch_ctx *x, int kind, int l, int ts = TX)
 {
     Items &it = W.it;
-    const int start = ((W.blocks + NXCD - 1) / NXCD) * NXCD;
+    // (items of one workgroup follow each other: that workgroup has the level
+    // to itself, and consecutive ones go to different XCDs)
+    const bool one = kind == OP_COARSE || kind == OP_MXCOARSE;
+    const int start = one ? W.blocks : ((W.blocks + NXCD - 1) / NXCD) * NXCD;
     const int k = it.n;
     it.start[k] = start;
     it.d[k] = x->dd + l;

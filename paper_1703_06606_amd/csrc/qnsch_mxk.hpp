@@ -472,6 +472,7 @@ __device__ __forceinline__ void k_mx_bottom_body(const IT &it, int nu1, int nu2,
 {
     extern __shared__ __attribute__((aligned(16))) float smf[];
     const int k = find_item(it);
+    if ((int)blockIdx.x != it_start(it, k)) return; // pads the list (k_bottom)
     const Desc &d = it_desc(it, k);
     const PhysF P = d.Pf;
     const int par = it_par(it, k), m1 = d.m1, m2 = d.m2, depth = d.depth;
