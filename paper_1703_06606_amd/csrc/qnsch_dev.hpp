@@ -227,24 +227,10 @@ __device__ __forceinline__ double frcp(double x)
 }
 __device__ __forceinline__ double rho_of(const Phys &P, double c) { return P.rho12 * frcp(P.drho * c + P.rho1); }
 __device__ __forceinline__ double visc_of(const Phys &P, double c) { return P.visc12 * frcp(P.dvisc * c + P.visc1); }
-// square root: hardware estimate of the reciprocal root refined by a coupled
-// Newton step for x and 1/(2 sqrt x) and a last correction (within an ulp;
-// half the instructions of the library's, which also covers the subnormal
-// range, left to it here)
-__device__ __forceinline__ double fsqrt(double x)
-{
-    if (x < 1e-280) return sqrt(x);
-    const double y = __builtin_amdgcn_rsq(x);
-    double g = x * y, h = 0.5 * y;
-    const double r = __builtin_fma(-h, g, 0.5);
-    g = __builtin_fma(g, r, g);
-    h = __builtin_fma(h, r, h);
-    return __builtin_fma(__builtin_fma(-g, g, x), h, g);
-}
 __device__ __forceinline__ double mob_of(const Phys &P, double c)
 {
     double q = c * (1.0 - c);
-    return fsqrt(q * q + P.mob_reg);
+    return sqrt(q * q + P.mob_reg);
 }
 __device__ __forceinline__ double dwell(double c)
 {
