@@ -290,8 +290,13 @@ static int smooth_mode(const qnsch_ctx *x, int l)
     auto wraps = [&](int n) {
         return (x->g.bc_x != QNSCH_BC_PERIODIC || D.m1 >= n) && (x->g.bc_y != QNSCH_BC_PERIODIC || D.m2 >= n);
     };
-    if (tiles(8) <= x->ncu && wraps(8 + Fused<2, 8>::EXT + 1)) return SM_TWO;
-    if (tiles(16) <= (l > 0 || x->opt.blocking >= 2 ? 2 : 1) * x->ncu && wraps(16 + Fused<1, 16>::EXT + 1)) return SM_ONE;
+    const bool one = wraps(16 + Fused<1, 16>::EXT + 1);
+    if (tiles(8) <= x->ncu && wraps(8 + Fused<2, 8>::EXT + 1)) {
+        int t1, t2; // (sweeps left over run one per launch)
+        two_sweeps(SM_TWO, x->opt.nu1, x->opt.nu2, t1, t2);
+        if (one || (2 * t1 == x->opt.nu1 && 2 * t2 == x->opt.nu2)) return SM_TWO;
+    }
+    if (tiles(16) <= (l > 0 || x->opt.blocking >= 2 ? 2 : 1) * x->ncu && one) return SM_ONE;
     return SM_HALF;
 }
 // one cycle; with acceleration its residual reduction records the result,
