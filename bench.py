@@ -115,10 +115,11 @@ def class_bytes(op, lev, launches, cells, opts):
     if op == "fused_sweep":
         return launches * SWEEP_B[fine] * n
     if op == "smooth":
-        # all sweeps of a smoothing in one launch (two): pre- and post-smoothing
-        # alternate, nu1 and nu2 sweeps, the latter taking the prolongation too
-        half = launches / 2.0
-        return (half * opts["nu1"] + half * opts["nu2"]) * SWEEP_B[False] * n + half * TRANSFER_B * n
+        # two sweeps a launch.  Of a cycle's launches on the level (the pairs of
+        # the pre- and the post-smoothing, an even number in all) one takes the
+        # prolongation too
+        per_cycle = (opts["nu1"] // 2 + opts["nu2"] // 2) // 2 * 2
+        return launches * 2 * SWEEP_B[fine] * n + launches / per_cycle * TRANSFER_B * n
     if op == "coarse_solve":
         # the cycle from this level on, in one workgroup: sweeps and transfers
         # of the levels above the coarsest, and the coarsest solve's sweeps
