@@ -93,11 +93,20 @@ OP_KERNEL = {
 }
 
 
-# kernels one operation launches (the residual reductions: the residual with
-# partial sums and their finalisation, which after a cycle shifts pbar too;
-# more than 512 partials are folded first, a kernel more)
-KERNELS_PER_OP = {"residual": 2, "residual_acc": 2, "residual0": 2, "step_end": 2, "dissipation": 2,
-                  "diagnostics": 2}
+# operations that reduce partial sums, and the cells whose sums are one partial:
+# the residual's tiles of 16 x 16, else blocks of 256
+REDUCTIONS = {"residual": True, "residual_acc": True, "residual0": True, "step_end": False, "dissipation": False,
+              "diagnostics": False}
+
+
+def kernels_of_op(op, m1, m2):
+    """kernels that one operation launches on an m1 x m2 finest level: a
+    reduction the sums themselves, the folding of more than 512 partials, and
+    the last step (which after a cycle shifts pbar too); else one"""
+    if op not in REDUCTIONS:
+        return 1
+    partials = -(-m1 // 16) * -(-m2 // 16) if REDUCTIONS[op] else -(-m1 * m2 // 256)
+    return 3 if partials > 512 else 2
 
 
 def kernel_of(op, lev):
@@ -765,7 +774,8 @@ def main():
         "roofline": rf,
         "copy_probe_GBps": copy_gbs,
         "step_breakdown": kernels,
-        "kernel_launches_per_vcycle": sum(n * KERNELS_PER_OP.get(op, 1) for (op, lev), (n, _) in bd.items())
+        "kernel_launches_per_vcycle": sum(n * kernels_of_op(op, cfg["grid"]["m1"], cfg["grid"]["m2"])
+                                          for (op, lev), (n, _) in bd.items())
                                       / max(1, sum(nv_bd)),
     }
     del g

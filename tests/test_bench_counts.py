@@ -16,3 +16,16 @@ def test_two_sweep_launch_bytes(nu1, nu2, per_cycle):
     cycles = 3
     assert B.class_bytes("smooth", 0, cycles * per_cycle, CELLS, opts) == cycles * (per_cycle * 208.0 + 100.0) * 2048
     assert B.class_bytes("smooth", 1, cycles * per_cycle, CELLS, opts) == cycles * (per_cycle * 288.0 + 100.0) * 512
+
+
+def test_kernels_of_a_reduction():
+    """more than 512 partials are folded first: 512 x 2048 has 4096 tiles, 256 x
+    512 exactly 512; 16 x 8208 has 513 of both kinds, 8 x 8200 513 tiles but 257
+    blocks of 256 cells"""
+    for op in ("residual", "residual0", "residual_acc", "step_end", "dissipation", "diagnostics"):
+        assert B.kernels_of_op(op, 256, 512) == 2
+        assert B.kernels_of_op(op, 512, 2048) == 3
+        assert B.kernels_of_op(op, 16, 8208) == 3
+    assert B.kernels_of_op("residual_acc", 8, 8200) == 3 and B.kernels_of_op("step_end", 8, 8200) == 2
+    for op in ("halfsweep", "smooth", "coarse_solve", "accelerate"):
+        assert B.kernels_of_op(op, 512, 2048) == 1
