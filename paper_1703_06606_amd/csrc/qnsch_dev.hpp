@@ -250,7 +250,7 @@ __device__ __forceinline__ double dwell(double c)
 enum { T_C = 0, T_CN, T_MU, T_P, T_RN, T_MV, T_RS, T_MOB, T_U, T_UN, T_V, T_VN, T_NF, T_U2 = T_NF, T_V2, T_ES };
 // the correction smoother's further fields (its T_MU, T_P, T_U, T_V hold
 // corrections): the correction of c and the change of density it induces
-enum { L_DC = T_ES, L_DRS, L_NF, L_ES = 20 };
+enum { L_DC = T_ES, L_DRS, L_ES = 20 };
 
 // A tile covers level cells i0-1 .. i0+W-2, j0-1 .. j0+H-2 (a tile of TX
 // columns: W = TX+3) in rows of S elements; at(i, j), q(f, i, j) take level
@@ -675,11 +675,6 @@ __device__ __forceinline__ void box_solve(const BoxAx<R> &x, const BoxOther<R> &
     tt = gd * (X0 + Xc * dc) + sp * p;
 }
 
-template <int AS = 0> __device__ __forceinline__ double ldf(const double *f, const View &L, int i, int j)
-{
-    return f ? lda<AS>(f, (size_t)j * L.pitch + i) : 0.0;
-}
-
 // face right-hand side of the lane's axis: the select is taken on the pointer
 // values (a select between the two struct members made the compiler stage
 // them in scratch memory)
@@ -842,7 +837,7 @@ template <int ES> struct CellPos {
     }
 };
 template <typename V, typename TT>
-__device__ __forceinline__ CellPos<TT::ES> cell_pos(const V &L, const TT &T, int i, int j, int ti, int tj, int hlf, int slot)
+__device__ __forceinline__ CellPos<TT::ES> cell_pos(const V &L, const TT &T, int i, int j, int hlf, int slot)
 {
     CellPos<TT::ES> c;
     c.a = make_ax(L, T, i, j, hlf, slot);
@@ -888,7 +883,7 @@ __device__ __forceinline__ void relax_cell(const Phys &P, const Kon<double> &K, 
         return;
     }
     constexpr int ES = TT::ES;
-    const CellPos<ES> b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
+    const CellPos<ES> b = cell_pos(L, T, i, j, hlf, slot);
     double *const e = T.at(ti, tj); // results go here, everything is read at s
     Hood<TT, double> H;
     const double *s = e;
@@ -1086,7 +1081,7 @@ __device__ __forceinline__ void relax_pj(const Phys &P, const Kon<double> &K, co
                                          double omega, double pomega, int slot)
 {
     constexpr int ES = TT::ES;
-    const CellPos<ES> b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
+    const CellPos<ES> b = cell_pos(L, T, i, j, hlf, slot);
     double *const e = T.at(ti, tj); // results go here, everything is read at s
     Hood<TT, double> H;
     double *s = e;

@@ -125,25 +125,28 @@ __device__ __forceinline__ int it_acc(const Items &it, int k) { return it.acc[k]
 __device__ __forceinline__ int it_acc(const Item1 &it, int) { return (it.w >> 2) - 1; }
 __device__ __forceinline__ int it_start(const Items &it, int k) { return it.start[k]; }
 __device__ __forceinline__ int it_start(const Item1 &, int) { return 0; }
-__device__ __forceinline__ int it_count(const Items &it) { return it.n; }
-__device__ __forceinline__ int it_count(const Item1 &) { return 1; }
 
 // The two kernels of an operation, NAME for a list of one item and NAME_n for
 // many, from its body NAME_body(list, ...).  PARAMS, ARGS: the further
 // parameters, in parentheses.  QN_KERNEL_PJ: a body with the template
-// parameter PJ (projection scheme; not served, so no NAME_n of it).
+// parameter PJ (projection scheme; not served, so no NAME_n of it).  QN_KERNEL1,
+// QN_KERNEL1_PJ: without NAME_n (operations that the server does not use).
 #define QN_MORE(...) , ##__VA_ARGS__
+#define QN_KERNEL1(NAME, ATTR, PARAMS, ARGS)                                                       \
+    __global__ ATTR void NAME(const Desc *__restrict__ d, int w, int cnt, const char *base, unsigned geom QN_MORE PARAMS) \
+    {                                                                                              \
+        NAME##_body(Item1{ d, w, cnt, base, geom } QN_MORE ARGS);                                  \
+    }
 #define QN_KERNEL(NAME, ATTR, PARAMS, ARGS)                                                        \
-    __global__ ATTR void NAME(const Desc *__restrict__ d, int w, int cnt, const char *base, unsigned geom QN_MORE PARAMS)                       \
-    {                                                                                              \
-        NAME##_body(Item1{ d, w, cnt, base, geom } QN_MORE ARGS);                                              \
-    }                                                                                              \
+    QN_KERNEL1(NAME, ATTR, PARAMS, ARGS)                                                           \
     __global__ ATTR void NAME##_n(Items it QN_MORE PARAMS) { NAME##_body(it QN_MORE ARGS); }
-#define QN_KERNEL_PJ(NAME, ATTR, PARAMS, ARGS)                                                     \
-    template <bool PJ> __global__ ATTR void NAME(const Desc *__restrict__ d, int w, int cnt, const char *base, unsigned geom QN_MORE PARAMS)    \
+#define QN_KERNEL1_PJ(NAME, ATTR, PARAMS, ARGS)                                                    \
+    template <bool PJ> __global__ ATTR void NAME(const Desc *__restrict__ d, int w, int cnt, const char *base, unsigned geom QN_MORE PARAMS) \
     {                                                                                              \
-        NAME##_body<PJ>(Item1{ d, w, cnt, base, geom } QN_MORE ARGS);                                          \
-    }                                                                                              \
+        NAME##_body<PJ>(Item1{ d, w, cnt, base, geom } QN_MORE ARGS);                              \
+    }
+#define QN_KERNEL_PJ(NAME, ATTR, PARAMS, ARGS)                                                     \
+    QN_KERNEL1_PJ(NAME, ATTR, PARAMS, ARGS)                                                        \
     __global__ ATTR void NAME##_n(Items it QN_MORE PARAMS) { NAME##_body<false>(it QN_MORE ARGS); }
 
 __device__ __forceinline__ View view_of(const Desc &d, int par)
@@ -336,7 +339,6 @@ QN_KERNEL_PJ(k_halfsweep_fine, HS_ATTR, (int colour, double omega), (colour, ome
 // two of 64 x 128 13.8 against 13.7, FP32 11.0 against 10.4).  The projection
 // scheme's registers do not fit nine waves (13.7 against 15.6 us).
 #define FUSED_BLK(PJ) ((PJ) ? 2 * TBLK : 2 * TBLK + 64)
-static constexpr bool PJ = false; // of the kernels over lists
 template <int NS, int TS> struct Fused {
     static constexpr int EXT = 4 * NS - 2;         // the first region: the tile widened by EXT cells
     static constexpr int W = TS + 2 * EXT + 3;     // rows and columns loaded
@@ -418,7 +420,6 @@ __device__ __forceinline__ void prolong_apply(const PSrc &C, const PRaw &r, int 
     if (!(C.bcy || jv >= 1)) dv = 0.0;
 }
 
-__device__ __forceinline__ PSrc psrc_of(const Items &, const Desc &d, int cpar) { return psrc_of(d, &d + 1, cpar); }
 __device__ __forceinline__ PSrc psrc_of(const Item1 &it, const Desc &d, int cpar)
 {
     if (!it.base) return psrc_of(d, &d + 1, cpar);
@@ -477,17 +478,16 @@ template <int NT, typename D> __device__ __forceinline__ void fused_load(const D
         s[T_V2] = s[T_V];
     }
 }
-template <bool PJ, int NS, int TS, typename IT>
-__device__ __forceinline__ void fused_body(const IT &it, int dir, double omega, int prolong)
+template <bool PJ, int NS, int TS>
+__device__ __forceinline__ void fused_body(const Item1 &it, int dir, double omega, int prolong)
 {
     typedef Fused<NS, TS> G;
     constexpr int NT = FUSED_BLK(PJ);
     extern __shared__ __attribute__((aligned(16))) double sm[];
-    const int k = find_item(it);
-    const Desc &d = it_desc(it, k);
+    const Desc &d = *it.d;
     int i0, j0; // of the tile
-    if (!item_tile_at<TS>(it, k, d, i0, j0)) return;
-    const int par = it_par(it, k);
+    if (!item_tile_at<TS>(it, 0, d, i0, j0)) return;
+    const int par = it_par(it, 0);
     View L = view_of(it, d, par);
     const LevOut o = out_of(it, d, par);
     View O = L; // where the sweep's cell results go
@@ -499,7 +499,7 @@ __device__ __forceinline__ void fused_body(const IT &it, int dir, double omega, 
     Tile T;
     T.s = sm; T.i0 = i0 - G::EXT; T.j0 = j0 - G::EXT; T.W = G::W; T.H = G::W; T.S = G::S;
     PSrc ps = {};
-    if (prolong) ps = psrc_of(it, d, it_cpar(it, k));
+    if (prolong) ps = psrc_of(it, d, it_cpar(it, 0));
     const auto &dc = consts_of(it, d);
     fused_load<NT>(dc, L, T, prolong, ps);
     const Phys P = dc.P;
@@ -549,16 +549,16 @@ __device__ __forceinline__ void fused_body(const IT &it, int dir, double omega, 
         }
     }
 }
-template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused_body(const IT &it, int dir, double omega, int prolong)
+template <bool PJ> __device__ __forceinline__ void k_hs_fused_body(const Item1 &it, int dir, double omega, int prolong)
 {
     fused_body<PJ, 1, 16>(it, dir, omega, prolong);
 }
-QN_KERNEL_PJ(k_hs_fused, __launch_bounds__(FUSED_BLK(PJ)), (int dir, double omega, int prolong), (dir, omega, prolong))
-template <bool PJ, typename IT> __device__ __forceinline__ void k_hs_fused2_body(const IT &it, int dir, double omega, int prolong)
+QN_KERNEL1_PJ(k_hs_fused, __launch_bounds__(FUSED_BLK(PJ)), (int dir, double omega, int prolong), (dir, omega, prolong))
+template <bool PJ> __device__ __forceinline__ void k_hs_fused2_body(const Item1 &it, int dir, double omega, int prolong)
 {
     fused_body<PJ, 2, 8>(it, dir, omega, prolong);
 }
-QN_KERNEL_PJ(k_hs_fused2, __launch_bounds__(FUSED_BLK(PJ)), (int dir, double omega, int prolong), (dir, omega, prolong))
+QN_KERNEL1_PJ(k_hs_fused2, __launch_bounds__(FUSED_BLK(PJ)), (int dir, double omega, int prolong), (dir, omega, prolong))
 
 // plain copy, used to measure the copy bandwidth and to calibrate counters
 __global__ __launch_bounds__(BLK) void k_copy_probe(const double *__restrict__ a, double *__restrict__ b, size_t n)

@@ -672,22 +672,20 @@ static int launch_op(int kind, int colour, const std::vector<std::pair<qnsch_ctx
             for (auto &pe : part) pe.first->L[pe.second].cur ^= 1;
             break;
         }
-        case OP_FUSED: {
+        case OP_FUSED:
+        case OP_MXFUSED: {
+            if (W.it.n != 1) return QNSCH_EINVAL; // (no server's: its requests run without blocking)
             const int dir = colour & 1, pro = colour & FUSED_PROLONG;
             const dim3 gr(W.blocks), bl(FUSED_BLK(pj));
-            constexpr size_t e = T_ES * sizeof(double);
-            if (!(colour & FUSED_TWO)) KLAUNCH_PJ(k_hs_fused, W, gr, bl, (Fused<1, 16>::LDS * e), s, dir, omega, pro);
-            else KLAUNCH_PJ(k_hs_fused2, W, gr, bl, (Fused<2, 8>::LDS * e), s, dir, omega, pro);
-            for (auto &pe : part) pe.first->L[pe.second].cur ^= 1;
-            break;
-        }
-        case OP_MXFUSED: {
-            const int dir = colour & 1, pro = colour & FUSED_PROLONG;
-            const dim3 gr(W.blocks), bl(FUSED_BLK(false));
-            constexpr size_t e = L_ES * sizeof(float);
+            const size_t lds = (two ? Fused<2, 8>::LDS : Fused<1, 16>::LDS)
+                             * (kind == OP_FUSED ? T_ES * sizeof(double) : L_ES * sizeof(float));
             const float om = (float)omega;
-            if (!(colour & FUSED_TWO)) KLAUNCH(k_mx_fused, W, gr, bl, (Fused<1, 16>::LDS * e), s, dir, om, pro);
-            else KLAUNCH(k_mx_fused2, W, gr, bl, (Fused<2, 8>::LDS * e), s, dir, om, pro);
+            if (kind == OP_MXFUSED && two) KLAUNCH1(k_mx_fused2, W, gr, bl, lds, s, dir, om, pro);
+            else if (kind == OP_MXFUSED) KLAUNCH1(k_mx_fused, W, gr, bl, lds, s, dir, om, pro);
+            else if (pj && two) KLAUNCH1(k_hs_fused2<true>, W, gr, bl, lds, s, dir, omega, pro);
+            else if (pj) KLAUNCH1(k_hs_fused<true>, W, gr, bl, lds, s, dir, omega, pro);
+            else if (two) KLAUNCH1(k_hs_fused2<false>, W, gr, bl, lds, s, dir, omega, pro);
+            else KLAUNCH1(k_hs_fused<false>, W, gr, bl, lds, s, dir, omega, pro);
             for (auto &pe : part) pe.first->L[pe.second].cur ^= 1;
             break;
         }
@@ -2192,8 +2190,9 @@ int qnsch_server_submit(qnsch_server *S, const qnsch_grid *g, const qnsch_params
     // no temporal blocking in a server: its launches merge the same sweep of
     // many requests and so fill the device, where a fused sweep's redundant
     // red work costs more than the launch it saves (measured on one MI355X,
-    // bursts of droplets: from 12 requests on up to 10 % lower throughput with
-    // it in FP64, up to 4 % in mixed precision)
+    // bursts of droplets, wall time with it against without: FP64 47 against
+    // 52 ms for 4 requests, 155 against 147 for 12, 376 against 331 for 32; mixed
+    // 39 against 42, 122 against 124, 292 against 276)
     r->o.blocking = 0;
     r->c0.assign(c0, c0 + (size_t)g->m1 * g->m2);
     r->nsteps = nsteps;

@@ -207,7 +207,7 @@ __device__ __forceinline__ void lrelax_cell(const PhysF &P, const Kon<float> &K,
                                             float omega, int slot = 0)
 {
     constexpr int ES = TileF::ES;
-    const CellPos<ES> b = cell_pos(L, T, i, j, ti, tj, hlf, slot);
+    const CellPos<ES> b = cell_pos(L, T, i, j, hlf, slot);
     float *const e = T.at(ti, tj); // results go here, everything is read at s
     Hood<TileF, float> H;
     const float *s = e;

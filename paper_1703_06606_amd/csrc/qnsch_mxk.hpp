@@ -160,17 +160,16 @@ __device__ __forceinline__ void mx_fused_load(const PhysF &P, const LView &L, co
         s[T_V2] = s[T_V];
     }
 }
-template <int NS, int TS, typename IT> __device__ __forceinline__ void mx_fused_body(const IT &it, int dir, float omega, int prolong)
+template <int NS, int TS> __device__ __forceinline__ void mx_fused_body(const Item1 &it, int dir, float omega, int prolong)
 {
     typedef Fused<NS, TS> G;
     extern __shared__ __attribute__((aligned(16))) float smf[];
-    const int k = find_item(it);
-    const Desc &d = it_desc(it, k);
+    const Desc &d = *it.d;
     int i0, j0; // of the tile
-    if (!item_tile_at<TS>(it, k, d, i0, j0)) return;
+    if (!item_tile_at<TS>(it, 0, d, i0, j0)) return;
     const PhysF P = d.Pf;
     const Kon<float> K = d.Kf;
-    const int par = it_par(it, k);
+    const int par = it_par(it, 0);
     LView L = lview_of(d, par);
     LView O = L;
     if (dir) {
@@ -181,7 +180,7 @@ template <int NS, int TS, typename IT> __device__ __forceinline__ void mx_fused_
     TileF T;
     T.s = smf; T.i0 = i0 - G::EXT; T.j0 = j0 - G::EXT; T.W = G::W; T.H = G::W; T.S = G::S;
     float *const un = d.dub[par ^ 1], *const vn = d.dvb[par ^ 1];
-    if (prolong) mx_fused_load<true>(P, L, T, psrcf_of(d, &d + 1, it_cpar(it, k)));
+    if (prolong) mx_fused_load<true>(P, L, T, psrcf_of(d, &d + 1, it_cpar(it, 0)));
     else mx_fused_load<false>(P, L, T, PSrcF());
     __syncthreads();
     const int hlf = threadIdx.x & 1;
@@ -223,16 +222,16 @@ template <int NS, int TS, typename IT> __device__ __forceinline__ void mx_fused_
         }
     }
 }
-template <typename IT> __device__ __forceinline__ void k_mx_fused_body(const IT &it, int dir, float omega, int prolong)
+__device__ __forceinline__ void k_mx_fused_body(const Item1 &it, int dir, float omega, int prolong)
 {
     mx_fused_body<1, 16>(it, dir, omega, prolong);
 }
-QN_KERNEL(k_mx_fused, __launch_bounds__(FUSED_BLK(false)), (int dir, float omega, int prolong), (dir, omega, prolong))
-template <typename IT> __device__ __forceinline__ void k_mx_fused2_body(const IT &it, int dir, float omega, int prolong)
+QN_KERNEL1(k_mx_fused, __launch_bounds__(FUSED_BLK(false)), (int dir, float omega, int prolong), (dir, omega, prolong))
+__device__ __forceinline__ void k_mx_fused2_body(const Item1 &it, int dir, float omega, int prolong)
 {
     mx_fused_body<2, 8>(it, dir, omega, prolong);
 }
-QN_KERNEL(k_mx_fused2, __launch_bounds__(FUSED_BLK(false)), (int dir, float omega, int prolong), (dir, omega, prolong))
+QN_KERNEL1(k_mx_fused2, __launch_bounds__(FUSED_BLK(false)), (int dir, float omega, int prolong), (dir, omega, prolong))
 
 // r - J delta on the item's level, restricted to the next coarser level
 // (cells: mean of four; faces: mean of the two coincident fine faces),
