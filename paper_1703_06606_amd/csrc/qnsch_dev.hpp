@@ -691,16 +691,15 @@ __device__ __forceinline__ const double *face_rhs(const Rhs &F, int hlf)
 // lane's order (own: T_U, T_UN).  All loads are issued before anything uses
 // one.  Where a launch lasts as long as the chain of its relaxations (few
 // waves, registers to spare), reading the tile at each use instead waits for
-// LDS some twenty times per relaxation, 24 half-sweeps in one workgroup 65 us
-// against 57.
+// LDS some twenty times per relaxation: it cost 8 of 65 us for 24 half-sweeps in
+// one workgroup.
 // A neighbour across a wall is read at its source in the level (the cell next
 // to the wall; the own velocity past a wall along the axis' side changes sign),
 // and with WRAP, in a tile that holds the whole level, one past a periodic end
 // at the other end.  So no half-sweep has to be followed by a copy of changed
-// values to their images, a pass over the ring and a barrier each: the bottom
-// levels from 16 x 32 on 67.1 us against 63.7, two fused sweeps of 64 x 128 cells
-// 15.4 against 13.5.  (The
-// tile holds zeros on the faces of a high wall.  What is past a wall along the
+// values to their images, a pass over the ring and a barrier each: 3.4 of 67 us of
+// the bottom levels from 16 x 32 on, two fused sweeps of 64 x 128 cells 15.4 against
+// 13.5.  (The tile holds zeros on the faces of a high wall.  What is past a wall along the
 // axis is read for the face on the wall only, whose equation is not used.)
 __device__ __forceinline__ double flip(double x, unsigned m)
 {
@@ -821,9 +820,10 @@ template <typename TT, typename R> struct Hood {
 // workgroup's LDS).  HOOD: the neighbourhood is read into registers first.
 //
 // Against a box assembled and eliminated as a 5x5 matrix, coefficients formed
-// per cell and a tile of one array per field, a half-sweep takes 700 instead
-// of 911 vector instructions per wave and 143 instead of 200 registers (three
-// waves per SIMD instead of two): 50.4 -> 38.0 us on 512 x 2048 (MI355X).
+// per cell and a tile of one array per field, a half-sweep of a finest level
+// takes 683 instead of 911 vector instructions per wave and 150 instead of 200
+// registers (three waves per SIMD instead of two): 50.4 -> 36 us on 512 x 2048
+// (MI355X).
 
 // what a sweep of one cell starts from
 template <int ES> struct CellPos {

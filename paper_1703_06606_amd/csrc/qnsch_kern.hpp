@@ -247,9 +247,9 @@ __device__ __forceinline__ Rhs rhs_of(const Desc &d)
 }
 
 // Workgroups are dispatched round-robin over the XCDs, each with its own L2.
-// Items of many tiles start at multiples of NXCD and their tiles are renumbered so that an
-// XCD gets a contiguous band of tiles: neighbouring tiles, which read each
-// other's halos, share one L2.
+// Items of many tiles start at multiples of NXCD and their tiles are renumbered
+// so that an XCD gets a contiguous band of tiles: neighbouring tiles, which
+// read each other's halos, share one L2.
 // (TS: the side of a square tile; it_cnt holds the tiles per row)
 template <int TS, typename IT> __device__ __forceinline__ int item_tile_at(const IT &it, int k, const Desc &d, int &i0, int &j0)
 {
@@ -260,12 +260,12 @@ template <int TS, typename IT> __device__ __forceinline__ int item_tile_at(const
     j0 = (t / tx) * TS;
     return lin < n;
 }
-// (W: the elements that the tile's cells read, -1 .. TX+1 along an axis for a
-// box, whose high face is an unknown, -1 .. TX for a residual)
 // places per slot of a simulation's partials: as many as its finest level has
 // tiles (no fewer than blocks of BLK cells)
 __device__ __forceinline__ int part_stride(const Desc &d) { return ((d.m1 + TX - 1) / TX) * ((d.m2 + TY - 1) / TY); }
 
+// (W: the elements that the tile's cells read, -1 .. TX+1 along an axis for a
+// box, whose high face is an unknown, -1 .. TX for a residual)
 template <typename TT, int W = TX + 3, int S = TILE_S, typename R, typename IT>
 __device__ __forceinline__ TT item_tile(R *sm, const IT &it, int k, const Desc &d)
 {
@@ -336,8 +336,10 @@ QN_KERNEL_PJ(k_halfsweep_fine, HS_ATTR, (int colour, double omega), (colour, ome
 // faces from buffer par to par ^ 1.
 // Threads: the tile's 23 x 23 elements load in one round (512 threads take a
 // second one for 17 elements: one sweep of 128 x 256 cells 10.3 us against 9.7,
-// two of 64 x 128 13.8 against 13.7, FP32 11.0 against 10.4).  The projection
-// scheme's registers do not fit nine waves (13.7 against 15.6 us).
+// two of 64 x 128 13.8 against 13.7, FP32 11.0 against 10.4).  Nine waves may have
+// 168 registers each: the FP64 kernels then spill 12 (one sweep) and 20 bytes
+// (two) per lane, none with 512 threads, which the times above include.  The
+// projection scheme's 177 registers do not fit (13.7 against 15.6 us).
 #define FUSED_BLK(PJ) ((PJ) ? 2 * TBLK : 2 * TBLK + 64)
 template <int NS, int TS> struct Fused {
     static constexpr int EXT = 4 * NS - 2;         // the first region: the tile widened by EXT cells
@@ -577,17 +579,15 @@ __device__ __forceinline__ double rw_mean(double a, double b, double c, double d
 // fine residual r = f - N(w) restricted to the coarse grid together with the
 // iterate (cells: mean of the four children; faces: mean of the two coincident
 // fine faces), and the FAS right-hand side f_H = N_H(R w) + R r of the coarse
-// cells.  A tile of fine cells covers (TX/2) x (TY/2) coarse cells, one lane
-// pair each; N_H is evaluated on a coarse tile whose halo takes R w from the
-// fine arrays directly (the neighbouring workgroups write the coarse iterate
-// meanwhile).
+// cells.  A tile of fine cells covers (TX/2) x (TY/2) coarse cells.  One lane per
+// fine cell (waves 0-3, a coarse cell's children in a quad of lanes, summed by
+// DPP), a fifth wave for the residuals of the tile's 64 coarse cells meanwhile:
+// N_H is evaluated on a coarse tile whose halo takes R w from the fine arrays
+// directly (the neighbouring workgroups write the coarse iterate meanwhile).
 //
 // Single-slot elements of 12 values and tiles of only what a residual reads, 18 x
 // 18, fit three workgroups in a CU's LDS instead of two: 512 x 2048 cells 52
 // instead of 71 us.  (Rows of 20 elements keep a quad's cells on different banks.)
-// One lane per fine cell (waves 0-3, a coarse cell's children in a quad of
-// lanes, summed by DPP), a fifth wave for the residuals of the tile's 64 coarse
-// cells meanwhile.
 #define RBLK (TBLK + 64)
 #define CTILE_S (TX / 2 + 2)
 static_assert((TX / 2) * (TY / 2) == 64, "k_restrict: one wave of coarse cells");
@@ -701,7 +701,7 @@ QN_KERNEL_PJ(k_restrict, __launch_bounds__(RBLK), (int set), (set))
 // memory round trips), for the level's way from and to memory and for an
 // image map of the whole tile.  Per cycle of the 256 x 512 droplet (16 x 32, 8 x 16,
 // 4 x 8 cells: 24 half-sweeps), five smoothing launches of 20.8 us and two restrictions of
-// 6.4 us became one launch of 57 us (MI355X).
+// 6.4 us became one launch of 61 us (MI355X).
 //
 // LDS of a level: its tile (rows of an even number of elements), the
 // right-hand sides, the restricted iterate (coarser levels), the images.
@@ -1037,9 +1037,6 @@ template <typename IT> __device__ __forceinline__ void k_prolong_body(const IT &
 }
 QN_KERNEL(k_prolong, __launch_bounds__(BLK), (), ())
 
-// wave64 + LDS block sum of NRED values (blocks of NT threads).  Within a
-// wave each exchange halves the number of slots a lane is responsible for
-// (lane l ends with the sum of slot l / 4): 17 exchanges instead of 6 per slot.
 // Sums over the block of its threads' first N values (a power of two), through
 // N * NT doubles of LDS that nothing else holds any more: a value's NT terms
 // are added by NT / N threads each, in a fixed order.  Against a reduction in
@@ -1065,6 +1062,9 @@ template <int NT, int N> __device__ __forceinline__ void block_sum_lds(const dou
     if (g == 0) out[(size_t)q * st] = s;
     if (N < NRED && threadIdx.x >= N && threadIdx.x < NRED) out[(size_t)threadIdx.x * st] = 0.0;
 }
+// wave64 + LDS block sum of NRED values (blocks of NT threads).  Within a
+// wave each exchange halves the number of slots a lane is responsible for
+// (lane l ends with the sum of slot l / 4): 17 exchanges instead of 6 per slot.
 template <int NT> __device__ __forceinline__ void block_sum_store(double (&v)[NRED], double *out, int st)
 {
     static_assert(NRED == 16, "block_sum_store");
